@@ -51,6 +51,38 @@ inline hipError_t wait_stream(hipStream_t st) {
   return e;
 }
 
+// What a device kernel hands to a waiting host call: one slot of pinned host memory, written by the kernel that has the
+// result. The host polls the slot, so there is no copy kernel and no wait for the end of the stream behind it.
+struct HostMail {
+  long long value;
+  int status;
+  unsigned posted;
+};
+__device__ inline void post_mail(HostMail* m, long long value, int status) {
+  m->value = value;
+  m->status = status;
+  __threadfence_system();
+  __hip_atomic_store(&m->posted, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A slot taken from a process-wide list for the duration of one call and given back at its end (defined in prof.hip; the
+// list grows to the largest number of calls that were ever inside the library at once, at most MAIL_SLOTS).
+class MailSlot {
+ public:
+  MailSlot();
+  ~MailSlot();
+  MailSlot(const MailSlot&) = delete;
+  MailSlot& operator=(const MailSlot&) = delete;
+  bool ok() const { return m_ != nullptr; }
+  HostMail* dev() const { return m_; }
+  hipError_t wait(hipStream_t st);   // until the slot is posted; an error if the stream fails or drains without it
+  long long value() const { return m_->value; }
+  int status() const { return m_->status; }
+
+ private:
+  HostMail* m_;
+};
+
 // Carves aligned sub-buffers out of a caller workspace; `used()` is what a size query reports.
 struct Carver {
   char* base;

@@ -169,6 +169,66 @@ int32_t exclusive_scan_i32(hipStream_t st, const int32_t* in, int32_t* out, int6
   return HGNN_OK;
 }
 
+// Degrees -> row_ptr (blockIdx.y = 0) and source counts -> colT_ptr (1) in one launch without any hand-over between
+// workgroups: each adds up everything in front of its own 4,096 values before it scans them. That is n^2 / 8192 reads
+// from the L2 (3 MB at n = 80,000), which up to SCAN_PAIR_MAX cost less than the two further launches of the block-sum
+// form (7,105 atoms: 2 x 8.9 us by one walking workgroup -> 5 us; 80,000: 6 launches of 4.5 us -> 7 us). The last
+// workgroup of the degrees also posts the result of the counting call to the host.
+constexpr int64_t SCAN_PAIR_MAX = 131072;
+constexpr int SP_BLK = 4096;
+__global__ void __launch_bounds__(1024)
+k_scan_pair(const int32_t* __restrict__ in0, int32_t* __restrict__ out0, const int32_t* __restrict__ in1,
+            int32_t* __restrict__ out1, int n, const int32_t* __restrict__ status, HostMail* mail) {
+  __shared__ long long sh_front[16];
+  __shared__ int sh_own[16];
+  const int32_t* in = blockIdx.y ? in1 : in0;
+  int32_t* out = blockIdx.y ? out1 : out0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int base = blockIdx.x * SP_BLK;
+  long long front = 0;
+  for (int i = tid * 4; i < base; i += SP_BLK) {     // base is a multiple of SP_BLK: whole 16-byte groups
+    const int4 v = *reinterpret_cast<const int4*>(in + i);
+    front += ((long long)v.x + v.y) + ((long long)v.z + v.w);
+  }
+  const int i0 = base + tid * 4;
+  int v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = i0 + k < n ? in[i0 + k] : 0;
+  const int own = (v[0] + v[1]) + (v[2] + v[3]);
+  int incl = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+    front += __shfl_xor(front, o);
+  }
+  if (lane == 63) {
+    sh_own[wave] = incl;
+    sh_front[wave] = front;
+  }
+  __syncthreads();
+  long long before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    before += sh_front[w] + (w < wave ? sh_own[w] : 0);
+    all += sh_front[w] + sh_own[w];
+  }
+  int ex = (int)before + incl - own;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (i0 + k < n) out[i0 + k] = ex;
+    ex += v[k];
+  }
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+    out[n] = (int)all;
+    if (blockIdx.y == 0) post_mail(mail, all, status[0]);
+  }
+}
+// larger batches: the total behind the block sums of the last scan, posted by a launch of its own
+__global__ void k_post_total(const long long* __restrict__ total, const int32_t* __restrict__ status, HostMail* mail) {
+  post_mail(mail, *total, status[0]);
+}
+
 // ---------------------------------------------------------------------------------------------
 // per-graph metadata
 // ---------------------------------------------------------------------------------------------
@@ -194,12 +254,6 @@ constexpr float FRAC_TOL = 1e-5f;
 constexpr float BIN_MARGIN = 1.001f;  // bins are at least 1.001 * rc wide: absorbs float32 binning error
 constexpr int NB_MAX = 256;
 
-// two ranges in one launch (n2 <= n1)
-__global__ void k_fill2_i32(int32_t* p1, int64_t n1, int32_t* p2, int64_t n2, int32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n1) p1[i] = v;
-  if (i < n2) p2[i] = v;
-}
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -214,21 +268,107 @@ __device__ inline float wave_max(float x) {
   return x;
 }
 
+// Bins and image reach of one graph from its extent (not periodic: bounding box mn .. mx) or its cell. Called by a whole
+// wavefront with the same arguments; lane k < 3 works out lattice direction k (the double-precision divisions and
+// square roots of the three directions are the longest chain of the binning). Returns the number of bins.
+__device__ inline int graph_meta(int lo, int hi, bool periodic, const float* __restrict__ cell_g, const float* mn,
+                                 const float* mx, float rc, GMeta* __restrict__ m, int32_t* __restrict__ status) {
+  const int lane = threadIdx.x & 63;
+  const int k = lane < 3 ? lane : 0;
+  const double rcm = (double)rc * (double)BIN_MARGIN;
+  double hgt;
+  if (lane == 0) {
+    m->lo = lo;
+    m->hi = hi;
+  }
+  if (lane < 9) m->cell[lane] = periodic ? cell_g[lane] : 0.f;
+  if (periodic) {
+    double C[9];
+    for (int q = 0; q < 9; ++q) C[q] = (double)cell_g[q];
+    // cross product of the other two lattice vectors
+    const double u0 = C[(3 * k + 3) % 9], u1 = C[(3 * k + 4) % 9], u2 = C[(3 * k + 5) % 9];
+    const double w0 = C[(3 * k + 6) % 9], w1 = C[(3 * k + 7) % 9], w2 = C[(3 * k + 8) % 9];
+    const double c0 = u1 * w2 - u2 * w1, c1 = u2 * w0 - u0 * w2, c2 = u0 * w1 - u1 * w0;
+    const double det = __shfl(C[0] * c0 + C[1] * c1 + C[2] * c2, 0);   // lane 0: first vector . (second x third)
+    if (!(fabs(det) >= 1e-6)) {
+      if (lane == 0) {
+        atomicOr(status, ST_BAD_CELL);
+        m->periodic = 0;
+        for (int q = 0; q < 3; ++q) { m->nb[q] = 1; m->R[q] = 0; m->org[q] = 0.f; }
+        for (int q = 0; q < 9; ++q) m->inv[q] = 0.f;
+      }
+      return 1;
+    }
+    // inverse: column k of C^-1 is this cross product / det  (f_k = (pos . cr[k]) / det)
+    hgt = fabs(det) / sqrt(c0 * c0 + c1 * c1 + c2 * c2);
+    if (lane < 3) {
+      m->inv[k] = (float)(c0 / det);
+      m->inv[3 + k] = (float)(c1 / det);
+      m->inv[6 + k] = (float)(c2 / det);
+      m->org[k] = 0.f;
+    }
+  } else {
+    const float a = hi == lo ? 0.f : (k == 0 ? mn[0] : (k == 1 ? mn[1] : mn[2]));
+    const float b = hi == lo ? 0.f : (k == 0 ? mx[0] : (k == 1 ? mx[1] : mx[2]));
+    const double ext = (double)b - (double)a;
+    const double pad = 1e-3 * (1.0 + ext);
+    hgt = ext + 2.0 * pad;
+    if (lane < 3) {
+      m->inv[k] = k == 0 ? (float)(1.0 / hgt) : 0.f;
+      m->inv[3 + k] = k == 1 ? (float)(1.0 / hgt) : 0.f;
+      m->inv[6 + k] = k == 2 ? (float)(1.0 / hgt) : 0.f;
+      m->org[k] = (float)((double)a - pad);
+    }
+  }
+  const double q = floor(hgt / rcm);
+  const int mine = q < 1.0 ? 1 : (q > (double)NB_MAX ? NB_MAX : (int)q);
+  int nb[3] = {__shfl(mine, 0), __shfl(mine, 1), __shfl(mine, 2)};
+  // keep the number of bins proportional to the number of atoms (bounded workspace)
+  const long long nat = hi - lo;
+  const long long cap = 4 * nat > 1 ? 4 * nat : 1;
+  while ((long long)nb[0] * nb[1] * nb[2] > cap) {
+    const int t = (nb[0] >= nb[1] && nb[0] >= nb[2]) ? 0 : (nb[1] >= nb[2] ? 1 : 2);
+    nb[t] -= 1;
+  }
+  if (lane < 3) {
+    const int n = k == 0 ? nb[0] : (k == 1 ? nb[1] : nb[2]);
+    int R = (int)ceil(rcm / (hgt / n));
+    if (R < 1) R = 1;
+    if (!periodic && R > n - 1) R = n - 1;  // nothing outside the bounding box
+    if (R > 127) {
+      atomicOr(status, ST_BAD_CELL);
+      R = 0;
+    }
+    m->nb[k] = n;
+    m->R[k] = R;
+    if (k == 0) m->periodic = periodic ? 1 : 0;
+  }
+  return nb[0] * nb[1] * nb[2];
+}
+
+__device__ inline bool bad_range(int g, int G, int N, int lo, int hi) {
+  return lo > hi || lo < 0 || hi > N || (g == 0 && lo != 0) || (g == G - 1 && hi != N);
+}
+// Bins of graph g start at this place of the bin arrays: a graph has at most max(4 atoms, 1) bins, and one more entry
+// ends its last bin, so no scan over the graphs is needed to place them.
+__device__ inline int first_bin(int lo, int g) { return 4 * lo + 2 * g; }
+__device__ inline void no_bins(GMeta* m, int lo, int g) {
+  *m = GMeta{};
+  m->nb[0] = m->nb[1] = m->nb[2] = 1;
+  m->bin_off = first_bin(lo, g);
+}
+
 // one wavefront (block of 64) per graph
 __global__ void k_graph_meta(int N, int G, const float* __restrict__ pos, const int32_t* __restrict__ graph_off,
                              const float* __restrict__ cell, const uint8_t* __restrict__ pbc, float rc,
-                             GMeta* __restrict__ meta, int32_t* __restrict__ nbins, int32_t* __restrict__ status) {
+                             GMeta* __restrict__ meta, int32_t* __restrict__ status) {
   const int g = blockIdx.x;
   const int lane = threadIdx.x;
-  int lo = graph_off[g], hi = graph_off[g + 1];
-  bool bad = (lo > hi) || (lo < 0) || (hi > N) || (g == 0 && lo != 0) || (g == G - 1 && hi != N);
-  if (bad) {
+  const int lo = graph_off[g], hi = graph_off[g + 1];
+  if (bad_range(g, G, N, lo, hi)) {
     if (lane == 0) {
       atomicOr(status, ST_BAD_OFFSETS);
-      GMeta m = {};
-      m.nb[0] = m.nb[1] = m.nb[2] = 1;
-      meta[g] = m;
-      nbins[g] = 1;
+      no_bins(&meta[g], 0, g);
     }
     return;
   }
@@ -249,85 +389,8 @@ __global__ void k_graph_meta(int N, int G, const float* __restrict__ pos, const 
       mx[c] = wave_max(mx[c]);
     }
   }
-  if (lane != 0) return;
-  GMeta m = {};
-  m.lo = lo;
-  m.hi = hi;
-  m.periodic = periodic ? 1 : 0;
-  const double rcm = (double)rc * (double)BIN_MARGIN;
-  double hgt[3];
-  if (periodic) {
-    double C[9];
-    for (int k = 0; k < 9; ++k) {
-      m.cell[k] = cell[9 * (size_t)g + k];
-      C[k] = (double)m.cell[k];
-    }
-    // cross products of the other two lattice vectors
-    double cr[3][3];
-    for (int k = 0; k < 3; ++k) {
-      const double* u = &C[3 * ((k + 1) % 3)];
-      const double* w = &C[3 * ((k + 2) % 3)];
-      cr[k][0] = u[1] * w[2] - u[2] * w[1];
-      cr[k][1] = u[2] * w[0] - u[0] * w[2];
-      cr[k][2] = u[0] * w[1] - u[1] * w[0];
-    }
-    double det = C[0] * cr[0][0] + C[1] * cr[0][1] + C[2] * cr[0][2];
-    if (!(fabs(det) >= 1e-6)) {
-      atomicOr(status, ST_BAD_CELL);
-      m.nb[0] = m.nb[1] = m.nb[2] = 1;
-      m.periodic = 0;
-      meta[g] = m;
-      nbins[g] = 1;
-      return;
-    }
-    // inverse: column k of C^-1 is cr[k] / det  (f_k = (pos . cr[k]) / det)
-    for (int k = 0; k < 3; ++k) {
-      double nrm = sqrt(cr[k][0] * cr[k][0] + cr[k][1] * cr[k][1] + cr[k][2] * cr[k][2]);
-      hgt[k] = fabs(det) / nrm;
-      for (int c = 0; c < 3; ++c) m.inv[3 * c + k] = (float)(cr[k][c] / det);
-    }
-    m.org[0] = m.org[1] = m.org[2] = 0.f;
-  } else {
-    for (int c = 0; c < 3; ++c) {
-      if (hi == lo) { mn[c] = 0.f; mx[c] = 0.f; }
-      double ext = (double)mx[c] - (double)mn[c];
-      double pad = 1e-3 * (1.0 + ext);
-      hgt[c] = ext + 2.0 * pad;
-      m.org[c] = (float)((double)mn[c] - pad);
-      m.inv[3 * c + c] = (float)(1.0 / hgt[c]);
-    }
-  }
-  long long nat = hi - lo;
-  int nb[3];
-  for (int k = 0; k < 3; ++k) {
-    double q = floor(hgt[k] / rcm);
-    nb[k] = q < 1.0 ? 1 : (q > (double)NB_MAX ? NB_MAX : (int)q);
-  }
-  // keep the number of bins proportional to the number of atoms (bounded workspace)
-  long long cap = 4 * nat > 1 ? 4 * nat : 1;
-  while ((long long)nb[0] * nb[1] * nb[2] > cap) {
-    int k = (nb[0] >= nb[1] && nb[0] >= nb[2]) ? 0 : (nb[1] >= nb[2] ? 1 : 2);
-    nb[k] -= 1;
-  }
-  for (int k = 0; k < 3; ++k) {
-    double w = hgt[k] / nb[k];
-    int R = (int)ceil(rcm / w);
-    if (R < 1) R = 1;
-    if (!periodic && R > nb[k] - 1) R = nb[k] - 1;  // nothing outside the bounding box
-    if (R > 127) {
-      atomicOr(status, ST_BAD_CELL);
-      R = 0;
-    }
-    m.nb[k] = nb[k];
-    m.R[k] = R;
-  }
-  meta[g] = m;
-  nbins[g] = nb[0] * nb[1] * nb[2];
-}
-
-__global__ void k_set_bin_off(int G, GMeta* __restrict__ meta, const int32_t* __restrict__ bin_off) {
-  int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < G) meta[g].bin_off = bin_off[g];
+  graph_meta(lo, hi, periodic, cell + 9 * (size_t)g, mn, mx, rc, &meta[g], status);
+  if (lane == 0) meta[g].bin_off = first_bin(lo, g);
 }
 
 __device__ inline int find_graph(const int32_t* __restrict__ graph_off, int G, int i) {
@@ -341,6 +404,158 @@ __device__ inline int find_graph(const int32_t* __restrict__ graph_off, int G, i
   return lo;
 }
 
+// bin of an atom inside its graph; outside: a fractional coordinate outside the cell (also NaN)
+__device__ inline int atom_bin_of(const GMeta& m, float x, float y, float z, bool& outside) {
+  const float d[3] = {x - m.org[0], y - m.org[1], z - m.org[2]};
+  int b[3];
+  outside = false;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    float f = d[0] * m.inv[k] + d[1] * m.inv[3 + k] + d[2] * m.inv[6 + k];
+    outside = outside || !(f >= -FRAC_TOL && f <= 1.0f + FRAC_TOL);
+    int q = (int)floorf(f * (float)m.nb[k]);
+    b[k] = q < 0 ? 0 : (q >= m.nb[k] ? m.nb[k] - 1 : q);
+  }
+  return (b[0] * m.nb[1] + b[1]) * m.nb[2] + b[2];
+}
+
+// Small batches (at most BIN_GRAPHS_MAX atoms): everything between the input and the search in one launch, one
+// workgroup per graph. A graph's atoms are contiguous in the batch, so its bins' runs are too: histogram, scan and
+// placement stay inside the workgroup, in LDS (seven launches of 2-14 us before: the atomics of a molecule's atoms on
+// its one or two bins in memory alone were 13 + 13 us at 7,105 atoms). Larger batches keep the grid-wide kernels below,
+// where one large graph is spread over many workgroups.
+constexpr int BIN_GRAPHS_MAX = 16384;
+constexpr int BG_BINS = 4096;    // bins of a graph counted in LDS; more: in the workspace
+struct BinArgs {
+  int N, G;
+  const float* pos;
+  const int32_t* graph_off;
+  const float* cell;
+  const uint8_t* pbc;
+  float rc;
+  GMeta* meta;
+  int32_t *atom_graph, *atom_bin, *bin_cnt, *bin_start, *bin_atoms;
+  float4* spos;
+  int32_t *status, *nlist;
+  int2* list;
+  int home;                      // destination atoms of a work item
+};
+__global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
+  __shared__ GMeta m;
+  __shared__ int hist[BG_BINS];
+  __shared__ float red[4][6];
+  __shared__ int wsum[4][2];
+  __shared__ int s_at;
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lo = p.graph_off[g], hi = p.graph_off[g + 1];
+  if (bad_range(g, p.G, p.N, lo, hi)) {              // reported by the host; nothing is searched
+    if (tid == 0) {
+      atomicOr(p.status, ST_BAD_OFFSETS);
+      no_bins(&p.meta[g], 0, g);
+    }
+    return;
+  }
+  const bool periodic = (p.pbc != nullptr) && (p.cell != nullptr) && (p.pbc[g] != 0);
+  float mn[3] = {3.0e38f, 3.0e38f, 3.0e38f}, mx[3] = {-3.0e38f, -3.0e38f, -3.0e38f};
+  if (!periodic) {
+    for (int i = lo + tid; i < hi; i += 256) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float x = p.pos[3 * (size_t)i + c];
+        mn[c] = fminf(mn[c], x);
+        mx[c] = fmaxf(mx[c], x);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      mn[c] = wave_min(mn[c]);
+      mx[c] = wave_max(mx[c]);
+      if (lane == 0) { red[wave][c] = mn[c]; red[wave][3 + c] = mx[c]; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      for (int c = 0; c < 3; ++c) { mn[c] = fminf(mn[c], red[w][c]); mx[c] = fmaxf(mx[c], red[w][3 + c]); }
+  }
+  const int off = first_bin(lo, g);
+  if (wave == 0) {
+    graph_meta(lo, hi, periodic, p.cell + 9 * (size_t)g, mn, mx, p.rc, &m, p.status);
+    if (lane == 0) m.bin_off = off;
+  }
+  __syncthreads();
+  if (tid == 0) p.meta[g] = m;
+  const int nbins = m.nb[0] * m.nb[1] * m.nb[2];
+  const bool in_lds = nbins <= BG_BINS;
+  int* cnt = p.bin_cnt + off;                        // cleared by the launch before
+  if (in_lds)
+    for (int b = tid; b < nbins; b += 256) hist[b] = 0;
+  __syncthreads();
+  for (int i = lo + tid; i < hi; i += 256) {
+    bool outside;
+    const int b = atom_bin_of(m, p.pos[3 * (size_t)i], p.pos[3 * (size_t)i + 1], p.pos[3 * (size_t)i + 2], outside);
+    if (outside && periodic) atomicOr(p.status, ST_OUT_OF_CELL);
+    p.atom_graph[i] = g;
+    p.atom_bin[i] = off + b;
+    if (in_lds) atomicAdd(&hist[b], 1); else atomicAdd(&cnt[b], 1);
+  }
+  if (!in_lds) __threadfence();
+  __syncthreads();
+  // bins -> first record of every bin, and the work list (1,024 bins at a time)
+  int carry = lo;
+  for (int b0 = 0; b0 < nbins; b0 += 1024) {
+    int c[4], own = 0, items = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int b = b0 + tid * 4 + u;
+      c[u] = b < nbins ? (in_lds ? hist[b] : __hip_atomic_load(&cnt[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
+      own += c[u];
+      items += (c[u] + p.home - 1) / p.home;
+    }
+    int ia = own, ii = items;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int ua = __shfl_up(ia, o), ui = __shfl_up(ii, o);
+      if (lane >= o) { ia += ua; ii += ui; }
+    }
+    if (lane == 63) { wsum[wave][0] = ia; wsum[wave][1] = ii; }
+    __syncthreads();
+    int ta = 0, ti = 0, ba = 0, bi = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) { ba += wsum[w][0]; bi += wsum[w][1]; }
+      ta += wsum[w][0];
+      ti += wsum[w][1];
+    }
+    if (tid == 0) s_at = atomicAdd(p.nlist, ti);
+    __syncthreads();
+    int at = s_at + bi + ii - items, ex = carry + ba + ia - own;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int b = b0 + tid * 4 + u;
+      if (b < nbins) {
+        p.bin_start[off + b] = ex;
+        if (in_lds) hist[b] = ex; else cnt[b] = ex;   // from here on: the bin's next free record
+        for (int k = 0; k < c[u]; k += p.home, ++at)
+          if (at < p.N) p.list[at] = make_int2(off + b, k);   // (more only if bad offsets make graphs overlap)
+      }
+      ex += c[u];
+    }
+    carry += ta;
+    __syncthreads();
+  }
+  if (tid == 0) p.bin_start[off + nbins] = hi;
+  if (!in_lds) __threadfence();
+  __syncthreads();
+  for (int i = lo + tid; i < hi; i += 256) {
+    const float x = p.pos[3 * (size_t)i], y = p.pos[3 * (size_t)i + 1], z = p.pos[3 * (size_t)i + 2];
+    bool outside;
+    const int b = atom_bin_of(m, x, y, z, outside);
+    const int k = in_lds ? atomicAdd(&hist[b], 1) : atomicAdd(&cnt[b], 1);
+    p.bin_atoms[k] = i;
+    p.spos[k] = make_float4(x, y, z, __int_as_float(i));
+  }
+}
+
 __global__ void k_bin_atoms_count(int N, int G, const float* __restrict__ pos, const int32_t* __restrict__ graph_off,
                                   const GMeta* __restrict__ meta, int32_t* __restrict__ atom_graph,
                                   int32_t* __restrict__ atom_bin, int32_t* __restrict__ bin_cnt,
@@ -349,46 +564,37 @@ __global__ void k_bin_atoms_count(int N, int G, const float* __restrict__ pos, c
   if (i >= N) return;
   int g = find_graph(graph_off, G, i);
   const GMeta& m = meta[g];
-  float d[3] = {pos[3 * (size_t)i] - m.org[0], pos[3 * (size_t)i + 1] - m.org[1], pos[3 * (size_t)i + 2] - m.org[2]};
-  int b[3];
-  bool outside = false;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    float f = d[0] * m.inv[k] + d[1] * m.inv[3 + k] + d[2] * m.inv[6 + k];
-    outside = outside || !(f >= -FRAC_TOL && f <= 1.0f + FRAC_TOL);   // also catches NaN
-    int q = (int)floorf(f * (float)m.nb[k]);
-    b[k] = q < 0 ? 0 : (q >= m.nb[k] ? m.nb[k] - 1 : q);
-  }
+  bool outside;
+  const int bin = m.bin_off + atom_bin_of(m, pos[3 * (size_t)i], pos[3 * (size_t)i + 1], pos[3 * (size_t)i + 2], outside);
   if (outside && m.periodic) atomicOr(status, ST_OUT_OF_CELL);
-  int bin = m.bin_off + (b[0] * m.nb[1] + b[1]) * m.nb[2] + b[2];
   atom_graph[i] = g;
   atom_bin[i] = bin;
   atomicAdd(&bin_cnt[bin], 1);
 }
 
-// atoms in bin order: their index (for the slow path) and (x, y, z, index) as one 16-byte record
-__global__ void k_bin_atoms_fill(int N, const float* __restrict__ pos, const int32_t* __restrict__ atom_bin,
-                                 const int32_t* __restrict__ bin_start, int32_t* __restrict__ bin_cur,
-                                 int32_t* __restrict__ bin_atoms, float4* __restrict__ spos) {
+// atoms in bin order: their index (for the slow path) and (x, y, z, index) as one 16-byte record (the bin's count runs
+// down to its next free record); and, in the workgroups behind those of the atoms, the work list of the search: one
+// entry per `home` destination atoms of a non-empty bin (order does not matter)
+constexpr int SR_HOME = 16;
+__global__ void k_bin_place(int N, unsigned natom_blocks, const float* __restrict__ pos, const int32_t* __restrict__ atom_bin,
+                            const int32_t* __restrict__ bin_start, int32_t* __restrict__ bin_cnt,
+                            int32_t* __restrict__ bin_atoms, float4* __restrict__ spos, int64_t maxbins, int home,
+                            int32_t* __restrict__ nlist, int2* __restrict__ list) {
+  if (blockIdx.x >= natom_blocks) {
+    const int64_t b = (int64_t)(blockIdx.x - natom_blocks) * blockDim.x + threadIdx.x;
+    if (b >= maxbins) return;
+    const int c = bin_start[b + 1] - bin_start[b];
+    if (c <= 0) return;
+    int at = atomicAdd(nlist, (c + home - 1) / home);
+    for (int k = 0; k < c; k += home) list[at++] = make_int2((int)b, k);
+    return;
+  }
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
-  int bin = atom_bin[i];
-  int k = bin_start[bin] + atomicAdd(&bin_cur[bin], 1);
+  const int bin = atom_bin[i];
+  const int k = bin_start[bin] + atomicAdd(&bin_cnt[bin], -1) - 1;
   bin_atoms[k] = i;
   spos[k] = make_float4(pos[3 * (size_t)i], pos[3 * (size_t)i + 1], pos[3 * (size_t)i + 2], __int_as_float(i));
-}
-
-// work list of the search: one entry per SR_HOME destination atoms of a non-empty bin (order does not matter)
-constexpr int SR_HOME = 16;
-__global__ void k_bin_list(int64_t maxbins, const int32_t* __restrict__ bin_cnt, int32_t* __restrict__ nlist,
-                           int2* __restrict__ list) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= maxbins) return;
-  const int c = bin_cnt[b];
-  if (c <= 0) return;
-  const int n = (c + SR_HOME - 1) / SR_HOME;
-  const int at = atomicAdd(nlist, n);
-  for (int k = 0; k < n; ++k) list[at + k] = make_int2((int)b, k * SR_HOME);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -429,6 +635,7 @@ struct SearchArgs {
   const int2* list;
   const int32_t* status;
   float rc;
+  int home;                  // destination atoms of a work item (at most SR_HOME)
   // count
   int32_t* deg;
   int32_t* colT_cnt;
@@ -468,7 +675,7 @@ __global__ void __launch_bounds__(256) k_search(SearchArgs p) {
     const int hb = it.x, h0 = it.y;
     const int hb_start = p.bin_start[hb];
     const int hb_cnt = p.bin_start[hb + 1] - hb_start;
-    const int nhome = hb_cnt - h0 < SR_HOME ? hb_cnt - h0 : SR_HOME;
+    const int nhome = hb_cnt - h0 < p.home ? hb_cnt - h0 : p.home;
     const int i_first = __float_as_int(p.spos[hb_start].w);
     const GMeta& m = p.meta[p.atom_graph[i_first]];
     const int nb0 = m.nb[0], nb1 = m.nb[1], nb2 = m.nb[2];
@@ -733,16 +940,25 @@ __global__ void __launch_bounds__(256) k_search(SearchArgs p) {
 // slow path for rows longer than the LDS row: one wavefront per listed row walks the bins from memory,
 // stores the hits unordered and ranks them from memory
 // ---------------------------------------------------------------------------------------------
+// (the workgroups behind the first `nlong` write the two offset arrays that leave with the edges: first edge of every
+// graph, and the source groups' offsets)
 __global__ void __launch_bounds__(256)
-k_long_rows(const int32_t* __restrict__ novf, const int32_t* __restrict__ ovf_rows, const float* __restrict__ pos,
+k_long_rows(unsigned nlong, int N, int G, const int32_t* __restrict__ graph_off, int32_t* __restrict__ egp,
+            int32_t* __restrict__ colT_out, const int32_t* __restrict__ novf, const int32_t* __restrict__ ovf_rows, const float* __restrict__ pos,
             const GMeta* __restrict__ meta, const int32_t* __restrict__ atom_graph,
             const int32_t* __restrict__ atom_bin, const int32_t* __restrict__ bin_start,
             const int32_t* __restrict__ bin_atoms, float rc, const int32_t* __restrict__ row_ptr,
             int32_t* key_j, int32_t* key_c, int32_t* __restrict__ dst, int32_t* __restrict__ col,
             int8_t* __restrict__ shift, float* __restrict__ d2, float* __restrict__ rvec,
             const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ colT_cur, int32_t* __restrict__ unsorted) {
+  if (blockIdx.x >= nlong) {
+    const int64_t i = (int64_t)(blockIdx.x - nlong) * 256 + threadIdx.x;
+    if (i <= N) colT_out[i] = colT_ptr[i];
+    if (i <= G) egp[i] = row_ptr[graph_off[i]];
+    return;
+  }
   const int w0 = (int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int nw = (int)(((size_t)gridDim.x * blockDim.x) >> 6);
+  const int nw = (int)(((size_t)nlong * blockDim.x) >> 6);
   const int lane = threadIdx.x & 63;
   const int n = *novf;
   for (int r = w0; r < n; r += nw) {
@@ -829,25 +1045,24 @@ k_long_rows(const int32_t* __restrict__ novf, const int32_t* __restrict__ ovf_ro
   }
 }
 
-__global__ void k_edge_graph_ptr(int G, const int32_t* __restrict__ graph_off, const int32_t* __restrict__ row_ptr,
-                                 int32_t* __restrict__ egp) {
-  int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g <= G) egp[g] = row_ptr[graph_off[g]];
-}
-
 // ---------------------------------------------------------------------------------------------
 // transpose plan: the histogram of sources is taken by the counting search; the filling search deals the edges to
 // their source's group (any order, see k_search); here each group is put into ascending edge order, in place
 // ---------------------------------------------------------------------------------------------
 constexpr int TS_CAP = 512;   // group members ranked out of LDS; longer groups are ranked from memory
 __global__ void __launch_bounds__(256)
-k_rank_sources(int N, const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ permT, int32_t* __restrict__ copy) {
+k_rank_sources(int N, const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ permT, int32_t* __restrict__ copy,
+               int32_t* __restrict__ colT_cur, int32_t* __restrict__ novf) {
   // permT holds the groups as they were dealt; copy: room for one int per edge (long groups are ranked out of it)
   const int32_t* unsorted = permT;
   __shared__ __align__(16) int grp[4][TS_CAP + 4];
   const int j = (int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   if (j >= N) return;
+  if (lane == 0) {                 // the filling call leaves its counters at zero: it may be repeated after one count
+    colT_cur[j] = 0;
+    if (j == 0) *novf = 0;
+  }
   const int start = colT_ptr[j], end = colT_ptr[j + 1];
   const int n = end - start;
   if (n <= 0) return;
@@ -879,32 +1094,24 @@ k_rank_sources(int N, const int32_t* __restrict__ colT_ptr, int32_t* __restrict_
   }
 }
 
-__global__ void k_copy_i32(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
-
 // ---------------------------------------------------------------------------------------------
 // workspace layout
 // ---------------------------------------------------------------------------------------------
 struct NeighWs {
-  int32_t* status;      // [8]: 0 input errors, 1 work-list length, 2 rows left to the slow path
   GMeta* meta;          // [G]
-  int32_t* nbins;       // [G]
-  int32_t* bin_off;     // [G+1]
   int32_t* atom_graph;  // [N]
   int32_t* atom_bin;    // [N]
-  int32_t* zeroed;      // bin_cnt | bin_cur | colT_cnt | colT_cur, cleared by one launch
+  int32_t* zeroed;      // status | deg | colT_cnt | colT_cur | bin_cnt, cleared by one launch
   int64_t nzeroed;
-  int32_t* bin_cnt;     // [maxbins]
-  int32_t* bin_start;   // [maxbins+1]
-  int32_t* bin_cur;     // [maxbins]
-  int32_t* bin_atoms;   // [N]
-  float4* spos;         // [N] (x, y, z, atom) in bin order
-  int2* list;           // [N] work list of the search
+  int32_t* status;      // [8]: 0 input errors, 1 work-list length, 2 rows left to the slow path
   int32_t* deg;         // [N]
   int32_t* colT_cnt;    // [N]
   int32_t* colT_cur;    // [N]
+  int32_t* bin_cnt;     // [maxbins]
+  int32_t* bin_start;   // [maxbins+1]
+  int32_t* bin_atoms;   // [N]
+  float4* spos;         // [N] (x, y, z, atom) in bin order
+  int2* list;           // [N] work list of the search
   int32_t* colT_ptr;    // [N+1] kept from the counting call for the filling call
   int32_t* ovf_rows;    // [N]
   int32_t* scan;        // scratch
@@ -915,38 +1122,44 @@ struct NeighWs {
 static NeighWs carve_neigh(void* ws, int N, int G) {
   NeighWs w;
   Carver c(ws);
-  w.maxbins = 4ll * N + G + 1;
-  w.status = c.take<int32_t>(8);
+  w.maxbins = 4ll * N + 2ll * G + 2;      // first_bin() of the last graph + its bins + 1
   w.meta = c.take<GMeta>((size_t)G + 1);
-  w.nbins = c.take<int32_t>((size_t)G + 1);
-  w.bin_off = c.take<int32_t>((size_t)G + 2);
   w.atom_graph = c.take<int32_t>((size_t)N + 1);
   w.atom_bin = c.take<int32_t>((size_t)N + 1);
-  w.nzeroed = 2 * w.maxbins + 2 * ((int64_t)N + 1);
+  const int64_t n4 = (int64_t)(align_up((size_t)N + 1, 64));   // sub-arrays start at multiples of 256 bytes
+  w.nzeroed = 64 + 3 * n4 + (int64_t)align_up((size_t)w.maxbins, 64);
   w.zeroed = c.take<int32_t>((size_t)w.nzeroed);
-  w.bin_cnt = w.zeroed;
-  w.bin_cur = w.bin_cnt + w.maxbins;
-  w.colT_cnt = w.bin_cur + w.maxbins;
-  w.colT_cur = w.colT_cnt + N + 1;
+  w.status = w.zeroed;
+  w.deg = w.zeroed + 64;
+  w.colT_cnt = w.deg + n4;
+  w.colT_cur = w.colT_cnt + n4;
+  w.bin_cnt = w.colT_cur + n4;
   w.bin_start = c.take<int32_t>((size_t)w.maxbins + 1);
   w.bin_atoms = c.take<int32_t>((size_t)N + 1);
   w.spos = c.take<float4>((size_t)N + 1);
   w.list = c.take<int2>((size_t)N + 1);
-  w.deg = c.take<int32_t>((size_t)N + 1);
   w.colT_ptr = c.take<int32_t>((size_t)N + 2);
   w.ovf_rows = c.take<int32_t>((size_t)N + 1);
-  w.scan = c.take<int32_t>(scan_scratch_ints(w.maxbins + N + G + 8) + 8);
+  w.scan = c.take<int32_t>(scan_scratch_ints(w.maxbins + 8) + 8);
   w.bytes = c.used();
   return w;
 }
+__global__ void k_zero4(int4* p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = make_int4(0, 0, 0, 0);
+}
 
 static inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
+
+// destination atoms per work item, the same in the counting and the filling call
+static int home_atoms(int N) { (void)N; return SR_HOME; }
 
 static SearchArgs search_args(const NeighWs& w, int N, const float* pos, float rc) {
   SearchArgs a = {};
   a.N = N; a.pos = pos; a.meta = w.meta; a.atom_graph = w.atom_graph; a.bin_start = w.bin_start; a.spos = w.spos;
   a.nlist = w.status + 1; a.list = w.list; a.status = w.status; a.rc = rc;
   a.novf = w.status + 2; a.ovf_rows = w.ovf_rows;
+  a.home = home_atoms(N);
   return a;
 }
 
@@ -978,8 +1191,6 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
   HGNN_REQUIRE(ws_bytes >= w.bytes, HGNN_ERR_WORKSPACE_TOO_SMALL, "radius graph workspace: need %zu bytes, got %zu",
                w.bytes, ws_bytes);
   *E_host = 0;
-  k_fill_i32<<<1, 64, 0, st>>>(w.status, 8, 0);
-  HGNN_LAUNCH_CHECK("k_fill_i32");
   if (N == 0 || G == 0) {
     k_fill_i32<<<1, 64, 0, st>>>(row_ptr, 1, 0);
     k_fill_i32<<<1, 64, 0, st>>>(w.colT_ptr, 1, 0);
@@ -987,53 +1198,62 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
     HGNN_HIP(wait_stream(st));
     return HGNN_OK;
   }
+  MailSlot mail;
+  HGNN_REQUIRE(mail.ok(), HGNN_ERR_HIP, "could not allocate the pinned result slot");
   // Everything below is enqueued in one go: a bad offset or cell is recorded in status[0], leaves every later
   // kernel with in-range (if meaningless) indices, keeps the search from running, and is reported after the one
-  // synchronisation at the end.
+  // wait at the end.
   {
     ProfScope ps(PT_NEIGH_SETUP, st);
-    k_graph_meta<<<G, 64, 0, st>>>(N, G, pos, graph_off, cell, pbc, rc, w.meta, w.nbins, w.status);
-    HGNN_LAUNCH_CHECK("k_graph_meta");
-    HGNN_TRY(exclusive_scan_i32(st, w.nbins, w.bin_off, G, w.scan));
-    k_set_bin_off<<<nblk(G, 256), 256, 0, st>>>(G, w.meta, w.bin_off);
-    HGNN_LAUNCH_CHECK("k_set_bin_off");
-    k_fill_i32<<<nblk(w.nzeroed, 256), 256, 0, st>>>(w.zeroed, w.nzeroed, 0);
-    HGNN_LAUNCH_CHECK("k_fill_i32");
-    k_bin_atoms_count<<<nblk(N, 256), 256, 0, st>>>(N, G, pos, graph_off, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt,
-                                                    w.status);
-    HGNN_LAUNCH_CHECK("k_bin_atoms_count");
-    HGNN_TRY(exclusive_scan_i32(st, w.bin_cnt, w.bin_start, w.maxbins, w.scan));
-    k_bin_atoms_fill<<<nblk(N, 256), 256, 0, st>>>(N, pos, w.atom_bin, w.bin_start, w.bin_cur, w.bin_atoms, w.spos);
-    HGNN_LAUNCH_CHECK("k_bin_atoms_fill");
-    k_bin_list<<<nblk(w.maxbins, 256), 256, 0, st>>>(w.maxbins, w.bin_cnt, w.status + 1, w.list);
-    HGNN_LAUNCH_CHECK("k_bin_list");
+    k_zero4<<<nblk(w.nzeroed / 4, 256), 256, 0, st>>>(reinterpret_cast<int4*>(w.zeroed), w.nzeroed / 4);
+    HGNN_LAUNCH_CHECK("k_zero4");
+    const int home = home_atoms(N);
+    if (N <= BIN_GRAPHS_MAX) {
+      const BinArgs a = {N, G, pos, graph_off, cell, pbc, rc, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt, w.bin_start,
+                         w.bin_atoms, w.spos, w.status, w.status + 1, w.list, home};
+      k_bin_graphs<<<G, 256, 0, st>>>(a);
+      HGNN_LAUNCH_CHECK("k_bin_graphs");
+    } else {
+      k_graph_meta<<<G, 64, 0, st>>>(N, G, pos, graph_off, cell, pbc, rc, w.meta, w.status);
+      HGNN_LAUNCH_CHECK("k_graph_meta");
+      k_bin_atoms_count<<<nblk(N, 256), 256, 0, st>>>(N, G, pos, graph_off, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt,
+                                                      w.status);
+      HGNN_LAUNCH_CHECK("k_bin_atoms_count");
+      HGNN_TRY(exclusive_scan_i32(st, w.bin_cnt, w.bin_start, w.maxbins, w.scan));
+      const unsigned na = nblk(N, 256);
+      k_bin_place<<<na + nblk(w.maxbins, 256), 256, 0, st>>>(N, na, pos, w.atom_bin, w.bin_start, w.bin_cnt, w.bin_atoms,
+                                                             w.spos, w.maxbins, home, w.status + 1, w.list);
+      HGNN_LAUNCH_CHECK("k_bin_place");
+    }
   }
   {
     ProfScope ps(PT_NEIGH_COUNT, st);
     SearchArgs a = search_args(w, N, pos, rc);
     a.deg = w.deg; a.colT_cnt = w.colT_cnt;
-    // without a search (bad input) the degrees must still be defined for the scans below
-    k_fill_i32<<<nblk(N, 256), 256, 0, st>>>(w.deg, N, 0);
     k_search<false><<<SR_GRID < N ? SR_GRID : N, 256, 0, st>>>(a);
     HGNN_LAUNCH_CHECK("k_search<count>");
   }
-  long long total = 0;
-  int32_t status_h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   {
     ProfScope ps(PT_NEIGH_SETUP, st);
-    HGNN_TRY(exclusive_scan_i32(st, w.colT_cnt, w.colT_ptr, N, w.scan));
-    HGNN_TRY(exclusive_scan_i32(st, w.deg, row_ptr, N, w.scan));
+    if (N <= SCAN_PAIR_MAX) {
+      k_scan_pair<<<dim3(nblk(N, SP_BLK), 2), 1024, 0, st>>>(w.deg, row_ptr, w.colT_cnt, w.colT_ptr, N, w.status, mail.dev());
+      HGNN_LAUNCH_CHECK("k_scan_pair");
+    } else {
+      HGNN_TRY(exclusive_scan_i32(st, w.colT_cnt, w.colT_ptr, N, w.scan));
+      HGNN_TRY(exclusive_scan_i32(st, w.deg, row_ptr, N, w.scan));
+      const int64_t nbs = ((int64_t)N + SCAN_BLK - 1) / SCAN_BLK;   // the grand total sits behind the block sums
+      k_post_total<<<1, 1, 0, st>>>(reinterpret_cast<long long*>(w.scan) + nbs, w.status, mail.dev());
+      HGNN_LAUNCH_CHECK("k_post_total");
+    }
   }
-  // grand total (int64) sits behind the block sums of the last scan
-  int64_t nbs = ((int64_t)N + SCAN_BLK - 1) / SCAN_BLK;
-  HGNN_HIP(hipMemcpyAsync(&total, reinterpret_cast<long long*>(w.scan) + nbs, sizeof(total), hipMemcpyDeviceToHost, st));
-  HGNN_HIP(hipMemcpyAsync(status_h, w.status, sizeof(status_h), hipMemcpyDeviceToHost, st));
-  HGNN_HIP(wait_stream(st));
-  HGNN_REQUIRE(!(status_h[0] & ST_BAD_OFFSETS), HGNN_ERR_BAD_OFFSETS,
+  HGNN_HIP(mail.wait(st));
+  const long long total = mail.value();
+  const int status_h = mail.status();
+  HGNN_REQUIRE(!(status_h & ST_BAD_OFFSETS), HGNN_ERR_BAD_OFFSETS,
                "graph_off must start at 0, be non-decreasing and end at N");
-  HGNN_REQUIRE(!(status_h[0] & ST_BAD_CELL), HGNN_ERR_BAD_CELL,
+  HGNN_REQUIRE(!(status_h & ST_BAD_CELL), HGNN_ERR_BAD_CELL,
                "a periodic graph has a singular cell or needs more than 127 images per direction");
-  HGNN_REQUIRE(!(status_h[0] & ST_OUT_OF_CELL), HGNN_ERR_BAD_CELL,
+  HGNN_REQUIRE(!(status_h & ST_OUT_OF_CELL), HGNN_ERR_BAD_CELL,
                "an atom of a periodic graph lies outside its cell (fractional coordinates must be in [0, 1])");
   HGNN_REQUIRE(total < (1ll << 31), HGNN_ERR_OVERFLOW, "edge count %lld does not fit int32", total);
   *E_host = total;
@@ -1065,9 +1285,6 @@ extern "C" int32_t hgnn_radius_graph_fill(void* stream, int32_t N, int32_t G, co
   }
   int32_t* key_j = static_cast<int32_t*>(tmp);
   int32_t* key_c = key_j + E;
-  // this call's own counters start at zero, so that a second fill after one count works as the first
-  k_fill2_i32<<<nblk((int64_t)N + 1, 256), 256, 0, st>>>(w.colT_cur, (int64_t)N + 1, w.status + 2, 1, 0);
-  HGNN_LAUNCH_CHECK("k_fill2_i32");
   if (E > 0) {
     {
       ProfScope ps(PT_NEIGH_FILL, st);
@@ -1077,21 +1294,20 @@ extern "C" int32_t hgnn_radius_graph_fill(void* stream, int32_t N, int32_t G, co
       k_search<true><<<SR_GRID < N ? SR_GRID : N, 256, 0, st>>>(a);
       HGNN_LAUNCH_CHECK("k_search<fill>");
     }
+  }
+  {
     ProfScope ps(PT_NEIGH_EMIT, st);
     // rows longer than the LDS row (their number is only known on the device: a fixed grid walks the list)
-    const unsigned lgrid = N < 256 ? nblk((int64_t)N * 64, 256) : 64;
-    k_long_rows<<<lgrid, 256, 0, st>>>(w.status + 2, w.ovf_rows, pos, w.meta, w.atom_graph, w.atom_bin, w.bin_start,
-                                       w.bin_atoms, rc, row_ptr, key_j, key_c, dst, col, shift, d2, rvec, w.colT_ptr,
-                                       w.colT_cur, permT);
+    const unsigned nlong = E == 0 ? 0 : (N < 256 ? nblk((int64_t)N * 64, 256) : 64);
+    k_long_rows<<<nlong + nblk((int64_t)(N > G ? N : G) + 1, 256), 256, 0, st>>>(
+        nlong, N, G, graph_off, edge_graph_ptr, colT_ptr, w.status + 2, w.ovf_rows, pos, w.meta, w.atom_graph, w.atom_bin,
+        w.bin_start, w.bin_atoms, rc, row_ptr, key_j, key_c, dst, col, shift, d2, rvec, w.colT_ptr, w.colT_cur, permT);
     HGNN_LAUNCH_CHECK("k_long_rows");
   }
-  ProfScope pst(PT_NEIGH_TRANSPOSE, st);
-  k_edge_graph_ptr<<<nblk(G + 1, 256), 256, 0, st>>>(G, graph_off, row_ptr, edge_graph_ptr);
-  HGNN_LAUNCH_CHECK("k_edge_graph_ptr");
-  k_copy_i32<<<nblk((int64_t)N + 1, 256), 256, 0, st>>>(w.colT_ptr, colT_ptr, (int64_t)N + 1);
-  HGNN_LAUNCH_CHECK("k_copy_i32");
   if (E > 0) {
-    k_rank_sources<<<nblk((int64_t)N * 64, 256), 256, 0, st>>>(N, colT_ptr, permT, key_j);   // the keys are dead by now
+    ProfScope pst(PT_NEIGH_TRANSPOSE, st);
+    // (the keys of the slow path are dead by now; the counters of the filling pass go back to zero)
+    k_rank_sources<<<nblk((int64_t)N * 64, 256), 256, 0, st>>>(N, colT_ptr, permT, key_j, w.colT_cur, w.status + 2);
     HGNN_LAUNCH_CHECK("k_rank_sources");
   }
   return HGNN_OK;

@@ -1,6 +1,7 @@
 // Kernel-class timing with HIP events (see prof.h) and its exported control functions.
 #include "prof.h"
 
+#include <mutex>
 #include <vector>
 
 #include "common.h"
@@ -8,6 +9,51 @@
 namespace hgnn {
 
 uint64_t g_prof_mask = 0;
+
+// ---------------------------------------------------------------------------------------------
+// result slots (see common.h): one pinned allocation of MAIL_SLOTS lines, made by the first call that needs one
+// ---------------------------------------------------------------------------------------------
+namespace {
+constexpr int MAIL_SLOTS = 256;
+struct alignas(64) MailLine { HostMail mail; };   // a cache line each: slots of two calls do not share one
+std::mutex g_mail_lock;
+MailLine* g_mail_lines = nullptr;
+std::vector<int> g_mail_free;
+}  // namespace
+
+MailSlot::MailSlot() : m_(nullptr) {
+  std::lock_guard<std::mutex> hold(g_mail_lock);
+  if (!g_mail_lines) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, sizeof(MailLine) * MAIL_SLOTS, hipHostMallocPortable) != hipSuccess) return;
+    g_mail_lines = static_cast<MailLine*>(p);
+    for (int k = MAIL_SLOTS - 1; k >= 0; --k) g_mail_free.push_back(k);
+  }
+  if (g_mail_free.empty()) return;
+  m_ = &g_mail_lines[g_mail_free.back()].mail;
+  g_mail_free.pop_back();
+  m_->value = 0;
+  m_->status = 0;
+  __atomic_store_n(&m_->posted, 0u, __ATOMIC_RELEASE);
+}
+
+MailSlot::~MailSlot() {
+  if (!m_) return;
+  std::lock_guard<std::mutex> hold(g_mail_lock);
+  g_mail_free.push_back((int)(reinterpret_cast<MailLine*>(m_) - g_mail_lines));
+}
+
+hipError_t MailSlot::wait(hipStream_t st) {
+  for (;;) {
+    for (int k = 0; k < 256; ++k)
+      if (__atomic_load_n(&m_->posted, __ATOMIC_ACQUIRE)) return hipSuccess;
+    const hipError_t e = hipStreamQuery(st);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess) return e;
+    // the stream has drained: the slot was posted before that, or the kernel that posts it did not run
+    return __atomic_load_n(&m_->posted, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
+  }
+}
 
 namespace {
 struct Rec {

@@ -1,0 +1,63 @@
+"""Radius graph at the sizes where its kernels hand over to one another: batches of one workgroup per graph against
+grid-wide binning, bins counted in LDS against memory, one-launch against block-sum scans."""
+import numpy as np
+import pytest
+
+import oracle
+from hgnn_inputs import concat_graphs, small_mixed_batch
+from parity_util import assert_graph_equal
+from test_gpu_parity import gpu_graph
+
+pytestmark = pytest.mark.gpu
+
+
+def repeated(b, times):
+    """The batch's graphs over and over, and the oracle's graph of it put together from one copy."""
+    graphs = [(b.pos[b.graph_off[g]:b.graph_off[g + 1]], b.Z[b.graph_off[g]:b.graph_off[g + 1]],
+               b.cell[g] if b.pbc[g] else None) for g in range(b.G)]
+    return concat_graphs(graphs * times)
+
+
+def repeated_graph(one, b, times):
+    r = np.arange(times, dtype=np.int64)
+    ptr = lambda a, step: np.concatenate([(a[:-1].astype(np.int64)[None] + step * r[:, None]).ravel(),
+                                          [a[-1] + step * (times - 1)]]).astype(np.int32)
+    ids = lambda a, step: (a.astype(np.int64)[None] + step * r[:, None]).ravel().astype(np.int32)
+    E, N = one["E"], b.N
+    return dict(E=E * times, row_ptr=ptr(one["row_ptr"], E), colT_ptr=ptr(one["colT_ptr"], E),
+                edge_graph_ptr=ptr(one["edge_graph_ptr"], E), dst=ids(one["dst"], N), col=ids(one["col"], N),
+                permT=ids(one["permT"], E), shift=np.tile(one["shift"], (times, 1)), d2=np.tile(one["d2"], times),
+                rvec=np.tile(one["rvec"], (times, 1)))
+
+
+@pytest.mark.parametrize("atoms", [16384, 16385, 131072, 131073])
+def test_graph_of_many_small_structures(atoms):
+    print("many small structures", atoms, flush=True)
+    b = small_mixed_batch(11, n_mol=6, n_cry=2)
+    times = atoms // b.N
+    rest = atoms - times * b.N
+    one = oracle.radius_graph(b.pos, b.graph_off, b.cell, b.pbc, 4.0)
+    many = repeated(b, times)
+    want = repeated_graph(one, b, times)
+    if rest:     # fill up to the exact number with far-away single atoms: no edges
+        lone = [(np.zeros((1, 3), np.float32), np.ones(1, np.int32))] * rest
+        graphs = [(many.pos[many.graph_off[g]:many.graph_off[g + 1]], many.Z[many.graph_off[g]:many.graph_off[g + 1]],
+                   many.cell[g] if many.pbc[g] else None) for g in range(many.G)]
+        many = concat_graphs(graphs + lone)
+        for k in ("row_ptr", "colT_ptr", "edge_graph_ptr"):
+            want[k] = np.concatenate([want[k], np.full(rest, want["E"], np.int32)])
+    assert many.N == atoms
+    assert_graph_equal(gpu_graph(many, 4.0).to_numpy(), want)
+
+
+@pytest.mark.parametrize("side", [40.0, 60.0])
+def test_graph_of_a_sparse_structure_with_thousands_of_bins(side):
+    """1,300 atoms in a large box: about 2,700 and 5,200 bins, on either side of what the workgroup counts in LDS."""
+    print("sparse structure", side, flush=True)
+    rng = np.random.default_rng(5)
+    b = concat_graphs([(rng.uniform(0, side, (1300, 3)).astype(np.float32), np.ones(1300, np.int32))])
+    rc = 2.85
+    assert (np.floor(side / (1.001 * rc)) ** 3 > 4096) == (side > 50)
+    want = oracle.radius_graph(b.pos, b.graph_off, b.cell, b.pbc, rc)
+    assert want["E"] > 100
+    assert_graph_equal(gpu_graph(b, rc).to_numpy(), want)
