@@ -1,5 +1,6 @@
-"""Radius graph at the sizes where its kernels hand over to one another: batches of one workgroup per graph against
-grid-wide binning, bins counted in LDS against memory, one-launch against block-sum scans."""
+"""Radius graph and routing plan at the sizes where their kernels hand over to one another: batches of one workgroup per
+graph against grid-wide binning, bins counted in LDS against memory, one-launch against block-sum scans, sources placed by
+sixteen wavefronts against one."""
 import numpy as np
 import pytest
 
@@ -61,3 +62,28 @@ def test_graph_of_a_sparse_structure_with_thousands_of_bins(side):
     want = oracle.radius_graph(b.pos, b.graph_off, b.cell, b.pbc, rc)
     assert want["E"] > 100
     assert_graph_equal(gpu_graph(b, rc).to_numpy(), want)
+
+
+@pytest.mark.parametrize("G,S", [(1, 1), (63, 5), (65, 5), (1024, 64), (1025, 64), (2100, 64), (2100, 65)])
+def test_routing_plan_sizes(G, S):
+    import torch
+    from paper_2506_21788_amd import binding as B
+    print("routing plan", G, S, flush=True)
+    rng = np.random.default_rng(G + S)
+    sizes = rng.integers(0, 5, G)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    src = rng.integers(0, S, G).astype(np.int32)
+    N = int(off[-1])
+    plan = torch.full((B.multihead_plan_ints(N, G, S),), -7, dtype=torch.int32, device="cuda")
+    B.multihead_plan(N, G, S, torch.as_tensor(off).cuda(), torch.as_tensor(src).cuda(), plan)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in B.plan_fields(plan, N, G, S).items()}
+    # stable: graphs in batch order inside a source, atoms in graph order
+    order = np.argsort(src, kind="stable")
+    assert np.array_equal(got["graph_perm"], order)
+    assert np.array_equal(got["grp_graph_ptr"], np.searchsorted(src[order], np.arange(S + 1)))
+    atoms = np.concatenate([np.arange(off[g], off[g + 1]) for g in order]) if N else np.zeros(0)
+    assert np.array_equal(got["atom_perm"], atoms)
+    ag = np.repeat(np.arange(G), sizes)
+    assert np.array_equal(got["atom_graph"], ag)
+    assert np.array_equal(got["grp_atom_ptr"], np.searchsorted(src[ag][got["atom_perm"]], np.arange(S + 1)))
