@@ -43,18 +43,25 @@ __device__ __forceinline__ unsigned f2bf_bits(float x) { return pack_bf16x2(x, 0
 // 2^-23 |x||y| together, the size of the rounding of an fp32 product. The matrix cores run bf16 sixteen times as
 // fast as fp32, so the six products cost three eighths of the one.
 typedef unsigned u32x4_t_ __attribute__((ext_vector_type(4)));
+// two values as three bf16 pairs (x0 in the low halves)
+__device__ __forceinline__ void split_bf16x3_pair(float x0, float x1, unsigned (&o)[3]) {
+  const unsigned h = pack_bf16x2(x0, x1);
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+  const unsigned m = pack_bf16x2(r0, r1);
+  const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
+  o[0] = h;
+  o[1] = m;
+  o[2] = pack_bf16x2(s0, s1);
+}
 __device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8_t (&o)[3]) {
   u32x4_t_ w[3];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const float x0 = x[2 * t], x1 = x[2 * t + 1];
-    const unsigned h = pack_bf16x2(x0, x1);
-    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
-    const unsigned m = pack_bf16x2(r0, r1);
-    const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
-    w[0][t] = h;
-    w[1][t] = m;
-    w[2][t] = pack_bf16x2(s0, s1);
+    unsigned p[3];
+    split_bf16x3_pair(x[2 * t], x[2 * t + 1], p);
+    w[0][t] = p[0];
+    w[1][t] = p[1];
+    w[2][t] = p[2];
   }
 #pragma unroll
   for (int q = 0; q < 3; ++q) o[q] = __builtin_bit_cast(bf16x8_t, w[q]);

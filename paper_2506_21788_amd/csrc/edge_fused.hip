@@ -31,8 +31,15 @@ struct ECfg {
   static constexpr int WR = 4 / WC;                   // wavefronts over rows
   static constexpr int RB = (TM / 32) / WR;           // 32-row blocks per wavefront
   static constexpr int CB = NCB / WC;                 // 32-column blocks per wavefront
-  static constexpr int STRIDE = BF16 ? H + 8 : H + 4; // LDS row pitch (elements)
-  static constexpr size_t LDS_BYTES = (size_t)TM * STRIDE * (BF16 ? 2 : 4);
+  // fp32 operands: the A tile is kept as three bf16 planes (hi | mid | lo), split once by the wavefront that forms the
+  // value. Split as it is read, every value was split by each of the WC wavefronts, a quarter of the kernel's vector
+  // work at H = 128. At H = 256 three planes (101 KB) would leave one workgroup per compute unit instead of two: fp32.
+  static constexpr bool PLANES = !BF16 && H <= 128;
+  static constexpr int STRIDE = BF16 || PLANES ? H + 8 : H + 4; // LDS row pitch (elements)
+  // one 32-bit word of P, Q per lane and edge (bf16 pairs, or one column block): gathers are software-pipelined
+  static constexpr bool WORD = BF16 || CB == 1;
+  static constexpr size_t PLANE_BYTES = (size_t)TM * STRIDE * 2;   // one bf16 plane
+  static constexpr size_t LDS_BYTES = BF16 ? PLANE_BYTES : PLANES ? 3 * PLANE_BYTES : (size_t)TM * STRIDE * 4;
 };
 
 __device__ __forceinline__ float bf_bits_to_f(unsigned short b) { return __uint_as_float(((unsigned)b) << 16); }
@@ -57,10 +64,12 @@ __device__ __forceinline__ char* uoff(void* base, size_t bytes) { return reinter
 // 8 accumulator-mapped values of one half of a 32x32 block (column n of the tile, registers v = 8*vh .. 8*vh+7,
 // rows rbase + 8*(v>>2) + 4g + (v&3)): written row-major into the LDS tile and, operand-packed, to memory.
 // bf16 values are converted once. packed == null: only the LDS tile is written.
-template <bool BF16, int STRIDE>
+template <int H, bool BF16>
 __device__ __forceinline__ void emit_half(unsigned char* smem, int rbase, int g, int n, const float* vals, int vh,
                                           void* packed, size_t blk, int lane) {
-  if (BF16) {
+  using C = ECfg<H, BF16>;
+  constexpr int STRIDE = C::STRIDE;
+  if constexpr (BF16) {
     unsigned pk[4];
     unsigned short* s16 = reinterpret_cast<unsigned short*>(smem);
 #pragma unroll
@@ -76,9 +85,24 @@ __device__ __forceinline__ void emit_half(unsigned char* smem, int rbase, int g,
       if (packed) stg_nt<u32x4_t>(uoff(packed, (blk * 2 + vh) * 1024), lane * 16u, w);
     }
   } else {
-    float* s32 = reinterpret_cast<float*>(smem);
+    if constexpr (C::PLANES) {
+      unsigned short* s16 = reinterpret_cast<unsigned short*>(smem);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s32[(rbase + 8 * (2 * vh + (u >> 2)) + 4 * g + (u & 3)) * STRIDE + n] = vals[u];
+      for (int t = 0; t < 4; ++t) {
+        unsigned w[3];
+        split_bf16x3_pair(vals[2 * t], vals[2 * t + 1], w);
+        const int row = rbase + 8 * (2 * vh + (t >> 1)) + 4 * g + 2 * (t & 1);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          s16[q * (int)(C::PLANE_BYTES / 2) + row * STRIDE + n] = (unsigned short)(w[q] & 0xffffu);
+          s16[q * (int)(C::PLANE_BYTES / 2) + (row + 1) * STRIDE + n] = (unsigned short)(w[q] >> 16);
+        }
+      }
+    } else {
+      float* s32 = reinterpret_cast<float*>(smem);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s32[(rbase + 8 * (2 * vh + (u >> 2)) + 4 * g + (u & 3)) * STRIDE + n] = vals[u];
+    }
     char* pb = uoff(packed, (blk * 4 + 2 * vh) * 1024);
     const f32x4_t w0 = {vals[0], vals[1], vals[2], vals[3]};
     const f32x4_t w1 = {vals[4], vals[5], vals[6], vals[7]};
@@ -113,7 +137,7 @@ typedef unsigned u32x4_buf_t __attribute__((ext_vector_type(4)));
 template <int H, bool BF16>
 struct BRing {
   static constexpr int NKB = H / 16;
-  static constexpr int D = BF16 ? (NKB < 4 ? NKB : 4) : 2;   // steps in flight
+  static constexpr int D = BF16 || ECfg<H, BF16>::PLANES ? (NKB < 4 ? NKB : 4) : 2;   // steps in flight
   static constexpr int P = BF16 ? 1 : 3;                      // planes of B (fp32 operands: three bf16 terms)
   bf16x8_t b[D][ECfg<H, BF16>::CB][P];
   __amdgpu_buffer_rsrc_t rsrc;
@@ -174,8 +198,37 @@ __device__ __forceinline__ void tile_mma(const unsigned char* smem, const void* 
       // (without this the scheduler moves every refill down to the step that uses it)
       __builtin_amdgcn_sched_barrier(0);
     }
+  } else if constexpr (C::PLANES) {
+    // fp32 operands, A as three bf16 planes in LDS, B as three bf16 planes from L2 (launch_pack_x3): six bf16
+    // products per step of 16 k (see split_bf16x3); A fragments one step ahead
+    constexpr int NKB = H / 16;
+    constexpr int D = BRing<H, BF16>::D;
+    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * C::STRIDE + (lane >> 5) * 8) * 2);
+    asm volatile("" : "+v"(ao));
+    bf16x8_t a[2][C::RB][3];
+#pragma unroll
+    for (int i = 0; i < C::RB; ++i)
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        a[0][i][q] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * C::STRIDE) * 2 + q * C::PLANE_BYTES);
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      if (kb + 1 < NKB) {
+#pragma unroll
+        for (int i = 0; i < C::RB; ++i)
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            a[(kb + 1) & 1][i][q] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * C::STRIDE + (kb + 1) * 16) * 2 + q * C::PLANE_BYTES);
+      }
+#pragma unroll
+      for (int j = 0; j < C::CB; ++j)
+#pragma unroll
+        for (int i = 0; i < C::RB; ++i) acc[i][j] = mfma_bf16x3(a[kb & 1][i], ring.b[kb % D][j], kb == 0 ? zero : acc[i][j]);
+      if (kb + D < NKB) tile_b_load<H, BF16>(ring, wc, kb + D, ring.b[kb % D]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   } else {
-    // fp32 operands: the A tile stays fp32 in LDS and is split into three bf16 terms as it is read; B comes as
+    // fp32 operands at H = 256: the A tile stays fp32 in LDS and is split into three bf16 terms as it is read; B comes as
     // three bf16 planes (launch_pack_x3); six bf16 products per step of 16 k (see split_bf16x3)
     constexpr int NKB = H / 16;
     constexpr int D = BRing<H, BF16>::D;
@@ -298,6 +351,12 @@ struct PQPitch {
   static constexpr unsigned ROW = PAIRS ? H * 4u : 2u * H * 4u;
   static constexpr unsigned QOFF = PAIRS ? H * 2u : H * 4u;   // byte offset of the Q half inside a row
 };
+
+// column j of a gathered word: a half of a bf16 pair, or the word itself (fp32)
+template <bool PAIRS>
+__device__ __forceinline__ float word_column(unsigned w, int j) {
+  return !PAIRS ? __uint_as_float(w) : j == 0 ? __uint_as_float(w << 16) : __uint_as_float(w & 0xffff0000u);
+}
 
 // z1 = P[dst] + Q[col] + d2*w1d for 8 edges and this lane's CB column blocks. colb = byte offset of this
 // lane's first column inside the P half of a row.
@@ -437,13 +496,13 @@ __device__ __forceinline__ void attr_z1_block(const unsigned short* at, int rblk
 // ---------------------------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------------------------
-// Gathers of one group of 8 edges (bf16 pairs): the pair words of P[dst] and Q[col] and d2, from the tile's
-// scalars in LDS. Group gi of a wavefront: row block gi >> 1, register half gi & 1.
+// Gathers of one group of 8 edges (one 32-bit word per lane and edge: bf16 pairs, or the single fp32 column of the
+// variants with one column block per lane): the words of P[dst] and Q[col] and d2, from the tile's scalars in LDS. Group gi of a wavefront: row block gi >> 1, register half gi & 1.
 template <int H, bool BF16>
 __device__ __forceinline__ void fwd_issue_group(const void* PQ, const int* s, int wr, int gi, int g, unsigned colb,
                                                 unsigned (&wpo)[8], unsigned (&wqo)[8], float (&ddo)[8]) {
   using C = ECfg<H, BF16>;
-  using PQP = PQPitch<H, true>;
+  using PQP = PQPitch<H, BF16 && C::CB == 2>;
   const int rblk = wr * C::RB + (gi >> 1), vh = gi & 1;
   int di[8], ci[8];
   lds_rows8(s, rblk, vh, g, di);
@@ -457,7 +516,7 @@ __device__ __forceinline__ void fwd_issue_group(const void* PQ, const int* s, in
 }
 
 // One tile of the forward kernel. FULL: all TM edges of the tile exist (no masking anywhere).
-// wp0 / wq0 / dd0 (bf16 pairs only): the gathers of this tile's first group, asked for at the end of the previous
+// wp0 / wq0 / dd0 (one word per lane and edge only, see ECfg::WORD): the gathers of this tile's first group, asked for at the end of the previous
 // tile; on return they hold those of the next tile's first group.
 // ATTR: k > 1 edge attributes take the place of the d2 term (at: this tile's attributes in LDS, at_next / nxa: where and
 // what to store for the next tile, bW1a: this lane's attribute weights as matrix-core operands).
@@ -480,7 +539,7 @@ __device__ __forceinline__ void edge_fwd_tile(
     for (int i = 0; i < C::RB; ++i) attr_z1_block<C::CB>(at, wr * C::RB + i, lane, bW1a, zat[i]);
   }
   // ---- produce a1 for this wavefront's blocks: memory (operand-packed) and LDS (row-major)
-  if constexpr (PAIRS && FULL) {
+  if constexpr (C::WORD && FULL) {
     // Groups of 8 edges, software-pipelined: the gathers of the next group are in flight while this one is turned
     // into a1 (the accumulator registers are free in this phase and hold the second set of gathered words; a third
     // set would spill).
@@ -506,12 +565,11 @@ __device__ __forceinline__ void edge_fwd_tile(
         float vals[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const float zp = j == 0 ? __uint_as_float(wpc[u] << 16) : __uint_as_float(wpc[u] & 0xffff0000u);
-          const float zq = j == 0 ? __uint_as_float(wqc[u] << 16) : __uint_as_float(wqc[u] & 0xffff0000u);
+          const float zp = word_column<PAIRS>(wpc[u], j), zq = word_column<PAIRS>(wqc[u], j);
           if constexpr (ATTR) vals[u] = silu_f(zp + zq + zat[gi >> 1][j][8 * (gi & 1) + u]);
           else vals[u] = silu_f(zp + zq + ddc[u] * w1d[j]);
         }
-        emit_half<BF16, C::STRIDE>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
       }
     }
   } else
@@ -541,7 +599,7 @@ __device__ __forceinline__ void edge_fwd_tile(
           else vals[u] = silu_f(z[j][u]);
           if (!FULL && !((ok >> u) & 1u)) vals[u] = 0.f;
         }
-        emit_half<BF16, C::STRIDE>(smem, rblk * 32, g, n, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16>(smem, rblk * 32, g, n, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
       }
     }
   }
@@ -570,9 +628,6 @@ __device__ __forceinline__ void edge_fwd_tile(
 #pragma unroll
       for (int v = 0; v < 16; ++v)
         stg_nt<unsigned>(o, lane * 4u + v * 256u, pack_bf16x2(acc[i][0][v] + b2[0], acc[i][1][v] + b2[1]));
-      // the next tile's scalars are in LDS now: its first gathers travel behind the first block's stores, whose
-      // accumulators are free by then (past the last tile the scalars are zeros and the gathers read row 0)
-      if (FULL && i == 0) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
     } else {
 #pragma unroll
       for (int j = 0; j < C::CB; ++j) {
@@ -592,8 +647,13 @@ __device__ __forceinline__ void edge_fwd_tile(
         }
       }
     }
+    // the next tile's scalars are in LDS now: its first gathers travel behind the first block's stores, whose
+    // accumulators are free by then (past the last tile the scalars are zeros and the gathers read row 0)
+    if constexpr (C::WORD && FULL) {
+      if (i == 0) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
+    }
   }
-  if constexpr (PAIRS && !FULL) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
+  if constexpr (C::WORD && !FULL) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
 }
 
 template <int H, bool BF16, bool BRES_REQ, bool ATTR>
@@ -628,9 +688,9 @@ __global__ void __launch_bounds__(256, 2) k_edge_fwd(EdgeFwdArgs p, int ntiles) 
     if constexpr (ATTR) store_attr4(atb, tid, fetch_attr4(p.attr, p.k, tr.first, tr.end, E, tid));
   }
   __syncthreads();
-  unsigned wp0[8], wq0[8];   // bf16 pairs: gathers of the coming tile's first group (see edge_fwd_tile)
+  unsigned wp0[8], wq0[8];   // gathers of the coming tile's first group (see edge_fwd_tile)
   float dd0[8];
-  if constexpr (BF16 && C::CB == 2)
+  if constexpr (C::WORD)
     fwd_issue_group<H, BF16>(p.PQ, sc, wr, 0, lane >> 5, (unsigned)(wc * 32 + x) * 4u, wp0, wq0, dd0);
   int buf = 0;
   for (int tile = tr.first; tile < tr.end; tile += tr.step, buf ^= 1) {
@@ -1205,8 +1265,8 @@ int32_t launch_edge_cvec(hipStream_t st, int64_t E, const int32_t* dst, const fl
 // slot-major; *_next / nxa: where and what to store for the next tile; bW1a: the attribute weights as matrix-core
 // operands; gacc: running g_W1a of this wavefront's columns, slots in the accumulator rows).
 template <int H, bool BF16, bool FULL, bool ATTR, bool DSUM>
-__device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned char* smem, const int* s, int* s_next,
-                                              int nxt, int tile, int E, int tid, int wr, int wc, int lane,
+__device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned char* smem, const int* s, const int* sc,
+                                              int* s_new, int nxt, int tile, int E, int tid, int wr, int wc, int lane,
                                               const float (&w1d)[ECfg<H, BF16>::CB], const float (&wxn)[ECfg<H, BF16>::CB],
                                               float (&sb2)[ECfg<H, BF16>::CB], float (&swx)[ECfg<H, BF16>::CB],
                                               float (&sw1)[ECfg<H, BF16>::CB], const unsigned short* at,
@@ -1217,13 +1277,15 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   constexpr bool PAIRS = BF16 && C::CB == 2;
   constexpr unsigned GM_ROW = PAIRS ? H * 2u : 2u * H * 4u;   // row pitch of g_M in bytes (checked by the launcher)
   const int g = lane >> 5, x = lane & 31;
+  const int *s_col = sc + 2 * C::TM, *s_d2 = sc + 3 * C::TM, *s_c = sc + 4 * C::TM;
   // byte offset of this lane's first column inside a row: word wc*32 + x of bf16 pairs, else column wc*CB*32 + x
   const unsigned colb = (unsigned)((PAIRS ? wc * 32 : wc * C::CB * 32) + x) * 4u;
   static_assert(!DSUM || ((PAIRS || (!BF16 && H == 128)) && !ATTR),
                 "the in-kernel destination sums take 128 words per edge (bf16 pairs at H = 256, fp32 at H = 128)");
   // DSUM: the last phase also leaves the tile's g_z1 words row-major in LDS (row pitch of the A tile, which is no
   // longer needed then); this lane writes word wc*32 + x of the rows 4g + (constant)
-  constexpr int DPITCH = PAIRS ? C::STRIDE / 2 : C::STRIDE;
+  constexpr int DPITCH = PAIRS ? C::STRIDE / 2 : H + 4;
+  static_assert(!DSUM || (size_t)C::TM * DPITCH * 4 <= C::LDS_BYTES, "the words of g_z1 take the place of the A tile");
   unsigned* dsw = reinterpret_cast<unsigned*>(smem) + (4 * g) * DPITCH + wc * 32 + x;
   // the destinations of the edges next to the tile decide whether its first and last row are complete here
   int dprev = -1, dnext = -1;
@@ -1232,7 +1294,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
     if ((tile + 1) * C::TM < E) dnext = p.dst[(size_t)(tile + 1) * C::TM];
   }
   // ---- g_z2 = (alpha*g_M[dst] + c*wx) * silu'(z2): operand-packed to memory, row-major to LDS
-  if constexpr (PAIRS && FULL) {
+  if constexpr (C::WORD && FULL) {
     // groups of 8 edges, software-pipelined: the loads of the next group are in flight while this one is processed
     // (the accumulator registers are free in this phase; the same in the last phase, where they are not, spills)
     constexpr int NG = C::RB * 2;
@@ -1243,10 +1305,16 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
       const int eb = tile * (C::TM / 32) + rblk;
       int di[8];
       lds_rows8(s, rblk, vh, g, di);
-      lds_rows8(s + 3 * C::TM, rblk, vh, g, co);
-      const char* zp = uoff(p.z2_vm, (((size_t)eb * (C::NCB / 2) + wc) * 16 + 8 * vh) * 256);
+      lds_rows8(s_c, rblk, vh, g, co);
+      if constexpr (PAIRS || !BF16) {
+        const char* zp = uoff(p.z2_vm, (((size_t)eb * (PAIRS ? C::NCB / 2 : C::NCB) + wc) * 16 + 8 * vh) * 256);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) zo[u] = ldg_nt<unsigned>(zp, lane * 4u + u * 256u);
+        for (int u = 0; u < 8; ++u) zo[u] = ldg_nt<unsigned>(zp, lane * 4u + u * 256u);
+      } else {
+        const char* zp = uoff(p.z2_vm, (((size_t)eb * C::NCB + wc) * 16 + 8 * vh) * 128);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) zo[u] = (unsigned)ldg_nt<unsigned short>(zp, lane * 2u + u * 128u) << 16;
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u) go[u] = ldg_u32(p.gM, (unsigned)di[u] * GM_ROW + colb);
     };
@@ -1263,16 +1331,16 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
         float vals[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const float zz = j == 0 ? __uint_as_float(zw[sl][u] << 16) : __uint_as_float(zw[sl][u] & 0xffff0000u);
-          const float gmv = j == 0 ? __uint_as_float(gw[sl][u] << 16) : __uint_as_float(gw[sl][u] & 0xffff0000u);
+          const float zz = word_column<PAIRS>(zw[sl][u], j);
+          const float gmv = word_column<PAIRS>(gw[sl][u], j);
           float m, dm;
           silu_both(zz, m, dm);
-          const float gz = fmaf(cc[sl][u], wxn[j], gmv) * dm;   // the pair form holds alpha * g_M
+          const float gz = fmaf(cc[sl][u], wxn[j], PAIRS ? gmv : p.alpha * gmv) * dm;   // the pair form holds alpha * g_M
           vals[u] = gz;
           sb2[j] += gz;
           swx[j] += cc[sl][u] * m;
         }
-        emit_half<BF16, C::STRIDE>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
       }
 #pragma unroll
       for (int j = 0; j < C::CB; ++j) asm volatile("" : "+v"(sb2[j]), "+v"(swx[j]));
@@ -1288,7 +1356,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
       int di[8];
       float cc[8];
       lds_rows8(s, rblk, vh, g, di);
-      lds_rows8(s + 3 * C::TM, rblk, vh, g, cc);
+      lds_rows8(s_c, rblk, vh, g, cc);
       const unsigned ok = FULL ? 0xffu : rows8_mask(eb, vh, g, E);
       float gm[C::CB][8];
       unsigned zw[8];   // PAIRS: z2 of both column blocks, one word per edge
@@ -1333,7 +1401,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
           sb2[j] += gz;
           swx[j] += cc[u] * m;
         }
-        emit_half<BF16, C::STRIDE>(smem, rblk * 32, g, n, vals, vh, p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16>(smem, rblk * 32, g, n, vals, vh, p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
       }
       // the running column sums are complete for this group here: without this the compiler defers their chains
       // past the matrix product and keeps every operand alive (in scratch memory) until then
@@ -1346,7 +1414,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   __syncthreads();
   f32x16_t acc[C::RB][C::CB];
   tile_mma<H, BF16>(smem, p.W2Tp, wr, wc, lane, acc, ring);
-  s_next[tid] = nxt;
+  s_new[0] = nxt;
   if constexpr (ATTR) {
     store_attr4(at_next, tid, nxa);
     store_attr4_t(att_next, tid, nxa);
@@ -1354,16 +1422,16 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   __syncthreads();
   f32x16_t zat[C::CB];   // ATTR: attribute term of z1 of the 32-edge block at hand
   // ---- g_z1 = g_a1 * silu'(z1), z1 recomputed from the projected node features
-  if constexpr (PAIRS && FULL) {
+  if constexpr (C::WORD && FULL) {
     // the same pipelining; d2 is read from LDS when it is used so that only the gathered words live twice
-    using PQP = PQPitch<H, true>;
+    using PQP = PQPitch<H, PAIRS>;
     constexpr int NG = C::RB * 2;
     unsigned wp[2][8], wq[2][8];
     auto issue = [&](int gi, unsigned (&wpo)[8], unsigned (&wqo)[8]) {
       const int rblk = wr * C::RB + (gi >> 1), vh = gi & 1;
       int di[8], ci[8];
       lds_rows8(s, rblk, vh, g, di);
-      lds_rows8(s + C::TM, rblk, vh, g, ci);
+      lds_rows8(s_col, rblk, vh, g, ci);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         wpo[u] = ldg_u32(p.PQ, (unsigned)di[u] * PQP::ROW + colb);
@@ -1379,30 +1447,36 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
       const int rblk = wr * C::RB + i;
       const int eb = tile * (C::TM / 32) + rblk;
       float dd[8];
-      if constexpr (!ATTR) lds_rows8(s + 2 * C::TM, rblk, vh, g, dd);
+      if constexpr (!ATTR) lds_rows8(s_d2, rblk, vh, g, dd);
       if constexpr (ATTR) {
         if (vh == 0) attr_z1_block<C::CB>(at, rblk, lane, bW1a, zat);
       }
-      char* o = uoff(p.gz1_vm, (((size_t)eb * (C::NCB / 2) + wc) * 16 + 8 * vh) * 256);
-      float ga[2][8];
+      float ga[C::CB][8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float t0 = ATTR ? zat[0][8 * vh + u] : dd[u] * w1d[0];
-        const float t1 = ATTR ? zat[1][8 * vh + u] : dd[u] * w1d[1];
-        const float z0 = __uint_as_float(wp[sl][u] << 16) + __uint_as_float(wq[sl][u] << 16) + t0;
-        const float z1 = __uint_as_float(wp[sl][u] & 0xffff0000u) + __uint_as_float(wq[sl][u] & 0xffff0000u) + t1;
-        const float g0 = acc[i][0][8 * vh + u] * dsilu_f(z0);
-        const float g1 = acc[i][1][8 * vh + u] * dsilu_f(z1);
-        if constexpr (ATTR) {
-          ga[0][u] = g0;
-          ga[1][u] = g1;
-        } else {
-          sw1[0] += dd[u] * g0;
-          sw1[1] += dd[u] * g1;
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j) {
+          const float z = word_column<PAIRS>(wp[sl][u], j) + word_column<PAIRS>(wq[sl][u], j) +
+                          (ATTR ? zat[j][8 * vh + u] : dd[u] * w1d[j]);
+          ga[j][u] = acc[i][j][8 * vh + u] * dsilu_f(z);
+          if constexpr (!ATTR) sw1[j] += dd[u] * ga[j][u];
         }
-        const unsigned pw = pack_bf16x2(g0, g1);
-        stg_nt<unsigned>(o, lane * 4u + u * 256u, pw);
-        if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = pw;
+      if constexpr (PAIRS || !BF16) {
+        char* o = uoff(p.gz1_vm, (((size_t)eb * (PAIRS ? C::NCB / 2 : C::NCB) + wc) * 16 + 8 * vh) * 256);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const unsigned pw = PAIRS ? pack_bf16x2(ga[0][u], ga[C::CB - 1][u]) : __float_as_uint(ga[0][u]);
+          stg_nt<unsigned>(o, lane * 4u + u * 256u, pw);
+          if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = pw;
+        }
+      } else {
+        char* o = uoff(p.gz1_vm, (((size_t)eb * C::NCB + wc) * 16 + 8 * vh) * 128);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const unsigned pk = pack_bf16x2(ga[0][2 * t], ga[0][2 * t + 1]);
+          stg_nt<unsigned short>(o, lane * 2u + (2 * t) * 128u, (unsigned short)(pk & 0xffffu));
+          stg_nt<unsigned short>(o, lane * 2u + (2 * t + 1) * 128u, (unsigned short)(pk >> 16));
+        }
       }
       if constexpr (ATTR) {
         const bf16x8_t aT = attr_t_operand(att, rblk, vh, lane);
@@ -1425,8 +1499,8 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
       int di[8], ci[8];
       float dd[8];
       lds_rows8(s, rblk, vh, g, di);
-      lds_rows8(s + C::TM, rblk, vh, g, ci);
-      lds_rows8(s + 2 * C::TM, rblk, vh, g, dd);
+      lds_rows8(s_col, rblk, vh, g, ci);
+      lds_rows8(s_d2, rblk, vh, g, dd);
       float z[C::CB][8];
       gather_z1<H, C::CB, PAIRS>(p.PQ, di, ci, dd, w1d, colb, z);
       if constexpr (ATTR) {
@@ -1491,7 +1565,13 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
     static_assert(C::TM == 64 && DSUM_UNIT == C::TM, "one partial unit per tile, walked as two halves of 32 edges");
     __syncthreads();
     const unsigned* gw = reinterpret_cast<const unsigned*>(smem);
-    float2* carry = reinterpret_cast<float2*>(smem + C::LDS_BYTES + 8 * C::TM * 4);   // [128], see below
+    // [128] carried parts, see below. With planes they sit in the 16 bytes of padding behind each row of the last
+    // plane, which nothing else writes: 1 KB more would leave two workgroups per compute unit instead of three.
+    static_assert(!C::PLANES || ((size_t)C::TM * DPITCH * 4 <= 2 * C::PLANE_BYTES && 2 * C::TM == 128), "two carried parts per row");
+    auto carry = [&](int k) -> float2& {
+      return *reinterpret_cast<float2*>(C::PLANES ? smem + 2 * C::PLANE_BYTES + (k >> 1) * (C::STRIDE * 2) + H * 2 + (k & 1) * 8
+                                                  : smem + C::LDS_BYTES + 5 * C::TM * 4 + k * 8);
+    };
     const int hf = __builtin_amdgcn_readfirstlane(tid >> 7);   // the half of the tile that this wavefront walks
     const int w = tid & 127;
     const int dl = s[lane];
@@ -1531,7 +1611,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
       auto flush = [&](bool ef, bool last) {
         const int d = __builtin_amdgcn_readfirstlane(s[32 * hf + k0]);
         if (hf == 0 && last && cont) {
-          carry[w] = make_float2(a0, a1);
+          carry(w) = make_float2(a0, a1);
         } else if (hf == 1 && first && cont) {
           c0 = a0; c1 = a1; cd = d; cef = ef;
         } else {
@@ -1560,7 +1640,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
     }
     __syncthreads();   // the next tile's first phase writes the A tile again; the carried parts are in LDS
     if (hf == 1 && cont) {
-      const float2 c = carry[w];   // (written again two barriers into the next tile at the earliest)
+      const float2 c = carry(w);   // (written again two barriers into the next tile at the earliest)
       put((starts & 0xffffffffull) != 0ull, cef, cd, c.x + c0, c.y + c1);
     }
   }
@@ -1571,9 +1651,12 @@ __global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, i
   using C = ECfg<H, BF16>;
   static_assert(!ATTR || (BF16 && C::TM == 64), "edge attributes: bf16 operands, 64-edge tiles");
   extern __shared__ __align__(16) unsigned char smem[];
-  int* sc = reinterpret_cast<int*>(smem + C::LDS_BYTES);   // [2][4][TM] per-edge scalars dst|col|d2|c, double buffered
+  // Per-edge scalars [5][TM]: dst of this and the next tile | col | d2 | c. All are stored between the two barriers
+  // around the product: c (read before it only) is the next tile's by then, col and d2 (read behind it only) are this
+  // tile's and were asked for when the tile began. Twice all four would not leave room for three workgroups with planes.
+  int* sc = reinterpret_cast<int*>(smem + C::LDS_BYTES);
   // ATTR: [2][ATTR_TILE] attributes edge-major, then [2][ATTR_T_TILE] slot-major
-  unsigned short* atb = reinterpret_cast<unsigned short*>(smem + C::LDS_BYTES + 8 * C::TM * 4);
+  unsigned short* atb = reinterpret_cast<unsigned short*>(smem + C::LDS_BYTES + 5 * C::TM * 4);
   unsigned short* attb = atb + 2 * ATTR_TILE;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: tile addresses stay in scalar registers
@@ -1597,7 +1680,10 @@ __global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, i
     }
   }
   const TileRange tr = xcd_tile_range(ntiles);
-  sc[tid] = fetch_edge_scalar<C::TM, 4>(p.dst, p.col, p.d2, p.cvec, tr.first, tr.end, E, tid);
+  const int which = __builtin_amdgcn_readfirstlane(tid / C::TM);   // 0: dst, 1: col, 2: d2, 3: c
+  const int ahead = which == 0 || which == 3 ? tr.step : 0;
+  const int s0 = fetch_edge_scalar<C::TM, 4>(p.dst, p.col, p.d2, p.cvec, tr.first, tr.end, E, tid);
+  sc[tid + (which ? C::TM : 0)] = s0;
   if constexpr (ATTR) {
     const uint2 a0 = fetch_attr4(p.attr, p.k, tr.first, tr.end, E, tid);
     store_attr4(atb, tid, a0);
@@ -1607,20 +1693,20 @@ __global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, i
   int buf = 0;
   for (int tile = tr.first; tile < tr.end; tile += tr.step, buf ^= 1) {
     // the next tile's scalars travel while this tile is processed
-    const int nxt = fetch_edge_scalar<C::TM, 4>(p.dst, p.col, p.d2, p.cvec, tile + tr.step, tr.end, E, tid);
+    const int nxt = fetch_edge_scalar<C::TM, 4>(p.dst, p.col, p.d2, p.cvec, tile + ahead, tr.end, E, tid);
     uint2 nxa = make_uint2(0u, 0u);
     if constexpr (ATTR) nxa = fetch_attr4(p.attr, p.k, tile + tr.step, tr.end, E, tid);
-    const int* s = sc + buf * 4 * C::TM;
-    int* s_next = sc + (buf ^ 1) * 4 * C::TM;
+    const int* s = sc + buf * C::TM;
+    int* s_new = sc + tid + (which ? C::TM : (buf ^ 1) * C::TM);
     const unsigned short* at = atb + buf * ATTR_TILE;
     const unsigned short* att = attb + buf * ATTR_T_TILE;
     unsigned short* at_next = atb + (buf ^ 1) * ATTR_TILE;
     unsigned short* att_next = attb + (buf ^ 1) * ATTR_T_TILE;
     if ((tile + 1) * C::TM <= E)
-      edge_bwd_tile<H, BF16, true, ATTR, DSUM>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
+      edge_bwd_tile<H, BF16, true, ATTR, DSUM>(p, smem, s, sc, s_new, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
                                          at_next, att_next, nxa, bW1a, gacc);
     else
-      edge_bwd_tile<H, BF16, false, ATTR, DSUM>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
+      edge_bwd_tile<H, BF16, false, ATTR, DSUM>(p, smem, s, sc, s_new, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
                                           at_next, att_next, nxa, bW1a, gacc);
   }
   // ---- per-column partial sums of this wavefront: combine the two lane halves, one writer per column
@@ -1657,7 +1743,7 @@ static int32_t launch_edge_bwd_t(hipStream_t st, const EdgeBwdArgs& a) {
   using C = ECfg<H, BF16>;
   const int64_t ntiles = (a.E + C::TM - 1) / C::TM;
   static_assert(!(ATTR && DSUM), "the carried parts of the destination sums take the place of the attribute tiles");
-  constexpr size_t lds = C::LDS_BYTES + 8 * C::TM * 4 + (ATTR ? 2 * (ATTR_TILE + ATTR_T_TILE) * 2 : 0) + (DSUM ? 1024 : 0);
+  constexpr size_t lds = C::LDS_BYTES + 5 * C::TM * 4 + (ATTR ? 2 * (ATTR_TILE + ATTR_T_TILE) * 2 : 0) + (DSUM && !C::PLANES ? 1024 : 0);
   static int per_cu = 0;
   if (!per_cu) {
     HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>),
