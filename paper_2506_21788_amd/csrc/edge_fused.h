@@ -72,12 +72,15 @@ struct EdgeBwdArgs {
   const float* cvec;   // [E] c_e = alpha * (g_v[dst[e]] . rvec[e])
   const float* wx;     // [H]
   float alpha;
-  void* gz2_pk;        // out: g_z2, operand-packed
+  void* gz2_pk;        // out: g_z2, operand-packed (not written where edge_bwd_forms_w2())
   void* gz1_vm;        // out: g_z1, v-major (bf16 or fp32, like the operands)
   float* colpart;      // scratch: [splits][3][H] partial column sums (b2, wx, w1d)
   float* g_b2;         // out [H]
   float* g_wx;         // out [H]
   float* g_w1d;        // out [H] (null with edge attributes)
+  // where edge_bwd_forms_w2(): g_W2 = a1^T g_z2 with a1 = silu(z1), formed on the way
+  float* w2part = nullptr;       // scratch: wgrad_frag_partial_floats(H)
+  float* g_W2 = nullptr;         // out [H,H]
   // k > 1 edge attributes in place of d2 (see EdgeFwdArgs); g_W1a[j][c] = sum_e attr[e][j] g_z1[e][c]
   const float* attr = nullptr;
   int k = 0;
@@ -105,6 +108,9 @@ constexpr int DSUM_UNIT = 64;
 inline size_t edge_bwd_dpart_floats(int64_t E, int H) { return (size_t)((E + DSUM_UNIT - 1) / DSUM_UNIT) * 2 * H; }
 // the operand types and widths for which k_edge_bwd can form g_P itself (an edge's g_z1 is 128 words there)
 inline bool edge_bwd_sums_dst(int H, bool bf16) { return edge_pairs(H, bf16) || (!bf16 && H == 128); }
+// fp32 operands at H = 128: the reverse kernel forms g_W2 from the g_z2 it holds in LDS and the a1 it has when it
+// recomputes z1. The 128 x 128 accumulator is 64 registers per lane; at H = 256 (bf16 pairs) it would be 256.
+inline bool edge_bwd_forms_w2(int H, bool bf16) { return !bf16 && H == 128; }
 size_t edge_bwd_attrpart_floats(int H);
 size_t edge_bwd_colpart_floats(int H);
 int32_t launch_edge_bwd(hipStream_t st, int H, bool bf16, const EdgeBwdArgs& a);
@@ -123,11 +129,6 @@ int32_t launch_wgrad_frag(hipStream_t st, int H, bool bf16, int64_t E, const voi
 int32_t launch_wgrad_frag_recompute(hipStream_t st, int H, int64_t E, const int32_t* dst, const int32_t* col,
                                     const float* d2, const void* PQ, const float* w1d, const void* gz2_pk,
                                     float* partial, float* gW2);
-
-// The same for fp32 operands at H = 128 (PQ: [N, 2H] fp32); see a1_recomputed() in layer.hip for where it is used.
-int32_t launch_wgrad_frag_recompute32(hipStream_t st, int H, int64_t E, const int32_t* dst, const int32_t* col,
-                                      const float* d2, const float* PQ, const float* w1d, const void* gz2_pk,
-                                      float* partial, float* gW2);
 
 // out[i, 0..H) (row pitch ldo) = sum over t in ptr[i]:ptr[i+1] of X[perm ? perm[t] : t, :], X v-major (bf16 or
 // fp32), accumulated in fp32

@@ -39,6 +39,11 @@ struct ECfg {
   // one 32-bit word of P, Q per lane and edge (bf16 pairs, or one column block): gathers are software-pipelined
   static constexpr bool WORD = BF16 || CB == 1;
   static constexpr size_t PLANE_BYTES = (size_t)TM * STRIDE * 2;   // one bf16 plane
+  // the reverse kernel forms g_W2 as well (fp32 operands, H = 128); row pitch of its planes: see wgrad_group
+  static constexpr bool WGRAD = PLANES && H == 128;
+  static constexpr int BSTRIDE = WGRAD ? H + 16 : STRIDE;
+  static constexpr size_t BPLANE_BYTES = (size_t)TM * BSTRIDE * 2;
+  static constexpr size_t BLDS_BYTES = WGRAD ? 3 * BPLANE_BYTES : BF16 ? PLANE_BYTES : PLANES ? 3 * PLANE_BYTES : (size_t)TM * STRIDE * 4;
   static constexpr size_t LDS_BYTES = BF16 ? PLANE_BYTES : PLANES ? 3 * PLANE_BYTES : (size_t)TM * STRIDE * 4;
 };
 
@@ -64,11 +69,10 @@ __device__ __forceinline__ char* uoff(void* base, size_t bytes) { return reinter
 // 8 accumulator-mapped values of one half of a 32x32 block (column n of the tile, registers v = 8*vh .. 8*vh+7,
 // rows rbase + 8*(v>>2) + 4g + (v&3)): written row-major into the LDS tile and, operand-packed, to memory.
 // bf16 values are converted once. packed == null: only the LDS tile is written.
-template <int H, bool BF16>
+template <int H, bool BF16, int STRIDE>
 __device__ __forceinline__ void emit_half(unsigned char* smem, int rbase, int g, int n, const float* vals, int vh,
                                           void* packed, size_t blk, int lane) {
   using C = ECfg<H, BF16>;
-  constexpr int STRIDE = C::STRIDE;
   if constexpr (BF16) {
     unsigned pk[4];
     unsigned short* s16 = reinterpret_cast<unsigned short*>(smem);
@@ -94,8 +98,8 @@ __device__ __forceinline__ void emit_half(unsigned char* smem, int rbase, int g,
         const int row = rbase + 8 * (2 * vh + (t >> 1)) + 4 * g + 2 * (t & 1);
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-          s16[q * (int)(C::PLANE_BYTES / 2) + row * STRIDE + n] = (unsigned short)(w[q] & 0xffffu);
-          s16[q * (int)(C::PLANE_BYTES / 2) + (row + 1) * STRIDE + n] = (unsigned short)(w[q] >> 16);
+          s16[q * (C::TM * STRIDE) + row * STRIDE + n] = (unsigned short)(w[q] & 0xffffu);
+          s16[q * (C::TM * STRIDE) + (row + 1) * STRIDE + n] = (unsigned short)(w[q] >> 16);
         }
       }
     } else {
@@ -167,7 +171,7 @@ __device__ __forceinline__ void tile_mma_prefetch(const void* Bpacked, int wc, i
 // A tile (LDS, row-major, padded) x packed B block -> accumulators; same tiling as the row-tile GEMM.
 // The accumulators start from zero (the first step feeds a constant zero, so they need no clearing).
 // bf16: ring holds the B fragments of the first D steps (tile_mma_prefetch); each step asks for those of step + D.
-template <int H, bool BF16>
+template <int H, bool BF16, int STRIDE = ECfg<H, BF16>::STRIDE>
 __device__ __forceinline__ void tile_mma(const unsigned char* smem, const void* Bpacked, int wr, int wc, int lane,
                                          f32x16_t (&acc)[ECfg<H, BF16>::RB][ECfg<H, BF16>::CB], BRing<H, BF16>& ring) {
   using C = ECfg<H, BF16>;
@@ -177,17 +181,17 @@ __device__ __forceinline__ void tile_mma(const unsigned char* smem, const void* 
     constexpr int D = BRing<H, BF16>::D;
     // LDS byte offset of this lane's A fragment of the first row block and step (one register; row blocks and steps
     // are immediate offsets)
-    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * C::STRIDE + (lane >> 5) * 8) * 2);
+    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * STRIDE + (lane >> 5) * 8) * 2);
     asm volatile("" : "+v"(ao));
     bf16x8_t a[2][C::RB];   // A fragments of this step and the next
 #pragma unroll
-    for (int i = 0; i < C::RB; ++i) a[0][i] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * C::STRIDE) * 2);
+    for (int i = 0; i < C::RB; ++i) a[0][i] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * STRIDE) * 2);
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
       if (kb + 1 < NKB) {
 #pragma unroll
         for (int i = 0; i < C::RB; ++i)
-          a[(kb + 1) & 1][i] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * C::STRIDE + (kb + 1) * 16) * 2);
+          a[(kb + 1) & 1][i] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * STRIDE + (kb + 1) * 16) * 2);
       }
 #pragma unroll
       for (int j = 0; j < C::CB; ++j)
@@ -203,14 +207,14 @@ __device__ __forceinline__ void tile_mma(const unsigned char* smem, const void* 
     // products per step of 16 k (see split_bf16x3); A fragments one step ahead
     constexpr int NKB = H / 16;
     constexpr int D = BRing<H, BF16>::D;
-    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * C::STRIDE + (lane >> 5) * 8) * 2);
+    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * STRIDE + (lane >> 5) * 8) * 2);
     asm volatile("" : "+v"(ao));
     bf16x8_t a[2][C::RB][3];
 #pragma unroll
     for (int i = 0; i < C::RB; ++i)
 #pragma unroll
       for (int q = 0; q < 3; ++q)
-        a[0][i][q] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * C::STRIDE) * 2 + q * C::PLANE_BYTES);
+        a[0][i][q] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * STRIDE) * 2 + q * (C::TM * STRIDE * 2));
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
       if (kb + 1 < NKB) {
@@ -218,7 +222,7 @@ __device__ __forceinline__ void tile_mma(const unsigned char* smem, const void* 
         for (int i = 0; i < C::RB; ++i)
 #pragma unroll
           for (int q = 0; q < 3; ++q)
-            a[(kb + 1) & 1][i][q] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * C::STRIDE + (kb + 1) * 16) * 2 + q * C::PLANE_BYTES);
+            a[(kb + 1) & 1][i][q] = *reinterpret_cast<const bf16x8_t*>(smem + ao + (i * 32 * STRIDE + (kb + 1) * 16) * 2 + q * (C::TM * STRIDE * 2));
       }
 #pragma unroll
       for (int j = 0; j < C::CB; ++j)
@@ -232,14 +236,14 @@ __device__ __forceinline__ void tile_mma(const unsigned char* smem, const void* 
     // three bf16 planes (launch_pack_x3); six bf16 products per step of 16 k (see split_bf16x3)
     constexpr int NKB = H / 16;
     constexpr int D = BRing<H, BF16>::D;
-    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * C::STRIDE + (lane >> 5) * 8) * 4);
+    unsigned ao = (unsigned)(((wr * C::RB * 32 + (lane & 31)) * STRIDE + (lane >> 5) * 8) * 4);
     asm volatile("" : "+v"(ao));
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
       bf16x8_t a[C::RB][3];
 #pragma unroll
       for (int i = 0; i < C::RB; ++i) {
-        const unsigned char* ap = smem + ao + (i * 32 * C::STRIDE + kb * 16) * 4;
+        const unsigned char* ap = smem + ao + (i * 32 * STRIDE + kb * 16) * 4;
         const float4 lo = *reinterpret_cast<const float4*>(ap), hi = *reinterpret_cast<const float4*>(ap + 16);
         const float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
         split_bf16x3(x, a[i]);
@@ -569,7 +573,7 @@ __device__ __forceinline__ void edge_fwd_tile(
           if constexpr (ATTR) vals[u] = silu_f(zp + zq + zat[gi >> 1][j][8 * (gi & 1) + u]);
           else vals[u] = silu_f(zp + zq + ddc[u] * w1d[j]);
         }
-        emit_half<H, BF16>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16, C::STRIDE>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
       }
     }
   } else
@@ -599,7 +603,7 @@ __device__ __forceinline__ void edge_fwd_tile(
           else vals[u] = silu_f(z[j][u]);
           if (!FULL && !((ok >> u) & 1u)) vals[u] = 0.f;
         }
-        emit_half<H, BF16>(smem, rblk * 32, g, n, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16, C::STRIDE>(smem, rblk * 32, g, n, vals, vh, p.a1_pk, (size_t)eb * C::NCB + cblk, lane);
       }
     }
   }
@@ -1260,6 +1264,34 @@ int32_t launch_edge_cvec(hipStream_t st, int64_t E, const int32_t* dst, const fl
   return HGNN_OK;
 }
 
+// g_W2 += a1^T g_z2 over the 16 edges (block rblk, register half vh) whose a1 = silu(z1) this lane holds in 8 registers
+// (column wc*32 + (lane & 31)): split into three bf16 terms they ARE the A operand of a contraction over edges (lane group
+// g holds edges 16 vh + 4 g + 0..3 and + 8). The B operands, g_z2 of all columns in the same edge order, come out of the
+// row-major planes in LDS through transposing reads: of 16 lanes each names 8 bytes of one of four rows, and lane i
+// receives column i of the four. Row pitch H + 16: 72 words put four rows in banks 0, 8, 16, 24, so a 16-lane group meets
+// no conflict, and the row-wise reads of the product with W2^T (8 lanes x 16 bytes) none either.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+template <int H, int STRIDE>
+__device__ __forceinline__ void wgrad_group(const unsigned char* smem, int rblk, int vh, int lane, const float (&a1)[8],
+                                            f32x16_t (&wacc)[H / 32]) {
+  constexpr int PLANE = 64 * STRIDE * 2;
+  bf16x8_t a[3];
+  split_bf16x3(a1, a);
+  const unsigned char* base = smem + ((rblk * 32 + 16 * vh + 4 * (lane >> 5) + ((lane & 15) >> 2)) * STRIDE + (lane & 16) + (lane & 3) * 4) * 2;
+#pragma unroll
+  for (int nb = 0; nb < H / 32; ++nb) {
+    bf16x8_t b[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const unsigned char* src = base + q * PLANE + nb * 64;
+      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src));
+      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src + 8 * STRIDE * 2));
+      b[q] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    wacc[nb] = mfma_bf16x3(a, b, wacc[nb]);
+  }
+}
+
 // One tile of the reverse kernel. FULL: all TM edges of the tile exist (no masking anywhere).
 // ATTR: k > 1 edge attributes take the place of d2 (at / att: this tile's attributes in LDS, edge-major and
 // slot-major; *_next / nxa: where and what to store for the next tile; bW1a: the attribute weights as matrix-core
@@ -1272,8 +1304,10 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
                                               float (&sw1)[ECfg<H, BF16>::CB], const unsigned short* at,
                                               const unsigned short* att, unsigned short* at_next, unsigned short* att_next,
                                               uint2 nxa, const bf16x8_t (&bW1a)[ECfg<H, BF16>::CB],
-                                              f32x16_t (&gacc)[ECfg<H, BF16>::CB]) {
+                                              f32x16_t (&gacc)[ECfg<H, BF16>::CB],
+                                              f32x16_t (&wacc)[ECfg<H, BF16>::WGRAD ? H / 32 : 1]) {
   using C = ECfg<H, BF16>;
+  constexpr bool WG = C::WGRAD;
   constexpr bool PAIRS = BF16 && C::CB == 2;
   constexpr unsigned GM_ROW = PAIRS ? H * 2u : 2u * H * 4u;   // row pitch of g_M in bytes (checked by the launcher)
   const int g = lane >> 5, x = lane & 31;
@@ -1285,7 +1319,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   // DSUM: the last phase also leaves the tile's g_z1 words row-major in LDS (row pitch of the A tile, which is no
   // longer needed then); this lane writes word wc*32 + x of the rows 4g + (constant)
   constexpr int DPITCH = PAIRS ? C::STRIDE / 2 : H + 4;
-  static_assert(!DSUM || (size_t)C::TM * DPITCH * 4 <= C::LDS_BYTES, "the words of g_z1 take the place of the A tile");
+  static_assert(!DSUM || (size_t)C::TM * DPITCH * 4 <= C::BLDS_BYTES, "the words of g_z1 take the place of the A tile");
   unsigned* dsw = reinterpret_cast<unsigned*>(smem) + (4 * g) * DPITCH + wc * 32 + x;
   // the destinations of the edges next to the tile decide whether its first and last row are complete here
   int dprev = -1, dnext = -1;
@@ -1340,7 +1374,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
           sb2[j] += gz;
           swx[j] += cc[sl][u] * m;
         }
-        emit_half<H, BF16>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16, C::BSTRIDE>(smem, rblk * 32, g, cblk * 32 + x, vals, vh, WG ? nullptr : p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
       }
 #pragma unroll
       for (int j = 0; j < C::CB; ++j) asm volatile("" : "+v"(sb2[j]), "+v"(swx[j]));
@@ -1401,7 +1435,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
           sb2[j] += gz;
           swx[j] += cc[u] * m;
         }
-        emit_half<H, BF16>(smem, rblk * 32, g, n, vals, vh, p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
+        emit_half<H, BF16, C::BSTRIDE>(smem, rblk * 32, g, n, vals, vh, WG ? nullptr : p.gz2_pk, (size_t)eb * C::NCB + cblk, lane);
       }
       // the running column sums are complete for this group here: without this the compiler defers their chains
       // past the matrix product and keeps every operand alive (in scratch memory) until then
@@ -1413,7 +1447,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   tile_mma_prefetch<H, BF16>(p.W2Tp, wc, lane, ring);
   __syncthreads();
   f32x16_t acc[C::RB][C::CB];
-  tile_mma<H, BF16>(smem, p.W2Tp, wr, wc, lane, acc, ring);
+  tile_mma<H, BF16, C::BSTRIDE>(smem, p.W2Tp, wr, wc, lane, acc, ring);
   s_new[0] = nxt;
   if constexpr (ATTR) {
     store_attr4(at_next, tid, nxa);
@@ -1452,13 +1486,17 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
         if (vh == 0) attr_z1_block<C::CB>(at, rblk, lane, bW1a, zat);
       }
       float ga[C::CB][8];
+      [[maybe_unused]] float a1[8];   // WG: silu(z1), the other operand of g_W2
 #pragma unroll
       for (int u = 0; u < 8; ++u)
 #pragma unroll
         for (int j = 0; j < C::CB; ++j) {
           const float z = word_column<PAIRS>(wp[sl][u], j) + word_column<PAIRS>(wq[sl][u], j) +
                           (ATTR ? zat[j][8 * vh + u] : dd[u] * w1d[j]);
-          ga[j][u] = acc[i][j][8 * vh + u] * dsilu_f(z);
+          float dz;
+          if constexpr (WG) silu_both(z, a1[u], dz);
+          else dz = dsilu_f(z);
+          ga[j][u] = acc[i][j][8 * vh + u] * dz;
           if constexpr (!ATTR) sw1[j] += dd[u] * ga[j][u];
         }
       if constexpr (PAIRS || !BF16) {
@@ -1467,8 +1505,10 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
         for (int u = 0; u < 8; ++u) {
           const unsigned pw = PAIRS ? pack_bf16x2(ga[0][u], ga[C::CB - 1][u]) : __float_as_uint(ga[0][u]);
           stg_nt<unsigned>(o, lane * 4u + u * 256u, pw);
-          if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = pw;
+          if constexpr (WG) acc[i][0][8 * vh + u] = ga[0][u];   // to LDS behind the barrier below
+          else if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = pw;
         }
+        if constexpr (WG) wgrad_group<H, C::BSTRIDE>(smem, rblk, vh, lane, a1, wacc);
       } else {
         char* o = uoff(p.gz1_vm, (((size_t)eb * C::NCB + wc) * 16 + 8 * vh) * 128);
 #pragma unroll
@@ -1507,14 +1547,19 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
         if (vh == 0) attr_z1_block<C::CB>(at, rblk, lane, bW1a, zat);
       }
       float gv[C::CB][8];
+      [[maybe_unused]] float a1[8];
 #pragma unroll
       for (int j = 0; j < C::CB; ++j)
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const float zz = ATTR ? z[j][u] + zat[j][8 * vh + u] : z[j][u];
-          gv[j][u] = acc[i][j][8 * vh + u] * dsilu_f(zz);   // rows beyond E have acc == 0
+          float dz;
+          if constexpr (WG) silu_both(zz, a1[u], dz);
+          else dz = dsilu_f(zz);
+          gv[j][u] = acc[i][j][8 * vh + u] * dz;   // rows beyond E have acc == 0
           if constexpr (!ATTR) sw1[j] += dd[u] * gv[j][u];
         }
+      if constexpr (WG) wgrad_group<H, C::BSTRIDE>(smem, rblk, vh, lane, a1, wacc);   // rows beyond E: g_z2 == 0
       if constexpr (ATTR) {
         const bf16x8_t aT = attr_t_operand(att, rblk, vh, lane);
 #pragma unroll
@@ -1546,7 +1591,8 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
               stg_nt<float>(o, lane * 4u + u * 256u, gv[j][u]);
-              if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = __float_as_uint(gv[j][u]);
+              if constexpr (WG) acc[i][j][8 * vh + u] = gv[j][u];
+              else if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = __float_as_uint(gv[j][u]);
             }
           }
         }
@@ -1561,16 +1607,21 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   // for every thread of a wavefront: scalar branches on one ballot mask) the finished run goes to g_P when it is the
   // whole row, otherwise to the tile's partial slot: slot 1 when the row starts in this tile, slot 0 when it
   // started earlier. DsumFixRow adds a row's slots.
+  if constexpr (WG) {
+    __syncthreads();   // the planes of g_z2 have been read
+    if constexpr (DSUM) {
+#pragma unroll
+      for (int i = 0; i < C::RB; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) dsw[((wr * C::RB + i) * 32 + 8 * (v >> 2) + (v & 3)) * DPITCH] = __float_as_uint(acc[i][0][v]);
+    }
+  }
   if constexpr (DSUM) {
     static_assert(C::TM == 64 && DSUM_UNIT == C::TM, "one partial unit per tile, walked as two halves of 32 edges");
     __syncthreads();
     const unsigned* gw = reinterpret_cast<const unsigned*>(smem);
-    // [128] carried parts, see below. With planes they sit in the 16 bytes of padding behind each row of the last
-    // plane, which nothing else writes: 1 KB more would leave two workgroups per compute unit instead of three.
-    static_assert(!C::PLANES || ((size_t)C::TM * DPITCH * 4 <= 2 * C::PLANE_BYTES && 2 * C::TM == 128), "two carried parts per row");
-    auto carry = [&](int k) -> float2& {
-      return *reinterpret_cast<float2*>(C::PLANES ? smem + 2 * C::PLANE_BYTES + (k >> 1) * (C::STRIDE * 2) + H * 2 + (k & 1) * 8
-                                                  : smem + C::LDS_BYTES + 5 * C::TM * 4 + k * 8);
+    auto carry = [&](int k) -> float2& {   // [128], see below
+      return reinterpret_cast<float2*>(smem + C::BLDS_BYTES + 5 * C::TM * 4)[k];
     };
     const int hf = __builtin_amdgcn_readfirstlane(tid >> 7);   // the half of the tile that this wavefront walks
     const int w = tid & 127;
@@ -1646,17 +1697,20 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   }
 }
 
+// WGRAD (fp32 operands, H = 128): g_W2 is formed in the last phase out of the planes of g_z2 in LDS. As a kernel of its own
+// it read g_z2 back, gathered P and Q and formed the sigmoids once more. 7.2 M edges: 2883 + 1866 us as two kernels, 3618 us
+// as one with two workgroups per compute unit (64 accumulator registers); 81 k edges: 38 + 43 us, 46 us.
 template <int H, bool BF16, bool ATTR, bool DSUM>
-__global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, int ntiles) {
+__global__ void __launch_bounds__(256, ((ATTR || ECfg<H, BF16>::WGRAD) ? 2 : 3)) k_edge_bwd(EdgeBwdArgs p, int ntiles) {
   using C = ECfg<H, BF16>;
   static_assert(!ATTR || (BF16 && C::TM == 64), "edge attributes: bf16 operands, 64-edge tiles");
   extern __shared__ __align__(16) unsigned char smem[];
   // Per-edge scalars [5][TM]: dst of this and the next tile | col | d2 | c. All are stored between the two barriers
   // around the product: c (read before it only) is the next tile's by then, col and d2 (read behind it only) are this
   // tile's and were asked for when the tile began. Twice all four would not leave room for three workgroups with planes.
-  int* sc = reinterpret_cast<int*>(smem + C::LDS_BYTES);
+  int* sc = reinterpret_cast<int*>(smem + C::BLDS_BYTES);
   // ATTR: [2][ATTR_TILE] attributes edge-major, then [2][ATTR_T_TILE] slot-major
-  unsigned short* atb = reinterpret_cast<unsigned short*>(smem + C::LDS_BYTES + 5 * C::TM * 4);
+  unsigned short* atb = reinterpret_cast<unsigned short*>(smem + C::BLDS_BYTES + 5 * C::TM * 4);
   unsigned short* attb = atb + 2 * ATTR_TILE;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: tile addresses stay in scalar registers
@@ -1679,6 +1733,11 @@ __global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, i
       for (int v = 0; v < 16; ++v) gacc[j][v] = 0.f;
     }
   }
+  f32x16_t wacc[C::WGRAD ? C::NCB : 1];   // running g_W2: rows of this wavefront's column block, all columns
+#pragma unroll
+  for (int b = 0; b < (C::WGRAD ? C::NCB : 1); ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) wacc[b][v] = 0.f;
   const TileRange tr = xcd_tile_range(ntiles);
   const int which = __builtin_amdgcn_readfirstlane(tid / C::TM);   // 0: dst, 1: col, 2: d2, 3: c
   const int ahead = which == 0 || which == 3 ? tr.step : 0;
@@ -1704,10 +1763,17 @@ __global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, i
     unsigned short* att_next = attb + (buf ^ 1) * ATTR_T_TILE;
     if ((tile + 1) * C::TM <= E)
       edge_bwd_tile<H, BF16, true, ATTR, DSUM>(p, smem, s, sc, s_new, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
-                                         at_next, att_next, nxa, bW1a, gacc);
+                                         at_next, att_next, nxa, bW1a, gacc, wacc);
     else
       edge_bwd_tile<H, BF16, false, ATTR, DSUM>(p, smem, s, sc, s_new, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
-                                          at_next, att_next, nxa, bW1a, gacc);
+                                          at_next, att_next, nxa, bW1a, gacc, wacc);
+  }
+  if constexpr (C::WGRAD) {
+    float* o = p.w2part + (size_t)blockIdx.x * H * H + (size_t)wc * 32 * H + x;
+#pragma unroll
+    for (int b = 0; b < C::NCB; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[(8 * (v >> 2) + 4 * g + (v & 3)) * H + b * 32] = wacc[b][v];
   }
   // ---- per-column partial sums of this wavefront: combine the two lane halves, one writer per column
 #pragma unroll
@@ -1734,7 +1800,7 @@ __global__ void __launch_bounds__(256, ATTR ? 2 : 3) k_edge_bwd(EdgeBwdArgs p, i
   }
 }
 
-constexpr int EDGE_BWD_MAX_GRID = 2048;
+constexpr int EDGE_BWD_MAX_GRID = 2048;   // (the partials of g_W2 have room for as many at H = 128)
 size_t edge_bwd_colpart_floats(int H) { return (size_t)EDGE_BWD_MAX_GRID * 2 * 3 * H; }
 size_t edge_bwd_attrpart_floats(int H) { return (size_t)EDGE_BWD_MAX_GRID * 2 * ATTR_K * H; }
 
@@ -1743,12 +1809,12 @@ static int32_t launch_edge_bwd_t(hipStream_t st, const EdgeBwdArgs& a) {
   using C = ECfg<H, BF16>;
   const int64_t ntiles = (a.E + C::TM - 1) / C::TM;
   static_assert(!(ATTR && DSUM), "the carried parts of the destination sums take the place of the attribute tiles");
-  constexpr size_t lds = C::LDS_BYTES + 5 * C::TM * 4 + (ATTR ? 2 * (ATTR_TILE + ATTR_T_TILE) * 2 : 0) + (DSUM && !C::PLANES ? 1024 : 0);
+  constexpr size_t lds = C::BLDS_BYTES + 5 * C::TM * 4 + (ATTR ? 2 * (ATTR_TILE + ATTR_T_TILE) * 2 : 0) + (DSUM ? 1024 : 0);
   static int per_cu = 0;
   if (!per_cu) {
     HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    per_cu = resident_per_cu(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>), lds, ATTR ? 2 : 3);
+    per_cu = resident_per_cu(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>), lds, ATTR || C::WGRAD ? 2 : 3);
   }
   int64_t grid = (int64_t)num_cus() * per_cu;
   if (grid > EDGE_BWD_MAX_GRID) grid = EDGE_BWD_MAX_GRID;
@@ -1761,6 +1827,10 @@ static int32_t launch_edge_bwd_t(hipStream_t st, const EdgeBwdArgs& a) {
   }
   float* dest[4] = {a.g_b2, a.g_wx, a.g_w1d, nullptr};
   HGNN_TRY(launch_reduce_partials(st, a.colpart, (int)grid * C::WR, 3, H, dest, 1, 0));
+  if constexpr (C::WGRAD) {
+    float* wdest[4] = {a.g_W2, nullptr, nullptr, nullptr};
+    HGNN_TRY(launch_reduce_partials(st, a.w2part, (int)grid, 1, (long)H * H, wdest, 1, 0));
+  }
   if (ATTR) {
     float* adest[4] = {a.g_W1a, nullptr, nullptr, nullptr};
     HGNN_TRY(launch_reduce_partials(st, a.attrpart, (int)grid * C::WR, 1, (long)a.k * H, adest, 1, 0));
@@ -1777,6 +1847,7 @@ int32_t launch_edge_bwd(hipStream_t st, int H, bool bf16, const EdgeBwdArgs& a) 
                          a.ldgP % 4 == 0),
                HGNN_ERR_BAD_SHAPE,
                "in-kernel destination sums: bf16 operands at H = 256 or fp32 operands at H = 128, no edge attributes");
+  HGNN_REQUIRE(!edge_bwd_forms_w2(H, bf16) || (a.w2part && a.g_W2), HGNN_ERR_BAD_SHAPE, "no room for the gradient of W2");
   if (a.k > 1) {
     HGNN_REQUIRE(bf16 && a.k <= ATTR_K && a.W1a && a.attrpart && a.g_W1a && (a.attr || a.E == 0), HGNN_ERR_BAD_SHAPE,
                  "edge attributes on the fused kernels: bf16 operands, 2 <= k <= %d", ATTR_K);
@@ -2110,187 +2181,6 @@ __global__ void __launch_bounds__(512) k_wgrad_frag_rc(WgradRcArgs p) {
       }
 }
 
-// The recomputing weight gradient for fp32 operands at H = 128: the same scheme with four wavefronts (2 x 2 blocks
-// of the 128 x 128 accumulator each, two workgroups per compute unit). Every value is split into its three bf16
-// terms (split_bf16x3) once, by the wavefront that produces it, and the LDS stages hold three planes of ready
-// operands; the consumers take six products per block pair. A producer wavefront forms silu(z1) for 64 columns and
-// eight of a chunk's sixteen edges; it also splits one column block of the chunk's g_z2 (two 16-byte pieces per
-// lane, already in operand order) into the stage. Two stages, one barrier per chunk.
-struct WgradRc32Args {
-  int64_t nblk32;
-  int E;
-  const int32_t *dst, *col;
-  const float* d2;
-  const float* PQ;      // [N, 2H] fp32: P | Q
-  const float* w1d;
-  const void* gz2_pk;   // fp32, operand-packed; rows past the last edge of the last block hold zeros
-  float* partial;
-};
-
-template <int H>
-__global__ void __launch_bounds__(256, 2) k_wgrad_frag_rc32(WgradRc32Args p) {
-  constexpr int NCB = H / 32;
-  constexpr int PLANE = NCB * 1024;   // one bf16 plane of the four operand blocks of a chunk: [block][64 slots][8 bf16]
-  constexpr int STAGE = 3 * PLANE;
-  static_assert(H == 128, "four wavefronts, 2 x 2 blocks each");
-  using PQP = PQPitch<H, false>;
-  typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-  __shared__ __align__(16) unsigned char stage_a[2 * STAGE];
-  __shared__ __align__(16) unsigned char stage_b[2 * STAGE];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int x = lane & 31;
-  // as a producer: columns wcc * 64 + lane (block 2 wcc + (lane >> 5)), edges 8 hh .. 8 hh + 7 of the chunk: edge
-  // 8 hh + j is element 4 hh + (j & 3) of operand lane group j >> 2
-  const int wcc = w >> 1, hh = w & 1;
-  // as a consumer: A blocks 2 wa, 2 wa + 1; g_z2 blocks 2 wb, 2 wb + 1
-  const int wa = w >> 1, wb = w & 1;
-  f32x16_t acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const float w1 = p.w1d[wcc * 64 + lane];
-  const int G = gridDim.x, bid = blockIdx.x;
-  const int nblk = (int)p.nblk32;
-  const int E = p.E;
-  int bfirst, bstride, nmine;   // this workgroup's blocks, by XCD as in the bf16-pair kernel
-  if ((G & 7) == 0) {
-    const int xcd = bid & 7, r = bid >> 3;
-    bstride = G >> 3;
-    const int lo = (int)((int64_t)nblk * xcd / 8), hi = (int)((int64_t)nblk * (xcd + 1) / 8);
-    nmine = hi - lo > r ? (hi - lo - r + bstride - 1) / bstride : 0;
-    bfirst = lo + r;
-  } else {
-    bstride = G;
-    nmine = nblk > bid ? (nblk - bid + G - 1) / G : 0;
-    bfirst = bid;
-  }
-  const int nchunk = nmine * 2;   // two 16-edge chunks per 32-edge block
-  const unsigned colb = (unsigned)(wcc * 64 + lane) * 4u;
-  // lanes 0..7 fetch dst, 8..15 col, 16..23 d2 of the wavefront's eight edges
-  const int32_t* const idx_arr = lane < 8 ? p.dst : (lane < 16 ? p.col : reinterpret_cast<const int32_t*>(p.d2));
-  unsigned char* const a_out = stage_a + (2 * wcc + (lane >> 5)) * 1024 + x * 16 + 8 * hh;
-
-  auto chunk_blk = [&](int c) { const int cc = c < nchunk ? c : nchunk - 1; return bfirst + (cc >> 1) * bstride; };
-  auto chunk_half = [&](int c) { const int cc = c < nchunk ? c : nchunk - 1; return cc & 1; };
-  auto load_iv = [&](int c, int& iv) {
-    const int e = chunk_blk(c) * 32 + chunk_half(c) * 16 + 8 * hh + (lane & 7);
-    iv = 0;
-    if (lane < 24 && e < E) iv = idx_arr[e];   // past the last edge: row 0 (always valid), and g_z2 is zero there
-  };
-  auto gather = [&](const int iv, float (&vp)[8], float (&vq)[8]) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const unsigned rd = (unsigned)__builtin_amdgcn_readlane(iv, u), rc = (unsigned)__builtin_amdgcn_readlane(iv, 8 + u);
-      vp[u] = ldg_f32(uoff(p.PQ, rd * PQP::ROW), colb);
-      vq[u] = ldg_f32(uoff(p.PQ, rc * PQP::ROW + PQP::QOFF), colb);
-    }
-  };
-  // this wavefront's column block (w) of the chunk's g_z2: the two pieces are elements 0..3 and 4..7 of every slot
-  auto load_b = [&](int c, f32x4_t (&b)[2]) {
-    const char* src = uoff(p.gz2_pk, (((size_t)chunk_blk(c) * NCB + w) * 4 + 2 * chunk_half(c)) * 1024);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) b[s] = ldg_nt<f32x4_t>(src + s * 1024, lane * 16u);
-  };
-  auto stage_b_put = [&](int st, const f32x4_t (&b)[2]) {
-    const float xs[8] = {b[0][0], b[0][1], b[0][2], b[0][3], b[1][0], b[1][1], b[1][2], b[1][3]};
-    bf16x8_t o[3];
-    split_bf16x3(xs, o);
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      *reinterpret_cast<bf16x8_t*>(stage_b + st * STAGE + q * PLANE + w * 1024 + lane * 16) = o[q];
-  };
-  auto stage_a_put = [&](int c, int st, const float (&vp)[8], const float (&vq)[8], const int iv) {
-    const float keep = c < nchunk ? 1.f : 0.f;   // uniform over the workgroup; chunks past the end give zeros
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float d = __int_as_float(__builtin_amdgcn_readlane(iv, 16 + u));
-      v[u] = silu_f(vp[u] + vq[u] + d * w1) * keep;
-    }
-    bf16x8_t o[3];
-    split_bf16x3(v, o);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const u32x4_t wv = __builtin_bit_cast(u32x4_t, o[q]);
-      unsigned char* dstp = a_out + st * STAGE + q * PLANE;
-      *reinterpret_cast<uint2*>(dstp) = make_uint2(wv[0], wv[1]);         // edges 8 hh + 0..3: lane group 0
-      *reinterpret_cast<uint2*>(dstp + 512) = make_uint2(wv[2], wv[3]);   // edges 8 hh + 4..7: lane group 1
-    }
-  };
-  auto mma = [&](int st) {
-    bf16x8_t a[2][3], b[2][3];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        a[i][q] = *reinterpret_cast<const bf16x8_t*>(stage_a + st * STAGE + q * PLANE + (2 * wa + i) * 1024 + lane * 16);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        b[j][q] = *reinterpret_cast<const bf16x8_t*>(stage_b + st * STAGE + q * PLANE + (2 * wb + j) * 1024 + lane * 16);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16x3(a[i], b[j], acc[i][j]);
-  };
-
-  if (nchunk > 0) {   // uniform over the workgroup
-    int iv[8];                    // index ring: slot = chunk mod 8
-    float vp[4][8], vq[4][8];     // gather ring: slot = chunk mod 4
-    f32x4_t bb[4][2];             // g_z2 load ring: slot = chunk mod 4
-    // prologue: indices of chunks 0..8, g_z2 and gathers of chunks 0..4, chunk 0 staged
-#pragma unroll
-    for (int k = 0; k < 8; ++k) load_iv(k, iv[k]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) load_b(k, bb[k]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) gather(iv[k], vp[k], vq[k]);
-    stage_b_put(0, bb[0]);
-    stage_a_put(0, 0, vp[0], vq[0], iv[0]);
-    load_b(4, bb[0]);   // chunk 4 takes the ring slots chunk 0 has just left
-    gather(iv[4], vp[0], vq[0]);
-    load_iv(8, iv[0]);
-    __syncthreads();
-    for (int c = 0; c < nchunk; c += 8) {
-      // step for chunk j = c + k: multiply chunk j out of its stage and form and stage chunk j + 1; then ask for the
-      // g_z2 and the gathers of chunk j + 5 (ring slots of chunk j + 1, just emptied) and the indices of chunk j + 9
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        mma(k & 1);
-        stage_b_put((k + 1) & 1, bb[(k + 1) & 3]);
-        stage_a_put(c + k + 1, (k + 1) & 1, vp[(k + 1) & 3], vq[(k + 1) & 3], iv[(k + 1) & 7]);
-        load_b(c + k + 5, bb[(k + 1) & 3]);
-        gather(iv[(k + 5) & 7], vp[(k + 1) & 3], vq[(k + 1) & 3]);
-        load_iv(c + k + 9, iv[(k + 1) & 7]);
-        // one matrix product, then a share of the vector work: the products of a step run behind its sigmoids and
-        // splits instead of blocking both wavefronts of the SIMD
-#pragma unroll
-        for (int i = 0; i < 24; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
-        }
-        __syncthreads();
-      }
-    }
-  }
-  float* out = p.partial + (size_t)blockIdx.x * H * H;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int k1 = (2 * wa + i) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int k2 = (2 * wb + j) * 32 + (lane & 31);
-        out[k1 * H + k2] = acc[i][j][v];
-      }
-}
-
 // most workgroups (= partial H x H results) of one launch: the partial buffer holds 32 Mi floats at every H
 constexpr int WGRAD_FRAG_MAX_GRID = 512;                        // at H = 256
 static int wgrad_frag_max_grid(int H) { return WGRAD_FRAG_MAX_GRID * (256 / H) * (256 / H); }
@@ -2348,31 +2238,6 @@ int32_t launch_wgrad_frag_recompute(hipStream_t st, int H, int64_t E, const int3
     ProfScope ps(PT_WGRAD_EDGE, st);
     k_wgrad_frag_rc<256><<<dim3((unsigned)grid), 512, 0, st>>>(a);
     HGNN_LAUNCH_CHECK("k_wgrad_frag_rc");
-  }
-  float* dest[4] = {gW2, nullptr, nullptr, nullptr};
-  return launch_reduce_partials(st, partial, (int)grid, 1, (long)H * H, dest, 1, 0);
-}
-
-int32_t launch_wgrad_frag_recompute32(hipStream_t st, int H, int64_t E, const int32_t* dst, const int32_t* col,
-                                      const float* d2, const float* PQ, const float* w1d, const void* gz2_pk,
-                                      float* partial, float* gW2) {
-  HGNN_REQUIRE(H == 128, HGNN_ERR_BAD_SHAPE, "the recomputing fp32 weight-gradient kernel exists at H = 128");
-  HGNN_REQUIRE(E >= 0 && E <= EDGE_MAX_E, HGNN_ERR_BAD_SHAPE, "edge kernels index edges with 32 bits (E = %lld)",
-               (long long)E);
-  // two workgroups per compute unit, each leaving one partial; fewer when there are fewer than two blocks for each
-  const int64_t nblk32 = (E + 31) / 32;
-  int64_t grid = 2 * (int64_t)num_cus();
-  if (grid > wgrad_frag_max_grid(H)) grid = wgrad_frag_max_grid(H);
-  if (grid > (nblk32 + 1) / 2) grid = (nblk32 + 1) / 2;
-  if (grid >= 8) grid &= ~(int64_t)7;
-  if (grid < 1) grid = 1;
-  WgradRc32Args a;
-  a.nblk32 = nblk32; a.E = (int)E; a.dst = dst; a.col = col; a.d2 = d2; a.PQ = PQ; a.w1d = w1d;
-  a.gz2_pk = gz2_pk; a.partial = partial;
-  {
-    ProfScope ps(PT_WGRAD_EDGE, st);
-    k_wgrad_frag_rc32<128><<<dim3((unsigned)grid), 256, 0, st>>>(a);
-    HGNN_LAUNCH_CHECK("k_wgrad_frag_rc32");
   }
   float* dest[4] = {gW2, nullptr, nullptr, nullptr};
   return launch_reduce_partials(st, partial, (int)grid, 1, (long)H * H, dest, 1, 0);

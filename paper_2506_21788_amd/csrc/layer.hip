@@ -44,9 +44,8 @@ struct LayerSaved {
   size_t bytes;
 };
 
-// a1 is recomputed (not stored) where the weight-gradient kernel can rebuild it from the gathers alone
-// a1 = silu(z1) is not stored but recomputed by the W2-gradient kernel: bf16 pairs (H = 256), and fp32 operands at
-// H = 128, with the squared length as the only edge attribute
+// a1 = silu(z1) is not stored but recomputed, from the gathers alone: by the W2-gradient kernel (bf16 pairs, H = 256) or by
+// the reverse edge kernel, which forms that gradient itself (fp32 operands, H = 128); d2 as the only edge attribute
 static bool a1_recomputed(int H, bool bf16, int k) { return (edge_pairs(H, bf16) || (!bf16 && H == 128)) && k == 1; }
 
 static LayerSaved carve_saved(void* p, int N, int64_t E, int H, bool bf16, int k = 1) {
@@ -87,7 +86,7 @@ static LayerWs carve_ws(void* p, int N, int64_t E, int H, bool bf16, int k = 1) 
   LayerWs w;
   w.packed = c.take<char>(6 * packed_block_bytes(H, bf16));
   w.packed_x3 = bf16 ? nullptr : c.take<char>(packed_x3_bytes(H));
-  w.gz2_pk = c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
+  w.gz2_pk = edge_bwd_forms_w2(H, bf16) ? nullptr : c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
   w.gz1_vm = c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
   w.cvec = c.take<float>((size_t)E + 4);
   w.g_z3 = c.take<float>((size_t)N * H);
@@ -439,6 +438,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
     else { e.gM = w.g_hM + H; e.ldgM = 2 * H; }
     e.cvec = w.cvec; e.wx = W + o.wx; e.alpha = alpha;
     e.gz2_pk = w.gz2_pk; e.gz1_vm = w.gz1_vm;
+    e.w2part = w.partial2; e.g_W2 = gW + o.W2;
     e.colpart = w.partial;
     e.g_b2 = gW + o.b2; e.g_wx = gW + o.wx; e.g_w1d = k > 1 ? nullptr : gW + o.W1 + 2 * HH;
     if (dsum_in_kernel) {
@@ -449,10 +449,9 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   }
   HGNN_TRY(stream_after(sx, st, ss.ev[2]));
   // side: g_W2 = a1^T g_z2 streams while the main stream runs the two segment sums
-  if (a1_recomputed(H, bf16, k) && !bf16)
-    HGNN_TRY(launch_wgrad_frag_recompute32(sx, H, E, dst, col, d2, reinterpret_cast<const float*>(s.PQ),
-                                           W + o.W1 + 2 * HH, w.gz2_pk, w.partial2, gW + o.W2));
-  else if (a1_recomputed(H, bf16, k))
+  if (edge_bwd_forms_w2(H, bf16)) {
+    // g_W2 left the edge kernel already
+  } else if (a1_recomputed(H, bf16, k))
     HGNN_TRY(launch_wgrad_frag_recompute(sx, H, E, dst, col, d2, s.PQ, W + o.W1 + 2 * HH, w.gz2_pk, w.partial2,
                                          gW + o.W2));
   else

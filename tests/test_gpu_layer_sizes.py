@@ -147,7 +147,7 @@ def test_layer_other_modes_edge_counts(H, dtype, E):
     _run_layer(N=300, E=E, H=H, dtype=dtype, seed=E)
 
 
-# fp32 operands at H = 128: the W2 gradient recomputes a1 in a kernel of its own (two 16-edge chunks per 32-edge block,
+# fp32 operands at H = 128: the W2 gradient recomputes a1 (two 16-edge chunks per 32-edge block,
 # eight-chunk trips, grids rounded to multiples of eight workgroups, one ragged block at most)
 @pytest.mark.parametrize("E", [0, 1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 511, 16385, 3 * 16384 + 45])
 def test_layer_f32_128_edge_counts(E):
