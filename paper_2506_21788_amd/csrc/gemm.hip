@@ -474,6 +474,258 @@ __global__ void __launch_bounds__(256, 3) k_gemm_chain(GemmArgs p1, GemmArgs p2,
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same products where the batch has few atoms: 16-row tiles
+// ---------------------------------------------------------------------------------------------
+// With fewer tiles than compute units such a launch takes as long as ONE tile takes, and a tile is a chain: load A, a
+// row of dependent matrix instructions per wavefront, an epilogue that loads its operands, and the same again for the
+// second product. This variant shortens the chain: 16-row tiles on the 16 x 16 matrix instructions, one 16-column block
+// per wavefront (two at H = 256), so a wavefront's product is a quarter of the instructions (half the instruction time)
+// of the 32-row form; both k chunks of A, the weights of the first chunk and all operands of the epilogues are asked for
+// at the start; weights are kept one whole chunk ahead in registers; results go from the accumulators straight to memory.
+template <int H, bool BF16>
+struct SmallCfg {
+  static constexpr int TM = 16;
+  static constexpr int WAVES = H == 64 ? 4 : 8;
+  static constexpr int THREADS = WAVES * 64;
+  static constexpr int CB = H / 16 / WAVES;              // 16-column blocks per wavefront
+  static constexpr int NKB = H / (BF16 ? 32 : 16);       // 16-byte operand loads per chunk of H
+  static constexpr int STRIDE = BF16 ? H + 8 : H + 4;    // LDS row pitch in elements
+  static constexpr int ESZ = BF16 ? 2 : 4;
+  static constexpr size_t A_BYTES = (size_t)TM * STRIDE * ESZ;
+  static constexpr size_t LDS_BYTES = 3 * A_BYTES;       // two k chunks of A | the first product's finished tile
+  // first column of block j: at H = 256 the two blocks are 32 columns apart, so that a lane owns both halves of a
+  // bf16 pair word (see edge_pairs())
+  __device__ static __forceinline__ int col0(int wave, int j) {
+    return H == 256 ? (wave >> 1) * 64 + (wave & 1) * 16 + 32 * j : wave * 16;
+  }
+};
+typedef unsigned u32x4s_t __attribute__((ext_vector_type(4)));
+template <int H, bool BF16>
+struct SmallAux {   // operands of an epilogue, in the accumulator mapping: row 4 (lane >> 4) + v, column lane & 15
+  static constexpr int CB = SmallCfg<H, BF16>::CB;
+  float bias[CB], mul[CB][4], a1[CB][4], a2[CB][4];
+  __device__ __forceinline__ void load(const GemmArgs& p, int cb, int grp, const long (&gr)[4], int wave, int c) {
+    const bool ub = p.bias && ((p.bias_cb_mask >> cb) & 1), ua = p.add1 && ((p.add1_cb_mask >> cb) & 1);
+#pragma unroll
+    for (int j = 0; j < CB; ++j) bias[j] = ub ? p.bias[grp * p.grp_bias_stride + SmallCfg<H, BF16>::col0(wave, j) + c] : 0.f;
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+      const int gc = cb * H + SmallCfg<H, BF16>::col0(wave, j) + c;
+      if (p.mul) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mul[j][v] = p.mul[gr[v] * p.ldmul + gc];
+      }
+      if (ua) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a1[j][v] = p.add1[gr[v] * p.ldadd1 + gc];
+      }
+      if (p.add2) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a2[j][v] = p.add2[gr[v] * p.ldadd2 + gc];
+      }
+    }
+  }
+};
+
+template <int H, bool BF16, bool CHAIN>
+__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmArgs p1, GemmArgs p2, int keep_silu) {
+  using C = SmallCfg<H, BF16>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* keep = smem + 2 * C::A_BYTES;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, hq = lane >> 4;
+  const int cb0 = blockIdx.y;   // a lone product takes one column block per workgroup, a chain all of them in turn
+  int grp = 0, rbeg, rend;
+  if (p2.grp_ptr) {
+    if (!tile_of_group(p2.grp_ptr, p2.S, C::TM, blockIdx.x, grp, rbeg, rend)) return;
+  } else {
+    rbeg = blockIdx.x * C::TM;
+    rend = p2.M;
+    if (rbeg >= rend) return;
+  }
+  const GemmArgs& pa = CHAIN ? p1 : p2;   // the product that reads A from memory
+  // ---- weights: lane (column c, quarter hq) of step kb takes k = kb * KS + hq * KS / 4 .. of its column, one 16-byte
+  // piece of the packed 32-column operand order (its own 32-column block, k step 2 kb + hq / 2, half hq & 1)
+  u32x4s_t b[C::NKB][C::CB];
+  auto b_rsrc = [&](const GemmArgs& p, int kc, int cb) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(reinterpret_cast<const char*>(p.B)) + (grp * p.grp_blk_stride + p.blk[kc][cb]) * (long)(H * H * C::ESZ), 0,
+        H * H * C::ESZ, 0x00020000);
+  };
+  unsigned bo[C::CB];
+#pragma unroll
+  for (int j = 0; j < C::CB; ++j) {
+    const int n0 = C::col0(wave, j);
+    bo[j] = (unsigned)((((n0 >> 5) * (2 * C::NKB) + (hq >> 1)) * 64 + (hq & 1) * 32 + (n0 & 16) + c) * 16);
+  }
+  auto load_b = [&](const __amdgpu_buffer_rsrc_t& rs, int kb) {
+#pragma unroll
+    for (int j = 0; j < C::CB; ++j) b[kb][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, bo[j], kb * 2048, 0);
+  };
+  {
+    const __amdgpu_buffer_rsrc_t rs = b_rsrc(pa, 0, CHAIN ? 0 : cb0);
+#pragma unroll
+    for (int kb = 0; kb < C::NKB; ++kb) load_b(rs, kb);
+  }
+  // ---- A: every k chunk at once
+  constexpr int CH = H / 4, NA = C::TM * CH / C::THREADS;   // 4-column pieces per thread and chunk
+  static_assert(C::TM * CH % C::THREADS == 0, "whole pieces per thread");
+  float4 av[2][NA];
+  long arow[NA];
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int pos = rbeg + (tid + u * C::THREADS) / CH;
+    arow[u] = pos < rend ? pos : rend - 1;
+    if (pa.row_idx) arow[u] = pa.row_idx[arow[u]];
+  }
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc)
+    if (kc < pa.nkc) {
+#pragma unroll
+      for (int u = 0; u < NA; ++u)
+        av[kc][u] = *reinterpret_cast<const float4*>(pa.A[kc] + arow[u] * pa.lda[kc] + ((tid + u * C::THREADS) % CH) * 4);
+    }
+  // ---- rows of this lane's accumulators and the epilogues' operands
+  long gr[4];
+  bool ok[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int pos = rbeg + 4 * hq + v;
+    ok[v] = pos < rend;
+    gr[v] = ok[v] ? pos : rend - 1;
+    if (p2.row_idx) gr[v] = p2.row_idx[gr[v]];
+  }
+  SmallAux<H, BF16> x1, x2;
+  if constexpr (CHAIN) x1.load(p1, 0, grp, gr, wave, c);
+  x2.load(p2, cb0, grp, gr, wave, c);
+  // ---- A to LDS
+  auto put_a = [&](unsigned char* dst, int r, int q, float4 w) {
+    if constexpr (BF16) *reinterpret_cast<uint2*>(dst + ((size_t)r * C::STRIDE + q * 4) * 2) = make_uint2(pack_bf16x2(w.x, w.y), pack_bf16x2(w.z, w.w));
+    else *reinterpret_cast<float4*>(dst + ((size_t)r * C::STRIDE + q * 4) * 4) = w;
+  };
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc)
+    if (kc < pa.nkc) {
+#pragma unroll
+      for (int u = 0; u < NA; ++u) {
+        const int r = (tid + u * C::THREADS) / CH;
+        float4 w = av[kc][u];
+        if (pa.a_silu) { w.x = silu_f(w.x); w.y = silu_f(w.y); w.z = silu_f(w.z); w.w = silu_f(w.w); }
+        if (rbeg + r >= rend) w = make_float4(0.f, 0.f, 0.f, 0.f);
+        put_a(smem + kc * C::A_BYTES, r, (tid + u * C::THREADS) % CH, w);
+      }
+    }
+  __syncthreads();
+  f32x4_t acc[C::CB];
+  auto clear = [&]() {
+#pragma unroll
+    for (int j = 0; j < C::CB; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  // one chunk; the weights of the next one take each register as it is used up
+  const unsigned ao = (unsigned)((c * C::STRIDE + hq * (16 / C::ESZ)) * C::ESZ);
+  auto multiply = [&](const unsigned char* a_lds, bool next, const __amdgpu_buffer_rsrc_t& rs) {
+    u32x4s_t a[C::NKB];
+#pragma unroll
+    for (int kb = 0; kb < C::NKB; ++kb) a[kb] = *reinterpret_cast<const u32x4s_t*>(a_lds + ao + kb * 64);
+#pragma unroll
+    for (int kb = 0; kb < C::NKB; ++kb) {
+#pragma unroll
+      for (int j = 0; j < C::CB; ++j) {
+        if constexpr (BF16) {
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[kb]), __builtin_bit_cast(bf16x8_t, b[kb][j]), acc[j], 0, 0, 0);
+        } else {
+          const f32x4_t af = __builtin_bit_cast(f32x4_t, a[kb]), bf = __builtin_bit_cast(f32x4_t, b[kb][j]);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[t], bf[t], acc[j], 0, 0, 0);
+        }
+      }
+      if (next) load_b(rs, kb);
+    }
+  };
+  // values of block j, row v of the accumulators through the epilogue
+  auto finish = [&](const GemmArgs& p, const SmallAux<H, BF16>& x, bool ua, int j, int v) {
+    float y = acc[j][v] + x.bias[j];
+    if (p.mul) y *= p.mul_is_z ? dsilu_f(x.mul[j][v]) : x.mul[j][v];
+    if (ua) y += x.a1[j][v];
+    if (p.add2) y += x.a2[j][v];
+    return y;
+  };
+  const unsigned char* a2 = smem;   // A of the second product
+  if constexpr (CHAIN) {
+    clear();
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc)
+      if (kc < p1.nkc) multiply(smem + kc * C::A_BYTES, true, kc + 1 < p1.nkc ? b_rsrc(p1, kc + 1, 0) : b_rsrc(p2, 0, 0));
+    const bool ua = p1.add1 && (p1.add1_cb_mask & 1);
+#pragma unroll
+    for (int j = 0; j < C::CB; ++j) {
+      const int n = C::col0(wave, j) + c;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float y = finish(p1, x1, ua, j, v);
+        if (ok[v]) p1.C[gr[v] * p1.ldc + n] = y;
+        if (keep_silu) y = silu_f(y);
+        if (!ok[v]) y = 0.f;
+        if constexpr (BF16) *reinterpret_cast<unsigned short*>(keep + ((4 * hq + v) * C::STRIDE + n) * 2) = (unsigned short)f2bf_bits(y);
+        else *reinterpret_cast<float*>(keep + ((4 * hq + v) * C::STRIDE + n) * 4) = y;
+      }
+    }
+    a2 = keep;
+    __syncthreads();
+  }
+  const int cbe = CHAIN ? p2.ncb : cb0 + 1;
+  for (int cb = cb0; cb < cbe; ++cb) {
+    clear();
+    if constexpr (CHAIN) {
+      multiply(a2, cb + 1 < cbe, b_rsrc(p2, 0, cb + 1 < cbe ? cb + 1 : cb));
+    } else {
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc)
+        if (kc < p2.nkc) multiply(a2 + kc * C::A_BYTES, kc + 1 < p2.nkc, b_rsrc(p2, kc + 1 < p2.nkc ? kc + 1 : kc, cb));
+    }
+    const bool ua = p2.add1 && ((p2.add1_cb_mask >> cb) & 1);
+    if constexpr (H == 256) {
+      if ((p2.pair_cb_mask >> cb) & 1) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (ok[v])
+            p2.Cpair[gr[v] * p2.ldpair + p2.pair_off[cb] + (wave >> 1) * 32 + (wave & 1) * 16 + c] =
+                pack_bf16x2((acc[0][v] + x2.bias[0]) * p2.pair_scale, (acc[1][v] + x2.bias[1]) * p2.pair_scale);
+        if (cb + 1 < cbe) x2.load(p2, cb + 1, grp, gr, wave, c);
+        continue;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < C::CB; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float y = finish(p2, x2, ua, j, v);
+        if (ok[v]) p2.C[gr[v] * p2.ldc + cb * H + C::col0(wave, j) + c] = y;
+      }
+    if (cb + 1 < cbe) x2.load(p2, cb + 1, grp, gr, wave, c);
+  }
+}
+
+// (rule: see small_gemm())
+template <int H, bool BF16>
+static int32_t launch_gemm_small_t(hipStream_t st, const GemmArgs* first, const GemmArgs& a, int keep_silu) {
+  using C = SmallCfg<H, BF16>;
+  const int tiles = (a.M + C::TM - 1) / C::TM + (a.grp_ptr ? a.S : 0);
+  ProfScope ps(a.tag, st);
+  if (first) k_gemm_small<H, BF16, true><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(*first, a, keep_silu);
+  else k_gemm_small<H, BF16, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(a, a, 0);
+  HGNN_LAUNCH_CHECK("k_gemm_small");
+  return HGNN_OK;
+}
+// The short chains win while the taller tiles would not give every compute unit one of them; beyond that twice the
+// tiles mean twice the weight traffic. Steps, 32 / 64-row tiles against 16-row tiles: 32 molecules (7 tiles) 485 -> 461 us,
+// a crystal's conservative forces (6) 944 -> 863, 16 crystals (32) 1175 -> 1083, 64 crystals (127) 1881 -> 1806,
+// 128 molecules (140) 973 -> 946, 203 molecules, energies and forces only (222) 315 -> 302; past the line 160 mixed
+// structures (338) 2980 -> 3028, 300 (600) 4885 -> 5094. fp32 operands at H = 256 keep the taller tiles: a chunk of
+// their weights is 128 registers.
+static bool small_gemm(int M, int tile_rows) { return (M + tile_rows - 1) / tile_rows <= num_cus(); }
+
 // workgroups of this variant that one CU holds at a time (asked once; also raises the LDS limit of the kernel)
 template <int H, bool BF16, int TM>
 static int gemm_resident_wgs() {
@@ -508,6 +760,9 @@ static int32_t launch_gemm_tm(hipStream_t st, const GemmArgs& a) {
 template <int H, bool BF16>
 static int32_t launch_gemm_t(hipStream_t st, const GemmArgs& a) {
   if (a.M <= 0) return HGNN_OK;
+  if constexpr (BF16 || H < 256) {
+    if (small_gemm(a.M, GemmCfg<H, BF16>::WR == 1 ? 32 : 64)) return launch_gemm_small_t<H, BF16>(st, nullptr, a, 0);
+  }
   if constexpr (GemmCfg<H, BF16>::WR == 1) return launch_gemm_tm<H, BF16, 32>(st, a);
   else return launch_gemm_tm<H, BF16, 64>(st, a);
 }
@@ -517,6 +772,9 @@ static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const 
   constexpr int TM = GemmCfg<H, BF16>::WR == 1 ? 32 : 64;
   using C = GemmCfg<H, BF16, TM>;
   if (second.M <= 0) return HGNN_OK;
+  if constexpr (BF16 || H < 256) {
+    if (small_gemm(second.M, TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu);
+  }
   constexpr size_t LDS = C::LDS_BYTES + C::A_BYTES;
   static bool raised = false;   // the kernel's LDS limit is raised once per variant
   if (!raised) {

@@ -164,6 +164,15 @@ def test_layer_atom_counts(H, dtype, N):
     _run_layer(N=N, E=3000, H=H, dtype=dtype, seed=N)
 
 
+# Atom counts around the 16-row tiles of small batches and the largest batch that takes them (256 taller tiles)
+@pytest.mark.parametrize("H,dtype,last", [(256, "bf16", 8192), (128, "f32", 8192), (128, "bf16", 8192), (64, "f32", 16384),
+                                          (64, "bf16", 16384)])
+@pytest.mark.parametrize("N", [2, 15, 16, 17, 33, 0, 1])
+def test_layer_atom_counts_of_small_row_tiles(N, H, dtype, last):
+    n = N if N > 1 else last + N
+    _run_layer(N=n, E=3000 if N < 2 else 40 * n, H=H, dtype=dtype, seed=n)
+
+
 # Widths other than 64 / 128 / 256 take the fragment-GEMM path (bf16 operands, width padded to a multiple of 128, rows
 # to 256): the paper's 866, widths on both sides of the padding steps, odd and small widths, edge counts around the
 # 16 / 32 / 256-row groups.
