@@ -832,9 +832,37 @@ struct SegCols {
   }
 };
 
+// Where there are few rows, one wavefront per row leaves most of the chip idle and a row's edges come four at a time, one
+// memory latency after the other: SEG_SPLIT wavefronts (one workgroup) then take consecutive parts of a row, whole trips of
+// four edges each, and the first one adds their sums in order out of LDS.
+constexpr int SEG_SPLIT = 4;
+struct SegPart {
+  int first, end;
+};
+__device__ __forceinline__ SegPart seg_part(int first, int end, int part) {
+  const int per = ((end - first + SEG_SPLIT - 1) / SEG_SPLIT + 3) & ~3;
+  const int lo = first + part * per;
+  return {lo < end ? lo : end, lo + per < end ? lo + per : end};
+}
+// v of the parts 1 .. SEG_SPLIT - 1 added to part 0's, in order; true for the wavefront that holds the sums
+template <int NV>
+__device__ __forceinline__ bool seg_combine(float (*sh)[NV][64], int part, int lane, float (&v)[NV]) {
+  if (part > 0) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) sh[part - 1][c][lane] = v[c];
+  }
+  __syncthreads();
+  if (part > 0) return false;
+#pragma unroll
+  for (int q = 0; q < SEG_SPLIT - 1; ++q)
+#pragma unroll
+    for (int c = 0; c < NV; ++c) v[c] += sh[q][c][lane];
+  return true;
+}
+
 // XE: also keep x_e = wx . m_e of every edge (for the gradient with respect to the edge vectors); v' is then summed
 // from the x_e (another summation order than without XE)
-template <int H, bool BF16, bool XE>
+template <int H, bool BF16, bool XE, bool SPLIT>
 __global__ void __launch_bounds__(256)
 k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict__ z2_vm,
              const float* __restrict__ rvec, const float* __restrict__ wx, float alpha,
@@ -842,17 +870,37 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
              float* __restrict__ xe) {
   using S = SegCols<H, BF16, BF16 && H == 256>;
   constexpr int NV = S::NPASS * S::PER;
-  const int i = __builtin_amdgcn_readfirstlane((int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+  const int part = SPLIT ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const int i = SPLIT ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane((int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6));
   const int lane = threadIdx.x & 63;
-  if (i >= N) return;
+  if (i >= N) return;   // (never with SPLIT: one workgroup per row)
   const int hp = lane >> 5, x = lane & 31;
-  const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
+  int e0 = row_ptr[i], e1 = row_ptr[i + 1];
+  if constexpr (SPLIT) {
+    const SegPart sp = seg_part(e0, e1, part);
+    e0 = sp.first;
+    e1 = sp.end;
+  }
+  __shared__ float sh[SPLIT ? SEG_SPLIT - 1 : 1][SPLIT ? NV + 3 : 1][64];
   unsigned loff[S::NPASS];   // kept as registers of their own: loads take a scalar base plus one of them
 #pragma unroll
   for (int c = 0; c < S::NPASS; ++c) {
     loff[c] = S::lane_off(c, hp, x);
     asm volatile("" : "+v"(loff[c]));
   }
+  auto combine = [&](float (&acc)[NV], float& sx, float& sy, float& sz) {
+    if constexpr (SPLIT) {
+      float v[NV + 3];
+#pragma unroll
+      for (int c = 0; c < NV; ++c) v[c] = acc[c];
+      v[NV] = sx; v[NV + 1] = sy; v[NV + 2] = sz;
+      if (!seg_combine<NV + 3>(sh, part, lane, v)) return false;
+#pragma unroll
+      for (int c = 0; c < NV; ++c) acc[c] = v[c];
+      sx = v[NV]; sy = v[NV + 1]; sz = v[NV + 2];
+    }
+    return true;
+  };
   if constexpr (XE) {
     float acc[NV], wl[NV];
 #pragma unroll
@@ -865,10 +913,12 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
     float sx = 0.f, sy = 0.f, sz = 0.f;
     constexpr int EPT = 4;
     for (int e = e0; e < e1; e += EPT) {   // four edges per trip (clamped at the end of the row)
-      float z[EPT][NV], xs[EPT];
+      float z[EPT][NV], xs[EPT], r[EPT][3];
 #pragma unroll
       for (int u = 0; u < EPT; ++u) {
         const int ee = e + u < e1 ? e + u : e1 - 1;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) r[u][k] = rvec[3 * (size_t)ee + k];
 #pragma unroll
         for (int c = 0; c < S::NPASS; ++c) S::fetch_u(z2_vm, ee, loff[c], &z[u][c * S::PER]);
       }
@@ -889,11 +939,12 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
         if (e + u < e1) {
           const size_t ee = (size_t)(e + u);
           if (lane == 0) xe[ee] = xs[u];
-          sx = fmaf(xs[u], rvec[3 * ee], sx);
-          sy = fmaf(xs[u], rvec[3 * ee + 1], sy);
-          sz = fmaf(xs[u], rvec[3 * ee + 2], sz);
+          sx = fmaf(xs[u], r[u][0], sx);
+          sy = fmaf(xs[u], r[u][1], sy);
+          sz = fmaf(xs[u], r[u][2], sz);
         }
     }
+    if (!combine(acc, sx, sy, sz)) return;
 #pragma unroll
     for (int c = 0; c < S::NPASS; ++c)
 #pragma unroll
@@ -944,6 +995,35 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
       sz = fmaf(t, r[u][2], sz);
     }
   }
+  if constexpr (SPLIT) {
+    // the remainder as one more trip, clamped at the end of the part
+    if (e < e1) {
+      float r[EPT][3], z[EPT][NV];
+#pragma unroll
+      for (int u = 0; u < EPT; ++u) {
+        const int ee = e + u < e1 ? e + u : e1 - 1;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) r[u][k] = rvec[3 * (size_t)ee + k];
+#pragma unroll
+        for (int c = 0; c < S::NPASS; ++c) S::fetch_u(z2_vm, ee, loff[c], &z[u][c * S::PER]);
+      }
+#pragma unroll
+      for (int u = 0; u < EPT; ++u)
+        if (e + u < e1) {
+          float t = 0.f;
+#pragma unroll
+          for (int c = 0; c < NV; ++c) {
+            const float m = silu_f(z[u][c]);
+            acc[c] += m;
+            t = fmaf(wl[c], m, t);
+          }
+          sx = fmaf(t, r[u][0], sx);
+          sy = fmaf(t, r[u][1], sy);
+          sz = fmaf(t, r[u][2], sz);
+        }
+    }
+    e = e1;
+  }
   for (; e < e1; ++e) {
     const float rx = rvec[3 * (size_t)e], ry = rvec[3 * (size_t)e + 1], rz = rvec[3 * (size_t)e + 2];
     float z[NV];
@@ -960,6 +1040,7 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
     sy = fmaf(t, ry, sy);
     sz = fmaf(t, rz, sz);
   }
+  if (!combine(acc, sx, sy, sz)) return;
 #pragma unroll
   for (int c = 0; c < S::NPASS; ++c)
 #pragma unroll
@@ -974,15 +1055,26 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
   }
 }
 
+// Fewer rows than the chip holds wavefronts (32 per compute unit). Per launch, without and with the split: 187 rows of 57
+// edges, H = 128 fp32, forward with x_e 36 -> 12.5 us, source sum with the dots 28 -> 9.8 us; steps: a crystal's conservative
+// forces 845 -> 694 us, 16 crystals 1083 -> 999, 64 crystals (4,096 rows) 1886 -> 1849, 128 molecules (4,600 rows)
+// 999 -> 976. Past the line it changes nothing (12,900 and 18,600 rows: within 1 %).
+static bool seg_split(int N) { return N <= num_cus() * 32; }
+
 int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, const int32_t* row_ptr, const void* z2_vm,
                           const float* rvec, const float* wx, float alpha, const float* v_in, float* M,
                           float* v_out, float* xe) {
   if (N <= 0) return HGNN_OK;
-  const unsigned grid = (unsigned)(((int64_t)N * 64 + 255) / 256);
+  const bool split = seg_split(N);
+  const unsigned grid = split ? (unsigned)N : (unsigned)(((int64_t)N * 64 + 255) / 256);
   ProfScope ps(PT_SEG_FWD, st);
-#define HGNN_SEGF(HH, BB)                                                                                        \
-  if (xe) k_seg_fwd_vm<HH, BB, true><<<grid, 256, 0, st>>>(N, row_ptr, z2_vm, rvec, wx, alpha, v_in, M, v_out, xe); \
-  else k_seg_fwd_vm<HH, BB, false><<<grid, 256, 0, st>>>(N, row_ptr, z2_vm, rvec, wx, alpha, v_in, M, v_out, xe)
+#define HGNN_SEGF1(HH, BB, XX, SS) \
+  k_seg_fwd_vm<HH, BB, XX, SS><<<grid, 256, 0, st>>>(N, row_ptr, z2_vm, rvec, wx, alpha, v_in, M, v_out, xe)
+#define HGNN_SEGF(HH, BB)                              \
+  if (xe && split) HGNN_SEGF1(HH, BB, true, true);     \
+  else if (xe) HGNN_SEGF1(HH, BB, true, false);        \
+  else if (split) HGNN_SEGF1(HH, BB, false, true);     \
+  else HGNN_SEGF1(HH, BB, false, false)
   switch (H) {
     case 64: if (bf16) { HGNN_SEGF(64, true); } else { HGNN_SEGF(64, false); } break;
     case 128: if (bf16) { HGNN_SEGF(128, true); } else { HGNN_SEGF(128, false); } break;
@@ -990,6 +1082,7 @@ int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, const int32_t
     default: return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256");
   }
 #undef HGNN_SEGF
+#undef HGNN_SEGF1
   HGNN_LAUNCH_CHECK("k_seg_fwd_vm");
   return HGNN_OK;
 }
@@ -1034,20 +1127,28 @@ struct DsumFixRow {
 
 // DOT: also dot[e] = sum_c wdot[c] X[e][c] for every edge of the list (the gradient with respect to d2 when X = g_z1
 // and wdot is the row of W1 that acts on d2)
-template <int H, bool BF16, bool DOT>
+template <int H, bool BF16, bool DOT, bool SPLIT>
 __global__ void __launch_bounds__(256)
 k_segsum_vm(int N, const int32_t* __restrict__ ptr, const int32_t* __restrict__ perm, const void* __restrict__ X,
             float* __restrict__ out, int ldo, const float* __restrict__ wdot, float* __restrict__ dot, DsumFix fix) {
   using S = SegCols<H, BF16, BF16 && H == 256>;
   constexpr int NV = S::NPASS * S::PER;
-  const int i = __builtin_amdgcn_readfirstlane((int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+  const int part = SPLIT ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const int i = SPLIT ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane((int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6));
   const int lane = threadIdx.x & 63;
-  if (i >= N) return;
+  if (i >= N) return;   // (never with SPLIT: one workgroup per row)
   const int hp = lane >> 5, x = lane & 31;
-  const int t0 = ptr[i], t1 = ptr[i + 1];
+  int t0 = ptr[i], t1 = ptr[i + 1];
+  if constexpr (SPLIT) {
+    const SegPart sp = seg_part(t0, t1, part);
+    t0 = sp.first;
+    t1 = sp.end;
+  }
+  __shared__ float sh[SPLIT ? SEG_SPLIT - 1 : 1][SPLIT ? NV : 1][64];
   // on request this wavefront also finishes atom i's row of another sum, the one the reverse edge kernel started
   DsumFixRow<H> fr;
-  if (fix.gP) fr.issue(i, lane, fix);
+  const bool fixes = fix.gP && part == 0;
+  if (fixes) fr.issue(i, lane, fix);
   if constexpr (DOT) {
     float acc[NV], wl[NV];
 #pragma unroll
@@ -1081,11 +1182,14 @@ k_segsum_vm(int N, const int32_t* __restrict__ ptr, const int32_t* __restrict__ 
         if (on && lane == 0) dot[ee[u]] = d;
       }
     }
+    if constexpr (SPLIT) {
+      if (!seg_combine<NV>(sh, part, lane, acc)) return;
+    }
 #pragma unroll
     for (int c = 0; c < S::NPASS; ++c)
 #pragma unroll
       for (int k = 0; k < S::PER; ++k) out[(size_t)i * ldo + S::column(c, hp, x, k)] = acc[c * S::PER + k];
-    if (fix.gP) fr.finish(i, lane, fix);
+    if (fixes) fr.finish(i, lane, fix);
     return;
   }
   float acc[NV];
@@ -1107,6 +1211,29 @@ k_segsum_vm(int N, const int32_t* __restrict__ ptr, const int32_t* __restrict__ 
 #pragma unroll
       for (int c = 0; c < NV; ++c) acc[c] += vv[u][c];
   }
+  if constexpr (SPLIT) {
+    // the remainder as one more trip, clamped at the end of the part
+    if (t < t1) {
+      size_t ee[EPT];
+#pragma unroll
+      for (int u = 0; u < EPT; ++u) {
+        const int tt = t + u < t1 ? t + u : t1 - 1;
+        ee[u] = perm ? (size_t)perm[tt] : (size_t)tt;
+      }
+      float vv[EPT][NV];
+#pragma unroll
+      for (int u = 0; u < EPT; ++u)
+#pragma unroll
+        for (int c = 0; c < S::NPASS; ++c) S::fetch(X, ee[u], c, hp, x, &vv[u][c * S::PER]);
+#pragma unroll
+      for (int u = 0; u < EPT; ++u)
+        if (t + u < t1) {
+#pragma unroll
+          for (int c = 0; c < NV; ++c) acc[c] += vv[u][c];
+        }
+    }
+    t = t1;
+  }
   for (; t < t1; ++t) {
     const size_t ea = perm ? (size_t)perm[t] : (size_t)t;
     float va[NV];
@@ -1115,11 +1242,14 @@ k_segsum_vm(int N, const int32_t* __restrict__ ptr, const int32_t* __restrict__ 
 #pragma unroll
     for (int c = 0; c < NV; ++c) acc[c] += va[c];
   }
+  if constexpr (SPLIT) {
+    if (!seg_combine<NV>(sh, part, lane, acc)) return;
+  }
 #pragma unroll
   for (int c = 0; c < S::NPASS; ++c)
 #pragma unroll
     for (int k = 0; k < S::PER; ++k) out[(size_t)i * ldo + S::column(c, hp, x, k)] = acc[c * S::PER + k];
-  if (fix.gP) fr.finish(i, lane, fix);
+  if (fixes) fr.finish(i, lane, fix);
 }
 
 int32_t launch_segsum_vm(hipStream_t st, int H, bool bf16, int N, const int32_t* ptr, const int32_t* perm,
@@ -1127,11 +1257,15 @@ int32_t launch_segsum_vm(hipStream_t st, int H, bool bf16, int N, const int32_t*
                          const DsumFix* fix) {
   if (N <= 0) return HGNN_OK;
   const DsumFix fx = fix ? *fix : DsumFix{nullptr, nullptr, nullptr, 0};
-  const unsigned grid = (unsigned)(((int64_t)N * 64 + 255) / 256);
+  const bool split = seg_split(N);
+  const unsigned grid = split ? (unsigned)N : (unsigned)(((int64_t)N * 64 + 255) / 256);
   ProfScope ps(tag, st);
-#define HGNN_SEGS(HH, BB)                                                                            \
-  if (dot) k_segsum_vm<HH, BB, true><<<grid, 256, 0, st>>>(N, ptr, perm, X_vm, out, ldo, wdot, dot, fx); \
-  else k_segsum_vm<HH, BB, false><<<grid, 256, 0, st>>>(N, ptr, perm, X_vm, out, ldo, wdot, dot, fx)
+#define HGNN_SEGS1(HH, BB, DD, SS) k_segsum_vm<HH, BB, DD, SS><<<grid, 256, 0, st>>>(N, ptr, perm, X_vm, out, ldo, wdot, dot, fx)
+#define HGNN_SEGS(HH, BB)                            \
+  if (dot && split) HGNN_SEGS1(HH, BB, true, true);  \
+  else if (dot) HGNN_SEGS1(HH, BB, true, false);     \
+  else if (split) HGNN_SEGS1(HH, BB, false, true);   \
+  else HGNN_SEGS1(HH, BB, false, false)
   switch (H) {
     case 64: if (bf16) { HGNN_SEGS(64, true); } else { HGNN_SEGS(64, false); } break;
     case 128: if (bf16) { HGNN_SEGS(128, true); } else { HGNN_SEGS(128, false); } break;
@@ -1139,6 +1273,7 @@ int32_t launch_segsum_vm(hipStream_t st, int H, bool bf16, int N, const int32_t*
     default: return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256");
   }
 #undef HGNN_SEGS
+#undef HGNN_SEGS1
   HGNN_LAUNCH_CHECK("k_segsum_vm");
   return HGNN_OK;
 }
