@@ -26,6 +26,14 @@ struct PackArgs {
   // multiply with when the operands are fp32
   void* x3_dst = nullptr;
   int x3_desc = 0;
+  // optional (groups == 1): the launch also forms cvec[e] = alpha * (g_v[dst[e],:] . rvec[e,:]), which the reverse edge
+  // kernel reads: both only need the call's inputs, and a launch of its own took 3-6 us per layer. (Formed inside the
+  // edge kernel, dst[e] -> g_v is a chain of two memory latencies at the start of each tile: 450 -> 483 us on 1.2 M edges.)
+  int64_t E = 0;
+  const int32_t* dst_e = nullptr;
+  const float *rvec = nullptr, *g_v = nullptr;
+  float alpha = 0.f;
+  float* cvec = nullptr;
 };
 int32_t launch_pack(hipStream_t st, int H, bool bf16, const PackArgs& a, int groups = 1, long src_grp_stride = 0,
                     long dst_grp_stride_elems = 0);

@@ -25,6 +25,15 @@ __global__ void k_pack(PackArgs a, int H, long src_grp_stride, long dst_grp_stri
   const int b = blockIdx.y;
   const int grp = blockIdx.z;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const int planes = a.nblocks + (a.x3_dst ? 1 : 0);
+  if (b >= planes) {
+    const int64_t plane = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (b - planes) * plane + idx; e < a.E; e += (gridDim.y - planes) * plane) {
+      const size_t i = (size_t)a.dst_e[e];
+      a.cvec[e] = a.alpha * (a.g_v[3 * i] * a.rvec[3 * e] + a.g_v[3 * i + 1] * a.rvec[3 * e + 1] + a.g_v[3 * i + 2] * a.rvec[3 * e + 2]);
+    }
+    return;
+  }
   if (idx >= H * H) return;
   if (b == a.nblocks) {   // the extra block as three bf16 planes (see split_bf16x3), each in the bf16 operand order
     const PackDesc d = a.d[a.x3_desc];
@@ -66,9 +75,13 @@ __global__ void k_pack(PackArgs a, int H, long src_grp_stride, long dst_grp_stri
 int32_t launch_pack(hipStream_t st, int H, bool bf16, const PackArgs& a, int groups, long src_grp_stride,
                     long dst_grp_stride_elems) {
   if (a.nblocks <= 0 || groups <= 0) return HGNN_OK;
+  HGNN_REQUIRE(groups == 1 || (!a.x3_dst && !a.cvec), HGNN_ERR_BAD_SHAPE, "pack: one group with the extra jobs");
+  HGNN_REQUIRE(!bf16 || !a.x3_dst, HGNN_ERR_BAD_SHAPE, "pack: bf16 planes go with fp32 operands");
   ProfScope ps(PT_PACK, st);
-  const bool x3 = a.x3_dst != nullptr && !bf16 && groups == 1;
-  dim3 grid((H * H + 255) / 256, a.nblocks + (x3 ? 1 : 0), groups);
+  const int xb = (H * H + 255) / 256;
+  int64_t eplanes = a.cvec ? (a.E + (int64_t)xb * 256 - 1) / ((int64_t)xb * 256) : 0;
+  if (eplanes > 8192) eplanes = 8192;   // (the y dimension ends at 65,535; the rest in a loop)
+  dim3 grid(xb, (unsigned)(a.nblocks + (a.x3_dst ? 1 : 0) + eplanes), groups);
   if (bf16) k_pack<true><<<grid, 256, 0, st>>>(a, H, src_grp_stride, dst_grp_stride_elems);
   else k_pack<false><<<grid, 256, 0, st>>>(a, H, src_grp_stride, dst_grp_stride_elems);
   HGNN_LAUNCH_CHECK("k_pack");

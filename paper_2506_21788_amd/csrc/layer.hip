@@ -381,6 +381,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   pk.d[4] = {o.W1, 1, H};
   pk.d[5] = {o.W1 + HH, 1, H};
   pk.x3_dst = w.packed_x3; pk.x3_desc = 3;   // fp32 operands: W2^T also as three bf16 planes
+  pk.E = E; pk.dst_e = dst; pk.rvec = rvec; pk.g_v = g_v_out; pk.alpha = alpha; pk.cvec = w.cvec;   // and c_e of every edge
   HGNN_TRY(launch_pack(st, H, bf16, pk));
 
   SideStream& ss = side_stream();
@@ -410,9 +411,8 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
     }
     HGNN_TRY(launch_gemm_chain(st, H, bf16, &g, g2, 0));
   }
-  // edge part: c_e, then g_z2 -> (x W2^T) -> g_z1 with the per-column sums. The fused edge kernel fills
+  // edge part: g_z2 -> (x W2^T) -> g_z1 with the per-column sums. The fused edge kernel fills
   // every CU by itself, so the side stream is drained first instead of competing with it.
-  HGNN_TRY(launch_edge_cvec(st, E, dst, rvec, g_v_out, alpha, w.cvec));
   HGNN_TRY(stream_after(st, sx, ss.ev[5]));
   // With bf16 pairs, or fp32 operands at H = 128, the reverse edge kernel also sums g_z1 per destination (out of the
   // tile it holds in LDS). The gradient with respect to d2 (on request: the dot of every g_z1 row with the d2 row of
