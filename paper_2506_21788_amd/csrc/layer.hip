@@ -118,8 +118,11 @@ SideStream& side_stream() {
   }
   return ss;
 }
-// `to` waits for everything enqueued on `from` so far
+// `to` waits for everything enqueued on `from` so far. One stream is in order by itself: an event recorded there only puts a
+// marker with a cache flush between two kernels, five per layer where no side stream is used. Without them: a crystal's
+// conservative forces 657 -> 595 us, 32 small molecules 432 -> 375, 128 molecules 972 -> 909, 64 crystals 1802 -> 1706.
 int32_t stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
+  if (to == from) return HGNN_OK;
   HGNN_HIP(hipEventRecord(ev, from));
   HGNN_HIP(hipStreamWaitEvent(to, ev, 0));
   return HGNN_OK;
