@@ -27,6 +27,11 @@ inline size_t frag_rows(int64_t E) { return (size_t)((E + 31) / 32 * 32); }
 // holds columns wc*64 + x (low half) and wc*64 + 32 + x (high half).
 inline bool edge_pairs(int H, bool bf16) { return bf16 && H == 256; }
 
+// Up to H = 128 the reverse kernel forms g_W2 from the g_z2 it holds in LDS and the a1 it has when it recomputes z1, so
+// neither is stored. The 128 x 128 accumulator is 64 registers per lane (64 x 64: 32); at H = 256 it would be 256, and
+// at H = 128 with k > 1 edge attributes, which need registers of their own, 72 registers spill.
+constexpr bool edge_bwd_forms_w2(int H, int k) { return H <= 64 || (H == 128 && k <= 1); }
+
 struct EdgeFwdArgs {
   int64_t E;
   const int32_t *dst, *col;
@@ -108,9 +113,6 @@ constexpr int DSUM_UNIT = 64;
 inline size_t edge_bwd_dpart_floats(int64_t E, int H) { return (size_t)((E + DSUM_UNIT - 1) / DSUM_UNIT) * 2 * H; }
 // the operand types and widths for which k_edge_bwd can form g_P itself (an edge's g_z1 is 128 words there)
 inline bool edge_bwd_sums_dst(int H, bool bf16) { return edge_pairs(H, bf16) || (!bf16 && H == 128); }
-// fp32 operands at H = 128: the reverse kernel forms g_W2 from the g_z2 it holds in LDS and the a1 it has when it
-// recomputes z1. The 128 x 128 accumulator is 64 registers per lane; at H = 256 (bf16 pairs) it would be 256.
-inline bool edge_bwd_forms_w2(int H, bool bf16) { return !bf16 && H == 128; }
 size_t edge_bwd_attrpart_floats(int H);
 size_t edge_bwd_colpart_floats(int H);
 int32_t launch_edge_bwd(hipStream_t st, int H, bool bf16, const EdgeBwdArgs& a);

@@ -39,11 +39,11 @@ struct ECfg {
   // one 32-bit word of P, Q per lane and edge (bf16 pairs, or one column block): gathers are software-pipelined
   static constexpr bool WORD = BF16 || CB == 1;
   static constexpr size_t PLANE_BYTES = (size_t)TM * STRIDE * 2;   // one bf16 plane
-  // the reverse kernel forms g_W2 as well (fp32 operands, H = 128); row pitch of its planes: see wgrad_group
-  static constexpr bool WGRAD = PLANES && H == 128;
+  // the reverse kernel forms g_W2 as well; row pitch of its planes: see wgrad_group
+  static constexpr bool WGRAD = edge_bwd_forms_w2(H, 1);
   static constexpr int BSTRIDE = WGRAD ? H + 16 : STRIDE;
   static constexpr size_t BPLANE_BYTES = (size_t)TM * BSTRIDE * 2;
-  static constexpr size_t BLDS_BYTES = WGRAD ? 3 * BPLANE_BYTES : BF16 ? PLANE_BYTES : PLANES ? 3 * PLANE_BYTES : (size_t)TM * STRIDE * 4;
+  static constexpr size_t BLDS_BYTES = BF16 ? BPLANE_BYTES : PLANES ? 3 * BPLANE_BYTES : (size_t)TM * STRIDE * 4;
   static constexpr size_t LDS_BYTES = BF16 ? PLANE_BYTES : PLANES ? 3 * PLANE_BYTES : (size_t)TM * STRIDE * 4;
 };
 
@@ -1400,30 +1400,34 @@ int32_t launch_edge_cvec(hipStream_t st, int64_t E, const int32_t* dst, const fl
 }
 
 // g_W2 += a1^T g_z2 over the 16 edges (block rblk, register half vh) whose a1 = silu(z1) this lane holds in 8 registers
-// (column wc*32 + (lane & 31)): split into three bf16 terms they ARE the A operand of a contraction over edges (lane group
-// g holds edges 16 vh + 4 g + 0..3 and + 8). The B operands, g_z2 of all columns in the same edge order, come out of the
-// row-major planes in LDS through transposing reads: of 16 lanes each names 8 bytes of one of four rows, and lane i
-// receives column i of the four. Row pitch H + 16: 72 words put four rows in banks 0, 8, 16, 24, so a 16-lane group meets
-// no conflict, and the row-wise reads of the product with W2^T (8 lanes x 16 bytes) none either.
+// (column wc*32 + (lane & 31)): rounded to bf16 (fp32 operands: split into three bf16 terms) they ARE the A operand of a
+// contraction over edges (lane group g holds edges 16 vh + 4 g + 0..3 and + 8). The B operands, g_z2 of all columns in the
+// same edge order, come out of the row-major planes in LDS through transposing reads: of 16 lanes each names 8 bytes of one
+// of four rows, and lane i receives column i of the four. Row pitch H + 16: 72 words (H = 64: 40) put four rows in banks
+// 0, 8, 16, 24 (0, 40, 16, 56), so a 16-lane group meets no conflict, and the row-wise reads of the product with W2^T
+// (8 lanes x 16 bytes) none either.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
-template <int H, int STRIDE>
+template <int H, bool BF16, int STRIDE>
 __device__ __forceinline__ void wgrad_group(const unsigned char* smem, int rblk, int vh, int lane, const float (&a1)[8],
                                             f32x16_t (&wacc)[H / 32]) {
   constexpr int PLANE = 64 * STRIDE * 2;
-  bf16x8_t a[3];
-  split_bf16x3(a1, a);
+  constexpr int NP = BF16 ? 1 : 3;
+  bf16x8_t a[NP];
+  if constexpr (BF16) a[0] = pack_operand8(a1);
+  else split_bf16x3(a1, a);
   const unsigned char* base = smem + ((rblk * 32 + 16 * vh + 4 * (lane >> 5) + ((lane & 15) >> 2)) * STRIDE + (lane & 16) + (lane & 3) * 4) * 2;
 #pragma unroll
   for (int nb = 0; nb < H / 32; ++nb) {
-    bf16x8_t b[3];
+    bf16x8_t b[NP];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < NP; ++q) {
       const unsigned char* src = base + q * PLANE + nb * 64;
       const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src));
       const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src + 8 * STRIDE * 2));
       b[q] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     }
-    wacc[nb] = mfma_bf16x3(a, b, wacc[nb]);
+    if constexpr (BF16) wacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], wacc[nb], 0, 0, 0);
+    else wacc[nb] = mfma_bf16x3(a, b, wacc[nb]);
   }
 }
 
@@ -1442,7 +1446,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
                                               f32x16_t (&gacc)[ECfg<H, BF16>::CB],
                                               f32x16_t (&wacc)[ECfg<H, BF16>::WGRAD ? H / 32 : 1]) {
   using C = ECfg<H, BF16>;
-  constexpr bool WG = C::WGRAD;
+  constexpr bool WG = edge_bwd_forms_w2(H, ATTR ? 2 : 1);
   constexpr bool PAIRS = BF16 && C::CB == 2;
   constexpr unsigned GM_ROW = PAIRS ? H * 2u : 2u * H * 4u;   // row pitch of g_M in bytes (checked by the launcher)
   const int g = lane >> 5, x = lane & 31;
@@ -1643,7 +1647,6 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
           if constexpr (WG) acc[i][0][8 * vh + u] = ga[0][u];   // to LDS behind the barrier below
           else if constexpr (DSUM) dsw[(rblk * 32 + 8 * (2 * vh + (u >> 2)) + (u & 3)) * DPITCH] = pw;
         }
-        if constexpr (WG) wgrad_group<H, C::BSTRIDE>(smem, rblk, vh, lane, a1, wacc);
       } else {
         char* o = uoff(p.gz1_vm, (((size_t)eb * C::NCB + wc) * 16 + 8 * vh) * 128);
 #pragma unroll
@@ -1653,6 +1656,7 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
           stg_nt<unsigned short>(o, lane * 2u + (2 * t + 1) * 128u, (unsigned short)(pk >> 16));
         }
       }
+      if constexpr (WG) wgrad_group<H, BF16, C::BSTRIDE>(smem, rblk, vh, lane, a1, wacc);
       if constexpr (ATTR) {
         const bf16x8_t aT = attr_t_operand(att, rblk, vh, lane);
 #pragma unroll
@@ -1689,12 +1693,16 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
         for (int u = 0; u < 8; ++u) {
           const float zz = ATTR ? z[j][u] + zat[j][8 * vh + u] : z[j][u];
           float dz;
-          if constexpr (WG) silu_both(zz, a1[u], dz);
-          else dz = dsilu_f(zz);
+          if constexpr (WG) {
+            silu_both(zz, a1[u], dz);
+            if (eb * 32 + 8 * (2 * vh + (u >> 2)) + 4 * g + (u & 3) >= E) a1[u] = 0.f;   // atom 0's row there: it may not be finite
+          } else {
+            dz = dsilu_f(zz);
+          }
           gv[j][u] = acc[i][j][8 * vh + u] * dz;   // rows beyond E have acc == 0
           if constexpr (!ATTR) sw1[j] += dd[u] * gv[j][u];
         }
-      if constexpr (WG) wgrad_group<H, C::BSTRIDE>(smem, rblk, vh, lane, a1, wacc);   // rows beyond E: g_z2 == 0
+      if constexpr (WG) wgrad_group<H, BF16, C::BSTRIDE>(smem, rblk, vh, lane, a1, wacc);   // rows beyond E: zeros
       if constexpr (ATTR) {
         const bf16x8_t aT = attr_t_operand(att, rblk, vh, lane);
 #pragma unroll
@@ -1832,11 +1840,13 @@ __device__ __forceinline__ void edge_bwd_tile(const EdgeBwdArgs& p, unsigned cha
   }
 }
 
-// WGRAD (fp32 operands, H = 128): g_W2 is formed in the last phase out of the planes of g_z2 in LDS. As a kernel of its own
-// it read g_z2 back, gathered P and Q and formed the sigmoids once more. 7.2 M edges: 2883 + 1866 us as two kernels, 3618 us
-// as one with two workgroups per compute unit (64 accumulator registers); 81 k edges: 38 + 43 us, 46 us.
+// WGRAD (H <= 128): g_W2 is formed in the last phase out of the planes of g_z2 in LDS. As a kernel of its own it read g_z2 and a1
+// (or P and Q) back, and g_z2 and, in the forward pass, a1 had to be written for it. fp32, H = 128: 7.2 M edges 2883 + 1866 us as
+// two kernels, 3618 us as one with two workgroups per compute unit (64 accumulator registers); 81 k edges 38 + 43 us, 46 us.
+// Whole steps: 1500 molecules, H = 64, fp32 4.02 -> 3.09 ms, bf16 2.86 -> 2.44, 600 molecules with 8 attributes 1.63 -> 1.42;
+// bf16, H = 128: 600 molecules 2.22 -> 1.87 ms, two cells of 10,000 atoms 4.42 -> 3.65.
 template <int H, bool BF16, bool ATTR, bool DSUM>
-__global__ void __launch_bounds__(256, ((ATTR || ECfg<H, BF16>::WGRAD) ? 2 : 3)) k_edge_bwd(EdgeBwdArgs p, int ntiles) {
+__global__ void __launch_bounds__(256, ((ATTR || H == 128) ? 2 : 3)) k_edge_bwd(EdgeBwdArgs p, int ntiles) {
   using C = ECfg<H, BF16>;
   static_assert(!ATTR || (BF16 && C::TM == 64), "edge attributes: bf16 operands, 64-edge tiles");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1903,8 +1913,8 @@ __global__ void __launch_bounds__(256, ((ATTR || ECfg<H, BF16>::WGRAD) ? 2 : 3))
       edge_bwd_tile<H, BF16, false, ATTR, DSUM>(p, smem, s, sc, s_new, nxt, tile, E, tid, wr, wc, lane, w1d, wxn, sb2, swx, sw1, at, att,
                                           at_next, att_next, nxa, bW1a, gacc, wacc);
   }
-  if constexpr (C::WGRAD) {
-    float* o = p.w2part + (size_t)blockIdx.x * H * H + (size_t)wc * 32 * H + x;
+  if constexpr (edge_bwd_forms_w2(H, ATTR ? 2 : 1)) {
+    float* o = p.w2part + (size_t)(blockIdx.x * C::WR + wr) * H * H + (size_t)wc * 32 * H + x;
 #pragma unroll
     for (int b = 0; b < C::NCB; ++b)
 #pragma unroll
@@ -1935,7 +1945,7 @@ __global__ void __launch_bounds__(256, ((ATTR || ECfg<H, BF16>::WGRAD) ? 2 : 3))
   }
 }
 
-constexpr int EDGE_BWD_MAX_GRID = 2048;   // (the partials of g_W2 have room for as many at H = 128)
+constexpr int EDGE_BWD_MAX_GRID = 2048;   // (the partials of g_W2 have room for as many at H = 128, for 8192 at H = 64)
 size_t edge_bwd_colpart_floats(int H) { return (size_t)EDGE_BWD_MAX_GRID * 2 * 3 * H; }
 size_t edge_bwd_attrpart_floats(int H) { return (size_t)EDGE_BWD_MAX_GRID * 2 * ATTR_K * H; }
 
@@ -1949,7 +1959,7 @@ static int32_t launch_edge_bwd_t(hipStream_t st, const EdgeBwdArgs& a) {
   if (!per_cu) {
     HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    per_cu = resident_per_cu(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>), lds, ATTR || C::WGRAD ? 2 : 3);
+    per_cu = resident_per_cu(reinterpret_cast<const void*>(&k_edge_bwd<H, BF16, ATTR, DSUM>), lds, ATTR || H == 128 ? 2 : 3);
   }
   int64_t grid = (int64_t)num_cus() * per_cu;
   if (grid > EDGE_BWD_MAX_GRID) grid = EDGE_BWD_MAX_GRID;
@@ -1962,9 +1972,9 @@ static int32_t launch_edge_bwd_t(hipStream_t st, const EdgeBwdArgs& a) {
   }
   float* dest[4] = {a.g_b2, a.g_wx, a.g_w1d, nullptr};
   HGNN_TRY(launch_reduce_partials(st, a.colpart, (int)grid * C::WR, 3, H, dest, 1, 0));
-  if constexpr (C::WGRAD) {
+  if constexpr (edge_bwd_forms_w2(H, ATTR ? 2 : 1)) {
     float* wdest[4] = {a.g_W2, nullptr, nullptr, nullptr};
-    HGNN_TRY(launch_reduce_partials(st, a.w2part, (int)grid, 1, (long)H * H, wdest, 1, 0));
+    HGNN_TRY(launch_reduce_partials(st, a.w2part, (int)grid * C::WR, 1, (long)H * H, wdest, 1, 0));
   }
   if (ATTR) {
     float* adest[4] = {a.g_W1a, nullptr, nullptr, nullptr};
@@ -1982,7 +1992,7 @@ int32_t launch_edge_bwd(hipStream_t st, int H, bool bf16, const EdgeBwdArgs& a) 
                          a.ldgP % 4 == 0),
                HGNN_ERR_BAD_SHAPE,
                "in-kernel destination sums: bf16 operands at H = 256 or fp32 operands at H = 128, no edge attributes");
-  HGNN_REQUIRE(!edge_bwd_forms_w2(H, bf16) || (a.w2part && a.g_W2), HGNN_ERR_BAD_SHAPE, "no room for the gradient of W2");
+  HGNN_REQUIRE(!edge_bwd_forms_w2(H, a.k) || (a.w2part && a.g_W2), HGNN_ERR_BAD_SHAPE, "no room for the gradient of W2");
   if (a.k > 1) {
     HGNN_REQUIRE(bf16 && a.k <= ATTR_K && a.W1a && a.attrpart && a.g_W1a && (a.attr || a.E == 0), HGNN_ERR_BAD_SHAPE,
                  "edge attributes on the fused kernels: bf16 operands, 2 <= k <= %d", ATTR_K);
@@ -2325,8 +2335,7 @@ template <int H, bool BF16>
 static int32_t launch_wgrad_frag_t(hipStream_t st, int64_t E, const void* a1_pk, const void* gz2_pk, float* partial,
                                    float* gW2) {
   const int64_t nblk32 = (E + 31) / 32;
-  // one workgroup per CU holds the whole accumulator at H = 256; narrower ones leave room for four (eight)
-  int64_t grid = (int64_t)num_cus() * (H == 256 ? 1 : (H == 128 ? 4 : 8));
+  int64_t grid = (int64_t)num_cus() * (H == 256 ? 1 : 4);   // one workgroup per CU holds the accumulator at H = 256
   if (grid > wgrad_frag_max_grid(H)) grid = wgrad_frag_max_grid(H);
   if (grid > nblk32) grid = nblk32;
   if (grid < 1) grid = 1;
@@ -2341,15 +2350,10 @@ static int32_t launch_wgrad_frag_t(hipStream_t st, int64_t E, const void* a1_pk,
 
 int32_t launch_wgrad_frag(hipStream_t st, int H, bool bf16, int64_t E, const void* a1_pk, const void* gz2_pk,
                           float* partial, float* gW2) {
-  switch (H) {
-    case 64: return bf16 ? launch_wgrad_frag_t<64, true>(st, E, a1_pk, gz2_pk, partial, gW2)
-                         : launch_wgrad_frag_t<64, false>(st, E, a1_pk, gz2_pk, partial, gW2);
-    case 128: return bf16 ? launch_wgrad_frag_t<128, true>(st, E, a1_pk, gz2_pk, partial, gW2)
-                          : launch_wgrad_frag_t<128, false>(st, E, a1_pk, gz2_pk, partial, gW2);
-    case 256: return bf16 ? launch_wgrad_frag_t<256, true>(st, E, a1_pk, gz2_pk, partial, gW2)
-                          : launch_wgrad_frag_t<256, false>(st, E, a1_pk, gz2_pk, partial, gW2);
-  }
-  return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
+  if (H == 256) return bf16 ? launch_wgrad_frag_t<256, true>(st, E, a1_pk, gz2_pk, partial, gW2)
+                            : launch_wgrad_frag_t<256, false>(st, E, a1_pk, gz2_pk, partial, gW2);
+  if (H == 128 && bf16) return launch_wgrad_frag_t<128, true>(st, E, a1_pk, gz2_pk, partial, gW2);
+  return set_error(HGNN_ERR_BAD_SHAPE, "the reverse edge kernel forms the W2 gradient of this layer (H = %d)", H);
 }
 
 int32_t launch_wgrad_frag_recompute(hipStream_t st, int H, int64_t E, const int32_t* dst, const int32_t* col,

@@ -44,9 +44,9 @@ struct LayerSaved {
   size_t bytes;
 };
 
-// a1 = silu(z1) is not stored but recomputed, from the gathers alone: by the W2-gradient kernel (bf16 pairs, H = 256) or by
-// the reverse edge kernel, which forms that gradient itself (fp32 operands, H = 128); d2 as the only edge attribute
-static bool a1_recomputed(int H, bool bf16, int k) { return (edge_pairs(H, bf16) || (!bf16 && H == 128)) && k == 1; }
+// a1 = silu(z1) is not stored but recomputed: by the reverse edge kernel where it forms the W2 gradient itself,
+// or by the W2-gradient kernel, from the gathers alone (bf16 pairs, H = 256, d2 as the only edge attribute)
+static bool a1_recomputed(int H, bool bf16, int k) { return edge_bwd_forms_w2(H, k) || (edge_pairs(H, bf16) && k == 1); }
 
 static LayerSaved carve_saved(void* p, int N, int64_t E, int H, bool bf16, int k = 1) {
   Carver c(p);
@@ -86,7 +86,7 @@ static LayerWs carve_ws(void* p, int N, int64_t E, int H, bool bf16, int k = 1) 
   LayerWs w;
   w.packed = c.take<char>(6 * packed_block_bytes(H, bf16));
   w.packed_x3 = bf16 ? nullptr : c.take<char>(packed_x3_bytes(H));
-  w.gz2_pk = edge_bwd_forms_w2(H, bf16) ? nullptr : c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
+  w.gz2_pk = edge_bwd_forms_w2(H, k) ? nullptr : c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
   w.gz1_vm = c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
   w.cvec = c.take<float>((size_t)E + 4);
   w.g_z3 = c.take<float>((size_t)N * H);
@@ -452,7 +452,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   }
   HGNN_TRY(stream_after(sx, st, ss.ev[2]));
   // side: g_W2 = a1^T g_z2 streams while the main stream runs the two segment sums
-  if (edge_bwd_forms_w2(H, bf16)) {
+  if (edge_bwd_forms_w2(H, k)) {
     // g_W2 left the edge kernel already
   } else if (a1_recomputed(H, bf16, k))
     HGNN_TRY(launch_wgrad_frag_recompute(sx, H, E, dst, col, d2, s.PQ, W + o.W1 + 2 * HH, w.gz2_pk, w.partial2,

@@ -154,6 +154,14 @@ def test_layer_f32_128_edge_counts(E):
     _run_layer(N=500, E=E, H=128, dtype="f32", seed=E + 7)
 
 
+# The other layers whose W2 gradient the reverse edge kernel forms: at H = 64 two wavefronts share the rows of a tile and leave
+# a partial each; no edge, a tile with an empty half, ragged tiles, more tiles than workgroups in flight
+@pytest.mark.parametrize("H,dtype", [(64, "f32"), (64, "bf16"), (128, "bf16")])
+@pytest.mark.parametrize("E", [0, 1, 31, 33, 63, 65, 8 * 64 - 1, 3 * 16384 + 45])
+def test_layer_w2_gradient_in_the_edge_kernel(E, H, dtype):
+    _run_layer(N=400, E=E, H=H, dtype=dtype, seed=E + 13)
+
+
 # Atom counts around the split rules of the atom-level weight gradients (about 64 rows per split, at most one round
 # of resident workgroups, whole workgroups per compute unit, a grid padded to groups of eight splits) and the row
 # tiles of the atom-level products; few edges, so that the atom-level kernels decide the outcome.
