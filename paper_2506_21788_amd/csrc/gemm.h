@@ -82,6 +82,9 @@ int32_t launch_gemm(hipStream_t st, int H, bool bf16, const GemmArgs& a);
 // keep_silu is set) from LDS instead of its own A; with first == nullptr the second one alone, its A tile (one k
 // chunk) staged once for all of its column blocks. One launch; no groups, no row indirection.
 int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu);
+// launch_pack() and a launch_gemm_chain() whose weights are among the packed blocks; one launch for small batches
+int32_t launch_pack_gemm_chain(hipStream_t st, int H, bool bf16, const PackArgs& pk, const GemmArgs* first,
+                               const GemmArgs& second, int keep_silu);
 
 // ---- transposed GEMM (sum over rows of outer products), split-K ------------------------------
 // block (ia, ib): out[k1][k2] = sum_r f(A[ia][r][k1]) * B[ib][r][k2]

@@ -20,22 +20,18 @@ namespace hgnn {
 // ---------------------------------------------------------------------------------------------
 // pack
 // ---------------------------------------------------------------------------------------------
-template <bool BF16>
-__global__ void k_pack(PackArgs a, int H, long src_grp_stride, long dst_grp_stride) {
-  const int b = blockIdx.y;
-  const int grp = blockIdx.z;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int planes = a.nblocks + (a.x3_dst ? 1 : 0);
-  if (b >= planes) {
-    const int64_t plane = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (b - planes) * plane + idx; e < a.E; e += (gridDim.y - planes) * plane) {
-      const size_t i = (size_t)a.dst_e[e];
-      a.cvec[e] = a.alpha * (a.g_v[3 * i] * a.rvec[3 * e] + a.g_v[3 * i + 1] * a.rvec[3 * e + 1] + a.g_v[3 * i + 2] * a.rvec[3 * e + 2]);
-    }
-    return;
+// c_e of edges first, first + step, ...
+__device__ __forceinline__ void pack_cvec(const PackArgs& a, int64_t first, int64_t step) {
+  for (int64_t e = first; e < a.E; e += step) {
+    const size_t i = (size_t)a.dst_e[e];
+    a.cvec[e] = a.alpha * (a.g_v[3 * i] * a.rvec[3 * e] + a.g_v[3 * i + 1] * a.rvec[3 * e + 1] + a.g_v[3 * i + 2] * a.rvec[3 * e + 2]);
   }
-  if (idx >= H * H) return;
-  if (b == a.nblocks) {   // the extra block as three bf16 planes (see split_bf16x3), each in the bf16 operand order
+}
+// element idx < H * H of block b of a group (b == nblocks: the extra block as three bf16 planes)
+template <bool BF16>
+__device__ __forceinline__ void pack_element(const PackArgs& a, int H, int b, int idx, int grp, long src_grp_stride,
+                                             long dst_grp_stride) {
+  if (b == a.nblocks) {   // (see split_bf16x3; each plane in the bf16 operand order)
     const PackDesc d = a.d[a.x3_desc];
     const int t = idx & 7, lane = (idx >> 3) & 63, kb = (idx >> 9) % (H / 16), nb = (idx >> 9) / (H / 16);
     const int n = nb * 32 + (lane & 31);
@@ -70,6 +66,20 @@ __global__ void k_pack(PackArgs a, int H, long src_grp_stride, long dst_grp_stri
   } else {
     reinterpret_cast<float*>(a.dst)[o] = v;
   }
+}
+
+template <bool BF16>
+__global__ void k_pack(PackArgs a, int H, long src_grp_stride, long dst_grp_stride) {
+  const int b = blockIdx.y;
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const int planes = a.nblocks + (a.x3_dst ? 1 : 0);
+  if (b >= planes) {
+    const int64_t plane = (int64_t)gridDim.x * blockDim.x;
+    pack_cvec(a, (b - planes) * plane + idx, (gridDim.y - planes) * plane);
+    return;
+  }
+  if (idx >= H * H) return;
+  pack_element<BF16>(a, H, b, idx, blockIdx.z, src_grp_stride, dst_grp_stride);
 }
 
 int32_t launch_pack(hipStream_t st, int H, bool bf16, const PackArgs& a, int groups, long src_grp_stride,
@@ -541,14 +551,30 @@ struct SmallAux {   // operands of an epilogue, in the accumulator mapping: row 
   }
 };
 
-template <int H, bool BF16, bool CHAIN>
-__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmArgs p1, GemmArgs p2, int keep_silu) {
+// RAW: the weights of these products are among the blocks that `pk` describes, and are not packed yet: workgroups beyond the
+// `tiles` of the products pack all of them for the kernels that follow, while the products read their own straight from the
+// fp32 source (rounded as the packing does), so that they need not wait for a packing launch. Source order: [in, out] for
+// a lone product, transposed for a chain (16-byte aligned), see launch_pack_gemm_chain().
+template <int H, bool BF16, bool CHAIN, bool RAW>
+__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmArgs p1, GemmArgs p2, int keep_silu, PackArgs pk,
+                                                                              int tiles) {
   using C = SmallCfg<H, BF16>;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* keep = smem + 2 * C::A_BYTES;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, hq = lane >> 4;
   const int cb0 = blockIdx.y;   // a lone product takes one column block per workgroup, a chain all of them in turn
+  if constexpr (RAW) {
+    if ((int)blockIdx.x >= tiles) {   // uniform over the workgroup, before any barrier
+      const int pb = ((int)blockIdx.x - tiles) * gridDim.y + blockIdx.y;
+      constexpr int XB = H * H / C::THREADS;   // workgroups per block
+      static_assert(H * H % C::THREADS == 0, "whole workgroups per block");
+      const int planes = pk.nblocks + (pk.x3_dst ? 1 : 0), eb = pb - planes * XB;
+      if (eb >= 0) pack_cvec(pk, (int64_t)eb * C::THREADS + tid, (int64_t)((gridDim.x - tiles) * gridDim.y - planes * XB) * C::THREADS);
+      else pack_element<BF16>(pk, H, pb / XB, (pb % XB) * C::THREADS + tid, 0, 0, 0);
+      return;
+    }
+  }
   int grp = 0, rbeg, rend;
   if (p2.grp_ptr) {
     if (!tile_of_group(p2.grp_ptr, p2.S, C::TM, blockIdx.x, grp, rbeg, rend)) return;
@@ -557,34 +583,72 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
     rend = p2.M;
     if (rbeg >= rend) return;
   }
+  constexpr int NKC = RAW ? 1 : 2;   // most k chunks of the product that reads A from memory
   const GemmArgs& pa = CHAIN ? p1 : p2;   // the product that reads A from memory
   // ---- weights: lane (column c, quarter hq) of step kb takes k = kb * KS + hq * KS / 4 .. of its column, one 16-byte
   // piece of the packed 32-column operand order (its own 32-column block, k step 2 kb + hq / 2, half hq & 1)
-  u32x4s_t b[C::NKB][C::CB];
-  auto b_rsrc = [&](const GemmArgs& p, int kc, int cb) {
-    return __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(reinterpret_cast<const char*>(p.B)) + (grp * p.grp_blk_stride + p.blk[kc][cb]) * (long)(H * H * C::ESZ), 0,
-        H * H * C::ESZ, 0x00020000);
+  constexpr int KT = BF16 ? 8 : 4;   // k per lane and step
+  u32x4s_t b[RAW ? 1 : C::NKB][C::CB];
+  float braw[RAW ? C::NKB : 1][C::CB][KT];
+  struct BSrc {
+    __amdgpu_buffer_rsrc_t rs;
+    const float* src;
+  };
+  auto b_src = [&](const GemmArgs& p, int kc, int cb) {
+    BSrc o;
+    if constexpr (RAW) {
+      o.src = pk.src + pk.d[p.blk[kc][cb]].src_off;
+    } else {
+      o.rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<char*>(reinterpret_cast<const char*>(p.B)) + (grp * p.grp_blk_stride + p.blk[kc][cb]) * (long)(H * H * C::ESZ), 0,
+          H * H * C::ESZ, 0x00020000);
+    }
+    return o;
   };
   unsigned bo[C::CB];
 #pragma unroll
   for (int j = 0; j < C::CB; ++j) {
     const int n0 = C::col0(wave, j);
-    bo[j] = (unsigned)((((n0 >> 5) * (2 * C::NKB) + (hq >> 1)) * 64 + (hq & 1) * 32 + (n0 & 16) + c) * 16);
+    if constexpr (RAW) bo[j] = CHAIN ? (n0 + c) * H + hq * KT : hq * KT * H + n0 + c;
+    else bo[j] = (unsigned)((((n0 >> 5) * (2 * C::NKB) + (hq >> 1)) * 64 + (hq & 1) * 32 + (n0 & 16) + c) * 16);
   }
-  auto load_b = [&](const __amdgpu_buffer_rsrc_t& rs, int kb) {
+  auto load_b = [&](const BSrc& o, int kb) {
 #pragma unroll
-    for (int j = 0; j < C::CB; ++j) b[kb][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, bo[j], kb * 2048, 0);
+    for (int j = 0; j < C::CB; ++j) {
+      if constexpr (RAW && CHAIN) {
+#pragma unroll
+        for (int t = 0; t < KT; t += 4) {
+          const float4 w = *reinterpret_cast<const float4*>(o.src + bo[j] + kb * 4 * KT + t);
+          braw[kb][j][t] = w.x; braw[kb][j][t + 1] = w.y; braw[kb][j][t + 2] = w.z; braw[kb][j][t + 3] = w.w;
+        }
+      } else if constexpr (RAW) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t) braw[kb][j][t] = o.src[bo[j] + (kb * 4 * KT + t) * H];
+      } else {
+        b[kb][j] = __builtin_amdgcn_raw_buffer_load_b128(o.rs, bo[j], kb * 2048, 0);
+      }
+    }
+  };
+  // the operand of step kb, block j
+  auto b_frag = [&](int kb, int j) {
+    if constexpr (RAW && BF16) {
+      const float(&w)[KT] = braw[kb][j];
+      return u32x4s_t{pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]), pack_bf16x2(w[4 % KT], w[5 % KT]), pack_bf16x2(w[6 % KT], w[7 % KT])};
+    } else if constexpr (RAW) {
+      return u32x4s_t{__float_as_uint(braw[kb][j][0]), __float_as_uint(braw[kb][j][1]), __float_as_uint(braw[kb][j][2]), __float_as_uint(braw[kb][j][3])};
+    } else {
+      return b[kb][j];
+    }
   };
   {
-    const __amdgpu_buffer_rsrc_t rs = b_rsrc(pa, 0, CHAIN ? 0 : cb0);
+    const BSrc rs = b_src(pa, 0, CHAIN ? 0 : cb0);
 #pragma unroll
     for (int kb = 0; kb < C::NKB; ++kb) load_b(rs, kb);
   }
   // ---- A: every k chunk at once
   constexpr int CH = H / 4, NA = C::TM * CH / C::THREADS;   // 4-column pieces per thread and chunk
   static_assert(C::TM * CH % C::THREADS == 0, "whole pieces per thread");
-  float4 av[2][NA];
+  float4 av[NKC][NA];
   long arow[NA];
 #pragma unroll
   for (int u = 0; u < NA; ++u) {
@@ -593,7 +657,7 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
     if (pa.row_idx) arow[u] = pa.row_idx[arow[u]];
   }
 #pragma unroll
-  for (int kc = 0; kc < 2; ++kc)
+  for (int kc = 0; kc < NKC; ++kc)
     if (kc < pa.nkc) {
 #pragma unroll
       for (int u = 0; u < NA; ++u)
@@ -618,7 +682,7 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
     else *reinterpret_cast<float4*>(dst + ((size_t)r * C::STRIDE + q * 4) * 4) = w;
   };
 #pragma unroll
-  for (int kc = 0; kc < 2; ++kc)
+  for (int kc = 0; kc < NKC; ++kc)
     if (kc < pa.nkc) {
 #pragma unroll
       for (int u = 0; u < NA; ++u) {
@@ -637,7 +701,7 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
   };
   // one chunk; the weights of the next one take each register as it is used up
   const unsigned ao = (unsigned)((c * C::STRIDE + hq * (16 / C::ESZ)) * C::ESZ);
-  auto multiply = [&](const unsigned char* a_lds, bool next, const __amdgpu_buffer_rsrc_t& rs) {
+  auto multiply = [&](const unsigned char* a_lds, bool next, const BSrc& rs) {
     u32x4s_t a[C::NKB];
 #pragma unroll
     for (int kb = 0; kb < C::NKB; ++kb) a[kb] = *reinterpret_cast<const u32x4s_t*>(a_lds + ao + kb * 64);
@@ -646,9 +710,9 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
 #pragma unroll
       for (int j = 0; j < C::CB; ++j) {
         if constexpr (BF16) {
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[kb]), __builtin_bit_cast(bf16x8_t, b[kb][j]), acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[kb]), __builtin_bit_cast(bf16x8_t, b_frag(kb, j)), acc[j], 0, 0, 0);
         } else {
-          const f32x4_t af = __builtin_bit_cast(f32x4_t, a[kb]), bf = __builtin_bit_cast(f32x4_t, b[kb][j]);
+          const f32x4_t af = __builtin_bit_cast(f32x4_t, a[kb]), bf = __builtin_bit_cast(f32x4_t, b_frag(kb, j));
 #pragma unroll
           for (int t = 0; t < 4; ++t) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[t], bf[t], acc[j], 0, 0, 0);
         }
@@ -668,8 +732,8 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
   if constexpr (CHAIN) {
     clear();
 #pragma unroll
-    for (int kc = 0; kc < 2; ++kc)
-      if (kc < p1.nkc) multiply(smem + kc * C::A_BYTES, true, kc + 1 < p1.nkc ? b_rsrc(p1, kc + 1, 0) : b_rsrc(p2, 0, 0));
+    for (int kc = 0; kc < NKC; ++kc)
+      if (kc < p1.nkc) multiply(smem + kc * C::A_BYTES, true, kc + 1 < p1.nkc ? b_src(p1, kc + 1, 0) : b_src(p2, 0, 0));
     const bool ua = p1.add1 && (p1.add1_cb_mask & 1);
 #pragma unroll
     for (int j = 0; j < C::CB; ++j) {
@@ -691,11 +755,11 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
   for (int cb = cb0; cb < cbe; ++cb) {
     clear();
     if constexpr (CHAIN) {
-      multiply(a2, cb + 1 < cbe, b_rsrc(p2, 0, cb + 1 < cbe ? cb + 1 : cb));
+      multiply(a2, cb + 1 < cbe, b_src(p2, 0, cb + 1 < cbe ? cb + 1 : cb));
     } else {
 #pragma unroll
-      for (int kc = 0; kc < 2; ++kc)
-        if (kc < p2.nkc) multiply(a2 + kc * C::A_BYTES, kc + 1 < p2.nkc, b_rsrc(p2, kc + 1 < p2.nkc ? kc + 1 : kc, cb));
+      for (int kc = 0; kc < NKC; ++kc)
+        if (kc < p2.nkc) multiply(a2 + kc * C::A_BYTES, kc + 1 < p2.nkc, b_src(p2, kc + 1 < p2.nkc ? kc + 1 : kc, cb));
     }
     const bool ua = p2.add1 && ((p2.add1_cb_mask >> cb) & 1);
     if constexpr (H == 256) {
@@ -726,9 +790,23 @@ static int32_t launch_gemm_small_t(hipStream_t st, const GemmArgs* first, const 
   using C = SmallCfg<H, BF16>;
   const int tiles = (a.M + C::TM - 1) / C::TM + (a.grp_ptr ? a.S : 0);
   ProfScope ps(a.tag, st);
-  if (first) k_gemm_small<H, BF16, true><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(*first, a, keep_silu);
-  else k_gemm_small<H, BF16, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(a, a, 0);
+  if (first) k_gemm_small<H, BF16, true, false><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(*first, a, keep_silu, PackArgs{}, tiles);
+  else k_gemm_small<H, BF16, false, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(a, a, 0, PackArgs{}, tiles);
   HGNN_LAUNCH_CHECK("k_gemm_small");
+  return HGNN_OK;
+}
+template <int H, bool BF16>
+static int32_t launch_pack_gemm_small_t(hipStream_t st, const PackArgs& pk, const GemmArgs* first, const GemmArgs& a, int keep_silu) {
+  using C = SmallCfg<H, BF16>;
+  const int tiles = (a.M + C::TM - 1) / C::TM, gy = first ? 1 : a.ncb;
+  int64_t eb = pk.cvec ? (pk.E + C::THREADS - 1) / C::THREADS : 0;
+  if (eb > 8192) eb = 8192;   // (the rest in a loop)
+  const int pack = (pk.nblocks + (pk.x3_dst ? 1 : 0)) * (H * H / C::THREADS) + (int)eb;
+  const dim3 grid(tiles + (pack + gy - 1) / gy, gy);
+  ProfScope ps(a.tag, st);
+  if (first) k_gemm_small<H, BF16, true, true><<<grid, C::THREADS, C::LDS_BYTES, st>>>(*first, a, keep_silu, pk, tiles);
+  else k_gemm_small<H, BF16, false, true><<<grid, C::THREADS, C::LDS_BYTES, st>>>(a, a, 0, pk, tiles);
+  HGNN_LAUNCH_CHECK("k_gemm_small (packing)");
   return HGNN_OK;
 }
 // The short chains win while the taller tiles would not give every compute unit one of them; beyond that twice the
@@ -805,7 +883,7 @@ static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const 
 // `first` (optional): one column block, its finished tile (through silu when keep_silu) is the A operand of `second`,
 // whose own A fields are then ignored; without `first`, `second` runs alone with its A tile (one k chunk) staged
 // once for all its column blocks.
-int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu) {
+static int32_t check_gemm_chain(int H, const GemmArgs* first, const GemmArgs& second) {
   for (const GemmArgs* g : {first, &second}) {
     if (!g) continue;
     HGNN_REQUIRE(!g->row_idx && !g->grp_ptr, HGNN_ERR_BAD_SHAPE, "gemm chain: no groups, no row indirection");
@@ -820,12 +898,50 @@ int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* firs
   } else {
     HGNN_REQUIRE(second.nkc == 1 && second.A[0], HGNN_ERR_BAD_SHAPE, "gemm chain: the lone product takes one k chunk");
   }
+  return HGNN_OK;
+}
+int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu) {
+  HGNN_TRY(check_gemm_chain(H, first, second));
   switch (H) {
     case 64: return bf16 ? launch_gemm_chain_t<64, true>(st, first, second, keep_silu) : launch_gemm_chain_t<64, false>(st, first, second, keep_silu);
     case 128: return bf16 ? launch_gemm_chain_t<128, true>(st, first, second, keep_silu) : launch_gemm_chain_t<128, false>(st, first, second, keep_silu);
     case 256: return bf16 ? launch_gemm_chain_t<256, true>(st, first, second, keep_silu) : launch_gemm_chain_t<256, false>(st, first, second, keep_silu);
   }
   return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
+}
+
+// One launch while the products read at most RAW_BYTES of unpacked weights (every 16-row tile reads its blocks whole, twice the
+// bytes of packed ones with bf16 operands). Per step, two launches against one: one molecule, forward 215 -> 208 us, 32 small
+// molecules 395 -> 377, a crystal's conservative forces 605 -> 598, 16 molecules at H = 128 497 -> 482; past the line nothing changes.
+constexpr long RAW_BYTES = 16l << 20;
+static bool pack_along(int H, const PackArgs& pk, const GemmArgs* first, const GemmArgs& second) {
+  if (H > 128 || second.M <= 0 || !small_gemm(second.M, H >= 128 ? 32 : 64)) return false;
+  if (first && first->nkc != 1) return false;
+  const int nblk = (first ? 1 : 0) + second.ncb;
+  if (((second.M + 15) / 16) * (long)nblk * H * H * 4 > RAW_BYTES) return false;
+  if (first && reinterpret_cast<uintptr_t>(pk.src) % 16 != 0) return false;
+  for (const GemmArgs* g : {first, &second}) {   // blocks of this packing, in the order of the source that the kernel reads
+    if (!g) continue;
+    if (g->B != pk.dst) return false;
+    for (int cb = 0; cb < g->ncb; ++cb) {
+      const long b = g->blk[0][cb];
+      if (b < 0 || b >= pk.nblocks || pk.d[b].sk != (first ? 1 : H) || pk.d[b].sn != (first ? H : 1)) return false;
+      if (first && pk.d[b].src_off % 4 != 0) return false;
+    }
+  }
+  return true;
+}
+int32_t launch_pack_gemm_chain(hipStream_t st, int H, bool bf16, const PackArgs& pk, const GemmArgs* first,
+                               const GemmArgs& second, int keep_silu) {
+  if (!pack_along(H, pk, first, second)) {
+    HGNN_TRY(launch_pack(st, H, bf16, pk));
+    return launch_gemm_chain(st, H, bf16, first, second, keep_silu);
+  }
+  HGNN_TRY(check_gemm_chain(H, first, second));
+  if (H == 64) return bf16 ? launch_pack_gemm_small_t<64, true>(st, pk, first, second, keep_silu)
+                           : launch_pack_gemm_small_t<64, false>(st, pk, first, second, keep_silu);
+  return bf16 ? launch_pack_gemm_small_t<128, true>(st, pk, first, second, keep_silu)
+              : launch_pack_gemm_small_t<128, false>(st, pk, first, second, keep_silu);
 }
 
 int32_t launch_gemm(hipStream_t st, int H, bool bf16, const GemmArgs& a) {

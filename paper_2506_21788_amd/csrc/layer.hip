@@ -215,9 +215,8 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
   pk.d[4] = {o.W3 + HH, H, 1};
   pk.d[5] = {o.W4, H, 1};
   pk.x3_dst = w.packed_x3; pk.x3_desc = 2;   // fp32 operands: W2 also as three bf16 planes
-  HGNN_TRY(launch_pack(st, H, bf16, pk));
 
-  {  // P | Q
+  {  // the packing, and P | Q
     GemmArgs g;
     g.A[0] = h_in; g.lda[0] = H; g.nkc = 1;
     g.B = w.packed; g.blk[0][0] = 0; g.blk[0][1] = 1; g.ncb = 2;
@@ -228,7 +227,7 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
       g.Cpair = reinterpret_cast<unsigned*>(s.PQ); g.ldpair = H; g.pair_cb_mask = 3;
       g.pair_off[0] = 0; g.pair_off[1] = H / 2;
     }
-    HGNN_TRY(launch_gemm_chain(st, H, bf16, nullptr, g, 0));   // h is staged once for both halves
+    HGNN_TRY(launch_pack_gemm_chain(st, H, bf16, pk, nullptr, g, 0));   // h is staged once for both halves
   }
   {  // per edge: a1 = silu(P[dst] + Q[col] + d2*w1d), z2 = a1 W2 + b2   (one fused kernel)
     EdgeFwdArgs e;
@@ -385,7 +384,6 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   pk.d[5] = {o.W1 + HH, 1, H};
   pk.x3_dst = w.packed_x3; pk.x3_desc = 3;   // fp32 operands: W2^T also as three bf16 planes
   pk.E = E; pk.dst_e = dst; pk.rvec = rvec; pk.g_v = g_v_out; pk.alpha = alpha; pk.cvec = w.cvec;   // and c_e of every edge
-  HGNN_TRY(launch_pack(st, H, bf16, pk));
 
   SideStream& ss = side_stream();
   HGNN_REQUIRE(ss.ok, HGNN_ERR_HIP, "could not create the side stream");
@@ -396,7 +394,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   ReduceQueueScope reductions(st, sx == st);
 
   // every gradient field is written below even when there is nothing to sum over
-  {  // g_z3 = (g_h' W4^T) * silu'(z3), and from the same tile [g_h' + g_h(a) | g_M] = g_z3 W3^T (+ g_h' on the first half)
+  {  // the packing and c_e; g_z3 = (g_h' W4^T) * silu'(z3), and from the same tile [g_h' + g_h(a) | g_M] = g_z3 W3^T (+ g_h' on the first half)
     GemmArgs g;
     g.A[0] = g_h_out; g.lda[0] = H;
     g.B = w.packed; g.blk[0][0] = 0;
@@ -412,7 +410,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
       g2.Cpair = w.gM_pk; g2.ldpair = H / 2; g2.pair_cb_mask = 2; g2.pair_off[1] = 0;
       g2.pair_scale = alpha;   // the pair form carries alpha * g_M
     }
-    HGNN_TRY(launch_gemm_chain(st, H, bf16, &g, g2, 0));
+    HGNN_TRY(launch_pack_gemm_chain(st, H, bf16, pk, &g, g2, 0));
   }
   // edge part: g_z2 -> (x W2^T) -> g_z1 with the per-column sums. The fused edge kernel fills
   // every CU by itself, so the side stream is drained first instead of competing with it.

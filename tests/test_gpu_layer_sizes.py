@@ -181,6 +181,42 @@ def test_layer_atom_counts_of_small_row_tiles(N, H, dtype, last):
     _run_layer(N=n, E=3000 if N < 2 else 40 * n, H=H, dtype=dtype, seed=n)
 
 
+# Batches whose first products run in one launch with the packing of the weights (up to 16 MB of weights read by all 16-row
+# tiles, forward and reverse pass each with a line of its own) and the next larger ones
+@pytest.mark.parametrize("H,dtype,N", [(64, "f32", 5456), (64, "bf16", 5457), (64, "f32", 8192), (64, "bf16", 8193),
+                                       (128, "f32", 1360), (128, "bf16", 1361), (128, "f32", 2048), (128, "bf16", 2049)])
+def test_layer_atom_counts_of_the_packing_launch(H, dtype, N):
+    _run_layer(N=N, E=2000, H=H, dtype=dtype, seed=N)
+
+
+@pytest.mark.parametrize("H,dtype", [(64, "f32"), (128, "bf16")])
+def test_layer_weights_at_any_alignment(H, dtype):
+    """Weights at a 4-byte boundary: the reverse pass packs in a launch of its own, with the same bits as a result."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+    rng = np.random.default_rng(H)
+    N, E, dt = 100, 1500, {"f32": B.F32, "bf16": B.BF16}[dtype]
+    row_ptr, dst, col, d2, rvec = _edges(rng, N, E)
+    colT_ptr, permT = oracle.transpose_plan(col, N)
+    W = torch.as_tensor(init_layer_weights(rng, H).astype(np.float32)).cuda()
+    g = [torch.as_tensor(np.ascontiguousarray(a)).cuda() for a in (row_ptr, dst, col, d2, rvec)]
+    plan = [torch.as_tensor(a.astype(np.int32)).cuda() for a in (colT_ptr, permT)]
+    h, gh = (torch.as_tensor(rng.standard_normal((N, H)).astype(np.float32)).cuda() for _ in range(2))
+    v, gv = (torch.as_tensor(rng.standard_normal((N, 3)).astype(np.float32)).cuda() for _ in range(2))
+    outs = []
+    for off in (0, 1, 2):
+        w = torch.empty(W.numel() + 4, device="cuda")[off:off + W.numel()].copy_(W)
+        assert w.data_ptr() % 16 == 4 * off
+        ws_b, saved_b = B.mp_layer_workspace_bytes(N, E, H, dt)
+        ws, saved = (torch.zeros(b, dtype=torch.uint8, device="cuda") for b in (ws_b, saved_b))
+        out = [torch.empty_like(x) for x in (h, v, h, v, W)]
+        B.mp_layer_fwd(N, E, H, dt, 0.1, *g, h, v, w, out[0], out[1], saved, ws)
+        B.mp_layer_bwd(N, E, H, dt, 0.1, *g, *plan, h, w, saved, gh, gv, out[2], out[3], out[4], ws)
+        outs.append([x.cpu().numpy().view(np.uint32) for x in out])
+    for o in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(outs[0], o))
+
+
 # Widths other than 64 / 128 / 256 take the fragment-GEMM path (bf16 operands, width padded to a multiple of 128, rows
 # to 256): the paper's 866, widths on both sides of the padding steps, odd and small widths, edge counts around the
 # 16 / 32 / 256-row groups.
