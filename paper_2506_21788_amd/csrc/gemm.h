@@ -78,6 +78,8 @@ struct GemmArgs {
   int tag = PT_GEMM_NODE;  // timing class
 };
 int32_t launch_gemm(hipStream_t st, int H, bool bf16, const GemmArgs& a);
+// two independent products; one launch for small batches
+int32_t launch_gemm_pair(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs& b);
 // Two products in a row per row tile, the second one reading the first one's finished tile (through silu when
 // keep_silu is set) from LDS instead of its own A; with first == nullptr the second one alone, its A tile (one k
 // chunk) staged once for all of its column blocks. One launch; no groups, no row indirection.
@@ -115,6 +117,8 @@ size_t wgrad_colsum_partial_floats(int H, int64_t M);   // room for the column s
 // wgrad_partial_floats(H, M, total blocks, 1) and wgrad_colsum_partial_floats(H, M) floats. At most 8 blocks and 4
 // B operands in total.
 int32_t launch_wgrad_multi(hipStream_t st, int H, bool bf16, const WgradArgs* jobs, int njobs);
+// Up to three products over rows, groups and partial buffers of their own (no column sums) in one launch.
+int32_t launch_wgrad_own_rows(hipStream_t st, int H, bool bf16, const WgradArgs* jobs, int njobs);
 int wgrad_splits(int64_t M);
 size_t wgrad_partial_floats(int H, int64_t M, int nblocks, int S);
 int32_t launch_wgrad(hipStream_t st, int H, bool bf16, const WgradArgs& a);
@@ -133,9 +137,13 @@ struct ColsumArgs {
   float* dest = nullptr;  // [H] (+ grp*grp_dest_stride)
   long grp_dest_stride = 0;
   float* partial = nullptr;  // scratch, colsum_partial_floats()
+  // optional: the sum of the weights as well, w_dest[grp*grp_dest_stride] = sum_r w[r]
+  float* w_dest = nullptr;
+  float* w_partial = nullptr;   // scratch, colsum_partial_floats() with H = 1
 };
 size_t colsum_partial_floats(int H, int64_t M, int S);
 int32_t launch_colsum(hipStream_t st, int H, const ColsumArgs& a);
+int32_t launch_colsum_multi(hipStream_t st, int H, const ColsumArgs* jobs, int njobs);   // up to four in one launch
 
 // dest[blk][i] (+ grp*grp_dest_stride) = sum over s < nsplit of partial[((grp*nsplit + s)*nblk + blk)*blk_elems + i],
 // summed in ascending s

@@ -555,10 +555,15 @@ struct SmallAux {   // operands of an epilogue, in the accumulator mapping: row 
 // `tiles` of the products pack all of them for the kernels that follow, while the products read their own straight from the
 // fp32 source (rounded as the packing does), so that they need not wait for a packing launch. Source order: [in, out] for
 // a lone product, transposed for a chain (16-byte aligned), see launch_pack_gemm_chain().
+// m: the two products of a chain, or lone products of one launch (blockIdx.z)
+struct GemmJobs {
+  GemmArgs job[2];
+};
 template <int H, bool BF16, bool CHAIN, bool RAW>
-__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmArgs p1, GemmArgs p2, int keep_silu, PackArgs pk,
-                                                                              int tiles) {
+__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmJobs m, int keep_silu, PackArgs pk, int tiles) {
   using C = SmallCfg<H, BF16>;
+  const GemmArgs& p1 = m.job[0];
+  const GemmArgs& p2 = m.job[CHAIN ? 1 : RAW ? 0 : blockIdx.z];
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* keep = smem + 2 * C::A_BYTES;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -790,8 +795,8 @@ static int32_t launch_gemm_small_t(hipStream_t st, const GemmArgs* first, const 
   using C = SmallCfg<H, BF16>;
   const int tiles = (a.M + C::TM - 1) / C::TM + (a.grp_ptr ? a.S : 0);
   ProfScope ps(a.tag, st);
-  if (first) k_gemm_small<H, BF16, true, false><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(*first, a, keep_silu, PackArgs{}, tiles);
-  else k_gemm_small<H, BF16, false, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(a, a, 0, PackArgs{}, tiles);
+  if (first) k_gemm_small<H, BF16, true, false><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, PackArgs{}, tiles);
+  else k_gemm_small<H, BF16, false, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{a, a}}, 0, PackArgs{}, tiles);
   HGNN_LAUNCH_CHECK("k_gemm_small");
   return HGNN_OK;
 }
@@ -804,8 +809,8 @@ static int32_t launch_pack_gemm_small_t(hipStream_t st, const PackArgs& pk, cons
   const int pack = (pk.nblocks + (pk.x3_dst ? 1 : 0)) * (H * H / C::THREADS) + (int)eb;
   const dim3 grid(tiles + (pack + gy - 1) / gy, gy);
   ProfScope ps(a.tag, st);
-  if (first) k_gemm_small<H, BF16, true, true><<<grid, C::THREADS, C::LDS_BYTES, st>>>(*first, a, keep_silu, pk, tiles);
-  else k_gemm_small<H, BF16, false, true><<<grid, C::THREADS, C::LDS_BYTES, st>>>(a, a, 0, pk, tiles);
+  if (first) k_gemm_small<H, BF16, true, true><<<grid, C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, pk, tiles);
+  else k_gemm_small<H, BF16, false, true><<<grid, C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{a, a}}, 0, pk, tiles);
   HGNN_LAUNCH_CHECK("k_gemm_small (packing)");
   return HGNN_OK;
 }
@@ -944,16 +949,45 @@ int32_t launch_pack_gemm_chain(hipStream_t st, int H, bool bf16, const PackArgs&
               : launch_pack_gemm_small_t<128, false>(st, pk, first, second, keep_silu);
 }
 
-int32_t launch_gemm(hipStream_t st, int H, bool bf16, const GemmArgs& a) {
+static int32_t check_gemm(int H, const GemmArgs& a) {
   HGNN_REQUIRE(a.nkc >= 1 && a.nkc <= 2 && a.ncb >= 1 && a.ncb <= 2, HGNN_ERR_BAD_SHAPE, "gemm: bad chunk counts");
   HGNN_REQUIRE(a.A[0] && a.B && (a.C || a.Cpair), HGNN_ERR_NULLPTR, "gemm: null operand");
   HGNN_REQUIRE(a.pair_cb_mask == 0 || (H == 256 && a.Cpair), HGNN_ERR_BAD_SHAPE, "gemm: pair output needs H = 256");
+  return HGNN_OK;
+}
+int32_t launch_gemm(hipStream_t st, int H, bool bf16, const GemmArgs& a) {
+  HGNN_TRY(check_gemm(H, a));
   switch (H) {
     case 64: return bf16 ? launch_gemm_t<64, true>(st, a) : launch_gemm_t<64, false>(st, a);
     case 128: return bf16 ? launch_gemm_t<128, true>(st, a) : launch_gemm_t<128, false>(st, a);
     case 256: return bf16 ? launch_gemm_t<256, true>(st, a) : launch_gemm_t<256, false>(st, a);
   }
   return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
+}
+
+template <int H, bool BF16>
+static int32_t launch_gemm_small_pair_t(hipStream_t st, const GemmArgs& a, const GemmArgs& b) {
+  using C = SmallCfg<H, BF16>;
+  const auto tiles = [](const GemmArgs& g) { return (g.M + C::TM - 1) / C::TM + (g.grp_ptr ? g.S : 0); };
+  const int ta = tiles(a), tb = tiles(b), t = ta > tb ? ta : tb;
+  ProfScope ps(a.tag, st);
+  k_gemm_small<H, BF16, false, false><<<dim3(t, a.ncb, 2), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{a, b}}, 0, PackArgs{}, t);
+  HGNN_LAUNCH_CHECK("k_gemm_small (two products)");
+  return HGNN_OK;
+}
+int32_t launch_gemm_pair(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs& b) {
+  const bool one = (bf16 || H < 256) && a.M > 0 && b.M > 0 && a.ncb == b.ncb && small_gemm(a.M > b.M ? a.M : b.M, H >= 128 ? 32 : 64);
+  if (!one) {
+    HGNN_TRY(launch_gemm(st, H, bf16, a));
+    return launch_gemm(st, H, bf16, b);
+  }
+  HGNN_TRY(check_gemm(H, a));
+  HGNN_TRY(check_gemm(H, b));
+  switch (H) {
+    case 64: return bf16 ? launch_gemm_small_pair_t<64, true>(st, a, b) : launch_gemm_small_pair_t<64, false>(st, a, b);
+    case 128: return bf16 ? launch_gemm_small_pair_t<128, true>(st, a, b) : launch_gemm_small_pair_t<128, false>(st, a, b);
+  }
+  return launch_gemm_small_pair_t<256, true>(st, a, b);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1033,7 +1067,7 @@ __global__ void __launch_bounds__(256) k_reduce_partials_tall(ReduceArgs a) {
 
 // several reductions in one launch: blockIdx.y counts the blocks of all jobs one after the other, blockIdx.z the
 // groups of the job with the most groups
-constexpr int REDUCE_QUEUE_MAX = 6;
+constexpr int REDUCE_QUEUE_MAX = 8;
 struct ReduceQueueArgs {
   ReduceArgs job[REDUCE_QUEUE_MAX];
   int njobs;
@@ -1134,18 +1168,21 @@ struct WgradCfg {
   static constexpr int TILES = H / OT;
 };
 
-// the jobs of one launch: their output tiles are numbered one job after the other (ny_off), so are their blocks in
-// the partial buffer (blk_off) and their B operands in the column-sum partials (cs_off)
+// the jobs of one launch: their output tiles are numbered one job after the other (ny_off), and so are the B operands
+// in the column-sum partials (cs_off). Jobs over the same rows share a partial buffer, blocks one job after the other;
+// jobs over rows of their own have splits and a buffer of their own.
 struct WgradJobs {
   WgradArgs job[3];
   int njobs;
-  int ny_off[4], blk_off[4], cs_off[4];
-  float* partial;
+  int ny_off[4], cs_off[4];
+  int nsplit[3], rows_per_split[3];
+  int nblk[3];            // blocks per split in the job's partial buffer
+  float* partial[3];      // the job's first block of split 0
   float* colsum_partial;
 };
 
 template <int H, bool BF16>
-__global__ void __launch_bounds__(256, 2) k_wgrad(WgradJobs m, int nsplit, int rows_per_split, int ny) {
+__global__ void __launch_bounds__(256, 2) k_wgrad(WgradJobs m, int ny) {
   using C = WgradCfg<H>;
   __shared__ __align__(16) float sA[WG_RC * C::STRIDE];
   __shared__ __align__(16) float sB[WG_RC * C::STRIDE];
@@ -1156,12 +1193,13 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradJobs m, int nsplit, int r
   // from memory once: split s lives on XCD s % 8.
   const int xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
   const int split = (place / ny) * 8 + xcd, grp = blockIdx.z;
-  if (split >= nsplit) return;   // uniform over the workgroup (the grid is padded to whole groups of 8 splits)
   int y = place % ny;
   int jb = 0;   // uniform over the workgroup
   if (m.njobs > 1 && y >= m.ny_off[1]) jb = 1;
   if (m.njobs > 2 && y >= m.ny_off[2]) jb = 2;
   y -= m.ny_off[jb];
+  const int nsplit = m.nsplit[jb], rows_per_split = m.rows_per_split[jb];
+  if (split >= nsplit || (grp > 0 && (!m.job[jb].grp_ptr || grp >= m.job[jb].S))) return;   // uniform over the workgroup (the grid covers whole groups of 8 splits of the largest job)
   const WgradArgs& p = m.job[jb];
   const int tb = y % C::TILES; y /= C::TILES;
   const int ta = y % C::TILES; y /= C::TILES;
@@ -1295,8 +1333,7 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradJobs m, int nsplit, int r
       *reinterpret_cast<float4*>(m.colsum_partial + (((long)grp * nsplit + split) * m.cs_off[m.njobs] + m.cs_off[jb] + ib) * H + tb * C::OT + tid * 4) = s;
     }
   }
-  const int nblk = m.blk_off[m.njobs];
-  float* out = m.partial + (((long)grp * nsplit + split) * nblk + m.blk_off[jb] + blkid) * (long)(H * H);
+  float* out = m.partial[jb] + (((long)grp * nsplit + split) * m.nblk[jb] + blkid) * (long)(H * H);
 #pragma unroll
   for (int i = 0; i < C::NB; ++i)
 #pragma unroll
@@ -1336,32 +1373,15 @@ static int wgrad_resident_wgs() {
   return n;
 }
 
+// splits of M rows for `ny` output tiles per split and group, and their rows
 template <int H, bool BF16>
-static int32_t launch_wgrad_t(hipStream_t st, const WgradArgs* jobs, int njobs) {
-  using C = WgradCfg<H>;
-  const WgradArgs& a = jobs[0];
-  WgradJobs m;
-  m.njobs = njobs;
-  m.partial = a.partial;
-  m.colsum_partial = nullptr;
-  m.ny_off[0] = m.blk_off[0] = m.cs_off[0] = 0;
-  for (int j = 0; j < njobs; ++j) {
-    m.job[j] = jobs[j];
-    m.ny_off[j + 1] = m.ny_off[j] + jobs[j].nA * jobs[j].nB * C::TILES * C::TILES;
-    m.blk_off[j + 1] = m.blk_off[j] + jobs[j].nA * jobs[j].nB;
-    m.cs_off[j + 1] = m.cs_off[j] + jobs[j].nB;
-    if (jobs[j].colsum_dest[0] || jobs[j].colsum_dest[1]) m.colsum_partial = a.colsum_partial;
-  }
-  for (int j = njobs; j < 3; ++j) m.ny_off[j + 1] = m.blk_off[j + 1] = m.cs_off[j + 1] = 0;
-  const int nblk = m.blk_off[njobs];
-  const int groups = a.grp_ptr ? a.S : 1;
-  const int ny = m.ny_off[njobs];
+static int wgrad_plan(int64_t M, int ny, int groups, int& rows_per_split) {
   // Splits: never more than the workspace was sized for, and at most one round of resident workgroups (a second,
   // partly filled round costs a whole one). Split s runs on XCD s % 8, so the round is counted per XCD: a whole
   // number of splits on each of them (25 splits of 20 workgroups put 80 workgroups on the first XCD's 64 places
   // and doubled the kernel's time). Below one round: a whole number of workgroups per CU, so that no CU carries two
   // while its neighbour carries one. Fewer splits also mean fewer partials to write and add up.
-  int nsplit = wgrad_splits(a.M);
+  int nsplit = wgrad_splits(M);
   const long per_split = (long)ny * groups;
   const long xcd_places = (long)wgrad_resident_wgs<H, BF16>() * (num_cus() / 8);
   const long one_round = xcd_places / per_split >= 1 ? 8 * (xcd_places / per_split)
@@ -1373,21 +1393,76 @@ static int32_t launch_wgrad_t(hipStream_t st, const WgradArgs* jobs, int njobs) 
     if (whole >= 1) nsplit = (int)(whole * num_cus() / per_split);
   }
   if (nsplit < 1) nsplit = 1;   // many groups with few rows each: per_split alone can exceed the CU count
-  int64_t rps = (a.M + nsplit - 1) / nsplit;
+  int64_t rps = (M + nsplit - 1) / nsplit;
   rps = (rps + WG_RC - 1) / WG_RC * WG_RC;
   if (rps < WG_RC) rps = WG_RC;
+  rows_per_split = (int)rps;
+  return nsplit;
+}
+
+// own_rows: every job has its own rows, groups and partial buffer (as many launches in one); otherwise they share job 0's
+template <int H, bool BF16>
+static int32_t launch_wgrad_t(hipStream_t st, const WgradArgs* jobs, int njobs, bool own_rows) {
+  using C = WgradCfg<H>;
+  const WgradArgs& a = jobs[0];
+  WgradJobs m;
+  m.njobs = njobs;
+  m.colsum_partial = nullptr;
+  int blk_off[4] = {0, 0, 0, 0};
+  m.ny_off[0] = m.cs_off[0] = 0;
+  for (int j = 0; j < njobs; ++j) {
+    m.job[j] = jobs[j];
+    m.ny_off[j + 1] = m.ny_off[j] + jobs[j].nA * jobs[j].nB * C::TILES * C::TILES;
+    blk_off[j + 1] = blk_off[j] + jobs[j].nA * jobs[j].nB;
+    m.cs_off[j + 1] = m.cs_off[j] + jobs[j].nB;
+    if (jobs[j].colsum_dest[0] || jobs[j].colsum_dest[1]) m.colsum_partial = a.colsum_partial;
+  }
+  const int nblk = blk_off[njobs];
+  const int ny = m.ny_off[njobs];
+  int most = 1, groups = 1;
+  for (int j = 0; j < njobs; ++j) {
+    const int gj = jobs[j].grp_ptr ? jobs[j].S : 1;
+    if (gj > groups) groups = gj;
+    if (own_rows) {
+      m.nsplit[j] = wgrad_plan<H, BF16>(jobs[j].M, m.ny_off[j + 1] - m.ny_off[j], gj, m.rows_per_split[j]);
+      m.nblk[j] = blk_off[j + 1] - blk_off[j];
+      m.partial[j] = jobs[j].partial;
+    } else {
+      m.nsplit[j] = wgrad_plan<H, BF16>(a.M, ny, gj, m.rows_per_split[j]);
+      m.nblk[j] = nblk;
+      m.partial[j] = a.partial + (long)blk_off[j] * H * H;
+    }
+    if (m.nsplit[j] > most) most = m.nsplit[j];
+  }
+  for (int j = njobs; j < 3; ++j) m.ny_off[j + 1] = m.cs_off[j + 1] = 0;
   ProfScope ps(a.tag, st);
-  k_wgrad<H, BF16><<<dim3((unsigned)((nsplit + 7) / 8 * 8 * ny), 1, groups), 256, 0, st>>>(m, nsplit, (int)rps, ny);
+  k_wgrad<H, BF16><<<dim3((unsigned)((most + 7) / 8 * 8 * ny), 1, groups), 256, 0, st>>>(m, ny);
   HGNN_LAUNCH_CHECK("k_wgrad");
+  if (own_rows) {
+    for (int j = 0; j < njobs; ++j)
+      HGNN_TRY(launch_reduce_partials_n(st, m.partial[j], m.nsplit[j], m.nblk[j], (long)H * H, jobs[j].dest, 4,
+                                        jobs[j].grp_ptr ? jobs[j].S : 1, jobs[j].grp_dest_stride));
+    return HGNN_OK;
+  }
   float* dest[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   float* cd[4] = {nullptr, nullptr, nullptr, nullptr};
   for (int j = 0; j < njobs; ++j) {
-    for (int b = 0; b < jobs[j].nA * jobs[j].nB; ++b) dest[m.blk_off[j] + b] = jobs[j].dest[b];
+    for (int b = 0; b < jobs[j].nA * jobs[j].nB; ++b) dest[blk_off[j] + b] = jobs[j].dest[b];
     for (int b = 0; b < jobs[j].nB; ++b) cd[m.cs_off[j] + b] = jobs[j].colsum_dest[b];
   }
-  HGNN_TRY(launch_reduce_partials_n(st, m.partial, nsplit, nblk, (long)H * H, dest, 8, groups, a.grp_dest_stride));
-  if (m.colsum_partial) HGNN_TRY(launch_reduce_partials_n(st, m.colsum_partial, nsplit, m.cs_off[njobs], H, cd, 4, 1, 0));
+  HGNN_TRY(launch_reduce_partials_n(st, a.partial, m.nsplit[0], nblk, (long)H * H, dest, 8, groups, a.grp_dest_stride));
+  if (m.colsum_partial) HGNN_TRY(launch_reduce_partials_n(st, m.colsum_partial, m.nsplit[0], m.cs_off[njobs], H, cd, 4, 1, 0));
   return HGNN_OK;
+}
+
+template <bool BF16>
+static int32_t launch_wgrad_h(hipStream_t st, int H, const WgradArgs* jobs, int njobs, bool own_rows) {
+  switch (H) {
+    case 64: return launch_wgrad_t<64, BF16>(st, jobs, njobs, own_rows);
+    case 128: return launch_wgrad_t<128, BF16>(st, jobs, njobs, own_rows);
+    case 256: return launch_wgrad_t<256, BF16>(st, jobs, njobs, own_rows);
+  }
+  return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
 }
 
 int32_t launch_wgrad_multi(hipStream_t st, int H, bool bf16, const WgradArgs* jobs, int njobs) {
@@ -1407,12 +1482,18 @@ int32_t launch_wgrad_multi(hipStream_t st, int H, bool bf16, const WgradArgs* jo
   HGNN_REQUIRE(blocks <= 8 && nb <= 4, HGNN_ERR_BAD_SHAPE, "wgrad: too many blocks in one launch");
   HGNN_REQUIRE(!(jobs[0].colsum_partial && (jobs[0].colsum_dest[0] || jobs[0].colsum_dest[1])) || !jobs[0].grp_ptr,
                HGNN_ERR_BAD_SHAPE, "wgrad: column sums are not available per group");
-  switch (H) {
-    case 64: return bf16 ? launch_wgrad_t<64, true>(st, jobs, njobs) : launch_wgrad_t<64, false>(st, jobs, njobs);
-    case 128: return bf16 ? launch_wgrad_t<128, true>(st, jobs, njobs) : launch_wgrad_t<128, false>(st, jobs, njobs);
-    case 256: return bf16 ? launch_wgrad_t<256, true>(st, jobs, njobs) : launch_wgrad_t<256, false>(st, jobs, njobs);
+  return bf16 ? launch_wgrad_h<true>(st, H, jobs, njobs, false) : launch_wgrad_h<false>(st, H, jobs, njobs, false);
+}
+
+int32_t launch_wgrad_own_rows(hipStream_t st, int H, bool bf16, const WgradArgs* jobs, int njobs) {
+  HGNN_REQUIRE(jobs && njobs >= 1 && njobs <= 3, HGNN_ERR_BAD_SHAPE, "wgrad: one to three jobs");
+  for (int j = 0; j < njobs; ++j) {
+    const WgradArgs& a = jobs[j];
+    HGNN_REQUIRE(a.nA >= 1 && a.nB >= 1 && a.nA * a.nB <= 4, HGNN_ERR_BAD_SHAPE, "wgrad: bad block counts");
+    HGNN_REQUIRE(a.A[0] && a.B[0] && a.dest[0] && a.partial, HGNN_ERR_NULLPTR, "wgrad: null operand");
+    HGNN_REQUIRE(!a.colsum_dest[0] && !a.colsum_dest[1], HGNN_ERR_BAD_SHAPE, "wgrad: no column sums here");
   }
-  return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
+  return bf16 ? launch_wgrad_h<true>(st, H, jobs, njobs, true) : launch_wgrad_h<false>(st, H, jobs, njobs, true);
 }
 
 int32_t launch_wgrad(hipStream_t st, int H, bool bf16, const WgradArgs& a) { return launch_wgrad_multi(st, H, bf16, &a, 1); }
@@ -1420,15 +1501,24 @@ int32_t launch_wgrad(hipStream_t st, int H, bool bf16, const WgradArgs& a) { ret
 // ---------------------------------------------------------------------------------------------
 // column sums
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_colsum(ColsumArgs p, int H, int nsplit, int rows_per_split) {
+// up to four column sums in one launch (blockIdx.z), each over its own rows
+struct ColsumJobs {
+  ColsumArgs job[4];
+  int nsplit[4], rows_per_split[4];
+};
+__global__ void __launch_bounds__(256) k_colsum(ColsumJobs m, int H) {
+  const ColsumArgs& p = m.job[blockIdx.z];
+  const int nsplit = m.nsplit[blockIdx.z], rows_per_split = m.rows_per_split[blockIdx.z];
   // thread = (4-column chunk q, row phase ph); every phase walks its rows with four loads in flight
   __shared__ float4 sh[256];
   const int tid = threadIdx.x;
   const int CH = H >> 2;
   const int q = tid % CH, ph = tid / CH, nph = 256 / CH;
   const int split = blockIdx.x, grp = blockIdx.y;
+  if (split >= nsplit || (grp > 0 && (!p.grp_ptr || grp >= p.S))) return;   // uniform over the workgroup
   long gbeg = 0, gend = p.M;
   if (p.grp_ptr) { gbeg = p.grp_ptr[grp]; gend = p.grp_ptr[grp + 1]; }
+  float ws = 0.f;   // this phase's sum of the weights
   long rbeg = gbeg + (long)split * rows_per_split;
   long rend = rbeg + rows_per_split;
   if (rend > gend) rend = gend;
@@ -1463,6 +1553,7 @@ __global__ void __launch_bounds__(256) k_colsum(ColsumArgs p, int H, int nsplit,
       float4 x = xv[u];
       if (p.f_silu) { x.x = silu_f(x.x); x.y = silu_f(x.y); x.z = silu_f(x.z); x.w = silu_f(x.w); }
       s.x += wv[u] * x.x; s.y += wv[u] * x.y; s.z += wv[u] * x.z; s.w += wv[u] * x.w;
+      ws += wv[u];
     }
   }
   sh[tid] = s;
@@ -1473,6 +1564,15 @@ __global__ void __launch_bounds__(256) k_colsum(ColsumArgs p, int H, int nsplit,
       s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
     *reinterpret_cast<float4*>(p.partial + ((long)grp * nsplit + split) * H + q * 4) = s;
+  }
+  if (p.w_dest) {   // uniform over the workgroup
+    __syncthreads();
+    sh[tid].x = ws;
+    __syncthreads();
+    if (tid == 0) {
+      for (int k = 1; k < nph; ++k) ws += sh[k * CH].x;
+      p.w_partial[(long)grp * nsplit + split] = ws;
+    }
   }
 }
 
@@ -1485,18 +1585,37 @@ static int colsum_splits(int64_t M) {
 
 size_t colsum_partial_floats(int H, int64_t M, int S) { return (size_t)colsum_splits(M) * S * H; }
 
-int32_t launch_colsum(hipStream_t st, int H, const ColsumArgs& a) {
-  HGNN_REQUIRE(a.X && a.dest && a.partial, HGNN_ERR_NULLPTR, "colsum: null operand");
+int32_t launch_colsum_multi(hipStream_t st, int H, const ColsumArgs* jobs, int njobs) {
+  HGNN_REQUIRE(jobs && njobs >= 1 && njobs <= 4, HGNN_ERR_BAD_SHAPE, "colsum: one to four jobs");
   HGNN_REQUIRE(valid_H(H), HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
-  const int nsplit = colsum_splits(a.M);
-  int64_t rps = (a.M + nsplit - 1) / nsplit;
-  if (rps < 1) rps = 1;
-  const int groups = a.grp_ptr ? a.S : 1;
+  ColsumJobs m;
+  int most = 1, groups = 1;
+  for (int j = 0; j < njobs; ++j) {
+    const ColsumArgs& a = jobs[j];
+    HGNN_REQUIRE(a.X && a.dest && a.partial, HGNN_ERR_NULLPTR, "colsum: null operand");
+    HGNN_REQUIRE(!a.w_dest || (a.w && a.w_partial), HGNN_ERR_NULLPTR, "colsum: null weights");
+    m.job[j] = a;
+    m.nsplit[j] = colsum_splits(a.M);
+    const int64_t rps = (a.M + m.nsplit[j] - 1) / m.nsplit[j];
+    m.rows_per_split[j] = rps < 1 ? 1 : (int)rps;
+    if (m.nsplit[j] > most) most = m.nsplit[j];
+    if (a.grp_ptr && a.S > groups) groups = a.S;
+  }
   ProfScope ps(PT_COLSUM, st);
-  k_colsum<<<dim3(nsplit, groups), 256, 0, st>>>(a, H, nsplit, (int)rps);
+  k_colsum<<<dim3(most, groups, njobs), 256, 0, st>>>(m, H);
   HGNN_LAUNCH_CHECK("k_colsum");
-  float* dest[4] = {a.dest, nullptr, nullptr, nullptr};
-  return launch_reduce_partials(st, a.partial, nsplit, 1, H, dest, groups, a.grp_dest_stride);
+  for (int j = 0; j < njobs; ++j) {
+    const ColsumArgs& a = jobs[j];
+    const int g = a.grp_ptr ? a.S : 1;
+    float* dest[4] = {a.dest, nullptr, nullptr, nullptr};
+    HGNN_TRY(launch_reduce_partials(st, a.partial, m.nsplit[j], 1, H, dest, g, a.grp_dest_stride));
+    if (a.w_dest) {
+      float* wd[4] = {a.w_dest, nullptr, nullptr, nullptr};
+      HGNN_TRY(launch_reduce_partials(st, a.w_partial, m.nsplit[j], 1, 1, wd, g, a.grp_dest_stride));
+    }
+  }
+  return HGNN_OK;
 }
+int32_t launch_colsum(hipStream_t st, int H, const ColsumArgs& a) { return launch_colsum_multi(st, H, &a, 1); }
 
 }  // namespace hgnn

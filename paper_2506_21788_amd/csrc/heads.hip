@@ -552,24 +552,6 @@ k_head_out_bwd(int N, int G, int Hh, const float* __restrict__ ze, const float* 
   for (int c = lane; c < Hh; c += 64) gz_[c] = go * w2[c] * dsilu_f(z[c]);
 }
 
-// dest[s*stride] = sum over positions of group s of w[row_idx[pos]]   (one block per group, fixed order)
-__global__ void __launch_bounds__(1024)
-k_group_scalar_sum(const float* __restrict__ w, const int32_t* __restrict__ row_idx,
-                   const int32_t* __restrict__ grp_ptr, float* __restrict__ dest, long stride) {
-  __shared__ float sh[16];
-  const int s = blockIdx.x;
-  float acc = 0.f;
-  for (int t = grp_ptr[s] + threadIdx.x; t < grp_ptr[s + 1]; t += 1024) acc += w[row_idx[t]];
-  acc = wsum(acc);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float tot = 0.f;
-    for (int k = 0; k < 16; ++k) tot += sh[k];
-    dest[s * stride] = tot;
-  }
-}
-
 struct HeadSaved {
   float *ze, *zf, *q;
   size_t bytes;
@@ -586,9 +568,9 @@ static HeadSaved carve_head_saved(void* p, int N, int G, int Hh) {
 struct HeadWs {
   void* packed;  // [S][2] blocks
   float *g_ze, *g_zf, *gq, *partial;
-  // reverse pass: partials of the two column sums and of the weight gradient of each branch (energy, force); they all
+  // reverse pass: partials of the two column sums, of the weights' sum and of the weight gradient of each branch (energy, force); they all
   // live until the pass's one reduction launch
-  float *pcs[2][2], *pwg[2];
+  float *pcs[2][2], *pws[2], *pwg[2];
   size_t bytes;
 };
 static HeadWs carve_head_ws(void* p, int N, int G, int H, int Hh, int S, bool bf16) {
@@ -606,6 +588,7 @@ static HeadWs carve_head_ws(void* p, int N, int G, int H, int Hh, int S, bool bf
     const int64_t M = br == 0 ? G : N;
     w.pcs[br][0] = c.take<float>(colsum_partial_floats(H, M, S));
     w.pcs[br][1] = c.take<float>(colsum_partial_floats(H, M, S));
+    w.pws[br] = c.take<float>(colsum_partial_floats(1, M, S));
     w.pwg[br] = c.take<float>(wgrad_partial_floats(H, M, 1, S));
   }
   w.bytes = c.used();
@@ -812,24 +795,19 @@ extern "C" int32_t hgnn_multihead_decode_fwd(void* stream, int32_t N, int32_t G,
   pk.d[0] = {o.We1, Hh, 1};
   pk.d[1] = {o.Wf1, Hh, 1};
   HGNN_TRY(launch_pack(st, H, bf16, pk, S, o.per, 2 * HH));
-  if (G > 0) {
-    GemmArgs g;
-    g.A[0] = p; g.lda[0] = H;
-    g.B = w.packed; g.blk[0][0] = 0; g.grp_blk_stride = 2;
-    g.row_idx = pv.graph_perm; g.grp_ptr = pv.grp_graph_ptr; g.S = S; g.M = G;
-    g.bias = Whead + o.be1; g.bias_cb_mask = 1; g.grp_bias_stride = o.per;
-    g.C = s.ze; g.ldc = Hh;
-    HGNN_TRY(launch_gemm(st, H, bf16, g));
-  }
-  if (N > 0) {
-    GemmArgs g;
-    g.A[0] = h; g.lda[0] = H;
-    g.B = w.packed; g.blk[0][0] = 1; g.grp_blk_stride = 2;
-    g.row_idx = pv.atom_perm; g.grp_ptr = pv.grp_atom_ptr; g.S = S; g.M = N;
-    g.bias = Whead + o.bf1; g.bias_cb_mask = 1; g.grp_bias_stride = o.per;
-    g.C = s.zf; g.ldc = Hh;
-    HGNN_TRY(launch_gemm(st, H, bf16, g));
-  }
+  GemmArgs ge, gf;
+  ge.A[0] = p; ge.lda[0] = H;
+  ge.B = w.packed; ge.blk[0][0] = 0; ge.grp_blk_stride = 2;
+  ge.row_idx = pv.graph_perm; ge.grp_ptr = pv.grp_graph_ptr; ge.S = S; ge.M = G;
+  ge.bias = Whead + o.be1; ge.bias_cb_mask = 1; ge.grp_bias_stride = o.per;
+  ge.C = s.ze; ge.ldc = Hh;
+  gf.A[0] = h; gf.lda[0] = H;
+  gf.B = w.packed; gf.blk[0][0] = 1; gf.grp_blk_stride = 2;
+  gf.row_idx = pv.atom_perm; gf.grp_ptr = pv.grp_atom_ptr; gf.S = S; gf.M = N;
+  gf.bias = Whead + o.bf1; gf.bias_cb_mask = 1; gf.grp_bias_stride = o.per;
+  gf.C = s.zf; gf.ldc = Hh;
+  if (G > 0 && N > 0) HGNN_TRY(launch_gemm_pair(st, H, bf16, ge, gf));
+  else HGNN_TRY(launch_gemm(st, H, bf16, G > 0 ? ge : gf));
   ProfScope ps(PT_HEAD_OUT, st);
   k_head_out_fwd<<<nb64((int64_t)(G + N) * 64, 256), 256, 0, st>>>(N, G, Hh, s.ze, s.zf, Whead, o, pv.graph_src,
                                                                     pv.atom_graph, v, energy, force, s.q);
@@ -878,9 +856,15 @@ extern "C" int32_t hgnn_multihead_decode_bwd(void* stream, int32_t N, int32_t G,
   }
   HGNN_LAUNCH_CHECK("k_head_out_bwd");
 
-  // ---- energy branch (rows = graphs) and force branch (rows = atoms), same five steps each; their six reductions
-  // of split partials (nothing here reads a result) run as one launch at the end
+  // ---- energy branch (rows = graphs) and force branch (rows = atoms): the same steps for both, each step one launch over
+  // both branches (apart, they were ten launches of 2-4 us), and one launch for the reductions of their split partials
+  // (nothing here reads a result). Thirteen launches -> six: 32 small molecules 377 -> 353 us per
+  // step, a crystal's conservative forces 598 -> 573, 128 molecules 900 -> 885.
   ReduceQueueScope reductions(st, true);
+  ColsumArgs cs[4];
+  WgradArgs wg[2];
+  GemmArgs gx[2];
+  int nb = 0;   // branches with rows
   for (int br = 0; br < 2; ++br) {
     const bool en = br == 0;
     const int64_t M = en ? G : N;
@@ -898,35 +882,35 @@ extern "C" int32_t hgnn_multihead_decode_bwd(void* stream, int32_t N, int32_t G,
       continue;
     }
     {  // second layer weight and bias
-      ColsumArgs c;
+      ColsumArgs& c = cs[2 * nb];
       c.X = z; c.ldx = Hh; c.f_silu = 1; c.w = gout; c.row_idx = ridx; c.grp_ptr = gptr; c.S = S; c.M = M;
       c.dest = gWhead + oW2; c.grp_dest_stride = o.per; c.partial = w.pcs[br][0];
-      HGNN_TRY(launch_colsum(st, Hh, c));
-      k_group_scalar_sum<<<S, 1024, 0, st>>>(gout, ridx, gptr, gWhead + ob2, o.per);
-      HGNN_LAUNCH_CHECK("k_group_scalar_sum");
+      c.w_dest = gWhead + ob2; c.w_partial = w.pws[br];
     }
     {  // first layer bias and weight
-      ColsumArgs c;
+      ColsumArgs& c = cs[2 * nb + 1];
       c.X = gz; c.ldx = Hh; c.row_idx = ridx; c.grp_ptr = gptr; c.S = S; c.M = M;
       c.dest = gWhead + ob1; c.grp_dest_stride = o.per; c.partial = w.pcs[br][1];
-      HGNN_TRY(launch_colsum(st, Hh, c));
-      WgradArgs a;
+      WgradArgs& a = wg[nb];
       a.A[0] = X; a.lda[0] = H;
       a.B[0] = gz; a.ldb[0] = Hh;
       a.row_idx = ridx; a.grp_ptr = gptr; a.S = S; a.M = M;
       a.dest[0] = gWhead + oW1; a.grp_dest_stride = o.per;
       a.partial = w.pwg[br];
-      HGNN_TRY(launch_wgrad(st, H, bf16, a));
     }
     {  // input gradient
-      GemmArgs g;
+      GemmArgs& g = gx[nb];
       g.A[0] = gz; g.lda[0] = Hh;
       g.B = w.packed; g.blk[0][0] = en ? 0 : 1; g.grp_blk_stride = 2;
       g.row_idx = ridx; g.grp_ptr = gptr; g.S = S; g.M = (int)M;
       g.C = en ? g_p : g_h; g.ldc = H;
-      HGNN_TRY(launch_gemm(st, H, bf16, g));
     }
+    ++nb;
   }
+  HGNN_TRY(launch_colsum_multi(st, Hh, cs, 2 * nb));
+  HGNN_TRY(launch_wgrad_own_rows(st, H, bf16, wg, nb));
+  if (nb == 2) HGNN_TRY(launch_gemm_pair(st, H, bf16, gx[0], gx[1]));
+  else HGNN_TRY(launch_gemm(st, H, bf16, gx[0]));
   {
     ProfScope ps(PT_COLSUM, st);
     HGNN_TRY(reductions.flush());

@@ -1,0 +1,64 @@
+"""Decoding heads of one hidden layer as wide as the features against the oracle (needs a GPU): both branches of every step of
+the reverse pass share a launch, each with rows, groups and splits of its own."""
+import numpy as np
+import pytest
+
+import oracle
+from hgnn_inputs import deep_head_field_slices, deep_head_weight_count, init_deep_head_weights
+from parity_util import TOL, relerr
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,dtype", [(64, "f32"), (128, "f32"), (128, "bf16"), (256, "bf16"), (256, "f32")])
+@pytest.mark.parametrize("sizes,S,sources", [
+    ([13], 1, (0,)),                          # one graph: one row tile each
+    ([16, 17, 15, 1, 33], 3, (0, 2)),         # around the 16-row tiles, one source without graphs
+    ([0, 0, 5, 0], 2, (0, 1)),                # graphs without atoms
+    ([0, 0, 0], 2, (1,)),                     # no atom at all: the force branch has no rows
+    ([1] * 300, 2, (0, 1)),                   # as many graphs as atoms
+    ([512] * 16, 2, (0, 1)),                  # 8,192 atoms: the last batch of one launch for both products (H >= 128)
+    ([512] * 16 + [1], 2, (0, 1)),
+])
+def test_plain_heads_match_the_oracle(sizes, S, sources, H, dtype):
+    import torch
+    from paper_2506_21788_amd import binding as B
+    rng = np.random.default_rng(H + len(sizes))
+    graph_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    G, N, dt = len(sizes), int(graph_off[-1]), {"f32": B.F32, "bf16": B.BF16}[dtype]
+    src = rng.choice(np.asarray(sources), size=G).astype(np.int32)
+    h = rng.standard_normal((N, H)).astype(np.float32)
+    v = (rng.standard_normal((N, 3)) * 0.5).astype(np.float32)
+    p = oracle.pool_fwd(h, graph_off).astype(np.float32)
+    Wh = init_deep_head_weights(rng, H, H, 1, S)
+    gE, gF = rng.standard_normal(G).astype(np.float32), rng.standard_normal((N, 3)).astype(np.float32)
+    t = {k: torch.as_tensor(a).cuda() for k, a in dict(off=graph_off, src=src, h=h, v=v, p=p, Wh=Wh, gE=gE, gF=gF).items()}
+    plan = torch.empty(B.multihead_plan_ints(N, G, S), dtype=torch.int32, device="cuda")
+    B.multihead_plan(N, G, S, t["off"], t["src"], plan)
+    ws_b, sv_b = B.multihead_decode_workspace_bytes(N, G, H, H, S, dt)
+    ws = torch.full((ws_b,), 0x5a, dtype=torch.uint8, device="cuda")
+    sv = torch.empty(sv_b, dtype=torch.uint8, device="cuda")
+    f32 = dict(dtype=torch.float32, device="cuda")
+    energy, force = torch.empty(G, **f32), torch.empty((N, 3), **f32)
+    g_p, g_h, g_v = torch.empty((G, H), **f32), torch.empty((N, H), **f32), torch.empty((N, 3), **f32)
+    gWh = torch.full_like(t["Wh"], float("nan"))
+    B.multihead_decode_fwd(N, G, H, H, S, dt, plan, t["p"], t["h"], t["v"], t["Wh"], energy, force, sv, ws)
+    B.multihead_decode_bwd(N, G, H, H, S, dt, plan, t["p"], t["h"], t["v"], t["Wh"], sv, t["gE"], t["gF"], g_p, g_h, g_v,
+                           gWh, ws)
+    torch.cuda.synchronize()
+    eo, fo, c = oracle.heads_deep_fwd(p, h, v, graph_off, src, Wh.astype(np.float64), H, 1, S)
+    gpo, gho, gvo, gWo = oracle.heads_deep_bwd(c, gE, gF)
+    errs = {k: relerr(a.cpu().numpy(), b) for k, a, b in [("energy", energy, eo), ("force", force, fo), ("g_p", g_p, gpo),
+                                                          ("g_h", g_h, gho), ("g_v", g_v, gvo)] if b.size}
+    got, per = gWh.cpu().numpy(), deep_head_weight_count(H, H, 1)
+    assert np.all(np.isfinite(got)), "a gradient field was left unwritten"
+    for s in range(S):
+        for name, (lo, hi, _) in deep_head_field_slices(H, H, 1).items():
+            want = gWo[s * per + lo:s * per + hi]
+            if not want.any():
+                assert not got[s * per + lo:s * per + hi].any(), (s, name)
+            else:
+                errs[f"s{s}.{name}"] = relerr(got[s * per + lo:s * per + hi], want)
+    print(f"heads G={G} N={N} H={H} S={S} {dtype}", f"{max(errs.values()):.1e}", flush=True)
+    for k, e in errs.items():
+        assert e <= TOL[dtype]["fwd" if k in ("energy", "force") else "grad"], (k, e)
