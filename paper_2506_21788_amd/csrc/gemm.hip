@@ -12,6 +12,8 @@
 // For fp32 the k index inside a block of 8 is permuted (lane half g takes k = 4g..4g+3 over four
 // consecutive instructions) so that both operands are fetched as one float4; the permutation is the
 // same for A and B and therefore cancels.
+#include <type_traits>
+
 #include "devmath.h"
 #include "gemm.h"
 
@@ -1164,7 +1166,8 @@ struct WgradCfg {
   static constexpr int OT = H < 128 ? H : 128;  // output tile edge
   static constexpr int WT = OT / 2;             // per-wave edge (2 x 2 wavefronts)
   static constexpr int NB = WT / 32;
-  static constexpr int STRIDE = OT + 4;
+  static constexpr int STRIDE = OT + 4;         // LDS row pitch, fp32 operands
+  static constexpr int BSTRIDE = OT + 16;       // bf16 operands (elements): four rows in four different groups of 8 banks
   static constexpr int TILES = H / OT;
 };
 
@@ -1181,11 +1184,25 @@ struct WgradJobs {
   float* colsum_partial;
 };
 
+// two transposing LDS reads: the eight rows of one lane's column (bf16)
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8_t lds_read_tr(const unsigned short* lo, const unsigned short* hi) {
+  const s16x4_t l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lo));
+  const s16x4_t h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(hi));
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 template <int H, bool BF16>
 __global__ void __launch_bounds__(256, 2) k_wgrad(WgradJobs m, int ny) {
   using C = WgradCfg<H>;
-  __shared__ __align__(16) float sA[WG_RC * C::STRIDE];
-  __shared__ __align__(16) float sB[WG_RC * C::STRIDE];
+  // bf16 operands are rounded when they are staged and read back with the transposing LDS reads (two per operand of 16
+  // rows, see wgrad_group() of the edge kernels). Kept as fp32 an operand was eight 4-byte reads and four conversions, done
+  // by each of the two wavefronts that share it. Steps at H = 256: mixed batch of 643 structures 9.45 -> 9.38 ms, 64 crystals
+  // 1651 -> 1636 us.
+  using ST = typename std::conditional<BF16, unsigned short, float>::type;
+  constexpr int SP = BF16 ? C::BSTRIDE : C::STRIDE;
+  __shared__ __align__(16) ST sA[WG_RC * SP];
+  __shared__ __align__(16) ST sB[WG_RC * SP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wa = wave >> 1, wb = wave & 1;
   // Workgroups are dealt to the 8 XCDs round-robin. The ny workgroups that read the same rows (one per output tile)
@@ -1263,30 +1280,26 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradJobs m, int ny) {
       if (p.a_silu) { a.x = silu_f(a.x); a.y = silu_f(a.y); a.z = silu_f(a.z); a.w = silu_f(a.w); }
       if (r0 + r >= rend) { a = make_float4(0.f, 0.f, 0.f, 0.f); b = a; }
       cs.x += b.x; cs.y += b.y; cs.z += b.z; cs.w += b.w;
-      *reinterpret_cast<float4*>(&sA[r * C::STRIDE + q * 4]) = a;
-      *reinterpret_cast<float4*>(&sB[r * C::STRIDE + q * 4]) = b;
+      if constexpr (BF16) {
+        *reinterpret_cast<uint2*>(&sA[r * SP + q * 4]) = make_uint2(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w));
+        *reinterpret_cast<uint2*>(&sB[r * SP + q * 4]) = make_uint2(pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w));
+      } else {
+        *reinterpret_cast<float4*>(&sA[r * SP + q * 4]) = a;
+        *reinterpret_cast<float4*>(&sB[r * SP + q * 4]) = b;
+      }
     }
     if (r0 + 2 * WG_RC < rend) fetch(r0 + 2 * WG_RC, va, vb);
     __syncthreads();
-    if (BF16) {
+    if constexpr (BF16) {
 #pragma unroll
       for (int ks = 0; ks < WG_RC / 16; ++ks) {
-        const int rr = ks * 16 + (lane >> 5) * 8;
+        // lane group g: rows 16 ks + 4 g + 0..3 and + 8 of its column, the same for both operands
+        const int lo = (ks * 16 + 4 * (lane >> 5) + ((lane & 15) >> 2)) * SP + (lane & 16) + (lane & 3) * 4;
         bf16x8_t a[C::NB], b[C::NB];
 #pragma unroll
         for (int i = 0; i < C::NB; ++i) {
-          const int ca = wa * C::WT + i * 32 + (lane & 31);
-          const int cbb = wb * C::WT + i * 32 + (lane & 31);
-          unsigned ua[4], ub[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            ua[t] = pack_bf16x2(sA[(rr + 2 * t) * C::STRIDE + ca], sA[(rr + 2 * t + 1) * C::STRIDE + ca]);
-            ub[t] = pack_bf16x2(sB[(rr + 2 * t) * C::STRIDE + cbb], sB[(rr + 2 * t + 1) * C::STRIDE + cbb]);
-          }
-          uint4 pa = make_uint4(ua[0], ua[1], ua[2], ua[3]);
-          uint4 pb = make_uint4(ub[0], ub[1], ub[2], ub[3]);
-          a[i] = *reinterpret_cast<bf16x8_t*>(&pa);
-          b[i] = *reinterpret_cast<bf16x8_t*>(&pb);
+          a[i] = lds_read_tr(&sA[lo + wa * C::WT + i * 32], &sA[lo + wa * C::WT + i * 32 + 8 * SP]);
+          b[i] = lds_read_tr(&sB[lo + wb * C::WT + i * 32], &sB[lo + wb * C::WT + i * 32 + 8 * SP]);
         }
 #pragma unroll
         for (int i = 0; i < C::NB; ++i)
