@@ -333,8 +333,10 @@ extern "C" int32_t hgnn_multihead_deep_bwd(void* stream, int32_t N, int32_t G, i
       k_deep_scalar_sum<<<S, 1024, 0, st>>>(gout, ridx, gptr, gWhead + o.bo[hd], o.per);
       HGNN_LAUNCH_CHECK("k_deep_scalar_sum");
     }
-    {  // g_z_D into fragment order
-      ToFragArgs t;
+    ToFragArgs tz;   // g_z_l into fragment order, its column sums (the bias gradient) formed on the way
+    {  // g_z_D
+      ToFragArgs& t = tz;
+      t.cs_partial = w.cs_partial;
       t.X = w.gzD[hd]; t.ldx = d.Hhp; t.ncol = Hh; t.Cp = d.Hhp; t.Mp = d.Mp[hd];
       t.grp_ptr = gptr; t.S = S; t.row_idx = ridx;
       t.R = w.R0; t.r_nkb = d.Hhp / 16;
@@ -343,14 +345,7 @@ extern "C" int32_t hgnn_multihead_deep_bwd(void* stream, int32_t N, int32_t G, i
     }
     for (int l = D; l >= 1; --l) {
       const int K = l == 1 ? H : Hh, Kp = l == 1 ? d.Hp : d.Hhp;
-      {  // bias gradient = column sums of g_z_l
-        ColsumRowsArgs c;
-        c.M = M; c.ncol = Hh; c.grp_ptr = gptr; c.S = S;
-        c.partial = w.cs_partial; c.dest = gWhead + o.b[hd][l]; c.dest_grp_stride = o.per;
-        if (l == D) { c.X = w.gzD[hd]; c.ldx = d.Hhp; c.row_idx = ridx; }
-        else { c.X = w.ga; c.ldx = d.Hhp; c.Z = s.z[hd][l]; c.ldz = d.Hhp; c.mode = 2; }
-        HGNN_TRY(launch_colsum_rows(st, c));
-      }
+      HGNN_TRY(launch_frag_colsum(st, tz, gWhead + o.b[hd][l], o.per));
       {  // the layer's input as T fragments: the gathered rows, or silu of the previous pre-activation
         ToFragArgs t;
         t.Mp = d.Mp[hd]; t.grp_ptr = gptr; t.S = S;
@@ -384,7 +379,9 @@ extern "C" int32_t hgnn_multihead_deep_bwd(void* stream, int32_t N, int32_t G, i
         HGNN_TRY(launch_fgemm_rows(st, g));
       }
       if (l > 1) {  // g_z_{l-1} = g_a_{l-1} silu'(z_{l-1})
-        ToFragArgs t;
+        tz = ToFragArgs{};
+        ToFragArgs& t = tz;
+        t.cs_partial = w.cs_partial;
         t.X = w.ga; t.ldx = d.Hhp; t.Z = s.z[hd][l - 1]; t.ldz = d.Hhp; t.mode = 2; t.ncol = Hh; t.Cp = d.Hhp;
         t.Mp = d.Mp[hd]; t.grp_ptr = gptr; t.S = S;
         t.R = w.R0; t.r_nkb = d.Hhp / 16;

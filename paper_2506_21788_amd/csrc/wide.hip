@@ -629,6 +629,7 @@ __global__ void __launch_bounds__(256) k_to_frag(ToFragArgs a) {
   const int hh = q >> 1, g = q & 1;
   const int c = slab * 128 + 2 * x;
   unsigned packed[8];   // [u]: columns c (low half), c + 1
+  float cs0 = 0.f, cs1 = 0.f;   // sums of this thread's rows (zeros in rows and columns past the end)
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
     const int r = tset_row(2 * rb + hh, g, u);   // row inside the group
@@ -657,6 +658,23 @@ __global__ void __launch_bounds__(256) k_to_frag(ToFragArgs a) {
     if (c + 1 >= a.ncol) x1 = 0.f;
     if (c >= a.ncol) x0 = 0.f;
     packed[u] = pack_bf16x2(x0, x1);
+    cs0 += x0;
+    cs1 += x1;
+  }
+  if (a.cs_partial) {   // uniform over the launch
+    __shared__ float2 cs[4][64];
+    cs[q][x] = make_float2(cs0, cs1);
+    __syncthreads();
+    if (q == 0) {
+#pragma unroll
+      for (int k = 1; k < 4; ++k) {
+        cs0 += cs[k][x].x;
+        cs1 += cs[k][x].y;
+      }
+      float* o = a.cs_partial + (long)(pad0 / 32 + rb) * a.ncol;
+      if (c < a.ncol) o[c] = cs0;
+      if (c + 1 < a.ncol) o[c + 1] = cs1;
+    }
   }
   if (a.T) {   // destination rows are the padded ones
     const long rb16 = pad0 / 16 + 2 * rb + hh;
@@ -708,8 +726,14 @@ int32_t launch_to_frag(hipStream_t st, const ToFragArgs& a) {
 // phases each sum a contiguous run of partials in ascending order, then the phases are added in ascending order.
 __global__ void __launch_bounds__(1024) k_reduce_cols(const float* __restrict__ partial, int nsplit, long stride,
                                                       int ncol, float* __restrict__ dest, long partial_grp_stride,
-                                                      long dest_grp_stride) {
+                                                      long dest_grp_stride, const int32_t* __restrict__ grp_ptr) {
   __shared__ float sh[16][64];
+  if (grp_ptr) {   // a partial per 32 rows of the padded row order (see ToFragArgs::cs_partial)
+    int pos0, n, pad0;
+    group_range(grp_ptr, blockIdx.y, pos0, n, pad0);
+    partial += (long)(pad0 / 32) * stride;
+    nsplit = (n + 31) / 32;
+  }
   const int cl = threadIdx.x & 63, ph = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + cl;
   const int per = (nsplit + 15) / 16;
@@ -738,9 +762,10 @@ __global__ void __launch_bounds__(1024) k_reduce_cols(const float* __restrict__ 
   }
 }
 static int32_t launch_reduce_cols(hipStream_t st, const float* partial, int nsplit, long stride, int ncol, float* dest,
-                                  int groups = 1, long partial_grp_stride = 0, long dest_grp_stride = 0) {
+                                  int groups = 1, long partial_grp_stride = 0, long dest_grp_stride = 0,
+                                  const int32_t* grp_ptr = nullptr) {
   k_reduce_cols<<<dim3((ncol + 63) / 64, groups), 1024, 0, st>>>(partial, nsplit, stride, ncol, dest, partial_grp_stride,
-                                                                 dest_grp_stride);
+                                                                 dest_grp_stride, grp_ptr);
   HGNN_LAUNCH_CHECK("k_reduce_cols");
   return HGNN_OK;
 }
@@ -782,7 +807,15 @@ __global__ void __launch_bounds__(256) k_colsum_rows(ColsumRowsArgs a, int nspli
   a.partial[((long)blockIdx.z * nsplit + blockIdx.y) * a.ncol + c] = s;
 }
 size_t colsum_rows_partial_floats(int M, int ncol, int S) {
-  return (size_t)((M + CS_ROWS - 1) / CS_ROWS + 1) * ncol * (S < 1 ? 1 : S);
+  const size_t s = S < 1 ? 1 : S;
+  const size_t rows = ((M + CS_ROWS - 1) / CS_ROWS + 1) * s, frag = (size_t)M / 32 + 8 * s + 1;   // (groups padded to 256 rows)
+  return (rows > frag ? rows : frag) * ncol;
+}
+int32_t launch_frag_colsum(hipStream_t st, const ToFragArgs& a, float* dest, long dest_grp_stride) {
+  HGNN_REQUIRE(a.cs_partial && dest, HGNN_ERR_NULLPTR, "column sums: null operand");
+  ProfScope ps(PT_COLSUM, st);
+  return launch_reduce_cols(st, a.cs_partial, (a.M + 31) / 32, a.ncol, a.ncol, dest, a.grp_ptr ? a.S : 1, 0, dest_grp_stride,
+                            a.grp_ptr);
 }
 int32_t launch_colsum_rows(hipStream_t st, const ColsumRowsArgs& a) {
   ProfScope ps(PT_COLSUM, st);
@@ -1227,7 +1260,7 @@ struct WideWs {
   float* cvec;              // [E]
   float* colpart;           // ELEM_MAX_BLOCKS x 2 x Hp (g_z2 kernel)
   float* colpart2;          // the same for the g_z1 kernel
-  float* cs_partial;        // column sums over atoms
+  float* cs_partial[2];     // column sums over atoms (g_b4, g_b3)
   float* partial;           // split partials of the atom-level weight-gradient products (side stream)
   size_t partial_floats;
   float* partial_e;         // split partials of g_W2 (caller's stream)
@@ -1253,7 +1286,8 @@ static WideWs carve_ws_w(void* p, const WideDims& d) {
   w.cvec = c.take<float>((size_t)d.E + 4);
   w.colpart = c.take<float>((size_t)ELEM_MAX_BLOCKS * 2 * d.Hp);
   w.colpart2 = c.take<float>((size_t)ELEM_MAX_BLOCKS * (1 + d.k) * d.Hp);
-  w.cs_partial = c.take<float>(colsum_rows_partial_floats(d.N, d.Hp, 1));
+  w.cs_partial[0] = c.take<float>(colsum_rows_partial_floats(d.N, d.Hp, 1));
+  w.cs_partial[1] = c.take<float>(colsum_rows_partial_floats(d.N, d.Hp, 1));
   w.partial_floats = (size_t)24 * 2 * d.Hp * d.Hp;
   w.partial = c.take<float>(w.partial_floats);
   w.partial_e_floats = (size_t)(d.Hp <= 512 ? 96 : 24) * d.Hp * d.Hp;   // narrow outputs need more splits to fill the chip
@@ -1357,14 +1391,6 @@ static int32_t wgrad_w(hipStream_t st, const WideDims& d, const char* A_T, int a
   a.tag = tag;
   return launch_fwgrad(st, a);
 }
-static int32_t colsum_w(hipStream_t st, const float* X, long ldx, const float* Z, long ldz, int mode, int M, int ncol,
-                        float* partial, float* dest) {
-  ColsumRowsArgs c;
-  c.X = X; c.ldx = ldx; c.Z = Z; c.ldz = ldz; c.mode = mode; c.M = M; c.ncol = ncol;
-  c.partial = partial; c.dest = dest;
-  return launch_colsum_rows(st, c);
-}
-
 int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
   const int k = a.k;   // edge attributes: a.attr [E, k], or d2 alone (k = 1) when a.attr is null
   const WideDims d(a.N, a.E, a.H, k);
@@ -1490,8 +1516,10 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   SideStream& ss = side_stream();
   HGNN_REQUIRE(ss.ok, HGNN_ERR_HIP, "could not create the side stream");
   hipStream_t sx = side_stream_enabled(true) ? ss.s : st;
+  // the column sums of both (g_b4, g_b3) are formed on the way
+  ToFragArgs u, t;
   {  // g_h' as R and T ([h ; M] and silu(z3) were left as T fragments by the forward pass)
-    ToFragArgs u;
+    u.cs_partial = w.cs_partial[0];
     u.X = a.g_h_out; u.ldx = H; u.M = d.N; u.Mp = d.Np; u.ncol = H; u.Cp = Hp;
     u.R = w.x_R; u.r_nkb = d.nkb; u.r_kb0 = 0;
     u.T = w.gh_T; u.t_ncb = d.ncb; u.t_cb0 = 0;
@@ -1501,14 +1529,14 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   // side: g_W4 = a3^T g_h', g_b4 = column sums of g_h'
   HGNN_TRY(wgrad_w(sx, d, s.a3_T, d.ncb, 0, d.ncb, w.gh_T, d.ncb, 0, d.ncb, d.Np, w.partial, w.partial_floats, gW + o.W4,
                    0, 0, PT_WGRAD_NODE));
-  HGNN_TRY(colsum_w(sx, a.g_h_out, H, nullptr, 0, 0, d.N, H, w.cs_partial, gW + o.b4));
+  HGNN_TRY(launch_frag_colsum(sx, u, gW + o.b4, 0));
   {  // g_a3 = g_h' W4^T
     FGemmArgs g = nn_args(w.x_R, d.nkb, d.Np / 32, w.packed, d.ncb, PT_GEMM_NODE);
     g.M = d.N; g.Cf = w.nodeA; g.ldc = Hp; g.ncol_f = Hp;
     HGNN_TRY(launch_fgemm_rows(st, g));
   }
   {  // g_z3 = g_a3 silu'(z3) as R and T
-    ToFragArgs t;
+    t.cs_partial = w.cs_partial[1];
     t.X = w.nodeA; t.ldx = Hp; t.Z = s.z3; t.ldz = Hp; t.mode = 2; t.M = d.N; t.Mp = d.Np; t.ncol = H; t.Cp = Hp;
     t.R = w.x_R; t.r_nkb = d.nkb; t.r_kb0 = 0;
     t.T = w.gz3_T; t.t_ncb = d.ncb; t.t_cb0 = 0;
@@ -1516,7 +1544,7 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   }
   HGNN_TRY(stream_after(sx, st, ss.ev[1]));
   // side: g_b3 = column sums of g_z3, g_W3 = [h ; M]^T g_z3
-  HGNN_TRY(colsum_w(sx, w.nodeA, Hp, s.z3, Hp, 2, d.N, H, w.cs_partial, gW + o.b3));
+  HGNN_TRY(launch_frag_colsum(sx, t, gW + o.b3, 0));
   HGNN_TRY(wgrad_w(sx, d, s.hM_T, 2 * d.ncb, 0, 2 * d.ncb, w.gz3_T, d.ncb, 0, d.ncb, d.Np, w.partial, w.partial_floats,
                    gW + o.W3, HH, 0, PT_WGRAD_NODE));
   {  // [g_h(a) | g_M] = g_z3 [W3a^T | W3b^T]: fp32 for the residual, bf16 for the edge gathers
@@ -1543,8 +1571,7 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   HGNN_TRY(stream_after(sx, st, ss.ev[2]));
   {  // side: g_b2, g_wx from the kernel's column sums
     ProfScope ps(PT_COLSUM, sx);
-    HGNN_TRY(launch_reduce_cols(sx, w.colpart, eg, 2 * Hp, H, gW + o.b2));
-    HGNN_TRY(launch_reduce_cols(sx, w.colpart + Hp, eg, 2 * Hp, H, gW + o.wx));
+    HGNN_TRY(launch_reduce_cols(sx, w.colpart, eg, 2 * Hp, H, gW + o.b2, 2, Hp, o.wx - o.b2));
   }
   // g_W2 = a1^T g_z2 fills the chip by itself: it stays on the caller's stream, with a partial buffer of its own
   HGNN_TRY(wgrad_w(st, d, s.a1_T, d.ncb, 0, d.ncb, w.gz2_T, d.ncb, 0, d.ncb, d.Ep, w.partial_e, w.partial_e_floats,
