@@ -215,37 +215,68 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
         for (int v = 0; v < 16; ++v)
           stg[(wi * 32 + 8 * (v >> 2) + 4 * g + (v & 3)) * 128 + wj * 64 + j * 32 + x] = acc[i][j][v];
       __syncthreads();
+      // the rows' places and residuals are asked for together, before the first store (the compiler cannot move a load
+      // across a store, so with each next to its use the eight rows were a chain of eight memory latencies)
+      long rows[8];
+      float res1[8][4], res2[8][4];
+#pragma unroll
+      for (int rr = 0; rr < 8; ++rr) {
+        const int lrow = rr * 8 + r8;
+        const int prow = (i0 + (lrow >> 5) * WI + i) * 32 + (lrow & 31);
+        rows[rr] = prow < mvalid ? prow : mvalid - 1;
+      }
+      if (p.row_idx) {   // scatter to the caller's rows
+#pragma unroll
+        for (int rr = 0; rr < 8; ++rr) rows[rr] = p.row_idx[pos0 + rows[rr] - pad0];
+      }
+      auto residual = [&](const float* base, long ld, float (&o)[8][4]) {
+        if (p.vec == 4 && col + 4 <= p.ncol_f) {
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr) {
+            const float4 t = *reinterpret_cast<const float4*>(base + rows[rr] * ld + col);
+            o[rr][0] = t.x; o[rr][1] = t.y; o[rr][2] = t.z; o[rr][3] = t.w;
+          }
+        } else if (p.vec >= 2 && col + 4 <= p.ncol_f) {
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr)
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2) {
+              const float2 t = *reinterpret_cast<const float2*>(base + rows[rr] * ld + col + 2 * h2);
+              o[rr][2 * h2] = t.x; o[rr][2 * h2 + 1] = t.y;
+            }
+        } else {
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) o[rr][t] = col + t < p.ncol_f ? base[rows[rr] * ld + col + t] : 0.f;
+        }
+      };
+      if (p.Cf && p.r1) residual(p.r1, p.ld1, res1);
+      if (p.Cf && p.r2) residual(p.r2, p.ld2, res2);
 #pragma unroll
       for (int rr = 0; rr < 8; ++rr) {
         const int lrow = rr * 8 + r8;
         const int prow = (i0 + (lrow >> 5) * WI + i) * 32 + (lrow & 31);
         if (prow < mvalid && col_ok) {
-          const long row = p.row_idx ? p.row_idx[pos0 + prow - pad0] : prow;   // scatter to the caller's rows
+          const long row = rows[rr];
           const float4 sv = *reinterpret_cast<const float4*>(&stg[lrow * 128 + c4]);
           float val[4] = {sv.x + bias4[0], sv.y + bias4[1], sv.z + bias4[2], sv.w + bias4[3]};
           if (p.Cf && col < p.ncol_f) {
             float* cp = p.Cf + row * p.ldc + col;
-            const float* p1 = p.r1 ? p.r1 + row * p.ld1 + col : nullptr;
-            const float* p2 = p.r2 ? p.r2 + row * p.ld2 + col : nullptr;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              if (p.r1) val[t] += res1[rr][t];
+              if (p.r2) val[t] += res2[rr][t];
+            }
             if (p.vec == 4 && col + 4 <= p.ncol_f) {
-              if (p1) { const float4 t = *reinterpret_cast<const float4*>(p1); val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w; }
-              if (p2) { const float4 t = *reinterpret_cast<const float4*>(p2); val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w; }
               *reinterpret_cast<float4*>(cp) = make_float4(val[0], val[1], val[2], val[3]);
             } else if (p.vec >= 2 && col + 4 <= p.ncol_f) {
 #pragma unroll
-              for (int h2 = 0; h2 < 2; ++h2) {
-                if (p1) { const float2 t = *reinterpret_cast<const float2*>(p1 + 2 * h2); val[2 * h2] += t.x; val[2 * h2 + 1] += t.y; }
-                if (p2) { const float2 t = *reinterpret_cast<const float2*>(p2 + 2 * h2); val[2 * h2] += t.x; val[2 * h2 + 1] += t.y; }
-                *reinterpret_cast<float2*>(cp + 2 * h2) = make_float2(val[2 * h2], val[2 * h2 + 1]);
-              }
+              for (int h2 = 0; h2 < 2; ++h2) *reinterpret_cast<float2*>(cp + 2 * h2) = make_float2(val[2 * h2], val[2 * h2 + 1]);
             } else {
 #pragma unroll
               for (int t = 0; t < 4; ++t)
-                if (col + t < p.ncol_f) {
-                  if (p1) val[t] += p1[t];
-                  if (p2) val[t] += p2[t];
-                  cp[t] = val[t];
-                }
+                if (col + t < p.ncol_f) cp[t] = val[t];
             }
           }
           if (p.Cb) {   // all columns of the tile (the pitch is a multiple of 128)
