@@ -111,8 +111,8 @@ inline DsumFix edge_bwd_dsum_fix(const EdgeBwdArgs& a) { return DsumFix{a.row_pt
 // 32-edge units nearly every row of 30 edges left partials: 160 MB of traffic per layer on config 4).
 constexpr int DSUM_UNIT = 64;
 inline size_t edge_bwd_dpart_floats(int64_t E, int H) { return (size_t)((E + DSUM_UNIT - 1) / DSUM_UNIT) * 2 * H; }
-// the operand types and widths for which k_edge_bwd can form g_P itself (an edge's g_z1 is 128 words there)
-inline bool edge_bwd_sums_dst(int H, bool bf16) { return edge_pairs(H, bf16) || (!bf16 && H == 128); }
+// the operand types and widths for which k_edge_bwd can form g_P itself (an edge's g_z1 is at most 128 words there)
+inline bool edge_bwd_sums_dst(int H, bool bf16) { return edge_pairs(H, bf16) || H <= 128; }
 size_t edge_bwd_attrpart_floats(int H);
 size_t edge_bwd_colpart_floats(int H);
 int32_t launch_edge_bwd(hipStream_t st, int H, bool bf16, const EdgeBwdArgs& a);

@@ -415,7 +415,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   // edge part: g_z2 -> (x W2^T) -> g_z1 with the per-column sums. The fused edge kernel fills
   // every CU by itself, so the side stream is drained first instead of competing with it.
   HGNN_TRY(stream_after(st, sx, ss.ev[5]));
-  // With bf16 pairs, or fp32 operands at H = 128, the reverse edge kernel also sums g_z1 per destination (out of the
+  // Except with fp32 operands at H = 256 the reverse edge kernel also sums g_z1 per destination (out of the
   // tile it holds in LDS). The gradient with respect to d2 (on request: the dot of every g_z1 row with the d2 row of
   // W1) is then formed by the source-sorted pass, which reads every edge's row exactly once as well.
   // HGNN_DSUM_IN_KERNEL=0 keeps the separate destination-sorted pass (for comparing the two).

@@ -141,6 +141,13 @@ def test_layer_row_lengths_with_destination_sums_in_the_edge_kernel(pattern, H, 
     _run_layer(N=N, E=E, H=H, dtype=dtype, seed=11, lengths=lengths)
 
 
+# The same rows in the other layers whose edges are at most 128 words (H = 64: two of the four wavefronts walk the tile)
+@pytest.mark.parametrize("H,dtype", [(64, "f32"), (64, "bf16"), (128, "bf16")])
+@pytest.mark.parametrize("pattern", ["mixed", "aligned", "long", "ones", "one_row", "tail_rows_empty"])
+def test_layer_row_lengths_with_destination_sums_of_narrow_layers(pattern, H, dtype, monkeypatch):
+    test_layer_row_lengths_with_destination_sums_in_the_edge_kernel(pattern, H, dtype, monkeypatch)
+
+
 @pytest.mark.parametrize("H,dtype,E", [(64, "f32", 1000), (64, "bf16", 4097), (128, "f32", 8191), (128, "bf16", 8193),
                                        (256, "f32", 4095)])
 def test_layer_other_modes_edge_counts(H, dtype, E):
