@@ -67,8 +67,12 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
   int ti, tj, split = 0;
   if (EPI == EPI_PART) {
     const int tiles = ((p.nI + C::TI - 1) / C::TI) * nTj;   // a last row tile may stick out past nI
-    const int t = q % tiles;
-    split = (q / tiles) * 8 + xcd;     // the launcher makes the split count a multiple of 8
+    int t = q % tiles;
+    split = (q / tiles) * 8 + xcd;     // the launcher makes the split count a multiple of 8,
+    if (p.grp_ptr) {                   // or there are groups, whose tiles fill the chip with few splits of each
+      split = blockIdx.x / tiles;
+      t = blockIdx.x % tiles;
+    }
     ti = t / nTj;
     tj = t % nTj;
   } else {
@@ -79,7 +83,7 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
   int i0 = ti * C::TI;
   const int j0 = tj * C::TJ;
   const int grp = blockIdx.z;
-  int mvalid = p.M, pos0 = 0, pad0 = 0, kbase = 0, knum = p.nkb;
+  int mvalid = p.M, pos0 = 0, pad0 = 0, kbase = 0, knum = p.nkb, kper = p.kper;
   if (p.grp_ptr) {
     int n;
     group_range(p.grp_ptr, grp, pos0, n, pad0);
@@ -87,14 +91,15 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
     if (EPI == EPI_PART) {
       kbase = pad0 / 16;
       knum = npad / 16;
+      kper = ((knum + p.nsplit - 1) / p.nsplit + 2 * C::KC - 1) / (2 * C::KC) * (2 * C::KC);   // the group's own rows, in whole pairs of steps
     } else {
       if (ti * C::TI * 32 >= npad) return;   // uniform over the workgroup, before any barrier
       i0 += pad0 / 32;
       mvalid = pad0 + n;
     }
   }
-  const int kbeg = kbase + split * p.kper;
-  const int kend = kbeg + p.kper < kbase + knum ? kbeg + p.kper : kbase + knum;
+  const int kbeg = kbase + split * kper;
+  const int kend = kbeg + kper < kbase + knum ? kbeg + kper : kbase + knum;
   const char* Bg = p.B + (long)grp * p.b_grp_stride;
 
   // pass s copies fragment f = 4 s + wave of the step: first the KC x TI fragments of A, then the KC x TJ of B
@@ -317,7 +322,7 @@ static int32_t launch_fgemm_t(hipStream_t st, const FGemmArgs& a) {
                    a.kper % (2 * C::KC) == 0 && a.kper > 0,
                HGNN_ERR_BAD_SHAPE, "fragment GEMM: %d x %d blocks, %d contraction blocks do not tile", a.nI, a.nJ, a.nkb);
   if (a.nI == 0 || a.nJ == 0) return HGNN_OK;
-  HGNN_REQUIRE(EPI == EPI_PART ? (a.nsplit % 8 == 0 && (long)a.nsplit * a.kper >= a.nkb) : (a.nsplit == 1 && a.kper == a.nkb),
+  HGNN_REQUIRE(EPI == EPI_PART ? ((a.nsplit % 8 == 0 || a.grp_ptr) && (long)a.nsplit * a.kper >= a.nkb) : (a.nsplit == 1 && a.kper == a.nkb),
                HGNN_ERR_BAD_SHAPE, "fragment GEMM: bad split of the contraction");
   const int groups = a.grp_ptr ? a.S : 1;
   const long nTi = (a.nI + C::TI - 1) / C::TI, nTj = (a.nJ + C::TJ - 1) / C::TJ;
@@ -1366,8 +1371,16 @@ int32_t launch_fwgrad(hipStream_t st, const FWgradArgs& a) {
   const long tiles = big ? big_tiles : (long)(a.nI / 4) * (a.nJ / 4) * groups;
   long want = ((big ? 2L : 3L) * num_cus() + tiles - 1) / tiles;
   if (want > cap) want = cap;
-  want = want / 8 * 8;   // a multiple of 8: one XCD per residue (see k_fgemm)
-  if (want < 8) want = 8;
+  if (a.grp_ptr) {
+    // Rows are dealt to a group's splits in the kernel (the host only knows that all rows could be in one group), and no
+    // split is made of less than 256 of them: every split writes and reads back a whole output block. 5 groups, widths
+    // 866 and 889: 128 graphs 22 + 30 us (products + sums of the partials) -> 10 + 15, 7,734 atoms 73 + 30 -> 41 + 20.
+    if (want > a.rows / 256) want = a.rows / 256;
+    if (want < 1) want = 1;
+  } else {
+    want = want / 8 * 8;   // a multiple of 8: one XCD per residue (see k_fgemm)
+    if (want < 8) want = 8;
+  }
   HGNN_REQUIRE(cap >= 8, HGNN_ERR_WORKSPACE_TOO_SMALL, "weight-gradient partials do not fit the workspace");
   int kper = (int)((g.nkb + want - 1) / want);
   kper = (kper + 3) / 4 * 4;   // whole pairs of steps
