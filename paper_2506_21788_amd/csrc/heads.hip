@@ -185,25 +185,23 @@ __global__ void k_pool_bwd(int N, int G, int H, int mode, const int32_t* __restr
 // ---------------------------------------------------------------------------------------------
 inline bool any_H(int H) { return H >= 1 && H <= 1024; }
 
-__global__ void k_embed_fwd_any(int N, int H, const int32_t* __restrict__ Z, const float* __restrict__ emb,
-                                float* __restrict__ h) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)N * H) return;
-  const int64_t i = idx / H;
-  const int c = (int)(idx - i * H);
+__global__ void k_embed_fwd_any(int H, const int32_t* __restrict__ Z, const float* __restrict__ emb, float* __restrict__ h) {
+  const int i = blockIdx.x;   // one workgroup per atom
   int z = Z[i];
   z = z < 0 ? 0 : (z > HGNN_ZMAX ? HGNN_ZMAX : z);
-  h[idx] = emb[(long)z * H + c];
+  for (int c = threadIdx.x; c < H; c += blockDim.x) h[(size_t)i * H + c] = emb[(long)z * H + c];
 }
 
 // block (z, chunk): the atoms of the chunk with Z == z are listed in ascending order (each thread scans 8 consecutive
-// atoms, an exclusive scan over the threads places its matches), then every column is summed over that list
+// atoms, an exclusive scan over the threads places its matches), then every column is summed over that list, its rows asked
+// for eight at a time (blockIdx.z: 256 columns). 7,734 atoms of 866 columns: 66 -> 19 us against one workgroup for all columns,
+// a scan by one thread and one row at a time
 __global__ void __launch_bounds__(256)
 k_embed_bwd_part_any(int N, int H, const int32_t* __restrict__ Z, const float* __restrict__ g_h,
                      float* __restrict__ part /*[nchunk][ZMAX+1][H]*/) {
   static_assert(EMB_CHUNK == 2048, "8 atoms per thread");
   __shared__ int list[EMB_CHUNK];
-  __shared__ int cnt[257];
+  __shared__ int wtot[4];
   const int z = blockIdx.x, chunk = blockIdx.y, tid = threadIdx.x;
   const int lo = chunk * EMB_CHUNK;
   const int hi = lo + EMB_CHUNK < N ? lo + EMB_CHUNK : N;
@@ -215,23 +213,35 @@ k_embed_bwd_part_any(int N, int H, const int32_t* __restrict__ Z, const float* _
     m[u] = i < hi && Z[i] == z;
     n += m[u] ? 1 : 0;
   }
-  cnt[tid + 1] = n;
-  if (tid == 0) cnt[0] = 0;
+  int incl = n;   // scan over the wavefront, then over the four wavefronts
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int t = __shfl_up(incl, d);
+    if ((tid & 63) >= d) incl += t;
+  }
+  if ((tid & 63) == 63) wtot[tid >> 6] = incl;
   __syncthreads();
-  if (tid == 0)
-    for (int k = 1; k <= 256; ++k) cnt[k] += cnt[k - 1];
-  __syncthreads();
-  int o = cnt[tid];
+  int o = incl - n, total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < (tid >> 6)) o += wtot[w];
+    total += wtot[w];
+  }
 #pragma unroll
   for (int u = 0; u < 8; ++u)
     if (m[u]) list[o++] = lo + tid * 8 + u;
   __syncthreads();
-  const int total = cnt[256];
-  for (int c = tid; c < H; c += 256) {
-    float acc = 0.f;
-    for (int k = 0; k < total; ++k) acc += g_h[(size_t)list[k] * H + c];
-    part[((size_t)chunk * (HGNN_ZMAX + 1) + z) * H + c] = acc;
+  const int c = blockIdx.z * 256 + tid;
+  if (c >= H) return;
+  float acc = 0.f;
+  for (int k = 0; k < total; k += 8) {   // (the last batch clamped, then left out)
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = g_h[(size_t)list[k + u < total ? k + u : total - 1] * H + c];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += k + u < total ? v[u] : 0.f;
   }
+  part[((size_t)chunk * (HGNN_ZMAX + 1) + z) * H + c] = acc;
 }
 
 // block (graph, 64-column slab): 4 row phases take every fourth atom, then the phases are added in order
@@ -253,18 +263,19 @@ k_pool_fwd_any(int H, int mode, const int32_t* __restrict__ graph_off, const flo
   }
 }
 
-__global__ void k_pool_bwd_any(int N, int G, int H, int mode, const int32_t* __restrict__ graph_off,
+// one workgroup per atom: its graph is found once (by scalar loads) and not by every element (7,734 atoms of 866 columns:
+// 43 -> 22 us)
+__global__ void k_pool_bwd_any(int G, int H, int mode, const int32_t* __restrict__ graph_off,
                                const float* __restrict__ g_p, float* __restrict__ g_h, int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)N * H) return;
-  const int i = (int)(idx / H);
-  const int c = (int)(idx - (int64_t)i * H);
+  const int i = blockIdx.x;
   const int g = find_graph_of_atom(graph_off, G, i);
   const int n = graph_off[g + 1] - graph_off[g];
   const float sc = (mode == HGNN_POOL_MEAN) ? 1.0f / (float)n : 1.0f;
-  float v = g_p[(size_t)g * H + c] * sc;
-  if (accumulate) v += g_h[idx];
-  g_h[idx] = v;
+  for (int c = threadIdx.x; c < H; c += blockDim.x) {
+    float v = g_p[(size_t)g * H + c] * sc;
+    if (accumulate) v += g_h[(size_t)i * H + c];
+    g_h[(size_t)i * H + c] = v;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -567,9 +578,9 @@ static HeadSaved carve_head_saved(void* p, int N, int G, int Hh) {
 }
 struct HeadWs {
   void* packed;  // [S][2] blocks
-  float *g_ze, *g_zf, *gq, *partial;
-  // reverse pass: partials of the two column sums, of the weights' sum and of the weight gradient of each branch (energy, force); they all
-  // live until the pass's one reduction launch
+  float *g_ze, *g_zf, *gq;
+  // reverse pass: partials of the two column sums, of the sum of their weights and of the weight gradient of each branch
+  // (energy, force); they all live until the pass's one reduction launch
   float *pcs[2][2], *pws[2], *pwg[2];
   size_t bytes;
 };
@@ -580,10 +591,6 @@ static HeadWs carve_head_ws(void* p, int N, int G, int H, int Hh, int S, bool bf
   w.g_ze = c.take<float>((size_t)G * Hh);
   w.g_zf = c.take<float>((size_t)N * Hh);
   w.gq = c.take<float>((size_t)N + 1);
-  const int64_t mx = N > G ? N : G;
-  size_t pf = wgrad_partial_floats(H, mx, 1, S);
-  size_t cf = colsum_partial_floats(H, mx, S);
-  w.partial = c.take<float>(pf > cf ? pf : cf);
   for (int br = 0; br < 2; ++br) {
     const int64_t M = br == 0 ? G : N;
     w.pcs[br][0] = c.take<float>(colsum_partial_floats(H, M, S));
@@ -612,6 +619,9 @@ using namespace hgnn;
 // is the one-hidden-layer case of the deep heads (same buffer layout)
 static bool heads_need_fragment_path(int H, int Hh) { return !valid_H(H) || Hh != H; }
 
+// threads of a workgroup that walks the H columns of one row
+static int row_threads(int H) { return H >= 256 ? 256 : (H + 63) / 64 * 64; }
+
 extern "C" int32_t hgnn_embed_fwd(void* stream, int32_t N, int32_t H, const int32_t* Z, const float* emb, float* h) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   HGNN_REQUIRE(N >= 0 && any_H(H), HGNN_ERR_BAD_SHAPE, "embed_fwd: bad N or H");
@@ -619,7 +629,7 @@ extern "C" int32_t hgnn_embed_fwd(void* stream, int32_t N, int32_t H, const int3
   HGNN_REQUIRE(Z && emb && h, HGNN_ERR_NULLPTR, "embed_fwd: null pointer");
   ProfScope ps(PT_EMBED, st);
   if (valid_H(H)) k_embed_fwd<<<nb64((int64_t)N * (H / 4), 256), 256, 0, st>>>(N, H, Z, emb, h);
-  else k_embed_fwd_any<<<nb64((int64_t)N * H, 256), 256, 0, st>>>(N, H, Z, emb, h);
+  else k_embed_fwd_any<<<N, row_threads(H), 0, st>>>(H, Z, emb, h);
   HGNN_LAUNCH_CHECK("k_embed_fwd");
   return HGNN_OK;
 }
@@ -640,7 +650,7 @@ static int32_t embed_bwd_launch(hipStream_t st, int32_t N, int32_t H, const int3
   ProfScope ps(PT_EMBED, st);
   if (nchunk > 0) {
     if (valid_H(H)) k_embed_bwd_part<<<dim3(HGNN_ZMAX + 1, nchunk), 1024, 0, st>>>(N, H, Z, g_h, part);
-    else k_embed_bwd_part_any<<<dim3(HGNN_ZMAX + 1, nchunk), 256, 0, st>>>(N, H, Z, g_h, part);
+    else k_embed_bwd_part_any<<<dim3(HGNN_ZMAX + 1, nchunk, (H + 255) / 256), 256, 0, st>>>(N, H, Z, g_h, part);
     HGNN_LAUNCH_CHECK("k_embed_bwd_part");
   }
   k_embed_bwd_sum<<<((HGNN_ZMAX + 1) * H + 255) / 256, 256, 0, st>>>(nchunk, H, part, g_emb);
@@ -724,7 +734,7 @@ extern "C" int32_t hgnn_pool_by_graph_bwd(void* stream, int32_t N, int32_t G, in
   HGNN_REQUIRE(G > 0 && graph_off && g_p && g_h, HGNN_ERR_NULLPTR, "pool_bwd: null pointer");
   ProfScope ps(PT_POOL, st);
   if (valid_H(H)) k_pool_bwd<<<nb64((int64_t)N * (H / 4), 256), 256, 0, st>>>(N, G, H, mode, graph_off, g_p, g_h, accumulate);
-  else k_pool_bwd_any<<<nb64((int64_t)N * H, 256), 256, 0, st>>>(N, G, H, mode, graph_off, g_p, g_h, accumulate);
+  else k_pool_bwd_any<<<N, row_threads(H), 0, st>>>(G, H, mode, graph_off, g_p, g_h, accumulate);
   HGNN_LAUNCH_CHECK("k_pool_bwd");
   return HGNN_OK;
 }
