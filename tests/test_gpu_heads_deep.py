@@ -116,3 +116,10 @@ def test_deep_heads_and_wide_layer_error_paths():
     assert code(lambda: B.mp_layer_fwd(N, 0, 300, B.BF16, 1.0, row_ptr, None, None, None, None, h300, v, W, out, f,
                                        torch.empty(lsv, dtype=torch.uint8, device="cuda"),
                                        torch.empty(64, dtype=torch.uint8, device="cuda"))) == -6
+
+
+# The rows of a source are split by their own number in the weight gradients: one source with all rows, many with few, one
+# with most of them
+@pytest.mark.parametrize("G,atoms,S,sources", [(60, (20, 30), 2, (1,)), (260, (1, 2), 3, None), (40, (50, 60), 5, (0, 0, 0, 0, 3))])
+def test_deep_heads_rows_unevenly_over_sources(G, atoms, S, sources):
+    _run(G, atoms, H=100, Hh=130, D=2, S=S, seed=G + S, sources=sources)

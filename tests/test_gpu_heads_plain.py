@@ -62,3 +62,24 @@ def test_plain_heads_match_the_oracle(sizes, S, sources, H, dtype):
     print(f"heads G={G} N={N} H={H} S={S} {dtype}", f"{max(errs.values()):.1e}", flush=True)
     for k, e in errs.items():
         assert e <= TOL[dtype]["fwd" if k in ("energy", "force") else "grad"], (k, e)
+
+
+# the embedding at widths of one and several 256-column slabs: chunks of 2,048 atoms, lists of matches around the batches of eight
+@pytest.mark.parametrize("N,H,elements", [(1, 300, 1), (9, 257, 1), (2049, 520, 1), (5000, 24, 40), (4096, 866, 3)])
+def test_embedding_at_other_widths(N, H, elements):
+    import torch
+    from paper_2506_21788_amd import binding as B
+    rng = np.random.default_rng(N + H)
+    Z = rng.choice(rng.permutation(B.ZMAX)[:elements] + 1, size=N).astype(np.int32)
+    emb = rng.standard_normal((B.ZMAX + 1, H)).astype(np.float32)
+    g = rng.standard_normal((N, H)).astype(np.float32)
+    tZ, te, tg = (torch.as_tensor(a).cuda() for a in (Z, emb, g))
+    h, ge = torch.full_like(tg, float("nan")), torch.full_like(te, float("nan"))
+    B.embed_fwd(N, H, tZ, te, h)
+    ws = torch.empty(B.embed_bwd_workspace_bytes(N, H), dtype=torch.uint8, device="cuda")
+    B.embed_bwd(N, H, tZ, tg, ge, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(h.cpu().numpy(), emb[Z])
+    want = np.zeros((B.ZMAX + 1, H))
+    np.add.at(want, Z, g.astype(np.float64))
+    assert relerr(ge.cpu().numpy(), want) <= TOL["f32"]["grad"]
