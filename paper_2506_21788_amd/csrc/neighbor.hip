@@ -448,13 +448,9 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
   __shared__ int s_at;
   const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = p.graph_off[g], hi = p.graph_off[g + 1];
-  if (bad_range(g, p.G, p.N, lo, hi)) {              // reported by the host; nothing is searched
-    if (tid == 0) {
-      atomicOr(p.status, ST_BAD_OFFSETS);
-      no_bins(&p.meta[g], 0, g);
-    }
-    return;
-  }
+  // With a bad offset anywhere (found by the launch before) no graph is binned: graphs that overlap would share bins, and
+  // count on top of one another's record places.
+  if (*p.status & ST_BAD_OFFSETS) return;
   const bool periodic = (p.pbc != nullptr) && (p.cell != nullptr) && (p.pbc[g] != 0);
   float mn[3] = {3.0e38f, 3.0e38f, 3.0e38f}, mx[3] = {-3.0e38f, -3.0e38f, -3.0e38f};
   if (!periodic) {
@@ -535,8 +531,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       if (b < nbins) {
         p.bin_start[off + b] = ex;
         if (in_lds) hist[b] = ex; else cnt[b] = ex;   // from here on: the bin's next free record
-        for (int k = 0; k < c[u]; k += p.home, ++at)
-          if (at < p.N) p.list[at] = make_int2(off + b, k);   // (more only if bad offsets make graphs overlap)
+        for (int k = 0; k < c[u]; k += p.home, ++at) p.list[at] = make_int2(off + b, k);
       }
       ex += c[u];
     }
@@ -1144,9 +1139,18 @@ static NeighWs carve_neigh(void* ws, int N, int G) {
   w.bytes = c.used();
   return w;
 }
-__global__ void k_zero4(int4* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = make_int4(0, 0, 0, 0);
+// Clears the counters; the first workgroup checks every graph's offsets meanwhile, and starts status[0] (the first of the
+// cleared words) with what it finds. n > 0.
+__global__ void __launch_bounds__(256)
+k_clear_and_check(int4* p, int64_t n, int N, int G, const int32_t* __restrict__ graph_off) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  int bad = 0;
+  if (blockIdx.x == 0) {
+#pragma unroll 4
+    for (int g = threadIdx.x; g < G; g += 256) bad |= bad_range(g, G, N, graph_off[g], graph_off[g + 1]) ? 1 : 0;
+    bad = __syncthreads_or(bad);
+  }
+  if (i < n) p[i] = make_int4(i == 0 && bad ? ST_BAD_OFFSETS : 0, 0, 0, 0);
 }
 
 static inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
@@ -1201,12 +1205,13 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
   MailSlot mail;
   HGNN_REQUIRE(mail.ok(), HGNN_ERR_HIP, "could not allocate the pinned result slot");
   // Everything below is enqueued in one go: a bad offset or cell is recorded in status[0], leaves every later
-  // kernel with in-range (if meaningless) indices, keeps the search from running, and is reported after the one
-  // wait at the end.
+  // kernel with in-range (if meaningless) indices or without work, keeps the search from running, and is reported after
+  // the one wait at the end.
   {
     ProfScope ps(PT_NEIGH_SETUP, st);
-    k_zero4<<<nblk(w.nzeroed / 4, 256), 256, 0, st>>>(reinterpret_cast<int4*>(w.zeroed), w.nzeroed / 4);
-    HGNN_LAUNCH_CHECK("k_zero4");
+    k_clear_and_check<<<nblk(w.nzeroed / 4, 256), 256, 0, st>>>(reinterpret_cast<int4*>(w.zeroed), w.nzeroed / 4, N, G,
+                                                                graph_off);
+    HGNN_LAUNCH_CHECK("k_clear_and_check");
     const int home = home_atoms(N);
     if (N <= BIN_GRAPHS_MAX) {
       const BinArgs a = {N, G, pos, graph_off, cell, pbc, rc, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt, w.bin_start,

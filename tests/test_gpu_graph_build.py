@@ -87,3 +87,28 @@ def test_routing_plan_sizes(G, S):
     ag = np.repeat(np.arange(G), sizes)
     assert np.array_equal(got["atom_graph"], ag)
     assert np.array_equal(got["grp_atom_ptr"], np.searchsorted(src[ag][got["atom_perm"]], np.arange(S + 1)))
+
+
+@pytest.mark.parametrize("off", [[0, 1, 0, 1], [0, 1, 0, 1, 0, 1, 0, 1], [0, 1, 1, 0, 1], [0, 1, 2], [-1, 1], [0, 0], [1, 1]])
+def test_overlapping_sparse_graphs_are_refused(off):
+    """Offsets (in units of the batch) that make graphs overlap, each of them with more bins than fit the LDS: refused,
+    with nothing stored outside the workspace, and the workspace serves the next batch."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+    print("overlapping sparse graphs", off, flush=True)
+    rng = np.random.default_rng(5)
+    N, G, rc = 1300, len(off) - 1, 2.85
+    b = concat_graphs([(rng.uniform(0, 60.0, (N, 3)).astype(np.float32), np.ones(N, np.int32))])
+    pos = torch.as_tensor(b.pos).cuda()
+    need, guard = B.radius_graph_workspace_bytes(N, G), 1 << 20
+    ws = torch.full((need + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    row_ptr = torch.full((N + 65,), -7, dtype=torch.int32, device="cuda")
+    with pytest.raises(B.HgnnError) as e:
+        B.radius_graph_count(N, G, pos, torch.tensor(off, dtype=torch.int32, device="cuda") * N, None, None, rc, ws, row_ptr)
+    assert e.value.code == -3      # HGNN_ERR_BAD_OFFSETS
+    assert bool((ws[need:] == 0x5A).all()) and bool((row_ptr[N + 1:] == -7).all())
+    want = oracle.radius_graph(b.pos, b.graph_off, b.cell, b.pbc, rc)
+    good = torch.tensor([0, N] + [N] * (G - 1), dtype=torch.int32, device="cuda")
+    assert B.radius_graph_count(N, G, pos, good, None, None, rc, ws, row_ptr) == want["E"]
+    assert np.array_equal(row_ptr[:N + 1].cpu().numpy(), want["row_ptr"])
+    assert bool((ws[need:] == 0x5A).all())
