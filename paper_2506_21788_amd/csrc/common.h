@@ -52,7 +52,8 @@ inline hipError_t wait_stream(hipStream_t st) {
 }
 
 // What a device kernel hands to a waiting host call: one slot of pinned host memory, written by the kernel that has the
-// result. The host polls the slot, so there is no copy kernel and no wait for the end of the stream behind it.
+// result, so there is no copy behind it. The call waits for the stream all the same: it is documented to leave with
+// every output written and every input read.
 struct HostMail {
   long long value;
   int status;
@@ -75,7 +76,7 @@ class MailSlot {
   MailSlot& operator=(const MailSlot&) = delete;
   bool ok() const { return m_ != nullptr; }
   HostMail* dev() const { return m_; }
-  hipError_t wait(hipStream_t st);   // until the slot is posted; an error if the stream fails or drains without it
+  hipError_t wait(hipStream_t st);   // until the stream has drained; an error if it fails, or drains with nothing posted
   long long value() const { return m_->value; }
   int status() const { return m_->status; }
 

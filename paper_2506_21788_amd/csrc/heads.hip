@@ -286,7 +286,6 @@ __global__ void k_pool_bwd_any(int G, int H, int mode, const int32_t* __restrict
 // wavefronts take 64 graphs each of a chunk of 1024; a wavefront ranks its graphs source by source with ballots and
 // lane scans, leaves its totals per source in LDS, and adds the totals of the wavefronts before it (643 graphs: 54 us
 // with one wavefront walking all graphs, 10 us with sixteen). More sources: one wavefront walks the graphs.
-// The caller waits for nothing but the check of the source ids, which is posted as soon as it is known.
 constexpr int PLAN_FEW = 64;
 __global__ void __launch_bounds__(1024)
 k_plan_graphs(int G, int S, const int32_t* __restrict__ graph_off, const int32_t* __restrict__ source_id, PlanView v,

@@ -173,7 +173,7 @@ int32_t exclusive_scan_i32(hipStream_t st, const int32_t* in, int32_t* out, int6
 // workgroups: each adds up everything in front of its own 4,096 values before it scans them. That is n^2 / 8192 reads
 // from the L2 (3 MB at n = 80,000), which up to SCAN_PAIR_MAX cost less than the two further launches of the block-sum
 // form (7,105 atoms: 2 x 8.9 us by one walking workgroup -> 5 us; 80,000: 6 launches of 4.5 us -> 7 us). The last
-// workgroup of the degrees also posts the result of the counting call to the host.
+// workgroup of the degrees, which has the total, also leaves the result of the counting call for the host.
 constexpr int64_t SCAN_PAIR_MAX = 131072;
 constexpr int SP_BLK = 4096;
 __global__ void __launch_bounds__(1024)

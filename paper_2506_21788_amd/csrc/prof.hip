@@ -44,15 +44,10 @@ MailSlot::~MailSlot() {
 }
 
 hipError_t MailSlot::wait(hipStream_t st) {
-  for (;;) {
-    for (int k = 0; k < 256; ++k)
-      if (__atomic_load_n(&m_->posted, __ATOMIC_ACQUIRE)) return hipSuccess;
-    const hipError_t e = hipStreamQuery(st);
-    if (e == hipErrorNotReady) continue;
-    if (e != hipSuccess) return e;
-    // the stream has drained: the slot was posted before that, or the kernel that posts it did not run
-    return __atomic_load_n(&m_->posted, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
-  }
+  const hipError_t e = wait_stream(st);
+  if (e != hipSuccess) return e;
+  // the stream has drained: the slot was posted before that, or the kernel that posts it did not run
+  return __atomic_load_n(&m_->posted, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
 }
 
 namespace {

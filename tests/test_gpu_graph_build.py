@@ -112,3 +112,42 @@ def test_overlapping_sparse_graphs_are_refused(off):
     assert B.radius_graph_count(N, G, pos, good, None, None, rc, ws, row_ptr) == want["E"]
     assert np.array_equal(row_ptr[:N + 1].cpu().numpy(), want["row_ptr"])
     assert bool((ws[need:] == 0x5A).all())
+
+
+def test_counting_and_routing_leave_a_drained_stream():
+    """Both calls are documented to synchronise: at their return nothing is left to run, on whatever stream the results
+    are read next. The routing of 40 million atoms takes a fraction of a millisecond after the source ids are checked."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+    other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+    N, G, S = 40_000_000, 2, 2
+    print("routing plan", N, G, S, flush=True)
+    off, src = torch.tensor([0, N // 2, N], dtype=torch.int32).cuda(), torch.tensor([1, 0], dtype=torch.int32).cuda()
+    plan = torch.full((B.multihead_plan_ints(N, G, S),), -7, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(mine):
+        B.multihead_plan(N, G, S, off, src, plan)
+        assert mine.query()
+    with torch.cuda.stream(other):
+        f = B.plan_fields(plan, N, G, S)
+        assert f["atom_perm"][[0, -1]].tolist() == [N // 2, N // 2 - 1] and f["atom_graph"][[0, -1]].tolist() == [0, 1]
+        assert int(f["atom_perm"].min()) == 0
+    del plan, f
+    for N in (131072, 131073):          # degrees scanned by one launch, or by block sums
+        print("counting", N, flush=True)
+        pos = torch.zeros((N, 3), device="cuda")
+        off = np.arange(0, N + 1, 2, dtype=np.int32)
+        off[-1] = N                     # pairs of atoms on one place, and an odd atom joins the last
+        sizes, G = np.diff(off), len(off) - 1
+        want = torch.as_tensor(np.concatenate([[0], np.cumsum(np.repeat(sizes - 1, sizes))]).astype(np.int32)).cuda()
+        off = torch.as_tensor(off).cuda()
+        ws = torch.zeros(B.radius_graph_workspace_bytes(N, G), dtype=torch.uint8, device="cuda")
+        row_ptr = torch.full((N + 1,), -7, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        for _ in range(20):
+            with torch.cuda.stream(mine):
+                row_ptr.fill_(-7)
+                E = B.radius_graph_count(N, G, pos, off, None, None, 1.0, ws, row_ptr)
+                assert mine.query()
+            with torch.cuda.stream(other):
+                assert torch.equal(row_ptr, want) and E == int(want[-1])
