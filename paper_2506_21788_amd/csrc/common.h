@@ -67,21 +67,28 @@ __device__ inline void post_mail(HostMail* m, long long value, int status) {
 }
 
 // A slot taken from a process-wide list for the duration of one call and given back at its end (defined in prof.hip; the
-// list grows to the largest number of calls that were ever inside the library at once, at most MAIL_SLOTS).
+// list grows to the largest number of calls that were ever inside the library at once, at most MAIL_SLOTS). Once a kernel
+// has been handed the slot, it goes back only when the stream has drained, also where the call ends with an error in
+// between: a post that comes late would otherwise land in the slot of another call.
 class MailSlot {
  public:
-  MailSlot();
+  MailSlot() = default;
   ~MailSlot();
   MailSlot(const MailSlot&) = delete;
   MailSlot& operator=(const MailSlot&) = delete;
-  bool ok() const { return m_ != nullptr; }
-  HostMail* dev() const { return m_; }
-  hipError_t wait(hipStream_t st);   // until the stream has drained; an error if it fails, or drains with nothing posted
+  int32_t take(hipStream_t st);   // st: the stream of the kernel that posts (not one under capture: it cannot be waited for)
+  HostMail* dev() {
+    lent_ = true;
+    return m_;
+  }
+  hipError_t wait();   // until the stream has drained; an error if it fails, or drains with nothing posted
   long long value() const { return m_->value; }
   int status() const { return m_->status; }
 
  private:
-  HostMail* m_;
+  HostMail* m_ = nullptr;
+  hipStream_t st_ = nullptr;
+  bool lent_ = false;   // a kernel that was given the slot may still be to run
 };
 
 // Carves aligned sub-buffers out of a caller workspace; `used()` is what a size query reports.

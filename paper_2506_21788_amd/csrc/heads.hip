@@ -751,14 +751,14 @@ extern "C" int32_t hgnn_multihead_plan(void* stream, int32_t N, int32_t G, int32
   HGNN_REQUIRE(plan && graph_off && (source_id || G == 0), HGNN_ERR_NULLPTR, "multihead_plan: null pointer");
   PlanView v = plan_view(plan, N, G, S);
   MailSlot mail;
-  HGNN_REQUIRE(mail.ok(), HGNN_ERR_HIP, "could not allocate the pinned result slot");
+  HGNN_TRY(mail.take(st));
   k_plan_graphs<<<1, 1024, 0, st>>>(G, S, graph_off, source_id, v, mail.dev());
   HGNN_LAUNCH_CHECK("k_plan_graphs");
   if (N > 0) {
     k_plan_atoms<<<nb64(N, 256), 256, 0, st>>>(N, G, graph_off, v);
     HGNN_LAUNCH_CHECK("k_plan_atoms");
   }
-  HGNN_HIP(mail.wait(st));
+  HGNN_HIP(mail.wait());
   HGNN_REQUIRE(mail.status() == 0, HGNN_ERR_BAD_SOURCE_ID, "a source id lies outside [0, %d)", S);
   return HGNN_OK;
 }

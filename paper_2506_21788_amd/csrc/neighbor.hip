@@ -1203,7 +1203,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
     return HGNN_OK;
   }
   MailSlot mail;
-  HGNN_REQUIRE(mail.ok(), HGNN_ERR_HIP, "could not allocate the pinned result slot");
+  HGNN_TRY(mail.take(st));
   // Everything below is enqueued in one go: a bad offset or cell is recorded in status[0], leaves every later
   // kernel with in-range (if meaningless) indices or without work, keeps the search from running, and is reported after
   // the one wait at the end.
@@ -1251,7 +1251,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
       HGNN_LAUNCH_CHECK("k_post_total");
     }
   }
-  HGNN_HIP(mail.wait(st));
+  HGNN_HIP(mail.wait());
   const long long total = mail.value();
   const int status_h = mail.status();
   HGNN_REQUIRE(!(status_h & ST_BAD_OFFSETS), HGNN_ERR_BAD_OFFSETS,

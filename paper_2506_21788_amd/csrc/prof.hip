@@ -21,31 +21,38 @@ MailLine* g_mail_lines = nullptr;
 std::vector<int> g_mail_free;
 }  // namespace
 
-MailSlot::MailSlot() : m_(nullptr) {
+int32_t MailSlot::take(hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  HGNN_HIP(hipStreamIsCapturing(st, &capture));
+  HGNN_REQUIRE(capture == hipStreamCaptureStatusNone, HGNN_ERR_HIP, "a call that synchronises its stream cannot be captured");
   std::lock_guard<std::mutex> hold(g_mail_lock);
   if (!g_mail_lines) {
     void* p = nullptr;
-    if (hipHostMalloc(&p, sizeof(MailLine) * MAIL_SLOTS, hipHostMallocPortable) != hipSuccess) return;
+    HGNN_HIP(hipHostMalloc(&p, sizeof(MailLine) * MAIL_SLOTS, hipHostMallocPortable));
     g_mail_lines = static_cast<MailLine*>(p);
     for (int k = MAIL_SLOTS - 1; k >= 0; --k) g_mail_free.push_back(k);
   }
-  if (g_mail_free.empty()) return;
+  HGNN_REQUIRE(!g_mail_free.empty(), HGNN_ERR_HIP, "could not allocate the pinned result slot");
   m_ = &g_mail_lines[g_mail_free.back()].mail;
   g_mail_free.pop_back();
+  st_ = st;
   m_->value = 0;
   m_->status = 0;
   __atomic_store_n(&m_->posted, 0u, __ATOMIC_RELEASE);
+  return HGNN_OK;
 }
 
 MailSlot::~MailSlot() {
   if (!m_) return;
+  if (lent_ && hipStreamSynchronize(st_) != hipSuccess) return;   // (never used again)
   std::lock_guard<std::mutex> hold(g_mail_lock);
   g_mail_free.push_back((int)(reinterpret_cast<MailLine*>(m_) - g_mail_lines));
 }
 
-hipError_t MailSlot::wait(hipStream_t st) {
-  const hipError_t e = wait_stream(st);
+hipError_t MailSlot::wait() {
+  const hipError_t e = wait_stream(st_);
   if (e != hipSuccess) return e;
+  lent_ = false;
   // the stream has drained: the slot was posted before that, or the kernel that posts it did not run
   return __atomic_load_n(&m_->posted, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
 }

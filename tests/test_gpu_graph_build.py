@@ -151,3 +151,50 @@ def test_counting_and_routing_leave_a_drained_stream():
                 assert mine.query()
             with torch.cuda.stream(other):
                 assert torch.equal(row_ptr, want) and E == int(want[-1])
+
+
+def test_refused_calls_keep_their_result_slot_until_nothing_can_post_to_it():
+    """A call that ends with an error after its kernel was enqueued (here: an error that the caller left behind) returns
+    with the stream drained, so that the kernel's result cannot land in the slot of the next call. Under capture the call is
+    refused before anything is enqueued. Neither uses the slots up."""
+    import ctypes
+    import torch
+    from paper_2506_21788_amd import binding as B
+    hip = ctypes.CDLL(B.LIB_PATH)      # symbols of the runtime that the library calls
+    b = small_mixed_batch(11, n_mol=6, n_cry=2)
+    want = oracle.radius_graph(b.pos, b.graph_off, b.cell, b.pbc, 4.0)
+    up = [torch.as_tensor(a).cuda() for a in (b.pos, b.graph_off, b.cell, b.pbc)]
+    src = torch.as_tensor(b.source_id).cuda()
+    S = int(b.source_id.max()) + 1
+    plan = torch.zeros(B.multihead_plan_ints(b.N, b.G, S), dtype=torch.int32, device="cuda")
+    ws = torch.zeros(B.radius_graph_workspace_bytes(b.N, b.G), dtype=torch.uint8, device="cuda")
+    row_ptr = torch.zeros(b.N + 1, dtype=torch.int32, device="cuda")
+    a = torch.rand((4096, 4096), device="cuda")
+    slow, quick = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for k in range(3):
+        print("left-over error", k, flush=True)
+        with torch.cuda.stream(slow):
+            for _ in range(10):
+                c = a @ a
+            assert not slow.query()
+            assert hip.hipSetDevice(9999) != 0
+            with pytest.raises(B.HgnnError, match="k_plan_graphs"):
+                B.multihead_plan(b.N, b.G, S, up[1], src, plan)
+            assert slow.query()
+        with torch.cuda.stream(quick):
+            assert B.radius_graph_count(b.N, b.G, *up, 4.0, ws, row_ptr) == want["E"]
+            assert np.array_equal(row_ptr.cpu().numpy(), want["row_ptr"])
+    del c
+    print("capture", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        a.zero_()
+        for _ in range(150):
+            with pytest.raises(B.HgnnError, match="captured"):
+                B.multihead_plan(b.N, b.G, S, up[1], src, plan)
+            with pytest.raises(B.HgnnError, match="captured"):
+                B.radius_graph_count(b.N, b.G, *up, 4.0, ws, row_ptr)
+    graph.replay()
+    assert B.radius_graph_count(b.N, b.G, *up, 4.0, ws, row_ptr) == want["E"]
+    assert float(a.abs().max()) == 0.0
