@@ -15,7 +15,8 @@
  *    aligned to 16 bytes. The caller owns every buffer (inputs, outputs, saved activations and
  *    workspaces); the library allocates no device memory and keeps no pointer after a call returns.
  *  - `stream` is a hipStream_t passed as void*. Calls only enqueue work on it, except where a
- *    function is documented to synchronise.
+ *    function is documented to synchronise: such a call returns when the stream has drained, cannot run on a stream
+ *    under capture (HIP), and the first one allocates 16 KB of pinned host memory that stay until the process ends.
  *  - Index type is int32. N atoms, G graphs, E directed edges, H hidden width, S sources.
  *    Edge e = (i <- j, s): i = dst[e] is the destination atom, j = col[e] the source atom, s the
  *    integer lattice shift applied to j.

@@ -66,8 +66,8 @@ __device__ inline void post_mail(HostMail* m, long long value, int status) {
   __hip_atomic_store(&m->posted, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// A slot taken from a process-wide list for the duration of one call and given back at its end (defined in prof.hip; the
-// list grows to the largest number of calls that were ever inside the library at once, at most MAIL_SLOTS). Once a kernel
+// A slot taken from a process-wide list of MAIL_SLOTS for the duration of one call and given back at its end (defined in
+// prof.hip; a call that finds all of them taken by others that are waiting is refused). Once a kernel
 // has been handed the slot, it goes back only when the stream has drained, also where the call ends with an error in
 // between: a post that comes late would otherwise land in the slot of another call.
 class MailSlot {

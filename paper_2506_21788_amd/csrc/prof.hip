@@ -11,14 +11,15 @@ namespace hgnn {
 uint64_t g_prof_mask = 0;
 
 // ---------------------------------------------------------------------------------------------
-// result slots (see common.h): one pinned allocation of MAIL_SLOTS lines, made by the first call that needs one
+// result slots (see common.h): one pinned allocation of MAIL_SLOTS lines, made by the first call that needs one, kept until
+// the process ends. Coherent by request: what a plain portable allocation is depends on the environment.
 // ---------------------------------------------------------------------------------------------
 namespace {
 constexpr int MAIL_SLOTS = 256;
 struct alignas(64) MailLine { HostMail mail; };   // a cache line each: slots of two calls do not share one
 std::mutex g_mail_lock;
 MailLine* g_mail_lines = nullptr;
-std::vector<int> g_mail_free;
+int g_mail_free[MAIL_SLOTS], g_mail_nfree = 0;   // (fixed: nothing here may throw through the C entries)
 }  // namespace
 
 int32_t MailSlot::take(hipStream_t st) {
@@ -28,13 +29,12 @@ int32_t MailSlot::take(hipStream_t st) {
   std::lock_guard<std::mutex> hold(g_mail_lock);
   if (!g_mail_lines) {
     void* p = nullptr;
-    HGNN_HIP(hipHostMalloc(&p, sizeof(MailLine) * MAIL_SLOTS, hipHostMallocPortable));
+    HGNN_HIP(hipHostMalloc(&p, sizeof(MailLine) * MAIL_SLOTS, hipHostMallocPortable | hipHostMallocCoherent));
     g_mail_lines = static_cast<MailLine*>(p);
-    for (int k = MAIL_SLOTS - 1; k >= 0; --k) g_mail_free.push_back(k);
+    for (int k = MAIL_SLOTS - 1; k >= 0; --k) g_mail_free[g_mail_nfree++] = k;
   }
-  HGNN_REQUIRE(!g_mail_free.empty(), HGNN_ERR_HIP, "could not allocate the pinned result slot");
-  m_ = &g_mail_lines[g_mail_free.back()].mail;
-  g_mail_free.pop_back();
+  HGNN_REQUIRE(g_mail_nfree > 0, HGNN_ERR_HIP, "all %d result slots are taken by calls that are waiting", MAIL_SLOTS);
+  m_ = &g_mail_lines[g_mail_free[--g_mail_nfree]].mail;
   st_ = st;
   m_->value = 0;
   m_->status = 0;
@@ -46,7 +46,7 @@ MailSlot::~MailSlot() {
   if (!m_) return;
   if (lent_ && hipStreamSynchronize(st_) != hipSuccess) return;   // (never used again)
   std::lock_guard<std::mutex> hold(g_mail_lock);
-  g_mail_free.push_back((int)(reinterpret_cast<MailLine*>(m_) - g_mail_lines));
+  g_mail_free[g_mail_nfree++] = (int)(reinterpret_cast<MailLine*>(m_) - g_mail_lines);
 }
 
 hipError_t MailSlot::wait() {
