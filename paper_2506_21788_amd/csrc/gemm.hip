@@ -1088,6 +1088,9 @@ __global__ void __launch_bounds__(256) k_reduce_partials(ReduceArgs a, int epb) 
 // several reductions in one launch: the workgroups of all jobs one after the other, in a job element blocks first, then the
 // blocks of the partials, then the groups (a three-dimensional grid over the largest job would be mostly empty workgroups)
 constexpr int REDUCE_QUEUE_MAX = 8;
+// A launch holds fewer than 2^32 threads in x. Two weight gradients at H = 256 pass that from about 32,400 sources on: what
+// does not fit runs as a launch of its own, with the groups in z.
+constexpr long REDUCE_QUEUE_WGS = (1L << 32) / 256 - 1;
 struct ReduceQueueArgs {
   ReduceArgs job[REDUCE_QUEUE_MAX];
   int njobs;
@@ -1152,7 +1155,7 @@ static int32_t launch_reduce_partials_n(hipStream_t st, const float* partial, in
   const unsigned xb = reduce_xblocks(blk_elems, nsplit);
   const long wgs = (long)xb * nblk * groups;
   if (tl_reduce_queue && wgs > 0 && tl_reduce_queue->q.njobs < REDUCE_QUEUE_MAX &&
-      tl_reduce_queue->q.off[tl_reduce_queue->q.njobs] + wgs <= 2147483647L) {
+      tl_reduce_queue->q.off[tl_reduce_queue->q.njobs] + wgs <= REDUCE_QUEUE_WGS) {
     // collected: runs with the others when the scope is flushed
     ReduceQueueArgs& q = tl_reduce_queue->q;
     const int j = q.njobs++;

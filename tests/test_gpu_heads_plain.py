@@ -64,6 +64,45 @@ def test_plain_heads_match_the_oracle(sizes, S, sources, H, dtype):
         assert e <= TOL[dtype]["fwd" if k in ("energy", "force") else "grad"], (k, e)
 
 
+def test_more_sources_than_one_launch_reduces():
+    """32,900 sources at H = 256: the weight gradients of the two branches no longer fit one launch of the reductions."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+    H, S, used = 256, 32900, [0, 17001, 32899]
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 61 GB of device memory")
+    print("heads of", S, "sources", flush=True)
+    rng = np.random.default_rng(8)
+    per = deep_head_weight_count(H, H, 1)
+    graph_off, src = np.array([0, 3, 4, 9], np.int32), np.array([2, 0, 1], np.int32)
+    N, G = 9, 3
+    h = rng.standard_normal((N, H)).astype(np.float32)
+    v = rng.standard_normal((N, 3)).astype(np.float32)
+    p = oracle.pool_fwd(h, graph_off).astype(np.float32)
+    Wh = init_deep_head_weights(rng, H, H, 1, 3)
+    gE, gF = rng.standard_normal(G).astype(np.float32), rng.standard_normal((N, 3)).astype(np.float32)
+    f32 = dict(dtype=torch.float32, device="cuda")
+    W, gW = torch.zeros((S, per), **f32), torch.full((S, per), float("nan"), **f32)
+    W[used] = torch.as_tensor(Wh.reshape(3, per)).cuda()
+    t = [torch.as_tensor(a).cuda() for a in (p, h, v)]
+    plan = torch.empty(B.multihead_plan_ints(N, G, S), dtype=torch.int32, device="cuda")
+    B.multihead_plan(N, G, S, torch.as_tensor(graph_off).cuda(), torch.tensor(used, dtype=torch.int32).cuda()[torch.as_tensor(src).long().cuda()], plan)
+    ws_b, sv_b = B.multihead_decode_workspace_bytes(N, G, H, H, S, B.BF16)
+    ws, sv = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (ws_b, sv_b))
+    out = dict(energy=torch.empty(G, **f32), force=torch.empty((N, 3), **f32))
+    grads = dict(g_p=torch.empty((G, H), **f32), g_h=torch.empty((N, H), **f32), g_v=torch.empty((N, 3), **f32))
+    B.multihead_decode_fwd(N, G, H, H, S, B.BF16, plan, *t, W, *out.values(), sv, ws)
+    B.multihead_decode_bwd(N, G, H, H, S, B.BF16, plan, *t, W, sv, torch.as_tensor(gE).cuda(), torch.as_tensor(gF).cuda(),
+                           *grads.values(), gW, ws)
+    eo, fo, c = oracle.heads_deep_fwd(p, h, v, graph_off, src, Wh.astype(np.float64), H, 1, 3)
+    want = dict(zip(("energy", "force", "g_p", "g_h", "g_v", "gW"), (eo, fo, *oracle.heads_deep_bwd(c, gE, gF))))
+    got = dict(out, **grads, gW=gW[used].ravel())
+    for k, x in got.items():
+        assert relerr(x.cpu().numpy(), want[k]) <= TOL["bf16"]["fwd"], k
+    gW[used] = 0.0
+    assert not any(bool((part != 0).any()) for part in gW.split(1000)), "a source without graphs has a gradient"
+
+
 # the embedding at widths of one and several 256-column slabs: chunks of 2,048 atoms, lists of matches around the batches of eight
 @pytest.mark.parametrize("N,H,elements", [(1, 300, 1), (9, 257, 1), (2049, 520, 1), (5000, 24, 40), (4096, 866, 3)])
 def test_embedding_at_other_widths(N, H, elements):
