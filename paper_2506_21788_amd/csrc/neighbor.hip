@@ -419,12 +419,17 @@ __device__ inline int atom_bin_of(const GMeta& m, float x, float y, float z, boo
   return (b[0] * m.nb[1] + b[1]) * m.nb[2] + b[2];
 }
 
-// Small batches (at most BIN_GRAPHS_MAX atoms): everything between the input and the search in one launch, one
+// Small batches of small graphs (see bin_by_graph()): everything between the input and the search in one launch, one
 // workgroup per graph. A graph's atoms are contiguous in the batch, so its bins' runs are too: histogram, scan and
 // placement stay inside the workgroup, in LDS (seven launches of 2-14 us before: the atomics of a molecule's atoms on
 // its one or two bins in memory alone were 13 + 13 us at 7,105 atoms). Larger batches keep the grid-wide kernels below,
-// where one large graph is spread over many workgroups.
-constexpr int BIN_GRAPHS_MAX = 16384;
+// where one large graph is spread over many workgroups, and so do batches of large graphs: the host knows the mean only.
+// Whole graph, grid-wide -> by graph: one cell of 4,000 atoms 129 -> 109 us, four of them 193 -> 184, one of 5,000 102 -> 104, of
+// 7,000 118 -> 123, of 16,000 168 -> 201, two of 7,000 178 -> 185; 470 molecules 96 -> 82.
+constexpr int BIN_GRAPHS_MAX = 16384, BIN_GRAPH_MEAN = 4500;
+static bool bin_by_graph(int N, int G) {
+  return N <= BIN_GRAPHS_MAX && G <= BIN_GRAPHS_MAX && N <= (int64_t)BIN_GRAPH_MEAN * G;
+}
 constexpr int BG_BINS = 4096;    // bins of a graph counted in LDS; more: in the workspace
 struct BinArgs {
   int N, G;
@@ -1213,7 +1218,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
                                                                 graph_off);
     HGNN_LAUNCH_CHECK("k_clear_and_check");
     const int home = home_atoms(N);
-    if (N <= BIN_GRAPHS_MAX) {
+    if (bin_by_graph(N, G)) {
       const BinArgs a = {N, G, pos, graph_off, cell, pbc, rc, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt, w.bin_start,
                          w.bin_atoms, w.spos, w.status, w.status + 1, w.list, home};
       k_bin_graphs<<<G, 256, 0, st>>>(a);

@@ -1,6 +1,8 @@
 """Radius graph and routing plan at the sizes where their kernels hand over to one another: batches of one workgroup per
 graph against grid-wide binning, bins counted in LDS against memory, one-launch against block-sum scans, sources placed by
 sixteen wavefronts against one."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
@@ -198,3 +200,35 @@ def test_refused_calls_keep_their_result_slot_until_nothing_can_post_to_it():
     graph.replay()
     assert B.radius_graph_count(b.N, b.G, *up, 4.0, ws, row_ptr) == want["E"]
     assert float(a.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("sizes", [(4500,), (4501,), (4625, 4376), (9000, 1)])
+def test_large_graphs_of_a_small_batch(sizes):
+    """Few large graphs are binned by grid-wide kernels although the batch is small, on either side of the mean that decides.
+    Each graph is one cluster of 125 atoms over and over (a lone atom at its end), at places that leave every difference of
+    coordinates exact, so that its edges are the cluster's."""
+    print("large graphs", sizes, flush=True)
+    rng = np.random.default_rng(6)
+    cluster = (rng.integers(0, 10 * 64, (125, 3)) / 64).astype(np.float32)
+    one = oracle.radius_graph(cluster, np.array([0, 125], np.int32), np.zeros((1, 3, 3), np.float32), np.zeros(1, np.uint8), 4.0)
+    place = np.stack(np.meshgrid(*[np.arange(5)] * 3, indexing="ij"), -1).reshape(-1, 3).astype(np.float32) * 64
+    graphs, parts, N, E = [], [], 0, 0
+    for n in sizes:
+        k = n // 125
+        pos = np.concatenate([cluster + place[c] for c in range(k)] + [place[k:k + 1]] * (n % 125))
+        graphs.append((pos, np.ones(n, np.int32)))
+        w = repeated_graph(one, SimpleNamespace(N=125), k) if k else None
+        parts.append((N, E, n, w))
+        N, E = N + n, E + (w["E"] if k else 0)
+    got = gpu_graph(concat_graphs(graphs), 4.0).to_numpy()
+    assert got["E"] == E and E > 1000
+    for n0, e0, n, w in parts:
+        if w is None:
+            continue
+        e1, m = e0 + w["E"], n // 125 * 125
+        for key, base in (("row_ptr", e0), ("colT_ptr", e0)):
+            assert np.array_equal(got[key][n0:n0 + m + 1], w[key] + base), key
+        for key, base in (("dst", n0), ("col", n0), ("permT", e0), ("shift", 0)):
+            assert np.array_equal(got[key][e0:e1], w[key] + base), key
+        assert np.array_equal(got["d2"][e0:e1].view(np.uint32), w["d2"].view(np.uint32))
+        assert np.array_equal(got["rvec"][e0:e1].view(np.uint32), w["rvec"].view(np.uint32))
