@@ -822,7 +822,12 @@ static int32_t launch_pack_gemm_small_t(hipStream_t st, const PackArgs& pk, cons
 // 128 molecules (140) 973 -> 946, 203 molecules, energies and forces only (222) 315 -> 302; past the line 160 mixed
 // structures (338) 2980 -> 3028, 300 (600) 4885 -> 5094. fp32 operands at H = 256 keep the taller tiles: a chunk of
 // their weights is 128 registers.
-static bool small_gemm(int M, int tile_rows) { return (M + tile_rows - 1) / tile_rows <= num_cus(); }
+// Groups count as a tile each: rows are rarely whole tiles of a group, every workgroup walks the groups to find its own, and
+// the shorter the tiles, the more workgroups walk. Heads, forward, taller tiles -> 16-row tiles: 400 rows, 200 groups,
+// H = 128, 70 -> 61 us; 4,600 rows, 64 groups 38 -> 37; past the line 8,000 rows, 64 groups 40 -> 44, 500 groups 169 -> 357.
+static bool small_gemm(const GemmArgs& a, int tile_rows) {
+  return (a.M + tile_rows - 1) / tile_rows + (a.grp_ptr ? a.S : 0) <= num_cus();
+}
 
 // workgroups of this variant that one CU holds at a time (asked once; also raises the LDS limit of the kernel)
 template <int H, bool BF16, int TM>
@@ -859,7 +864,7 @@ template <int H, bool BF16>
 static int32_t launch_gemm_t(hipStream_t st, const GemmArgs& a) {
   if (a.M <= 0) return HGNN_OK;
   if constexpr (BF16 || H < 256) {
-    if (small_gemm(a.M, GemmCfg<H, BF16>::WR == 1 ? 32 : 64)) return launch_gemm_small_t<H, BF16>(st, nullptr, a, 0);
+    if (small_gemm(a, GemmCfg<H, BF16>::WR == 1 ? 32 : 64)) return launch_gemm_small_t<H, BF16>(st, nullptr, a, 0);
   }
   if constexpr (GemmCfg<H, BF16>::WR == 1) return launch_gemm_tm<H, BF16, 32>(st, a);
   else return launch_gemm_tm<H, BF16, 64>(st, a);
@@ -871,7 +876,7 @@ static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const 
   using C = GemmCfg<H, BF16, TM>;
   if (second.M <= 0) return HGNN_OK;
   if constexpr (BF16 || H < 256) {
-    if (small_gemm(second.M, TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu);
+    if (small_gemm(second, TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu);
   }
   constexpr size_t LDS = C::LDS_BYTES + C::A_BYTES;
   static bool raised = false;   // the kernel's LDS limit is raised once per variant
@@ -922,7 +927,7 @@ int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* firs
 // molecules 395 -> 377, a crystal's conservative forces 605 -> 598, 16 molecules at H = 128 497 -> 482; past the line nothing changes.
 constexpr long RAW_BYTES = 16l << 20;
 static bool pack_along(int H, const PackArgs& pk, const GemmArgs* first, const GemmArgs& second) {
-  if (H > 128 || second.M <= 0 || !small_gemm(second.M, H >= 128 ? 32 : 64)) return false;
+  if (H > 128 || second.M <= 0 || !small_gemm(second, H >= 128 ? 32 : 64)) return false;
   if (first && first->nkc != 1) return false;
   const int nblk = (first ? 1 : 0) + second.ncb;
   if (((second.M + 15) / 16) * (long)nblk * H * H * 4 > RAW_BYTES) return false;
@@ -978,7 +983,8 @@ static int32_t launch_gemm_small_pair_t(hipStream_t st, const GemmArgs& a, const
   return HGNN_OK;
 }
 int32_t launch_gemm_pair(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs& b) {
-  const bool one = (bf16 || H < 256) && a.M > 0 && b.M > 0 && a.ncb == b.ncb && small_gemm(a.M > b.M ? a.M : b.M, H >= 128 ? 32 : 64);
+  const int rows = H >= 128 ? 32 : 64;
+  const bool one = (bf16 || H < 256) && a.M > 0 && b.M > 0 && a.ncb == b.ncb && small_gemm(a, rows) && small_gemm(b, rows);
   if (!one) {
     HGNN_TRY(launch_gemm(st, H, bf16, a));
     return launch_gemm(st, H, bf16, b);

@@ -64,6 +64,13 @@ def test_plain_heads_match_the_oracle(sizes, S, sources, H, dtype):
         assert e <= TOL[dtype]["fwd" if k in ("energy", "force") else "grad"], (k, e)
 
 
+# groups count as tiles where the short row tiles are chosen, and a launch of its own is taken for either branch past the line
+@pytest.mark.parametrize("H,dtype", [(64, "bf16"), (128, "f32"), (256, "bf16")])
+@pytest.mark.parametrize("sizes,S", [([30] * 20, 237), ([30] * 20, 238), ([1] * 300, 247), ([3] * 200, 500), ([800, 1, 900] * 4, 33)])
+def test_plain_heads_of_many_sources(sizes, S, H, dtype):
+    test_plain_heads_match_the_oracle(sizes, S, tuple(range(0, S, 3)), H, dtype)
+
+
 def test_more_sources_than_one_launch_reduces():
     """32,900 sources at H = 256: the weight gradients of the two branches no longer fit one launch of the reductions."""
     import torch
