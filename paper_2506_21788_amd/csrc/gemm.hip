@@ -875,8 +875,10 @@ static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const 
   constexpr int TM = GemmCfg<H, BF16>::WR == 1 ? 32 : 64;
   using C = GemmCfg<H, BF16, TM>;
   if (second.M <= 0) return HGNN_OK;
+  // (chains at H = 256 only while every compute unit has one 16-row tile at most, 512 threads that hold two blocks of both
+  // weights each: layer forward, 64- / 32-row tiles -> 16-row tiles, 4,000 atoms 44 -> 37 us, 5,000 44 -> 47, 8,000 49 -> 53)
   if constexpr (BF16 || H < 256) {
-    if (small_gemm(second, TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu);
+    if (small_gemm(second, H == 256 ? 16 : TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu);
   }
   constexpr size_t LDS = C::LDS_BYTES + C::A_BYTES;
   static bool raised = false;   // the kernel's LDS limit is raised once per variant
