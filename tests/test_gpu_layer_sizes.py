@@ -188,6 +188,12 @@ def test_layer_atom_counts_of_small_row_tiles(N, H, dtype, last):
     _run_layer(N=n, E=3000 if N < 2 else 40 * n, H=H, dtype=dtype, seed=n)
 
 
+# the last batch whose chains of products take 16-row tiles at H = 256, one per compute unit
+@pytest.mark.parametrize("N", [4096, 4097])
+def test_layer_atom_counts_of_short_chains(N):
+    _run_layer(N=N, E=5000, H=256, dtype="bf16", seed=N)
+
+
 # Batches whose first products run in one launch with the packing of the weights (up to 16 MB of weights read by all 16-row
 # tiles, forward and reverse pass each with a line of its own) and the next larger ones
 @pytest.mark.parametrize("H,dtype,N", [(64, "f32", 5456), (64, "bf16", 5457), (64, "f32", 8192), (64, "bf16", 8193),
