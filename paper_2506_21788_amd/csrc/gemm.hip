@@ -1536,21 +1536,24 @@ int32_t launch_wgrad(hipStream_t st, int H, bool bf16, const WgradArgs& a) { ret
 // ---------------------------------------------------------------------------------------------
 // column sums
 // ---------------------------------------------------------------------------------------------
-// up to four column sums in one launch (blockIdx.z), each over its own rows
+// up to four column sums in one launch, each over its own rows: the splits of all jobs one after the other (blockIdx.x; with
+// the jobs in z, 500 groups of two rows beside 500 of 40,000 were 625,000 workgroups without work, 120 us)
 struct ColsumJobs {
   ColsumArgs job[4];
-  int nsplit[4], rows_per_split[4];
+  int nsplit[4], rows_per_split[4], off[4];   // off: first split of the job (past the last one for jobs that are not there)
 };
 __global__ void __launch_bounds__(256) k_colsum(ColsumJobs m, int H) {
-  const ColsumArgs& p = m.job[blockIdx.z];
-  const int nsplit = m.nsplit[blockIdx.z], rows_per_split = m.rows_per_split[blockIdx.z];
+  const int jb = ((int)blockIdx.x >= m.off[1]) + ((int)blockIdx.x >= m.off[2]) + ((int)blockIdx.x >= m.off[3]);   // uniform
+  const ColsumArgs& p = m.job[jb];
+  const int nsplit = m.nsplit[jb], rows_per_split = m.rows_per_split[jb];
   // thread = (4-column chunk q, row phase ph); every phase walks its rows with four loads in flight
   __shared__ float4 sh[256];
+  __shared__ float shw[16];   // sum of the weights of every phase
   const int tid = threadIdx.x;
   const int CH = H >> 2;
   const int q = tid % CH, ph = tid / CH, nph = 256 / CH;
-  const int split = blockIdx.x, grp = blockIdx.y;
-  if (split >= nsplit || (grp > 0 && (!p.grp_ptr || grp >= p.S))) return;   // uniform over the workgroup
+  const int split = (int)blockIdx.x - m.off[jb], grp = blockIdx.y;
+  if (grp > 0 && (!p.grp_ptr || grp >= p.S)) return;   // uniform over the workgroup
   long gbeg = 0, gend = p.M;
   if (p.grp_ptr) { gbeg = p.grp_ptr[grp]; gend = p.grp_ptr[grp + 1]; }
   float ws = 0.f;   // this phase's sum of the weights
@@ -1558,6 +1561,11 @@ __global__ void __launch_bounds__(256) k_colsum(ColsumJobs m, int H) {
   long rend = rbeg + rows_per_split;
   if (rend > gend) rend = gend;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (rbeg >= rend) {   // uniform: most splits of most groups where there are many groups
+    if (ph == 0) *reinterpret_cast<float4*>(p.partial + ((long)grp * nsplit + split) * H + q * 4) = s;
+    if (p.w_dest && tid == 64) p.w_partial[(long)grp * nsplit + split] = 0.f;
+    return;
+  }
   for (long r0 = rbeg + ph; r0 < rend; r0 += 4 * nph) {
     float4 xv[4];
     float wv[4];
@@ -1592,6 +1600,7 @@ __global__ void __launch_bounds__(256) k_colsum(ColsumJobs m, int H) {
     }
   }
   sh[tid] = s;
+  if (q == 0) shw[ph] = ws;
   __syncthreads();
   if (ph == 0) {
     for (int k = 1; k < nph; ++k) {
@@ -1600,14 +1609,10 @@ __global__ void __launch_bounds__(256) k_colsum(ColsumJobs m, int H) {
     }
     *reinterpret_cast<float4*>(p.partial + ((long)grp * nsplit + split) * H + q * 4) = s;
   }
-  if (p.w_dest) {   // uniform over the workgroup
-    __syncthreads();
-    sh[tid].x = ws;
-    __syncthreads();
-    if (tid == 0) {
-      for (int k = 1; k < nph; ++k) ws += sh[k * CH].x;
-      p.w_partial[(long)grp * nsplit + split] = ws;
-    }
+  if (p.w_dest && tid == 64) {   // (another wavefront than the columns': CH <= 64)
+    ws = shw[0];
+    for (int k = 1; k < nph; ++k) ws += shw[k];
+    p.w_partial[(long)grp * nsplit + split] = ws;
   }
 }
 
@@ -1624,7 +1629,7 @@ int32_t launch_colsum_multi(hipStream_t st, int H, const ColsumArgs* jobs, int n
   HGNN_REQUIRE(jobs && njobs >= 1 && njobs <= 4, HGNN_ERR_BAD_SHAPE, "colsum: one to four jobs");
   HGNN_REQUIRE(valid_H(H), HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
   ColsumJobs m;
-  int most = 1, groups = 1;
+  int splits = 0, groups = 1;
   for (int j = 0; j < njobs; ++j) {
     const ColsumArgs& a = jobs[j];
     HGNN_REQUIRE(a.X && a.dest && a.partial, HGNN_ERR_NULLPTR, "colsum: null operand");
@@ -1633,11 +1638,13 @@ int32_t launch_colsum_multi(hipStream_t st, int H, const ColsumArgs* jobs, int n
     m.nsplit[j] = colsum_splits(a.M);
     const int64_t rps = (a.M + m.nsplit[j] - 1) / m.nsplit[j];
     m.rows_per_split[j] = rps < 1 ? 1 : (int)rps;
-    if (m.nsplit[j] > most) most = m.nsplit[j];
+    m.off[j] = splits;
+    splits += m.nsplit[j];
     if (a.grp_ptr && a.S > groups) groups = a.S;
   }
+  for (int j = njobs; j < 4; ++j) m.off[j] = splits;
   ProfScope ps(PT_COLSUM, st);
-  k_colsum<<<dim3(most, groups, njobs), 256, 0, st>>>(m, H);
+  k_colsum<<<dim3(splits, groups), 256, 0, st>>>(m, H);
   HGNN_LAUNCH_CHECK("k_colsum");
   for (int j = 0; j < njobs; ++j) {
     const ColsumArgs& a = jobs[j];
