@@ -71,6 +71,13 @@ def test_plain_heads_of_many_sources(sizes, S, H, dtype):
     test_plain_heads_match_the_oracle(sizes, S, tuple(range(0, S, 3)), H, dtype)
 
 
+# the weight gradients of both branches in one launch (few sources, or few rows) or in one each
+@pytest.mark.parametrize("H,dtype", [(64, "f32"), (128, "bf16"), (256, "bf16"), (256, "f32")])
+@pytest.mark.parametrize("sizes,S", [([100] * 81, 4), ([100] * 81, 5), ([100] * 80, 5), ([4000, 1, 4000, 100], 6)])
+def test_plain_heads_weight_gradients_of_both_branches(sizes, S, H, dtype):
+    test_plain_heads_match_the_oracle(sizes, S, tuple(range(S)), H, dtype)
+
+
 def test_more_sources_than_one_launch_reduces():
     """32,900 sources at H = 256: the weight gradients of the two branches no longer fit one launch of the reductions."""
     import torch
