@@ -1062,13 +1062,21 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
 // edges, H = 128 fp32, forward with x_e 36 -> 12.5 us, source sum with the dots 28 -> 9.8 us; steps: a crystal's conservative
 // forces 845 -> 694 us, 16 crystals 1083 -> 999, 64 crystals (4,096 rows) 1886 -> 1849, 128 molecules (4,600 rows)
 // 999 -> 976. Past the line it changes nothing (12,900 and 18,600 rows: within 1 %).
-static bool seg_split(int N) { return N <= num_cus() * 32; }
+// And rows long enough for their number: the split saves time with every trip of a row, and costs it with every row
+// (wavefronts without a trip, and the sum over the four). The least mean row is N / (per_cu * compute units). Whole layers,
+// without -> with the split, H = 128 bf16, forward (per_cu = 2; 4 at H = 256, where a trip is twice as long): 8,000 rows of 2
+// edges 32 -> 36 us, of 8 40 -> 41, of 30 69 -> 64, 2,000 rows of 4 23 -> 23, of 17 31 -> 27; reverse, one sum (per_cu = 8):
+// 8,000 rows of 1 edge 60 -> 62, of 4 77 -> 72, 2,000 rows of 1 51 -> 50, of 4 56 -> 51, with the dots of every edge
+// (per_cu = 16) 6,000 rows of 2 68 -> 65, 8,000 70 -> 71.
+static bool seg_split(int N, int64_t E, int per_cu) {
+  return N <= num_cus() * 32 && E * per_cu * num_cus() >= (int64_t)N * N;
+}
 
-int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, const int32_t* row_ptr, const void* z2_vm,
+int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, int64_t E, const int32_t* row_ptr, const void* z2_vm,
                           const float* rvec, const float* wx, float alpha, const float* v_in, float* M,
                           float* v_out, float* xe) {
   if (N <= 0) return HGNN_OK;
-  const bool split = seg_split(N);
+  const bool split = seg_split(N, E, H == 256 ? 4 : 2);
   const unsigned grid = split ? (unsigned)N : (unsigned)(((int64_t)N * 64 + 255) / 256);
   ProfScope ps(PT_SEG_FWD, st);
 #define HGNN_SEGF1(HH, BB, XX, SS) \
@@ -1255,12 +1263,12 @@ k_segsum_vm(int N, const int32_t* __restrict__ ptr, const int32_t* __restrict__ 
   if (fixes) fr.finish(i, lane, fix);
 }
 
-int32_t launch_segsum_vm(hipStream_t st, int H, bool bf16, int N, const int32_t* ptr, const int32_t* perm,
+int32_t launch_segsum_vm(hipStream_t st, int H, bool bf16, int N, int64_t E, const int32_t* ptr, const int32_t* perm,
                          const void* X_vm, float* out, int ldo, int tag, const float* wdot, float* dot,
                          const DsumFix* fix) {
   if (N <= 0) return HGNN_OK;
   const DsumFix fx = fix ? *fix : DsumFix{nullptr, nullptr, nullptr, 0};
-  const bool split = seg_split(N);
+  const bool split = seg_split(N, E, dot ? 16 : 8);
   const unsigned grid = split ? (unsigned)N : (unsigned)(((int64_t)N * 64 + 255) / 256);
   ProfScope ps(tag, st);
 #define HGNN_SEGS1(HH, BB, DD, SS) k_segsum_vm<HH, BB, DD, SS><<<grid, 256, 0, st>>>(N, ptr, perm, X_vm, out, ldo, wdot, dot, fx)

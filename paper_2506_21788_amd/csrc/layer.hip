@@ -241,7 +241,7 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     e.a1_pk = s.a1_pk; e.z2_vm = s.z2_vm;
     HGNN_TRY(launch_edge_fwd(st, H, bf16, e));
   }
-  HGNN_TRY(launch_seg_fwd_vm(st, H, bf16, N, row_ptr, s.z2_vm, rvec, W + o.wx, alpha, v_in, s.M, v_out,
+  HGNN_TRY(launch_seg_fwd_vm(st, H, bf16, N, E, row_ptr, s.z2_vm, rvec, W + o.wx, alpha, v_in, s.M, v_out,
                              keep_xe ? s.xe : nullptr));
   {  // z3 = [h ; M] W3 + b3
     GemmArgs g;
@@ -462,18 +462,18 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
     // g_P left the edge kernel already
   } else if (k > 1) {
     // several attributes: the gradient with respect to them (on request) is a pass of its own over g_z1
-    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, row_ptr, nullptr, w.gz1_vm, w.g_PQ, 2 * H, PT_SEGSUM_DST));
+    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, E, row_ptr, nullptr, w.gz1_vm, w.g_PQ, 2 * H, PT_SEGSUM_DST));
     if (g_d2) HGNN_TRY(launch_gattr_vm(st, H, E, w.gz1_vm, W + o.W1 + 2 * HH, k, g_d2));
   } else {
-    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, row_ptr, nullptr, w.gz1_vm, w.g_PQ, 2 * H, PT_SEGSUM_DST,
+    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, E, row_ptr, nullptr, w.gz1_vm, w.g_PQ, 2 * H, PT_SEGSUM_DST,
                               W + o.W1 + 2 * HH, g_d2));
   }
   if (g_rvec) HGNN_TRY(launch_edge_grvec(st, E, dst, s.xe, g_v_out, alpha, g_rvec));
   if (dsum_in_kernel)   // g_Q, the rows of g_P that cross tiles, and g_d2 where it is asked for
-    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, colT_ptr, permT, w.gz1_vm, w.g_PQ + H, 2 * H, PT_SEGSUM_SRC,
+    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, E, colT_ptr, permT, w.gz1_vm, w.g_PQ + H, 2 * H, PT_SEGSUM_SRC,
                               g_d2 ? W + o.W1 + 2 * HH : nullptr, g_d2, &dfix));
   else
-    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, colT_ptr, permT, w.gz1_vm, w.g_PQ + H, 2 * H, PT_SEGSUM_SRC));  // g_Q
+    HGNN_TRY(launch_segsum_vm(st, H, bf16, N, E, colT_ptr, permT, w.gz1_vm, w.g_PQ + H, 2 * H, PT_SEGSUM_SRC));  // g_Q
   {  // g_h = (g_h' + g_h(a)) + g_P W1a^T + g_Q W1b^T
     GemmArgs g;
     g.A[0] = w.g_PQ; g.lda[0] = 2 * H; g.A[1] = w.g_PQ + H; g.lda[1] = 2 * H; g.nkc = 2;

@@ -194,6 +194,14 @@ def test_layer_atom_counts_of_short_chains(N):
     _run_layer(N=N, E=5000, H=256, dtype="bf16", seed=N)
 
 
+# 2,000 rows around the mean lengths from which four wavefronts share a row (256 compute units): the sums of the forward pass, and
+# those of the reverse pass
+@pytest.mark.parametrize("H,dtype,E", [(64, "f32", 7812), (64, "bf16", 7813), (128, "f32", 7813), (256, "bf16", 3906),
+                                       (256, "f32", 3907), (64, "bf16", 1953), (128, "bf16", 1954), (256, "bf16", 1954)])
+def test_layer_rows_around_the_split_of_a_row(H, dtype, E):
+    _run_layer(N=2000, E=E, H=H, dtype=dtype, seed=E + H)
+
+
 # Batches whose first products run in one launch with the packing of the weights (up to 16 MB of weights read by all 16-row
 # tiles, forward and reverse pass each with a line of its own) and the next larger ones
 @pytest.mark.parametrize("H,dtype,N", [(64, "f32", 5456), (64, "bf16", 5457), (64, "f32", 8192), (64, "bf16", 8193),
