@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
     const int tiles = ((p.nI + C::TI - 1) / C::TI) * nTj;   // a last row tile may stick out past nI
     int t = q % tiles;
     split = (q / tiles) * 8 + xcd;     // the launcher makes the split count a multiple of 8,
-    if (p.grp_ptr) {                   // or there are groups, whose tiles fill the chip with few splits of each
+    if (p.nsplit % 8 != 0) {           // or there are groups, whose tiles fill the chip with few splits of each
       split = blockIdx.x / tiles;
       t = blockIdx.x % tiles;
     }
@@ -1372,10 +1372,13 @@ int32_t launch_fwgrad(hipStream_t st, const FWgradArgs& a) {
   long want = ((big ? 2L : 3L) * num_cus() + tiles - 1) / tiles;
   if (want > cap) want = cap;
   if (a.grp_ptr) {
-    // Rows are dealt to a group's splits in the kernel (the host only knows that all rows could be in one group), and no
-    // split is made of less than 256 of them: every split writes and reads back a whole output block. 5 groups, widths
-    // 866 and 889: 128 graphs 22 + 30 us (products + sums of the partials) -> 10 + 15, 7,734 atoms 73 + 30 -> 41 + 20.
+    // Rows are dealt to a group's splits in the kernel (the host only knows that all rows could be in one group). There are
+    // no more splits than 256 rows of all groups make: every split of every group writes and reads back a whole output
+    // block, also those that are left without rows. 5 groups, widths 866 and 889: 128 graphs 22 + 30 us (products + sums of
+    // the partials) -> 10 + 15, 7,734 atoms 73 + 30 -> 41 + 20. From 8 on they are a multiple of 8 as well (one group, 16,000 rows: 21
+    // us, with its 16 splits spread over all XCDs 33 us).
     if (want > a.rows / 256) want = a.rows / 256;
+    if (want >= 8) want = want / 8 * 8;
     if (want < 1) want = 1;
   } else {
     want = want / 8 * 8;   // a multiple of 8: one XCD per residue (see k_fgemm)

@@ -123,3 +123,10 @@ def test_deep_heads_and_wide_layer_error_paths():
 @pytest.mark.parametrize("G,atoms,S,sources", [(60, (20, 30), 2, (1,)), (260, (1, 2), 3, None), (40, (50, 60), 5, (0, 0, 0, 0, 3))])
 def test_deep_heads_rows_unevenly_over_sources(G, atoms, S, sources):
     _run(G, atoms, H=100, Hh=130, D=2, S=S, seed=G + S, sources=sources)
+
+
+# Splits by the XCD (a multiple of eight) or one after the other; one source, whose row products have an epilogue of their own,
+# with few rows and with enough for the 256 x 128 tiles
+@pytest.mark.parametrize("G,atoms,S", [(80, (20, 30), 1), (80, (50, 60), 1), (80, (50, 60), 2), (5, (3, 9), 1), (200, (655, 655), 1)])
+def test_deep_heads_split_orders_and_one_source(G, atoms, S):
+    _run(G, atoms, H=100, Hh=130, D=2, S=S, seed=G + S)
