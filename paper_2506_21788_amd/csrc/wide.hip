@@ -51,7 +51,8 @@ struct FCfg {
   static_assert(NF % NW == 0, "fragments per step must divide among the wavefronts");
 };
 
-template <int WI, int WJ, int EPI, int NW = 4, int KC = 2>
+// RB: rows per batch of the row epilogue
+template <int WI, int WJ, int EPI, int RB = 8, int NW = 4, int KC = 2>
 __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemmArgs p) {
   static_assert(EPI == EPI_ROW || EPI == EPI_PART, "results as T fragments come from k_fgemm_ad");
   using C = FCfg<WI, WJ, NW, KC>;
@@ -220,75 +221,78 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
         for (int v = 0; v < 16; ++v)
           stg[(wi * 32 + 8 * (v >> 2) + 4 * g + (v & 3)) * 128 + wj * 64 + j * 32 + x] = acc[i][j][v];
       __syncthreads();
-      // the rows' places and residuals are asked for together, before the first store (the compiler cannot move a load
+      // the places and residuals of RB rows are asked for together, before the first store (the compiler cannot move a load
       // across a store, so with each next to its use the eight rows were a chain of eight memory latencies)
-      long rows[8];
-      float res1[8][4], res2[8][4];
 #pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int lrow = rr * 8 + r8;
-        const int prow = (i0 + (lrow >> 5) * WI + i) * 32 + (lrow & 31);
-        rows[rr] = prow < mvalid ? prow : mvalid - 1;
-      }
-      if (p.row_idx) {   // scatter to the caller's rows
+      for (int r0 = 0; r0 < 8; r0 += RB) {
+        int rows[RB];
+        float res1[RB][4], res2[RB][4];
 #pragma unroll
-        for (int rr = 0; rr < 8; ++rr) rows[rr] = p.row_idx[pos0 + rows[rr] - pad0];
-      }
-      auto residual = [&](const float* base, long ld, float (&o)[8][4]) {
-        if (p.vec == 4 && col + 4 <= p.ncol_f) {
-#pragma unroll
-          for (int rr = 0; rr < 8; ++rr) {
-            const float4 t = *reinterpret_cast<const float4*>(base + rows[rr] * ld + col);
-            o[rr][0] = t.x; o[rr][1] = t.y; o[rr][2] = t.z; o[rr][3] = t.w;
-          }
-        } else if (p.vec >= 2 && col + 4 <= p.ncol_f) {
-#pragma unroll
-          for (int rr = 0; rr < 8; ++rr)
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-              const float2 t = *reinterpret_cast<const float2*>(base + rows[rr] * ld + col + 2 * h2);
-              o[rr][2 * h2] = t.x; o[rr][2 * h2 + 1] = t.y;
-            }
-        } else {
-#pragma unroll
-          for (int rr = 0; rr < 8; ++rr)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) o[rr][t] = col + t < p.ncol_f ? base[rows[rr] * ld + col + t] : 0.f;
+        for (int u = 0; u < RB; ++u) {
+          const int lrow = (r0 + u) * 8 + r8;
+          const int prow = (i0 + (lrow >> 5) * WI + i) * 32 + (lrow & 31);
+          rows[u] = prow < mvalid ? prow : mvalid - 1;
         }
-      };
-      if (p.Cf && p.r1) residual(p.r1, p.ld1, res1);
-      if (p.Cf && p.r2) residual(p.r2, p.ld2, res2);
+        if (p.row_idx) {   // scatter to the caller's rows
 #pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int lrow = rr * 8 + r8;
-        const int prow = (i0 + (lrow >> 5) * WI + i) * 32 + (lrow & 31);
-        if (prow < mvalid && col_ok) {
-          const long row = rows[rr];
-          const float4 sv = *reinterpret_cast<const float4*>(&stg[lrow * 128 + c4]);
-          float val[4] = {sv.x + bias4[0], sv.y + bias4[1], sv.z + bias4[2], sv.w + bias4[3]};
-          if (p.Cf && col < p.ncol_f) {
-            float* cp = p.Cf + row * p.ldc + col;
+          for (int u = 0; u < RB; ++u) rows[u] = p.row_idx[pos0 + rows[u] - pad0];
+        }
+        auto residual = [&](const float* base, long ld, float (&o)[RB][4]) {
+          if (p.vec == 4 && col + 4 <= p.ncol_f) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              if (p.r1) val[t] += res1[rr][t];
-              if (p.r2) val[t] += res2[rr][t];
+            for (int u = 0; u < RB; ++u) {
+              const float4 t = *reinterpret_cast<const float4*>(base + rows[u] * ld + col);
+              o[u][0] = t.x; o[u][1] = t.y; o[u][2] = t.z; o[u][3] = t.w;
             }
-            if (p.vec == 4 && col + 4 <= p.ncol_f) {
-              *reinterpret_cast<float4*>(cp) = make_float4(val[0], val[1], val[2], val[3]);
-            } else if (p.vec >= 2 && col + 4 <= p.ncol_f) {
+          } else if (p.vec >= 2 && col + 4 <= p.ncol_f) {
 #pragma unroll
-              for (int h2 = 0; h2 < 2; ++h2) *reinterpret_cast<float2*>(cp + 2 * h2) = make_float2(val[2 * h2], val[2 * h2 + 1]);
-            } else {
+            for (int u = 0; u < RB; ++u)
 #pragma unroll
-              for (int t = 0; t < 4; ++t)
-                if (col + t < p.ncol_f) cp[t] = val[t];
-            }
+              for (int h2 = 0; h2 < 2; ++h2) {
+                const float2 t = *reinterpret_cast<const float2*>(base + rows[u] * ld + col + 2 * h2);
+                o[u][2 * h2] = t.x; o[u][2 * h2 + 1] = t.y;
+              }
+          } else {
+#pragma unroll
+            for (int u = 0; u < RB; ++u)
+#pragma unroll
+              for (int t = 0; t < 4; ++t) o[u][t] = col + t < p.ncol_f ? base[rows[u] * ld + col + t] : 0.f;
           }
-          if (p.Cb) {   // all columns of the tile (the pitch is a multiple of 128)
-            uint2 w;
-            w.x = pack_bf16x2(val[0], val[1]);
-            w.y = pack_bf16x2(val[2], val[3]);
-            *reinterpret_cast<uint2*>(p.Cb + row * p.ldcb + col) = w;
+        };
+        if (p.Cf && p.r1) residual(p.r1, p.ld1, res1);
+        if (p.Cf && p.r2) residual(p.r2, p.ld2, res2);
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+          const int lrow = (r0 + u) * 8 + r8;
+          const int prow = (i0 + (lrow >> 5) * WI + i) * 32 + (lrow & 31);
+          if (prow < mvalid && col_ok) {
+            const long row = rows[u];
+            const float4 sv = *reinterpret_cast<const float4*>(&stg[lrow * 128 + c4]);
+            float val[4] = {sv.x + bias4[0], sv.y + bias4[1], sv.z + bias4[2], sv.w + bias4[3]};
+            if (p.Cf && col < p.ncol_f) {
+              float* cp = p.Cf + row * p.ldc + col;
+#pragma unroll
+              for (int t = 0; t < 4; ++t) {
+                if (p.r1) val[t] += res1[u][t];
+                if (p.r2) val[t] += res2[u][t];
+              }
+              if (p.vec == 4 && col + 4 <= p.ncol_f) {
+                *reinterpret_cast<float4*>(cp) = make_float4(val[0], val[1], val[2], val[3]);
+              } else if (p.vec >= 2 && col + 4 <= p.ncol_f) {
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) *reinterpret_cast<float2*>(cp + 2 * h2) = make_float2(val[2 * h2], val[2 * h2 + 1]);
+              } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                  if (col + t < p.ncol_f) cp[t] = val[t];
+              }
+            }
+            if (p.Cb) {   // all columns of the tile (the pitch is a multiple of 128)
+              uint2 w;
+              w.x = pack_bf16x2(val[0], val[1]);
+              w.y = pack_bf16x2(val[2], val[3]);
+              *reinterpret_cast<uint2*>(p.Cb + row * p.ldcb + col) = w;
+            }
           }
         }
       }
@@ -314,7 +318,7 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
   }
 }
 
-template <int WI, int WJ, int EPI, int NW = 4, int KC = 2>
+template <int WI, int WJ, int EPI, int RB = 8, int NW = 4, int KC = 2>
 static int32_t launch_fgemm_t(hipStream_t st, const FGemmArgs& a) {
   using C = FCfg<WI, WJ, NW, KC>;
   // (an even number of steps per workgroup: contraction counts are multiples of two steps)
@@ -330,12 +334,12 @@ static int32_t launch_fgemm_t(hipStream_t st, const FGemmArgs& a) {
   HGNN_REQUIRE(gx <= 2147483647L && groups <= 65535, HGNN_ERR_OVERFLOW, "fragment GEMM: grid too large");
   static bool lds_set = false;   // the ring may exceed the default dynamic LDS limit: raise it once per variant
   if (!lds_set) {
-    HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fgemm<WI, WJ, EPI, NW, KC>),
+    HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fgemm<WI, WJ, EPI, RB, NW, KC>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
     lds_set = true;
   }
   ProfScope ps(a.tag, st);
-  k_fgemm<WI, WJ, EPI, NW, KC><<<dim3((unsigned)gx, 1, groups), 64 * NW, C::LDS_BYTES, st>>>(a);
+  k_fgemm<WI, WJ, EPI, RB, NW, KC><<<dim3((unsigned)gx, 1, groups), 64 * NW, C::LDS_BYTES, st>>>(a);
   HGNN_LAUNCH_CHECK("k_fgemm");
   return HGNN_OK;
 }
@@ -1419,8 +1423,13 @@ int32_t launch_fgemm_rows(hipStream_t st, const FGemmArgs& a0) {
   a.vec = row_io_width(a);
   // few rows (atoms, graphs): 128 x 128 tiles give the launch enough workgroups to cover the chip
   const long big_tiles = (long)((a.nI + 7) / 8) * (a.nJ / 4) * (a.grp_ptr ? a.S : 1);
-  if (big_tiles < 4L * num_cus()) return launch_fgemm_t<2, 2, EPI_ROW>(st, a);
-  return launch_fgemm_t<4, 2, EPI_ROW>(st, a);
+  const bool small = big_tiles < 4L * num_cus();
+  // One group without residuals has nothing to ask for but the places of the rows, and with 126 instead of 150 registers
+  // (2 x 2 blocks) a fourth workgroup fits a compute unit: 16,000 rows, 866 and 889 columns, twelve products 444 -> 405 us.
+  // With more groups the batches win all the same: 4,600 rows of 5 groups 322 -> 296
+  if (a.grp_ptr && a.S == 1 && !a.r1 && !a.r2)
+    return small ? launch_fgemm_t<2, 2, EPI_ROW, 1>(st, a) : launch_fgemm_t<4, 2, EPI_ROW, 1>(st, a);
+  return small ? launch_fgemm_t<2, 2, EPI_ROW>(st, a) : launch_fgemm_t<4, 2, EPI_ROW>(st, a);
 }
 int32_t launch_fgemm_rows_T(hipStream_t st, const FGemmArgs& a) { return launch_fgemm_ad(st, a); }
 
