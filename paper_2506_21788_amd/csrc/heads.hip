@@ -185,11 +185,49 @@ __global__ void k_pool_bwd(int N, int G, int H, int mode, const int32_t* __restr
 // ---------------------------------------------------------------------------------------------
 inline bool any_H(int H) { return H >= 1 && H <= 1024; }
 
-__global__ void k_embed_fwd_any(int H, const int32_t* __restrict__ Z, const float* __restrict__ emb, float* __restrict__ h) {
-  const int i = blockIdx.x;   // one workgroup per atom
-  int z = Z[i];
-  z = z < 0 ? 0 : (z > HGNN_ZMAX ? HGNN_ZMAX : z);
-  for (int c = threadIdx.x; c < H; c += blockDim.x) h[(size_t)i * H + c] = emb[(long)z * H + c];
+// Rows of any width as flat runs: a workgroup takes R consecutive rows, finds out what depends on the row once per row, and
+// walks the R * H elements with all threads. A workgroup per row idles most of its lanes where rows are narrow (one of 64 at
+// H = 1), and a launch holds fewer than 2^32 threads; a thread per element of the whole tensor does the row's part for every
+// element and divides by H in 64 bits. Embedding, forward / pooling, reverse, thread per element -> workgroup per row -> runs:
+// 100,000 rows of 65 columns 11.7 / 38 us -> 25 / 61 -> 8.7 / 10.6, of 866 129 / 862 -> 75 / 293 -> 64 / 183; a million of 24
+// 43 / 232 -> 215 / 341 -> 19 / 51; 7,734 of 866 12 / 30 -> 8.3 / 17 -> 8.7 / 11.
+constexpr int ROWS_MAX = 256, ROW_ELEMS = 4096;
+struct RowRuns {
+  int R;
+  unsigned magic;   // ceil(2^32 / H): element / H is the upper half of element * magic (elements < 2^13, H <= 1024)
+  __device__ __forceinline__ int row(int e) const { return magic ? (int)__umulhi((unsigned)e, magic) : e; }
+};
+static RowRuns row_runs(int N, int H) {
+  RowRuns r;
+  r.R = ROW_ELEMS / H < 1 ? 1 : ROW_ELEMS / H > ROWS_MAX ? ROWS_MAX : ROW_ELEMS / H;
+  while (r.R > 1 && (N + r.R - 1) / r.R < 4 * num_cus()) r.R = (r.R + 1) / 2;   // (few rows: workgroups for every compute unit)
+  r.magic = H == 1 ? 0u : (unsigned)(((1ull << 32) + H - 1) / H);
+  return r;
+}
+static unsigned row_run_grid(int N, const RowRuns& r) { return (unsigned)(((int64_t)N + r.R - 1) / r.R); }
+
+__global__ void __launch_bounds__(256)
+k_embed_fwd_any(int N, int H, RowRuns rr, const int32_t* __restrict__ Z, const float* __restrict__ emb, float* __restrict__ h) {
+  __shared__ int first[ROWS_MAX];   // of the row's element in the table
+  const int64_t row0 = (int64_t)blockIdx.x * rr.R;
+  const int n = N - row0 < rr.R ? (int)(N - row0) : rr.R, total = n * H, tid = threadIdx.x;
+  if (tid < n) {
+    const int z = Z[row0 + tid];
+    first[tid] = (z < 0 ? 0 : z > HGNN_ZMAX ? HGNN_ZMAX : z) * H;
+  }
+  __syncthreads();
+  float* o = h + row0 * H;
+  for (int e0 = tid; e0 < total; e0 += 4 * 256) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = e0 + u * 256 < total ? e0 + u * 256 : total - 1, r = rr.row(e);
+      v[u] = emb[first[r] + e - r * H];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * 256 < total) o[e0 + u * 256] = v[u];
+  }
 }
 
 // block (z, chunk): the atoms of the chunk with Z == z are listed in ascending order (each thread scans 8 consecutive
@@ -263,18 +301,32 @@ k_pool_fwd_any(int H, int mode, const int32_t* __restrict__ graph_off, const flo
   }
 }
 
-// one workgroup per atom: its graph is found once (by scalar loads) and not by every element (7,734 atoms of 866 columns:
-// 43 -> 22 us)
-__global__ void k_pool_bwd_any(int G, int H, int mode, const int32_t* __restrict__ graph_off,
-                               const float* __restrict__ g_p, float* __restrict__ g_h, int accumulate) {
-  const int i = blockIdx.x;
-  const int g = find_graph_of_atom(graph_off, G, i);
-  const int n = graph_off[g + 1] - graph_off[g];
-  const float sc = (mode == HGNN_POOL_MEAN) ? 1.0f / (float)n : 1.0f;
-  for (int c = threadIdx.x; c < H; c += blockDim.x) {
-    float v = g_p[(size_t)g * H + c] * sc;
-    if (accumulate) v += g_h[(size_t)i * H + c];
-    g_h[(size_t)i * H + c] = v;
+// (see RowRuns: an atom's graph is found once and not by every element)
+__global__ void __launch_bounds__(256)
+k_pool_bwd_any(int N, int G, int H, RowRuns rr, int mode, const int32_t* __restrict__ graph_off,
+               const float* __restrict__ g_p, float* __restrict__ g_h, int accumulate) {
+  __shared__ int graph[ROWS_MAX];
+  __shared__ float scale[ROWS_MAX];
+  const int64_t row0 = (int64_t)blockIdx.x * rr.R;
+  const int n = N - row0 < rr.R ? (int)(N - row0) : rr.R, total = n * H, tid = threadIdx.x;
+  if (tid < n) {
+    const int g = find_graph_of_atom(graph_off, G, (int)row0 + tid);
+    graph[tid] = g;
+    scale[tid] = (mode == HGNN_POOL_MEAN) ? 1.0f / (float)(graph_off[g + 1] - graph_off[g]) : 1.0f;
+  }
+  __syncthreads();
+  float* o = g_h + row0 * H;
+  for (int e0 = tid; e0 < total; e0 += 4 * 256) {
+    float v[4], old[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = e0 + u * 256 < total ? e0 + u * 256 : total - 1, r = rr.row(e);
+      old[u] = accumulate ? o[e] : 0.f;
+      v[u] = g_p[(size_t)graph[r] * H + (e - r * H)] * scale[r];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * 256 < total) o[e0 + u * 256] = accumulate ? v[u] + old[u] : v[u];
   }
 }
 
@@ -618,9 +670,6 @@ using namespace hgnn;
 // is the one-hidden-layer case of the deep heads (same buffer layout)
 static bool heads_need_fragment_path(int H, int Hh) { return !valid_H(H) || Hh != H; }
 
-// threads of a workgroup that walks the H columns of one row
-static int row_threads(int H) { return H >= 256 ? 256 : (H + 63) / 64 * 64; }
-
 extern "C" int32_t hgnn_embed_fwd(void* stream, int32_t N, int32_t H, const int32_t* Z, const float* emb, float* h) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   HGNN_REQUIRE(N >= 0 && any_H(H), HGNN_ERR_BAD_SHAPE, "embed_fwd: bad N or H");
@@ -628,7 +677,10 @@ extern "C" int32_t hgnn_embed_fwd(void* stream, int32_t N, int32_t H, const int3
   HGNN_REQUIRE(Z && emb && h, HGNN_ERR_NULLPTR, "embed_fwd: null pointer");
   ProfScope ps(PT_EMBED, st);
   if (valid_H(H)) k_embed_fwd<<<nb64((int64_t)N * (H / 4), 256), 256, 0, st>>>(N, H, Z, emb, h);
-  else k_embed_fwd_any<<<N, row_threads(H), 0, st>>>(H, Z, emb, h);
+  else {
+    const RowRuns r = row_runs(N, H);
+    k_embed_fwd_any<<<row_run_grid(N, r), 256, 0, st>>>(N, H, r, Z, emb, h);
+  }
   HGNN_LAUNCH_CHECK("k_embed_fwd");
   return HGNN_OK;
 }
@@ -733,7 +785,10 @@ extern "C" int32_t hgnn_pool_by_graph_bwd(void* stream, int32_t N, int32_t G, in
   HGNN_REQUIRE(G > 0 && graph_off && g_p && g_h, HGNN_ERR_NULLPTR, "pool_bwd: null pointer");
   ProfScope ps(PT_POOL, st);
   if (valid_H(H)) k_pool_bwd<<<nb64((int64_t)N * (H / 4), 256), 256, 0, st>>>(N, G, H, mode, graph_off, g_p, g_h, accumulate);
-  else k_pool_bwd_any<<<N, row_threads(H), 0, st>>>(G, H, mode, graph_off, g_p, g_h, accumulate);
+  else {
+    const RowRuns r = row_runs(N, H);
+    k_pool_bwd_any<<<row_run_grid(N, r), 256, 0, st>>>(N, G, H, r, mode, graph_off, g_p, g_h, accumulate);
+  }
   HGNN_LAUNCH_CHECK("k_pool_bwd");
   return HGNN_OK;
 }

@@ -136,3 +136,34 @@ def test_embedding_at_other_widths(N, H, elements):
     want = np.zeros((B.ZMAX + 1, H))
     np.add.at(want, Z, g.astype(np.float64))
     assert relerr(ge.cpu().numpy(), want) <= TOL["f32"]["grad"]
+
+
+# whole rows as flat runs: one row up to 256 rows per workgroup, a last run that is short, more elements and rows than a launch
+# holds threads; values are copied, or multiplied once (and added once): equal bits
+@pytest.mark.parametrize("N,H", [(1, 1), (3, 1024), (1000, 65), (5000, 24), (300001, 24), (40001, 100), (9000, 333), (2049, 1023),
+                                 (70_000_001, 1), (70_000_001, 3)])
+def test_embedding_and_pooled_gradient_rows_at_other_widths(N, H):
+    import torch
+    from paper_2506_21788_amd import binding as B
+    print("rows", N, H, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N + H)
+    Z = torch.randint(0, B.ZMAX + 1, (N,), dtype=torch.int32, device="cuda", generator=gen)
+    emb = torch.randn((B.ZMAX + 1, H), device="cuda", generator=gen)
+    h = torch.full((N, H), float("nan"), device="cuda")
+    B.embed_fwd(N, H, Z, emb, h)
+    for a in range(0, N, 1 << 22):
+        assert torch.equal(h[a:a + (1 << 22)], emb[Z[a:a + (1 << 22)].long()])
+    off = torch.tensor([0, N // 3, N // 3, N - N // 7, N], dtype=torch.int32, device="cuda")   # one graph is empty
+    G = 4
+    g_p = torch.randn((G, H), device="cuda", generator=gen)
+    graph = torch.repeat_interleave(torch.arange(G, device="cuda"), off.diff().long())
+    for mode, scale in ((B.POOL_SUM, torch.ones(G, device="cuda")), (B.POOL_MEAN, 1.0 / off.diff().float())):
+        want = g_p * scale[:, None]
+        got = torch.full((N, H), float("nan"), device="cuda")
+        B.pool_by_graph_bwd(N, G, H, mode, off, g_p, got, False)
+        B.pool_by_graph_bwd(N, G, H, mode, off, g_p, h, True)
+        for a in range(0, N, 1 << 22):
+            w = want[graph[a:a + (1 << 22)]]
+            assert torch.equal(got[a:a + (1 << 22)], w)
+            if mode == B.POOL_SUM:
+                assert torch.equal(h[a:a + (1 << 22)], w + emb[Z[a:a + (1 << 22)].long()])
