@@ -232,8 +232,8 @@ k_embed_fwd_any(int N, int H, RowRuns rr, const int32_t* __restrict__ Z, const f
 
 // block (z, chunk): the atoms of the chunk with Z == z are listed in ascending order (each thread scans 8 consecutive
 // atoms, an exclusive scan over the threads places its matches), then every column is summed over that list, its rows asked
-// for eight at a time (blockIdx.z: 256 columns). 7,734 atoms of 866 columns: 66 -> 19 us against one workgroup for all columns,
-// a scan by one thread and one row at a time
+// for eight at a time (slabs of 256 columns, dealt to the workgroups in z). 7,734 atoms of 866 columns: 66 -> 19 us against one
+// workgroup for all columns, a scan by one thread and one row at a time
 __global__ void __launch_bounds__(256)
 k_embed_bwd_part_any(int N, int H, const int32_t* __restrict__ Z, const float* __restrict__ g_h,
                      float* __restrict__ part /*[nchunk][ZMAX+1][H]*/) {
@@ -269,17 +269,17 @@ k_embed_bwd_part_any(int N, int H, const int32_t* __restrict__ Z, const float* _
   for (int u = 0; u < 8; ++u)
     if (m[u]) list[o++] = lo + tid * 8 + u;
   __syncthreads();
-  const int c = blockIdx.z * 256 + tid;
-  if (c >= H) return;
-  float acc = 0.f;
-  for (int k = 0; k < total; k += 8) {   // (the last batch clamped, then left out)
-    float v[8];
+  for (int c = blockIdx.z * 256 + tid; c < H; c += gridDim.z * 256) {
+    float acc = 0.f;
+    for (int k = 0; k < total; k += 8) {   // (the last batch clamped, then left out)
+      float v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = g_h[(size_t)list[k + u < total ? k + u : total - 1] * H + c];
+      for (int u = 0; u < 8; ++u) v[u] = g_h[(size_t)list[k + u < total ? k + u : total - 1] * H + c];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc += k + u < total ? v[u] : 0.f;
+      for (int u = 0; u < 8; ++u) acc += k + u < total ? v[u] : 0.f;
+    }
+    part[((size_t)chunk * (HGNN_ZMAX + 1) + z) * H + c] = acc;
   }
-  part[((size_t)chunk * (HGNN_ZMAX + 1) + z) * H + c] = acc;
 }
 
 // block (graph, 64-column slab): 4 row phases take every fourth atom, then the phases are added in order
@@ -701,7 +701,11 @@ static int32_t embed_bwd_launch(hipStream_t st, int32_t N, int32_t H, const int3
   ProfScope ps(PT_EMBED, st);
   if (nchunk > 0) {
     if (valid_H(H)) k_embed_bwd_part<<<dim3(HGNN_ZMAX + 1, nchunk), 1024, 0, st>>>(N, H, Z, g_h, part);
-    else k_embed_bwd_part_any<<<dim3(HGNN_ZMAX + 1, nchunk, (H + 255) / 256), 256, 0, st>>>(N, H, Z, g_h, part);
+    else {
+      // each slab lists the chunk's matches for itself: slabs of their own only up to about eight workgroups per compute unit
+      const int room = 8 * num_cus() / ((HGNN_ZMAX + 1) * nchunk), slabs = (H + 255) / 256;
+      k_embed_bwd_part_any<<<dim3(HGNN_ZMAX + 1, nchunk, room < 1 ? 1 : room < slabs ? room : slabs), 256, 0, st>>>(N, H, Z, g_h, part);
+    }
     HGNN_LAUNCH_CHECK("k_embed_bwd_part");
   }
   k_embed_bwd_sum<<<((HGNN_ZMAX + 1) * H + 255) / 256, 256, 0, st>>>(nchunk, H, part, g_emb);

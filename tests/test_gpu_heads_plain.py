@@ -167,3 +167,9 @@ def test_embedding_and_pooled_gradient_rows_at_other_widths(N, H):
             assert torch.equal(got[a:a + (1 << 22)], w)
             if mode == B.POOL_SUM:
                 assert torch.equal(h[a:a + (1 << 22)], w + emb[Z[a:a + (1 << 22)].long()])
+
+
+# the column slabs of the embedding's gradient: workgroups of their own for few chunks of atoms, dealt to fewer for many
+@pytest.mark.parametrize("N,H", [(2048, 1000), (10241, 600), (22529, 1000), (45057, 300)])
+def test_embedding_gradient_of_many_atoms_at_other_widths(N, H):
+    test_embedding_at_other_widths(N, H, 20)
