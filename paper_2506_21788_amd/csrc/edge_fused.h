@@ -103,7 +103,7 @@ struct EdgeBwdArgs {
   const int32_t* row_ptr = nullptr;   // [N+1], the rows of dst
   int N = 0;
 };
-// The caller passes this to the launch_segsum_vm call that follows (the source-sorted sum: one wavefront per atom as
+// The caller passes this to the launch_segsum_vm call that follows (the source-sorted sum: a wavefront for every atom as
 // well), which adds the partials on its way; a launch of its own for that would cost about 20 us.
 inline DsumFix edge_bwd_dsum_fix(const EdgeBwdArgs& a) { return DsumFix{a.row_ptr, a.dpart, a.gP, a.ldgP}; }
 // edges per unit of those sums: the kernel's 64-edge tile. Its two halves are walked by two wavefronts each and the
@@ -134,7 +134,7 @@ int32_t launch_wgrad_frag_recompute(hipStream_t st, int H, int64_t E, const int3
 
 // out[i, 0..H) (row pitch ldo) = sum over t in ptr[i]:ptr[i+1] of X[perm ? perm[t] : t, :], X v-major (bf16 or
 // fp32), accumulated in fp32
-// fix (optional): wavefront i also finishes row i of the g_P that the reverse edge kernel started (H = 128 or 256)
+// fix (optional): wavefront i also finishes row i of the g_P that the reverse edge kernel started
 // dot (optional): [E] out, dot[e] = sum_c wdot[c] X[e][c] for every edge of the list
 int32_t launch_segsum_vm(hipStream_t st, int H, bool bf16, int N, int64_t E, const int32_t* ptr, const int32_t* perm,
                          const void* X_vm, float* out, int ldo, int tag, const float* wdot = nullptr,

@@ -138,14 +138,11 @@ int32_t launch_to_frag(hipStream_t st, const ToFragArgs& a);
 // it again (one pair of launches per layer and head layer, 43 + 20 us each at 7,700 atoms and 866 columns)
 int32_t launch_frag_colsum(hipStream_t st, const ToFragArgs& a, float* dest, long dest_grp_stride);
 
-// dest[group * dest_grp_stride + c] = sum over the rows (of each group) of w[row] * f(X[row][c]), c < ncol;
-// f as in ToFragArgs::mode, w optional; fixed summation order
+// dest[group * dest_grp_stride + c] = sum over the rows (of each group) of w[row] * silu(X[row][c]), c < ncol; fixed
+// summation order
 struct ColsumRowsArgs {
   const float* X = nullptr;
   long ldx = 0;
-  const float* Z = nullptr;
-  long ldz = 0;
-  int mode = 0;
   const float* w = nullptr;
   int M = 0;                          // rows (ungrouped), or the largest possible group
   int ncol = 0;

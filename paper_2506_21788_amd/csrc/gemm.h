@@ -121,7 +121,6 @@ int32_t launch_wgrad_multi(hipStream_t st, int H, bool bf16, const WgradArgs* jo
 int32_t launch_wgrad_own_rows(hipStream_t st, int H, bool bf16, const WgradArgs* jobs, int njobs);
 int wgrad_splits(int64_t M);
 size_t wgrad_partial_floats(int H, int64_t M, int nblocks, int S);
-int32_t launch_wgrad(hipStream_t st, int H, bool bf16, const WgradArgs& a);
 
 // ---- column sums ----------------------------------------------------------------------------
 // out[c] = sum_r w[r] * f(X[r][c])   (w optional; f = identity or silu), grouped like the above
@@ -142,7 +141,6 @@ struct ColsumArgs {
   float* w_partial = nullptr;   // scratch, colsum_partial_floats() with H = 1
 };
 size_t colsum_partial_floats(int H, int64_t M, int S);
-int32_t launch_colsum(hipStream_t st, int H, const ColsumArgs& a);
 int32_t launch_colsum_multi(hipStream_t st, int H, const ColsumArgs* jobs, int njobs);   // up to four in one launch
 
 // dest[blk][i] (+ grp*grp_dest_stride) = sum over s < nsplit of partial[((grp*nsplit + s)*nblk + blk)*blk_elems + i],

@@ -1544,8 +1544,6 @@ int32_t launch_wgrad_own_rows(hipStream_t st, int H, bool bf16, const WgradArgs*
   return bf16 ? launch_wgrad_h<true>(st, H, jobs, njobs, true) : launch_wgrad_h<false>(st, H, jobs, njobs, true);
 }
 
-int32_t launch_wgrad(hipStream_t st, int H, bool bf16, const WgradArgs& a) { return launch_wgrad_multi(st, H, bf16, &a, 1); }
-
 // ---------------------------------------------------------------------------------------------
 // column sums
 // ---------------------------------------------------------------------------------------------
@@ -1671,6 +1669,5 @@ int32_t launch_colsum_multi(hipStream_t st, int H, const ColsumArgs* jobs, int n
   }
   return HGNN_OK;
 }
-int32_t launch_colsum(hipStream_t st, int H, const ColsumArgs& a) { return launch_colsum_multi(st, H, &a, 1); }
 
 }  // namespace hgnn

@@ -326,7 +326,7 @@ extern "C" int32_t hgnn_multihead_deep_bwd(void* stream, int32_t N, int32_t G, i
     const float* gout = hd == 0 ? g_energy : w.gq;   // per-row upstream scalar, caller's row order
     {  // output layer: g_wo = sum gout * silu(z_D), g_bo = sum gout
       ColsumRowsArgs c;
-      c.X = s.z[hd][D]; c.ldx = d.Hhp; c.mode = 1; c.w = gout; c.M = M; c.ncol = Hh;
+      c.X = s.z[hd][D]; c.ldx = d.Hhp; c.w = gout; c.M = M; c.ncol = Hh;
       c.grp_ptr = gptr; c.S = S; c.row_idx = ridx;
       c.partial = w.cs_partial; c.dest = gWhead + o.wo[hd]; c.dest_grp_stride = o.per;
       HGNN_TRY(launch_colsum_rows(st, c));

@@ -116,47 +116,9 @@ size_t scan_scratch_ints(int64_t n) {
   return (size_t)(2 * (nb + 2));  // int64 entries counted in int32 units
 }
 
-// short inputs: one workgroup walks the array in chunks of SCAN_BLK with a running carry (one launch instead of three);
-// leaves the same block sums and grand total behind as the three-kernel form
-__global__ void k_scan_small(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
-                             long long* __restrict__ blocksum) {
-  __shared__ int sh[SCAN_T];
-  long long carry = 0;
-  const int64_t nb = (n + SCAN_BLK - 1) / SCAN_BLK;
-  for (int64_t b = 0; b < nb; ++b) {
-    const int64_t base = b * SCAN_BLK + (int64_t)threadIdx.x * SCAN_PER;
-    int v[SCAN_PER];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < SCAN_PER; ++k) {
-      v[k] = (base + k < n) ? in[base + k] : 0;
-      s += v[k];
-    }
-    int tot;
-    int ex = block_exclusive_scan_256(s, &tot, sh);
-#pragma unroll
-    for (int k = 0; k < SCAN_PER; ++k) {
-      if (base + k < n) out[base + k] = (int32_t)(carry + ex);
-      ex += v[k];
-    }
-    if (threadIdx.x == 0) blocksum[b] = carry;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) {
-    blocksum[nb] = carry;
-    out[n] = (int32_t)carry;
-  }
-}
-constexpr int64_t SCAN_SMALL_MAX = 16 * SCAN_BLK;
-
 int32_t exclusive_scan_i32(hipStream_t st, const int32_t* in, int32_t* out, int64_t n, int32_t* scratch) {
   long long* bs = reinterpret_cast<long long*>(scratch);
   int64_t nb = (n + SCAN_BLK - 1) / SCAN_BLK;
-  if (n <= SCAN_SMALL_MAX) {
-    k_scan_small<<<dim3(1), dim3(SCAN_T), 0, st>>>(in, out, n, bs);
-    HGNN_LAUNCH_CHECK("k_scan_small");
-    return HGNN_OK;
-  }
   if (nb > 0) {
     k_scan_local<<<dim3((unsigned)nb), dim3(SCAN_T), 0, st>>>(in, out, n, bs);
     HGNN_LAUNCH_CHECK("k_scan_local");
@@ -238,7 +200,7 @@ struct GMeta {
   float org[3];
   int nb[3];       // bins per lattice direction
   int R[3];        // search reach in bins
-  int bin_off;     // first global bin of this graph (filled after the scan)
+  int bin_off;     // first global bin of this graph (see first_bin())
   int periodic;
   int lo, hi;      // atom range
 };
@@ -431,6 +393,7 @@ static bool bin_by_graph(int N, int G) {
   return N <= BIN_GRAPHS_MAX && G <= BIN_GRAPHS_MAX && N <= (int64_t)BIN_GRAPH_MEAN * G;
 }
 constexpr int BG_BINS = 4096;    // bins of a graph counted in LDS; more: in the workspace
+constexpr int SR_HOME = 16;      // destination atoms of a work item of the search
 struct BinArgs {
   int N, G;
   const float* pos;
@@ -443,7 +406,6 @@ struct BinArgs {
   float4* spos;
   int32_t *status, *nlist;
   int2* list;
-  int home;                      // destination atoms of a work item
 };
 __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
   __shared__ GMeta m;
@@ -510,7 +472,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       const int b = b0 + tid * 4 + u;
       c[u] = b < nbins ? (in_lds ? hist[b] : __hip_atomic_load(&cnt[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
       own += c[u];
-      items += (c[u] + p.home - 1) / p.home;
+      items += (c[u] + SR_HOME - 1) / SR_HOME;
     }
     int ia = own, ii = items;
 #pragma unroll
@@ -536,7 +498,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       if (b < nbins) {
         p.bin_start[off + b] = ex;
         if (in_lds) hist[b] = ex; else cnt[b] = ex;   // from here on: the bin's next free record
-        for (int k = 0; k < c[u]; k += p.home, ++at) p.list[at] = make_int2(off + b, k);
+        for (int k = 0; k < c[u]; k += SR_HOME, ++at) p.list[at] = make_int2(off + b, k);
       }
       ex += c[u];
     }
@@ -574,19 +536,18 @@ __global__ void k_bin_atoms_count(int N, int G, const float* __restrict__ pos, c
 
 // atoms in bin order: their index (for the slow path) and (x, y, z, index) as one 16-byte record (the bin's count runs
 // down to its next free record); and, in the workgroups behind those of the atoms, the work list of the search: one
-// entry per `home` destination atoms of a non-empty bin (order does not matter)
-constexpr int SR_HOME = 16;
+// entry per SR_HOME destination atoms of a non-empty bin (order does not matter)
 __global__ void k_bin_place(int N, unsigned natom_blocks, const float* __restrict__ pos, const int32_t* __restrict__ atom_bin,
                             const int32_t* __restrict__ bin_start, int32_t* __restrict__ bin_cnt,
-                            int32_t* __restrict__ bin_atoms, float4* __restrict__ spos, int64_t maxbins, int home,
+                            int32_t* __restrict__ bin_atoms, float4* __restrict__ spos, int64_t maxbins,
                             int32_t* __restrict__ nlist, int2* __restrict__ list) {
   if (blockIdx.x >= natom_blocks) {
     const int64_t b = (int64_t)(blockIdx.x - natom_blocks) * blockDim.x + threadIdx.x;
     if (b >= maxbins) return;
     const int c = bin_start[b + 1] - bin_start[b];
     if (c <= 0) return;
-    int at = atomicAdd(nlist, (c + home - 1) / home);
-    for (int k = 0; k < c; k += home) list[at++] = make_int2((int)b, k);
+    int at = atomicAdd(nlist, (c + SR_HOME - 1) / SR_HOME);
+    for (int k = 0; k < c; k += SR_HOME) list[at++] = make_int2((int)b, k);
     return;
   }
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -635,7 +596,6 @@ struct SearchArgs {
   const int2* list;
   const int32_t* status;
   float rc;
-  int home;                  // destination atoms of a work item (at most SR_HOME)
   // count
   int32_t* deg;
   int32_t* colT_cnt;
@@ -675,7 +635,7 @@ __global__ void __launch_bounds__(256) k_search(SearchArgs p) {
     const int hb = it.x, h0 = it.y;
     const int hb_start = p.bin_start[hb];
     const int hb_cnt = p.bin_start[hb + 1] - hb_start;
-    const int nhome = hb_cnt - h0 < p.home ? hb_cnt - h0 : p.home;
+    const int nhome = hb_cnt - h0 < SR_HOME ? hb_cnt - h0 : SR_HOME;
     const int i_first = __float_as_int(p.spos[hb_start].w);
     const GMeta& m = p.meta[p.atom_graph[i_first]];
     const int nb0 = m.nb[0], nb1 = m.nb[1], nb2 = m.nb[2];
@@ -1160,15 +1120,11 @@ k_clear_and_check(int4* p, int64_t n, int N, int G, const int32_t* __restrict__ 
 
 static inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
-// destination atoms per work item, the same in the counting and the filling call
-static int home_atoms(int N) { (void)N; return SR_HOME; }
-
 static SearchArgs search_args(const NeighWs& w, int N, const float* pos, float rc) {
   SearchArgs a = {};
   a.N = N; a.pos = pos; a.meta = w.meta; a.atom_graph = w.atom_graph; a.bin_start = w.bin_start; a.spos = w.spos;
   a.nlist = w.status + 1; a.list = w.list; a.status = w.status; a.rc = rc;
   a.novf = w.status + 2; a.ovf_rows = w.ovf_rows;
-  a.home = home_atoms(N);
   return a;
 }
 
@@ -1217,10 +1173,9 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
     k_clear_and_check<<<nblk(w.nzeroed / 4, 256), 256, 0, st>>>(reinterpret_cast<int4*>(w.zeroed), w.nzeroed / 4, N, G,
                                                                 graph_off);
     HGNN_LAUNCH_CHECK("k_clear_and_check");
-    const int home = home_atoms(N);
     if (bin_by_graph(N, G)) {
       const BinArgs a = {N, G, pos, graph_off, cell, pbc, rc, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt, w.bin_start,
-                         w.bin_atoms, w.spos, w.status, w.status + 1, w.list, home};
+                         w.bin_atoms, w.spos, w.status, w.status + 1, w.list};
       k_bin_graphs<<<G, 256, 0, st>>>(a);
       HGNN_LAUNCH_CHECK("k_bin_graphs");
     } else {
@@ -1232,7 +1187,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
       HGNN_TRY(exclusive_scan_i32(st, w.bin_cnt, w.bin_start, w.maxbins, w.scan));
       const unsigned na = nblk(N, 256);
       k_bin_place<<<na + nblk(w.maxbins, 256), 256, 0, st>>>(N, na, pos, w.atom_bin, w.bin_start, w.bin_cnt, w.bin_atoms,
-                                                             w.spos, w.maxbins, home, w.status + 1, w.list);
+                                                             w.spos, w.maxbins, w.status + 1, w.list);
       HGNN_LAUNCH_CHECK("k_bin_place");
     }
   }

@@ -811,7 +811,7 @@ static int32_t launch_reduce_cols(hipStream_t st, const float* partial, int nspl
 }
 
 constexpr int CS_ROWS = 16;   // rows per partial of k_colsum_rows
-// partial[group][split][c] = sum over the split's rows of w * f(X[r][c])   (blockIdx.y: split, blockIdx.z: group)
+// partial[group][split][c] = sum over the split's rows of w * silu(X[r][c])   (blockIdx.y: split, blockIdx.z: group)
 __global__ void __launch_bounds__(256) k_colsum_rows(ColsumRowsArgs a, int nsplit) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= a.ncol) return;
@@ -823,7 +823,7 @@ __global__ void __launch_bounds__(256) k_colsum_rows(ColsumRowsArgs a, int nspli
     // all rows of the partial are asked for before the first is used (rows past the end: the last one again, left
     // out of the sum); summed in row order
     long sr[CS_ROWS];
-    float xv[CS_ROWS], zv[CS_ROWS], wv[CS_ROWS];
+    float xv[CS_ROWS], wv[CS_ROWS];
 #pragma unroll
     for (int u = 0; u < CS_ROWS; ++u) {
       const int r = r0 + u < n ? r0 + u : n - 1;
@@ -832,15 +832,11 @@ __global__ void __launch_bounds__(256) k_colsum_rows(ColsumRowsArgs a, int nspli
 #pragma unroll
     for (int u = 0; u < CS_ROWS; ++u) {
       xv[u] = a.X[sr[u] * a.ldx + c];
-      zv[u] = a.mode == 2 ? a.Z[sr[u] * a.ldz + c] : 0.f;
-      wv[u] = a.w ? a.w[sr[u]] : 1.f;
+      wv[u] = a.w[sr[u]];
     }
 #pragma unroll
     for (int u = 0; u < CS_ROWS; ++u) {
-      float v = xv[u];
-      if (a.mode == 1) v = silu_f(v);
-      else if (a.mode == 2) v *= dsilu_f(zv[u]);
-      if (a.w) v *= wv[u];
+      const float v = silu_f(xv[u]) * wv[u];
       if (r0 + u < n) s += v;
     }
   }
