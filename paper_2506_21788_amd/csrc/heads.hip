@@ -305,6 +305,7 @@ k_pool_fwd_any(int H, int mode, const int32_t* __restrict__ graph_off, const flo
 __global__ void __launch_bounds__(256)
 k_pool_bwd_any(int N, int G, int H, RowRuns rr, int mode, const int32_t* __restrict__ graph_off,
                const float* __restrict__ g_p, float* __restrict__ g_h, int accumulate) {
+#pragma clang fp contract(off)   // the scaled value is rounded before it is added
   __shared__ int graph[ROWS_MAX];
   __shared__ float scale[ROWS_MAX];
   const int64_t row0 = (int64_t)blockIdx.x * rr.R;
@@ -317,16 +318,17 @@ k_pool_bwd_any(int N, int G, int H, RowRuns rr, int mode, const int32_t* __restr
   __syncthreads();
   float* o = g_h + row0 * H;
   for (int e0 = tid; e0 < total; e0 += 4 * 256) {
-    float v[4], old[4];
+    float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int e = e0 + u * 256 < total ? e0 + u * 256 : total - 1, r = rr.row(e);
-      old[u] = accumulate ? o[e] : 0.f;
-      v[u] = g_p[(size_t)graph[r] * H + (e - r * H)] * scale[r];
+      const float old = accumulate ? o[e] : 0.f;
+      const float x = g_p[(size_t)graph[r] * H + (e - r * H)] * scale[r];
+      v[u] = accumulate ? x + old : x;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (e0 + u * 256 < total) o[e0 + u * 256] = accumulate ? v[u] + old[u] : v[u];
+      if (e0 + u * 256 < total) o[e0 + u * 256] = v[u];
   }
 }
 
