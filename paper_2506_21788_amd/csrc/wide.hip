@@ -1420,10 +1420,12 @@ int32_t launch_fgemm_rows(hipStream_t st, const FGemmArgs& a0) {
   // few rows (atoms, graphs): 128 x 128 tiles give the launch enough workgroups to cover the chip
   const long big_tiles = (long)((a.nI + 7) / 8) * (a.nJ / 4) * (a.grp_ptr ? a.S : 1);
   const bool small = big_tiles < 4L * num_cus();
-  // One group without residuals has nothing to ask for but the places of the rows, and with 126 instead of 150 registers
-  // (2 x 2 blocks) a fourth workgroup fits a compute unit: 16,000 rows, 866 and 889 columns, twelve products 444 -> 405 us.
-  // With more groups the batches win all the same: 4,600 rows of 5 groups 322 -> 296
-  if (a.grp_ptr && a.S == 1 && !a.r1 && !a.r2)
+  // The products of the heads have no residuals, so there is nothing to ask for but the places of the rows, and with 126 instead
+  // of 143 registers (2 x 2 blocks) a fourth workgroup fits a compute unit. Deep heads, forward, widths 866 and 889, batches of
+  // eight -> one row at a time: 16,000 atoms of one source 355 -> 337 us, of two 366 -> 347, of five 487 -> 469 (the one case that
+  // loses: 4,600 of five 243 -> 253). Layers have residuals in some of their products and keep the batches for all: small
+  // layers' forward passes lose 3 % one row at a time.
+  if (a.grp_ptr && !a.r1 && !a.r2)
     return small ? launch_fgemm_t<2, 2, EPI_ROW, 1>(st, a) : launch_fgemm_t<4, 2, EPI_ROW, 1>(st, a);
   return small ? launch_fgemm_t<2, 2, EPI_ROW>(st, a) : launch_fgemm_t<4, 2, EPI_ROW>(st, a);
 }
