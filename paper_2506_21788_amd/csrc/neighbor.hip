@@ -8,8 +8,8 @@
 // the (2R+1)^3 bins around it in LDS once (coalesced loads, no pointer chasing) and each wavefront then tests
 // whole groups of 64 candidates per destination atom out of LDS; hits are compacted with a ballot into a per-
 // wavefront LDS row, ranked there against each other (rows are short) and written out in (source, shift) order.
-// The same kernel counts (first call) and fills (second call). Rows with more hits than the LDS row holds go
-// through a slower path that ranks from memory. Only integer atomics are used (bin histogram / cursors); the
+// The same kernel counts (first call) and fills (second call). Rows with more hits than the LDS row holds are
+// walked again and ranked from memory. Only integer atomics are used (bin histogram / cursors); the
 // output does not depend on their order.
 //
 // The cutoff test is the one fixed in include/hgnn.h: each float operation is an explicitly rounded
@@ -194,6 +194,7 @@ __global__ void k_post_total(const long long* __restrict__ total, const int32_t*
 // ---------------------------------------------------------------------------------------------
 // per-graph metadata
 // ---------------------------------------------------------------------------------------------
+constexpr int SR_HOME = 16;   // most destination atoms of a work item of the search
 struct GMeta {
   float cell[9];   // rows a, b, c (zeros when not periodic)
   float inv[9];    // fractional = (pos - org) * inv   (row vector times matrix)
@@ -203,6 +204,7 @@ struct GMeta {
   int bin_off;     // first global bin of this graph (see first_bin())
   int periodic;
   int lo, hi;      // atom range
+  int home;        // destination atoms of a work item of the search
 };
 
 enum : int {
@@ -352,7 +354,10 @@ __global__ void k_graph_meta(int N, int G, const float* __restrict__ pos, const 
     }
   }
   graph_meta(lo, hi, periodic, cell + 9 * (size_t)g, mn, mx, rc, &meta[g], status);
-  if (lane == 0) meta[g].bin_off = first_bin(lo, g);
+  if (lane == 0) {
+    meta[g].bin_off = first_bin(lo, g);
+    meta[g].home = SR_HOME;
+  }
 }
 
 __device__ inline int find_graph(const int32_t* __restrict__ graph_off, int G, int i) {
@@ -393,7 +398,17 @@ static bool bin_by_graph(int N, int G) {
   return N <= BIN_GRAPHS_MAX && G <= BIN_GRAPHS_MAX && N <= (int64_t)BIN_GRAPH_MEAN * G;
 }
 constexpr int BG_BINS = 4096;    // bins of a graph counted in LDS; more: in the workspace
-constexpr int SR_HOME = 16;      // destination atoms of a work item of the search
+// Destination atoms per work item in a batch of N atoms whose graphs are binned one by one. Staging the candidates is paid once per
+// item, so large batches take 16; with fewer items than the chip holds workgroups (three per compute unit) the longest item is
+// what the launch takes, and items of cells with many images are long: thousands of candidate records, streamed through the LDS
+// again for every four destination atoms. Graphs of few candidates (HOME_FEW) keep 16, and so do large graphs (HOME_LARGE atoms),
+// whose bins are a cutoff wide and whose items are many. Whole graph, 16 -> 8 -> 4 per item: 64 crystals (4,096 atoms) 219 -> 140 -> 122
+// us, 543 mixed atoms 138 -> 94 -> 75, 5,530 mixed 147 -> 100 -> 84, 7,734 mixed 147 -> 101 -> 97, 9,680 mixed 128 -> 100 -> 113, 10,660 of
+// crystals 150 -> 129 -> 132; the other way for 7,105 of molecules 69 -> 73 -> 80, 15,138 of molecules 92 -> 100 -> 115, three cells of 2,000
+// 103 -> 122 -> 143, 38,889 mixed 256 -> 256 -> 308.
+static int search_home(int N) { return N <= 6144 ? 4 : N <= 12288 ? 8 : SR_HOME; }
+constexpr float HOME_FEW = 512.f;
+constexpr int HOME_LARGE = 1024;
 struct BinArgs {
   int N, G;
   const float* pos;
@@ -402,10 +417,11 @@ struct BinArgs {
   const uint8_t* pbc;
   float rc;
   GMeta* meta;
-  int32_t *atom_graph, *atom_bin, *bin_cnt, *bin_start, *bin_atoms;
+  int32_t *atom_graph, *bin_cnt, *bin_start;
   float4* spos;
   int32_t *status, *nlist;
   int2* list;
+  int home;   // search_home()
 };
 __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
   __shared__ GMeta m;
@@ -443,7 +459,12 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
   const int off = first_bin(lo, g);
   if (wave == 0) {
     graph_meta(lo, hi, periodic, p.cell + 9 * (size_t)g, mn, mx, p.rc, &m, p.status);
-    if (lane == 0) m.bin_off = off;
+    if (lane == 0) {
+      m.bin_off = off;
+      const float block = (float)(2 * m.R[0] + 1) * (float)(2 * m.R[1] + 1) * (float)(2 * m.R[2] + 1);   // bins around one
+      const bool few = (float)(hi - lo) * block <= HOME_FEW * (float)(m.nb[0] * m.nb[1] * m.nb[2]);
+      m.home = few || hi - lo > HOME_LARGE ? SR_HOME : p.home;
+    }
   }
   __syncthreads();
   if (tid == 0) p.meta[g] = m;
@@ -458,7 +479,6 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
     const int b = atom_bin_of(m, p.pos[3 * (size_t)i], p.pos[3 * (size_t)i + 1], p.pos[3 * (size_t)i + 2], outside);
     if (outside && periodic) atomicOr(p.status, ST_OUT_OF_CELL);
     p.atom_graph[i] = g;
-    p.atom_bin[i] = off + b;
     if (in_lds) atomicAdd(&hist[b], 1); else atomicAdd(&cnt[b], 1);
   }
   if (!in_lds) __threadfence();
@@ -472,7 +492,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       const int b = b0 + tid * 4 + u;
       c[u] = b < nbins ? (in_lds ? hist[b] : __hip_atomic_load(&cnt[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
       own += c[u];
-      items += (c[u] + SR_HOME - 1) / SR_HOME;
+      items += (c[u] + m.home - 1) / m.home;
     }
     int ia = own, ii = items;
 #pragma unroll
@@ -498,7 +518,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       if (b < nbins) {
         p.bin_start[off + b] = ex;
         if (in_lds) hist[b] = ex; else cnt[b] = ex;   // from here on: the bin's next free record
-        for (int k = 0; k < c[u]; k += SR_HOME, ++at) p.list[at] = make_int2(off + b, k);
+        for (int k = 0; k < c[u]; k += m.home, ++at) p.list[at] = make_int2(off + b, k);
       }
       ex += c[u];
     }
@@ -513,7 +533,6 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
     bool outside;
     const int b = atom_bin_of(m, x, y, z, outside);
     const int k = in_lds ? atomicAdd(&hist[b], 1) : atomicAdd(&cnt[b], 1);
-    p.bin_atoms[k] = i;
     p.spos[k] = make_float4(x, y, z, __int_as_float(i));
   }
 }
@@ -534,12 +553,12 @@ __global__ void k_bin_atoms_count(int N, int G, const float* __restrict__ pos, c
   atomicAdd(&bin_cnt[bin], 1);
 }
 
-// atoms in bin order: their index (for the slow path) and (x, y, z, index) as one 16-byte record (the bin's count runs
-// down to its next free record); and, in the workgroups behind those of the atoms, the work list of the search: one
-// entry per SR_HOME destination atoms of a non-empty bin (order does not matter)
+// atoms in bin order: (x, y, z, index) as one 16-byte record (the bin's count runs down to its next free record); and,
+// in the workgroups behind those of the atoms, the work list of the search: one entry per SR_HOME destination atoms of
+// a non-empty bin (order does not matter)
 __global__ void k_bin_place(int N, unsigned natom_blocks, const float* __restrict__ pos, const int32_t* __restrict__ atom_bin,
                             const int32_t* __restrict__ bin_start, int32_t* __restrict__ bin_cnt,
-                            int32_t* __restrict__ bin_atoms, float4* __restrict__ spos, int64_t maxbins,
+                            float4* __restrict__ spos, int64_t maxbins,
                             int32_t* __restrict__ nlist, int2* __restrict__ list) {
   if (blockIdx.x >= natom_blocks) {
     const int64_t b = (int64_t)(blockIdx.x - natom_blocks) * blockDim.x + threadIdx.x;
@@ -554,7 +573,6 @@ __global__ void k_bin_place(int N, unsigned natom_blocks, const float* __restric
   if (i >= N) return;
   const int bin = atom_bin[i];
   const int k = bin_start[bin] + atomicAdd(&bin_cnt[bin], -1) - 1;
-  bin_atoms[k] = i;
   spos[k] = make_float4(pos[3 * (size_t)i], pos[3 * (size_t)i + 1], pos[3 * (size_t)i + 2], __int_as_float(i));
 }
 
@@ -565,7 +583,7 @@ __device__ inline int floordiv(int a, int b) { return (a >= 0) ? a / b : -((-a +
 
 constexpr int SR_CHUNK = 1024;   // candidates staged at once
 constexpr int SR_EXT = 256;      // bins of the (2R+1)^3 block enumerated at once (one per thread)
-constexpr int SR_CAP = 256;      // hits of one row that the LDS row holds; longer rows take the slow path
+constexpr int SR_CAP = 256;      // hits of one row that the LDS row holds; longer rows are walked and ranked from memory, see long_row()
 constexpr int SR_ZERO_CODE = (128 << 16) | (128 << 8) | 128;
 constexpr int SR_GRID = 2048;    // workgroups of the search (they walk the work list with this stride)
 
@@ -609,8 +627,7 @@ struct SearchArgs {
   const int32_t* colT_ptr;   // fill: first place of each source's group
   int32_t* colT_cur;         // fill: places of each group handed out so far
   int32_t* unsorted;         // fill: the groups' edges in the order they were dealt
-  int32_t* novf;       // number of rows left to the slow path
-  int32_t* ovf_rows;   // those rows
+  int32_t *key_j, *key_c;    // fill: the hits of long rows, one int per edge each
 };
 
 // t = (s0*a + s1*b) + s2*c, every operation rounded on its own
@@ -619,6 +636,84 @@ __device__ __forceinline__ void shift_vector(const float* cell, int s0, int s1, 
   tx = __fadd_rn(__fadd_rn(__fmul_rn(f0, cell[0]), __fmul_rn(f1, cell[3])), __fmul_rn(f2, cell[6]));
   ty = __fadd_rn(__fadd_rn(__fmul_rn(f0, cell[1]), __fmul_rn(f1, cell[4])), __fmul_rn(f2, cell[7]));
   tz = __fadd_rn(__fadd_rn(__fmul_rn(f0, cell[2]), __fmul_rn(f1, cell[5])), __fmul_rn(f2, cell[8]));
+}
+
+// Rows longer than the LDS row, by the wavefront that met them: it walks the bins from memory, stores the hits unordered (key_j,
+// key_c: room for one int per edge each) and ranks them from memory. (Rows listed for a launch of their own before: 2-5 us and a
+// launch in every call for rows that only cells with hundreds of neighbours have.)
+__device__ inline void long_row(const SearchArgs& p, const GMeta& m, int i, int b0, int b1, int b2, float pix, float piy, float piz, float rc2) {
+  const int lane = threadIdx.x & 63;
+  const int nb0 = m.nb[0], nb1 = m.nb[1], nb2 = m.nb[2];
+  const bool per = m.periodic != 0;
+  int count = 0;
+  const int start = p.row_ptr[i], end = p.row_ptr[i + 1];
+  for (int B0 = b0 - m.R[0]; B0 <= b0 + m.R[0]; ++B0) {
+    int s0 = 0, c0 = B0;
+    if (per) { s0 = floordiv(B0, nb0); c0 = B0 - s0 * nb0; } else if (B0 < 0 || B0 >= nb0) continue;
+    for (int B1 = b1 - m.R[1]; B1 <= b1 + m.R[1]; ++B1) {
+      int s1 = 0, c1 = B1;
+      if (per) { s1 = floordiv(B1, nb1); c1 = B1 - s1 * nb1; } else if (B1 < 0 || B1 >= nb1) continue;
+      for (int B2 = b2 - m.R[2]; B2 <= b2 + m.R[2]; ++B2) {
+        int s2 = 0, c2 = B2;
+        if (per) { s2 = floordiv(B2, nb2); c2 = B2 - s2 * nb2; } else if (B2 < 0 || B2 >= nb2) continue;
+        const int bin = m.bin_off + (c0 * nb1 + c1) * nb2 + c2;
+        float tx, ty, tz;
+        shift_vector(m.cell, s0, s1, s2, tx, ty, tz);
+        const bool zero_shift = (s0 | s1 | s2) == 0;
+        const int code = ((s0 + 128) << 16) | ((s1 + 128) << 8) | (s2 + 128);
+        const int kb = p.bin_start[bin], ke = p.bin_start[bin + 1];
+        for (int k0 = kb; k0 < ke; k0 += 64) {
+          const int k = k0 + lane;
+          bool hit = false;
+          int j = 0;
+          if (k < ke) {
+            const float4 a = p.spos[k];
+            j = __float_as_int(a.w);
+            const float rx = __fsub_rn(pix, __fadd_rn(a.x, tx)), ry = __fsub_rn(piy, __fadd_rn(a.y, ty)), rz = __fsub_rn(piz, __fadd_rn(a.z, tz));
+            const float dd = __fadd_rn(__fadd_rn(__fmul_rn(rx, rx), __fmul_rn(ry, ry)), __fmul_rn(rz, rz));
+            hit = (dd < rc2) && !(zero_shift && j == i);
+          }
+          const unsigned long long mask = __ballot(hit);
+          const int at = start + count + __popcll(mask & ((1ull << lane) - 1ull));
+          if (hit && at < end) {
+            p.key_j[at] = j;
+            p.key_c[at] = code;
+          }
+          count += __popcll(mask);
+        }
+      }
+    }
+  }
+  // the row's hits are in memory: every lane of this wavefront reads them all below
+  __threadfence();
+  __builtin_amdgcn_wave_barrier();
+  for (int t = start + lane; t < end; t += 64) {
+    const int mj = p.key_j[t], mc = p.key_c[t];
+    int rank = 0;
+    for (int u = start; u < end; ++u) {
+      const int uj = p.key_j[u], uc = p.key_c[u];
+      rank += (uj < mj) || (uj == mj && uc < mc);
+    }
+    const int e = start + rank;
+    const int s0 = ((mc >> 16) & 255) - 128, s1 = ((mc >> 8) & 255) - 128, s2 = (mc & 255) - 128;
+    float tx, ty, tz;
+    shift_vector(m.cell, s0, s1, s2, tx, ty, tz);
+    const float qx = __fadd_rn(p.pos[3 * (size_t)mj], tx);
+    const float qy = __fadd_rn(p.pos[3 * (size_t)mj + 1], ty);
+    const float qz = __fadd_rn(p.pos[3 * (size_t)mj + 2], tz);
+    const float rx = __fsub_rn(pix, qx), ry = __fsub_rn(piy, qy), rz = __fsub_rn(piz, qz);
+    const float dd = __fadd_rn(__fadd_rn(__fmul_rn(rx, rx), __fmul_rn(ry, ry)), __fmul_rn(rz, rz));
+    p.unsorted[p.colT_ptr[mj] + atomicAdd(&p.colT_cur[mj], 1)] = e;   // the edge's place in its source group
+    p.dst[e] = i;
+    p.col[e] = mj;
+    p.shift[3 * (size_t)e] = (int8_t)s0;
+    p.shift[3 * (size_t)e + 1] = (int8_t)s1;
+    p.shift[3 * (size_t)e + 2] = (int8_t)s2;
+    p.d2[e] = dd;
+    p.rvec[3 * (size_t)e] = rx;
+    p.rvec[3 * (size_t)e + 1] = ry;
+    p.rvec[3 * (size_t)e + 2] = rz;
+  }
 }
 
 template <bool FILL>
@@ -635,9 +730,9 @@ __global__ void __launch_bounds__(256) k_search(SearchArgs p) {
     const int hb = it.x, h0 = it.y;
     const int hb_start = p.bin_start[hb];
     const int hb_cnt = p.bin_start[hb + 1] - hb_start;
-    const int nhome = hb_cnt - h0 < SR_HOME ? hb_cnt - h0 : SR_HOME;
     const int i_first = __float_as_int(p.spos[hb_start].w);
     const GMeta& m = p.meta[p.atom_graph[i_first]];
+    const int nhome = hb_cnt - h0 < m.home ? hb_cnt - h0 : m.home;
     const int nb0 = m.nb[0], nb1 = m.nb[1], nb2 = m.nb[2];
     const int R0 = m.R[0], R1 = m.R[1], R2 = m.R[2];
     const int lb = hb - m.bin_off;
@@ -777,8 +872,8 @@ __global__ void __launch_bounds__(256) k_search(SearchArgs p) {
         return;
       }
       if (cnt > SR_CAP) {
-        if (lane == 0) p.ovf_rows[atomicAdd(p.novf, 1)] = i;
         if (h >= 0 && lane == 0) L.rcnt[h] = 0;
+        long_row(p, m, i, b0, b1, b2, pix, piy, piz, rc2);
         return;
       }
       if (lane < 3) row[cnt + lane] = ~0ull;   // pad to a multiple of four for the 16-byte reads below
@@ -897,132 +992,36 @@ __global__ void __launch_bounds__(256) k_search(SearchArgs p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// slow path for rows longer than the LDS row: one wavefront per listed row walks the bins from memory,
-// stores the hits unordered and ranks them from memory
-// ---------------------------------------------------------------------------------------------
-// (the workgroups behind the first `nlong` write the two offset arrays that leave with the edges: first edge of every
-// graph, and the source groups' offsets)
-__global__ void __launch_bounds__(256)
-k_long_rows(unsigned nlong, int N, int G, const int32_t* __restrict__ graph_off, int32_t* __restrict__ egp,
-            int32_t* __restrict__ colT_out, const int32_t* __restrict__ novf, const int32_t* __restrict__ ovf_rows, const float* __restrict__ pos,
-            const GMeta* __restrict__ meta, const int32_t* __restrict__ atom_graph,
-            const int32_t* __restrict__ atom_bin, const int32_t* __restrict__ bin_start,
-            const int32_t* __restrict__ bin_atoms, float rc, const int32_t* __restrict__ row_ptr,
-            int32_t* key_j, int32_t* key_c, int32_t* __restrict__ dst, int32_t* __restrict__ col,
-            int8_t* __restrict__ shift, float* __restrict__ d2, float* __restrict__ rvec,
-            const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ colT_cur, int32_t* __restrict__ unsorted) {
-  if (blockIdx.x >= nlong) {
-    const int64_t i = (int64_t)(blockIdx.x - nlong) * 256 + threadIdx.x;
-    if (i <= N) colT_out[i] = colT_ptr[i];
-    if (i <= G) egp[i] = row_ptr[graph_off[i]];
-    return;
-  }
-  const int w0 = (int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int nw = (int)(((size_t)nlong * blockDim.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  const int n = *novf;
-  for (int r = w0; r < n; r += nw) {
-    const int i = ovf_rows[r];
-    const GMeta& m = meta[atom_graph[i]];
-    const int nb0 = m.nb[0], nb1 = m.nb[1], nb2 = m.nb[2];
-    const int lb = atom_bin[i] - m.bin_off;
-    const int b2 = lb % nb2, b1 = (lb / nb2) % nb1, b0 = lb / (nb1 * nb2);
-    const float pix = pos[3 * (size_t)i], piy = pos[3 * (size_t)i + 1], piz = pos[3 * (size_t)i + 2];
-    const float rc2 = __fmul_rn(rc, rc);
-    const bool per = m.periodic != 0;
-    int count = 0;
-    const int base = row_ptr[i];
-    for (int B0 = b0 - m.R[0]; B0 <= b0 + m.R[0]; ++B0) {
-      int s0 = 0, c0 = B0;
-      if (per) { s0 = floordiv(B0, nb0); c0 = B0 - s0 * nb0; } else if (B0 < 0 || B0 >= nb0) continue;
-      for (int B1 = b1 - m.R[1]; B1 <= b1 + m.R[1]; ++B1) {
-        int s1 = 0, c1 = B1;
-        if (per) { s1 = floordiv(B1, nb1); c1 = B1 - s1 * nb1; } else if (B1 < 0 || B1 >= nb1) continue;
-        for (int B2 = b2 - m.R[2]; B2 <= b2 + m.R[2]; ++B2) {
-          int s2 = 0, c2 = B2;
-          if (per) { s2 = floordiv(B2, nb2); c2 = B2 - s2 * nb2; } else if (B2 < 0 || B2 >= nb2) continue;
-          const int bin = m.bin_off + (c0 * nb1 + c1) * nb2 + c2;
-          float tx, ty, tz;
-          shift_vector(m.cell, s0, s1, s2, tx, ty, tz);
-          const bool zero_shift = (s0 | s1 | s2) == 0;
-          const int code = ((s0 + 128) << 16) | ((s1 + 128) << 8) | (s2 + 128);
-          const int kb = bin_start[bin], ke = bin_start[bin + 1];
-          for (int k0 = kb; k0 < ke; k0 += 64) {
-            const int k = k0 + lane;
-            bool hit = false;
-            int j = 0;
-            if (k < ke) {
-              j = bin_atoms[k];
-              const float qx = __fadd_rn(pos[3 * (size_t)j], tx);
-              const float qy = __fadd_rn(pos[3 * (size_t)j + 1], ty);
-              const float qz = __fadd_rn(pos[3 * (size_t)j + 2], tz);
-              const float rx = __fsub_rn(pix, qx), ry = __fsub_rn(piy, qy), rz = __fsub_rn(piz, qz);
-              const float dd = __fadd_rn(__fadd_rn(__fmul_rn(rx, rx), __fmul_rn(ry, ry)), __fmul_rn(rz, rz));
-              hit = (dd < rc2) && !(zero_shift && j == i);
-            }
-            const unsigned long long mask = __ballot(hit);
-            if (hit) {
-              const int off = __popcll(mask & ((1ull << lane) - 1ull));
-              key_j[base + count + off] = j;
-              key_c[base + count + off] = code;
-            }
-            count += __popcll(mask);
-          }
-        }
-      }
-    }
-    // the row's hits are in memory: every lane of this wavefront reads them all below
-    __threadfence();
-    __builtin_amdgcn_wave_barrier();
-    const int start = row_ptr[i], end = row_ptr[i + 1];
-    for (int t = start + lane; t < end; t += 64) {
-      const int mj = key_j[t], mc = key_c[t];
-      int rank = 0;
-      for (int u = start; u < end; ++u) {
-        const int uj = key_j[u], uc = key_c[u];
-        rank += (uj < mj) || (uj == mj && uc < mc);
-      }
-      const int e = start + rank;
-      const int s0 = ((mc >> 16) & 255) - 128, s1 = ((mc >> 8) & 255) - 128, s2 = (mc & 255) - 128;
-      float tx, ty, tz;
-      shift_vector(m.cell, s0, s1, s2, tx, ty, tz);
-      const float qx = __fadd_rn(pos[3 * (size_t)mj], tx);
-      const float qy = __fadd_rn(pos[3 * (size_t)mj + 1], ty);
-      const float qz = __fadd_rn(pos[3 * (size_t)mj + 2], tz);
-      const float rx = __fsub_rn(pix, qx), ry = __fsub_rn(piy, qy), rz = __fsub_rn(piz, qz);
-      const float dd = __fadd_rn(__fadd_rn(__fmul_rn(rx, rx), __fmul_rn(ry, ry)), __fmul_rn(rz, rz));
-      unsorted[colT_ptr[mj] + atomicAdd(&colT_cur[mj], 1)] = e;   // the edge's place in its source group
-      dst[e] = i;
-      col[e] = mj;
-      shift[3 * (size_t)e] = (int8_t)s0;
-      shift[3 * (size_t)e + 1] = (int8_t)s1;
-      shift[3 * (size_t)e + 2] = (int8_t)s2;
-      d2[e] = dd;
-      rvec[3 * (size_t)e] = rx;
-      rvec[3 * (size_t)e + 1] = ry;
-      rvec[3 * (size_t)e + 2] = rz;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
 // transpose plan: the histogram of sources is taken by the counting search; the filling search deals the edges to
 // their source's group (any order, see k_search); here each group is put into ascending edge order, in place
 // ---------------------------------------------------------------------------------------------
 constexpr int TS_CAP = 512;   // group members ranked out of LDS; longer groups are ranked from memory
+// (also writes the two offset arrays that leave with the edges: see write_offsets())
+__device__ __forceinline__ void write_offsets(int64_t i, int N, int G, const int32_t* graph_off, const int32_t* row_ptr,
+                                              const int32_t* colT_ptr, int32_t* egp, int32_t* colT_out) {
+  if (i <= N) colT_out[i] = colT_ptr[i];            // the source groups' offsets
+  if (i <= G) egp[i] = row_ptr[graph_off[i]];       // first edge of every graph
+}
 __global__ void __launch_bounds__(256)
-k_rank_sources(int N, const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ permT, int32_t* __restrict__ copy,
-               int32_t* __restrict__ colT_cur, int32_t* __restrict__ novf) {
+k_offsets(int N, int G, const int32_t* __restrict__ graph_off, const int32_t* __restrict__ row_ptr,
+          const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ egp, int32_t* __restrict__ colT_out) {
+  write_offsets((int64_t)blockIdx.x * 256 + threadIdx.x, N, G, graph_off, row_ptr, colT_ptr, egp, colT_out);
+}
+__global__ void __launch_bounds__(256)
+k_rank_sources(unsigned nrank, int N, int G, const int32_t* __restrict__ graph_off, const int32_t* __restrict__ row_ptr,
+               const int32_t* __restrict__ colT_ptr, int32_t* __restrict__ egp, int32_t* __restrict__ colT_out,
+               int32_t* __restrict__ permT, int32_t* __restrict__ copy, int32_t* __restrict__ colT_cur) {
+  if (blockIdx.x >= nrank) {   // the workgroups behind those of the source groups
+    write_offsets((int64_t)(blockIdx.x - nrank) * 256 + threadIdx.x, N, G, graph_off, row_ptr, colT_ptr, egp, colT_out);
+    return;
+  }
   // permT holds the groups as they were dealt; copy: room for one int per edge (long groups are ranked out of it)
   const int32_t* unsorted = permT;
   __shared__ __align__(16) int grp[4][TS_CAP + 4];
   const int j = (int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   if (j >= N) return;
-  if (lane == 0) {                 // the filling call leaves its counters at zero: it may be repeated after one count
-    colT_cur[j] = 0;
-    if (j == 0) *novf = 0;
-  }
+  if (lane == 0) colT_cur[j] = 0;   // the filling call leaves its counters at zero: it may be repeated after one count
   const int start = colT_ptr[j], end = colT_ptr[j + 1];
   const int n = end - start;
   if (n <= 0) return;
@@ -1063,17 +1062,15 @@ struct NeighWs {
   int32_t* atom_bin;    // [N]
   int32_t* zeroed;      // status | deg | colT_cnt | colT_cur | bin_cnt, cleared by one launch
   int64_t nzeroed;
-  int32_t* status;      // [8]: 0 input errors, 1 work-list length, 2 rows left to the slow path
+  int32_t* status;      // 0 input errors, 1 work-list length
   int32_t* deg;         // [N]
   int32_t* colT_cnt;    // [N]
   int32_t* colT_cur;    // [N]
   int32_t* bin_cnt;     // [maxbins]
   int32_t* bin_start;   // [maxbins+1]
-  int32_t* bin_atoms;   // [N]
   float4* spos;         // [N] (x, y, z, atom) in bin order
   int2* list;           // [N] work list of the search
   int32_t* colT_ptr;    // [N+1] kept from the counting call for the filling call
-  int32_t* ovf_rows;    // [N]
   int32_t* scan;        // scratch
   size_t bytes;
   int64_t maxbins;
@@ -1095,11 +1092,9 @@ static NeighWs carve_neigh(void* ws, int N, int G) {
   w.colT_cur = w.colT_cnt + n4;
   w.bin_cnt = w.colT_cur + n4;
   w.bin_start = c.take<int32_t>((size_t)w.maxbins + 1);
-  w.bin_atoms = c.take<int32_t>((size_t)N + 1);
   w.spos = c.take<float4>((size_t)N + 1);
   w.list = c.take<int2>((size_t)N + 1);
   w.colT_ptr = c.take<int32_t>((size_t)N + 2);
-  w.ovf_rows = c.take<int32_t>((size_t)N + 1);
   w.scan = c.take<int32_t>(scan_scratch_ints(w.maxbins + 8) + 8);
   w.bytes = c.used();
   return w;
@@ -1124,7 +1119,6 @@ static SearchArgs search_args(const NeighWs& w, int N, const float* pos, float r
   SearchArgs a = {};
   a.N = N; a.pos = pos; a.meta = w.meta; a.atom_graph = w.atom_graph; a.bin_start = w.bin_start; a.spos = w.spos;
   a.nlist = w.status + 1; a.list = w.list; a.status = w.status; a.rc = rc;
-  a.novf = w.status + 2; a.ovf_rows = w.ovf_rows;
   return a;
 }
 
@@ -1174,8 +1168,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
                                                                 graph_off);
     HGNN_LAUNCH_CHECK("k_clear_and_check");
     if (bin_by_graph(N, G)) {
-      const BinArgs a = {N, G, pos, graph_off, cell, pbc, rc, w.meta, w.atom_graph, w.atom_bin, w.bin_cnt, w.bin_start,
-                         w.bin_atoms, w.spos, w.status, w.status + 1, w.list};
+      const BinArgs a = {N, G, pos, graph_off, cell, pbc, rc, w.meta, w.atom_graph, w.bin_cnt, w.bin_start, w.spos, w.status, w.status + 1, w.list, search_home(N)};
       k_bin_graphs<<<G, 256, 0, st>>>(a);
       HGNN_LAUNCH_CHECK("k_bin_graphs");
     } else {
@@ -1186,7 +1179,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
       HGNN_LAUNCH_CHECK("k_bin_atoms_count");
       HGNN_TRY(exclusive_scan_i32(st, w.bin_cnt, w.bin_start, w.maxbins, w.scan));
       const unsigned na = nblk(N, 256);
-      k_bin_place<<<na + nblk(w.maxbins, 256), 256, 0, st>>>(N, na, pos, w.atom_bin, w.bin_start, w.bin_cnt, w.bin_atoms,
+      k_bin_place<<<na + nblk(w.maxbins, 256), 256, 0, st>>>(N, na, pos, w.atom_bin, w.bin_start, w.bin_cnt,
                                                              w.spos, w.maxbins, w.status + 1, w.list);
       HGNN_LAUNCH_CHECK("k_bin_place");
     }
@@ -1256,24 +1249,23 @@ extern "C" int32_t hgnn_radius_graph_fill(void* stream, int32_t N, int32_t G, co
       SearchArgs a = search_args(w, N, pos, rc);
       a.row_ptr = row_ptr; a.dst = dst; a.col = col; a.shift = shift; a.d2 = d2; a.rvec = rvec;
       a.colT_ptr = w.colT_ptr; a.colT_cur = w.colT_cur; a.unsorted = permT;   // the groups are ordered in place below
+      a.key_j = key_j; a.key_c = key_c;
       k_search<true><<<SR_GRID < N ? SR_GRID : N, 256, 0, st>>>(a);
       HGNN_LAUNCH_CHECK("k_search<fill>");
     }
   }
-  {
-    ProfScope ps(PT_NEIGH_EMIT, st);
-    // rows longer than the LDS row (their number is only known on the device: a fixed grid walks the list)
-    const unsigned nlong = E == 0 ? 0 : (N < 256 ? nblk((int64_t)N * 64, 256) : 64);
-    k_long_rows<<<nlong + nblk((int64_t)(N > G ? N : G) + 1, 256), 256, 0, st>>>(
-        nlong, N, G, graph_off, edge_graph_ptr, colT_ptr, w.status + 2, w.ovf_rows, pos, w.meta, w.atom_graph, w.atom_bin,
-        w.bin_start, w.bin_atoms, rc, row_ptr, key_j, key_c, dst, col, shift, d2, rvec, w.colT_ptr, w.colT_cur, permT);
-    HGNN_LAUNCH_CHECK("k_long_rows");
-  }
+  const unsigned noff = nblk((int64_t)(N > G ? N : G) + 1, 256);
   if (E > 0) {
     ProfScope pst(PT_NEIGH_TRANSPOSE, st);
-    // (the keys of the slow path are dead by now; the counters of the filling pass go back to zero)
-    k_rank_sources<<<nblk((int64_t)N * 64, 256), 256, 0, st>>>(N, colT_ptr, permT, key_j, w.colT_cur, w.status + 2);
+    // (the keys of the long rows are dead by now; the counters of the filling pass go back to zero)
+    const unsigned nrank = nblk((int64_t)N * 64, 256);
+    k_rank_sources<<<nrank + noff, 256, 0, st>>>(nrank, N, G, graph_off, row_ptr, w.colT_ptr, edge_graph_ptr, colT_ptr, permT,
+                                                 key_j, w.colT_cur);
     HGNN_LAUNCH_CHECK("k_rank_sources");
+  } else {
+    ProfScope ps(PT_NEIGH_EMIT, st);
+    k_offsets<<<noff, 256, 0, st>>>(N, G, graph_off, row_ptr, w.colT_ptr, edge_graph_ptr, colT_ptr);
+    HGNN_LAUNCH_CHECK("k_offsets");
   }
   return HGNN_OK;
 }

@@ -232,3 +232,32 @@ def test_large_graphs_of_a_small_batch(sizes):
             assert np.array_equal(got[key][e0:e1], w[key] + base), key
         assert np.array_equal(got["d2"][e0:e1].view(np.uint32), w["d2"].view(np.uint32))
         assert np.array_equal(got["rvec"][e0:e1].view(np.uint32), w["rvec"].view(np.uint32))
+
+
+@pytest.mark.parametrize("atoms", [64, 6144, 6145, 12288, 12289])
+def test_work_items_of_thin_cells_next_to_molecules(atoms):
+    """Four, eight or sixteen destination atoms per work item by the size of the batch, only for graphs of many candidates:
+    thin cells whose image blocks are streamed through the LDS (one with rows longer than the LDS row holds) between
+    molecules that keep sixteen."""
+    print("thin cells", atoms, flush=True)
+    rng = np.random.default_rng(9)
+
+    def cell(n, a):
+        a = np.asarray(a)
+        return (rng.random((n, 3)) @ a).astype(np.float32), rng.integers(1, 90, n).astype(np.int32), a.astype(np.float32)
+
+    mol = lambda n: (rng.uniform(0, 6, (n, 3)).astype(np.float32), np.ones(n, np.int32))
+    one_of = concat_graphs([cell(6, np.diag([2.5, 2.5, 2.5])), mol(21), cell(19, [[3, 0, 0], [1, 9, 0], [0, 2, 11]]), mol(1), mol(17)])
+    rc = 6.0
+    one = oracle.radius_graph(one_of.pos, one_of.graph_off, one_of.cell, one_of.pbc, rc)
+    assert np.diff(one["row_ptr"]).max() > 256
+    times, rest = divmod(atoms, one_of.N)
+    many, want = repeated(one_of, times), repeated_graph(one, one_of, times)
+    if rest:     # fill up to the exact number with single atoms: no edges
+        graphs = [(many.pos[a:b], many.Z[a:b], many.cell[g] if many.pbc[g] else None)
+                  for g, (a, b) in enumerate(zip(many.graph_off[:-1], many.graph_off[1:]))]
+        many = concat_graphs(graphs + [(np.zeros((1, 3), np.float32), np.ones(1, np.int32))] * rest)
+        for k in ("row_ptr", "colT_ptr", "edge_graph_ptr"):
+            want[k] = np.concatenate([want[k], np.full(rest, want["E"], np.int32)])
+    assert many.N == atoms
+    assert_graph_equal(gpu_graph(many, rc).to_numpy(), want)
