@@ -562,11 +562,10 @@ struct GemmJobs {
   GemmArgs job[2];
 };
 template <int H, bool BF16, bool CHAIN, bool RAW>
-__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmJobs m, int keep_silu, PackArgs pk, int tiles) {
+__device__ __forceinline__ void gemm_small(const GemmJobs& m, int keep_silu, const PackArgs& pk, int tiles, unsigned char* smem) {
   using C = SmallCfg<H, BF16>;
   const GemmArgs& p1 = m.job[0];
   const GemmArgs& p2 = m.job[CHAIN ? 1 : RAW ? 0 : blockIdx.z];
-  extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* keep = smem + 2 * C::A_BYTES;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, hq = lane >> 4;
@@ -789,6 +788,12 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(Gem
       }
     if (cb + 1 < cbe) x2.load(p2, cb + 1, grp, gr, wave, c);
   }
+}
+
+template <int H, bool BF16, bool CHAIN, bool RAW>
+__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmJobs m, int keep_silu, PackArgs pk, int tiles) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  gemm_small<H, BF16, CHAIN, RAW>(m, keep_silu, pk, tiles, smem);
 }
 
 // (rule: see small_gemm())
@@ -1033,9 +1038,11 @@ __device__ __forceinline__ float reduce_range(const float* p, long step, int k0,
   return s;
 }
 
+// (T: threads per workgroup)
 // wide blocks: one thread per element
+template <int T>
 __device__ __forceinline__ void reduce_wide(const ReduceArgs& a, int bx, int blk, int grp) {
-  const long i = (long)bx * 256 + threadIdx.x;
+  const long i = (long)bx * T + threadIdx.x;
   if (i >= a.blk_elems || !a.dest[blk]) return;
   const float* p = a.partial + ((long)grp * a.nsplit * a.nblk + blk) * a.blk_elems + i;
   const long step = (long)a.nblk * a.blk_elems;
@@ -1046,11 +1053,11 @@ __device__ __forceinline__ void reduce_wide(const ReduceArgs& a, int bx, int blk
   a.dest[blk][grp * a.grp_dest_stride + i] = reduce_range(p, step, 0, a.nsplit);
 }
 
-// Many partials: 256 / EPB threads per element take a contiguous share of the partials each (in order), then the shares are
-// added in order. sh: 256 floats of LDS. Every thread of the workgroup calls it.
-template <int EPB>
+// Many partials: T / EPB threads per element take a contiguous share of the partials each (in order), then the shares are
+// added in order. sh: T floats of LDS. Every thread of the workgroup calls it.
+template <int EPB, int T>
 __device__ __forceinline__ void reduce_tall(const ReduceArgs& a, int bx, int blk, int grp, float* sh) {
-  constexpr int PH = 256 / EPB;
+  constexpr int PH = T / EPB;
   const int e = threadIdx.x % EPB, ph = threadIdx.x / EPB;
   const long i = (long)bx * EPB + e;
   const int per = (a.nsplit + PH - 1) / PH;
@@ -1082,15 +1089,17 @@ static unsigned reduce_xblocks(long blk_elems, int nsplit) {
   const int epb = reduce_epb(blk_elems, nsplit);
   return (unsigned)((blk_elems + epb - 1) / epb);
 }
+// (epb: elements per 256 threads; the threads that share an element stay as many in a larger workgroup)
+template <int T>
 __device__ __forceinline__ void reduce_any(const ReduceArgs& a, int epb, int bx, int blk, int grp, float* sh) {
-  if (epb == 16) reduce_tall<16>(a, bx, blk, grp, sh);
-  else if (epb == 32) reduce_tall<32>(a, bx, blk, grp, sh);
-  else reduce_wide(a, bx, blk, grp);
+  if (epb == 16) reduce_tall<16 * T / 256, T>(a, bx, blk, grp, sh);
+  else if (epb == 32) reduce_tall<32 * T / 256, T>(a, bx, blk, grp, sh);
+  else reduce_wide<T>(a, bx, blk, grp);
 }
 
 __global__ void __launch_bounds__(256) k_reduce_partials(ReduceArgs a, int epb) {
   __shared__ float sh[256];
-  reduce_any(a, epb, blockIdx.x, blockIdx.y, blockIdx.z, sh);
+  reduce_any<256>(a, epb, blockIdx.x, blockIdx.y, blockIdx.z, sh);
 }
 
 // several reductions in one launch: the workgroups of all jobs one after the other, in a job element blocks first, then the
@@ -1099,20 +1108,48 @@ constexpr int REDUCE_QUEUE_MAX = 8;
 // A launch holds fewer than 2^32 threads in x. Two weight gradients at H = 256 pass that from about 32,400 sources on: what
 // does not fit runs as a launch of its own, with the groups in z.
 constexpr long REDUCE_QUEUE_WGS = (1L << 32) / 256 - 1;
+// Most that share a launch with a product (small batches only, by the rule of the products). Long reductions run into the few
+// workgroups that the product's registers leave room for. Two launches -> one: 32 small molecules (2.7 MB of partials) 338 -> 318 us
+// per step, a crystal's conservative forces (12 MB) 523 -> 504, 16 molecules at H = 128 (13 MB) 485 -> 467, 128 molecules (51 MB)
+// 850 -> 834, 8 crystals (79 MB) 688 -> 677; past the line 64 crystals (101 MB) 1599 -> 1620.
+constexpr long REDUCE_WITH_BYTES = 80L << 20, REDUCE_WITH_WGS = 1L << 20;
 struct ReduceQueueArgs {
   ReduceArgs job[REDUCE_QUEUE_MAX];
   int njobs;
   long off[REDUCE_QUEUE_MAX + 1];
   int xblocks[REDUCE_QUEUE_MAX];
   int epb[REDUCE_QUEUE_MAX];
+  long bytes() const {   // of the partials
+    long b = 0;
+    for (int j = 0; j < njobs; ++j) b += (off[j + 1] - off[j]) / xblocks[j] * job[j].blk_elems * job[j].nsplit * 4;
+    return b;
+  }
 };
+template <int T>
+__device__ __forceinline__ void reduce_queue(const ReduceQueueArgs& q, long wg, float* sh) {
+  int j = 0;   // uniform over the workgroup
+  while (j + 1 < q.njobs && wg >= q.off[j + 1]) ++j;
+  const int r = (int)(wg - q.off[j]);
+  const int bx = r % q.xblocks[j], y = r / q.xblocks[j];
+  reduce_any<T>(q.job[j], q.epb[j], bx, y % q.job[j].nblk, y / q.job[j].nblk, sh);
+}
 __global__ void __launch_bounds__(256) k_reduce_queue(ReduceQueueArgs q) {
   __shared__ float sh[256];
-  int j = 0;   // uniform over the workgroup
-  while (j + 1 < q.njobs && (long)blockIdx.x >= q.off[j + 1]) ++j;
-  const int r = (int)((long)blockIdx.x - q.off[j]);
-  const int bx = r % q.xblocks[j], y = r / q.xblocks[j];
-  reduce_any(q.job[j], q.epb[j], bx, y % q.job[j].nblk, y / q.job[j].nblk, sh);
+  reduce_queue<256>(q, blockIdx.x, sh);
+}
+// One or two lone products of a small batch (blockIdx.z) and the reductions that wait for the end of a reverse pass: neither reads
+// what the other writes, and both are launches of 4-10 us that leave most of the chip idle. Workgroups behind the `tiles` of
+// the products take the reductions.
+template <int H, bool BF16>
+__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small_reduce(GemmJobs m, ReduceQueueArgs q, int tiles) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  static_assert(SmallCfg<H, BF16>::LDS_BYTES >= SmallCfg<H, BF16>::THREADS * sizeof(float), "a float per thread");
+  if ((int)blockIdx.x < tiles) {
+    gemm_small<H, BF16, false, false>(m, 0, PackArgs{}, tiles, smem);
+  } else {
+    const long wg = (long)((int)blockIdx.x - tiles) * gridDim.z + blockIdx.z;
+    if (wg < q.off[q.njobs]) reduce_queue<SmallCfg<H, BF16>::THREADS>(q, wg, reinterpret_cast<float*>(smem));
+  }
 }
 
 struct ReduceQueue {
@@ -1142,6 +1179,48 @@ int32_t ReduceQueueScope::flush() {
   q.njobs = 0;
   HGNN_LAUNCH_CHECK("k_reduce_queue");
   return HGNN_OK;
+}
+
+template <int H, bool BF16>
+static int32_t launch_gemm_small_reduce_t(hipStream_t st, const GemmArgs& a, const GemmArgs* b, ReduceQueueArgs q) {
+  using C = SmallCfg<H, BF16>;
+  long begin = q.off[0], end = q.off[1];
+  for (int j = 0; j < q.njobs; ++j) {   // the same jobs in workgroups of this size
+    const int epb = q.epb[j] * (C::THREADS / 256);
+    const long rows = (end - begin) / q.xblocks[j];   // partial blocks x groups
+    begin = end;
+    if (j + 2 <= q.njobs) end = q.off[j + 2];
+    q.xblocks[j] = (int)((q.job[j].blk_elems + epb - 1) / epb);
+    q.off[j + 1] = q.off[j] + rows * q.xblocks[j];
+  }
+  const auto tiles_of = [](const GemmArgs& g) { return (g.M + C::TM - 1) / C::TM + (g.grp_ptr ? g.S : 0); };
+  const int ta = tiles_of(a), tb = b ? tiles_of(*b) : 0, tiles = ta > tb ? ta : tb, gz = b ? 2 : 1;
+  ProfScope ps(a.tag, st);
+  k_gemm_small_reduce<H, BF16><<<dim3((unsigned)(tiles + (q.off[q.njobs] + gz - 1) / gz), 1, gz), C::THREADS, C::LDS_BYTES, st>>>(
+      GemmJobs{{a, b ? *b : a}}, q, tiles);
+  HGNN_LAUNCH_CHECK("k_gemm_small_reduce");
+  return HGNN_OK;
+}
+int32_t ReduceQueueScope::flush_with(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs* b) {
+  const int rows = H >= 128 ? 32 : 64;
+  const bool one = active_ && tl_reduce_queue->q.njobs > 0 && tl_reduce_queue->st == st && (bf16 || H < 256) && a.M > 0 && a.ncb == 1 &&
+                   small_gemm(a, rows) && (!b || (b->M > 0 && b->ncb == 1 && small_gemm(*b, rows))) &&
+                   tl_reduce_queue->q.off[tl_reduce_queue->q.njobs] <= REDUCE_WITH_WGS && tl_reduce_queue->q.bytes() <= REDUCE_WITH_BYTES;
+  if (!one) {
+    if (b) HGNN_TRY(launch_gemm_pair(st, H, bf16, a, *b));
+    else HGNN_TRY(launch_gemm(st, H, bf16, a));
+    ProfScope ps(PT_MISC, st);
+    return flush();
+  }
+  HGNN_TRY(check_gemm(H, a));
+  if (b) HGNN_TRY(check_gemm(H, *b));
+  const ReduceQueueArgs q = tl_reduce_queue->q;
+  tl_reduce_queue->q.njobs = 0;   // (off[0] stays 0)
+  switch (H) {
+    case 64: return bf16 ? launch_gemm_small_reduce_t<64, true>(st, a, b, q) : launch_gemm_small_reduce_t<64, false>(st, a, b, q);
+    case 128: return bf16 ? launch_gemm_small_reduce_t<128, true>(st, a, b, q) : launch_gemm_small_reduce_t<128, false>(st, a, b, q);
+  }
+  return launch_gemm_small_reduce_t<256, true>(st, a, b, q);
 }
 
 static int32_t launch_reduce_partials_n(hipStream_t st, const float* partial, int nsplit, int nblk, long blk_elems,

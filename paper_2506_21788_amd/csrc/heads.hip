@@ -979,11 +979,5 @@ extern "C" int32_t hgnn_multihead_decode_bwd(void* stream, int32_t N, int32_t G,
   }
   HGNN_TRY(launch_colsum_multi(st, Hh, cs, 2 * nb));
   HGNN_TRY(launch_wgrad_own_rows(st, H, bf16, wg, nb));
-  if (nb == 2) HGNN_TRY(launch_gemm_pair(st, H, bf16, gx[0], gx[1]));
-  else HGNN_TRY(launch_gemm(st, H, bf16, gx[0]));
-  {
-    ProfScope ps(PT_COLSUM, st);
-    HGNN_TRY(reductions.flush());
-  }
-  return HGNN_OK;
+  return reductions.flush_with(st, H, bf16, gx[0], nb == 2 ? &gx[1] : nullptr);
 }

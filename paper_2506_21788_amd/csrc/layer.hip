@@ -474,15 +474,6 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
                               g_d2 ? W + o.W1 + 2 * HH : nullptr, g_d2, &dfix));
   else
     HGNN_TRY(launch_segsum_vm(st, H, bf16, N, E, colT_ptr, permT, w.gz1_vm, w.g_PQ + H, 2 * H, PT_SEGSUM_SRC));  // g_Q
-  {  // g_h = (g_h' + g_h(a)) + g_P W1a^T + g_Q W1b^T
-    GemmArgs g;
-    g.A[0] = w.g_PQ; g.lda[0] = 2 * H; g.A[1] = w.g_PQ + H; g.lda[1] = 2 * H; g.nkc = 2;
-    g.B = w.packed; g.blk[0][0] = 4; g.blk[1][0] = 5;
-    g.M = N;
-    g.add1 = w.g_hM; g.ldadd1 = 2 * H;
-    g.C = g_h_in; g.ldc = H;
-    HGNN_TRY(launch_gemm(st, H, bf16, g));
-  }
   {  // the three atom-level weight gradients of the layer and their bias sums in one launch, once all their operands
      // exist: gW4 = silu(z3)^T g_h', gb4 | gW3 = [h ; M]^T g_z3, gb3 | gW1a = h^T g_P, gW1b = h^T g_Q, gb1 = sum_i g_P_i
     HGNN_TRY(stream_after(sx, st, ss.ev[3]));
@@ -503,13 +494,19 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
     j[0].partial = w.partial3; j[0].colsum_partial = w.cs_partial;
     HGNN_TRY(launch_wgrad_multi(sx, H, bf16, j, 3));
   }
-  {
+  if (g_v_in != g_v_out) {   // g_v passes through: a reduction of one partial is a copy (joins the launch below)
     ProfScope ps(PT_MISC, st);
-    if (g_v_in != g_v_out && N > 0) {   // g_v passes through: a reduction of one partial is a copy (joins the launch below)
-      float* dest[4] = {g_v_in, nullptr, nullptr, nullptr};
-      HGNN_TRY(launch_reduce_partials(st, g_v_out, 1, 1, (long)N * 3, dest, 1, 0));
-    }
-    HGNN_TRY(reductions.flush());
+    float* dest[4] = {g_v_in, nullptr, nullptr, nullptr};
+    HGNN_TRY(launch_reduce_partials(st, g_v_out, 1, 1, (long)N * 3, dest, 1, 0));
+  }
+  {  // g_h = (g_h' + g_h(a)) + g_P W1a^T + g_Q W1b^T, and the reductions
+    GemmArgs g;
+    g.A[0] = w.g_PQ; g.lda[0] = 2 * H; g.A[1] = w.g_PQ + H; g.lda[1] = 2 * H; g.nkc = 2;
+    g.B = w.packed; g.blk[0][0] = 4; g.blk[1][0] = 5;
+    g.M = N;
+    g.add1 = w.g_hM; g.ldadd1 = 2 * H;
+    g.C = g_h_in; g.ldc = H;
+    HGNN_TRY(reductions.flush_with(st, H, bf16, g));
   }
   HGNN_TRY(stream_after(st, sx, ss.ev[4]));   // join: the caller's stream now also orders after every gradient
   return HGNN_OK;

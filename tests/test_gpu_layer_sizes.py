@@ -210,6 +210,14 @@ def test_layer_atom_counts_of_the_packing_launch(H, dtype, N):
     _run_layer(N=N, E=2000, H=H, dtype=dtype, seed=N)
 
 
+# The reductions of a reverse pass share a launch with its last product (up to 80 MB of partials) or have one of their own: 256 partials
+# of the W2 gradient are 64 MB at H = 256, five blocks per 64 atoms come on top
+@pytest.mark.parametrize("H,dtype,N,E", [(256, "bf16", 300, 20000), (256, "bf16", 3000, 20000), (128, "f32", 17, 40000),
+                                         (128, "bf16", 5000, 40000), (64, "f32", 16001, 40000), (256, "f32", 300, 20000)])
+def test_layer_reductions_with_the_last_product(H, dtype, N, E):
+    _run_layer(N=N, E=E, H=H, dtype=dtype, seed=N + H)
+
+
 @pytest.mark.parametrize("H,dtype", [(64, "f32"), (128, "bf16")])
 def test_layer_weights_at_any_alignment(H, dtype):
     """Weights at a 4-byte boundary: the reverse pass packs in a launch of its own, with the same bits as a result."""
