@@ -172,3 +172,23 @@ def test_embedding_and_pooled_gradient_rows_at_other_widths(N, H):
 @pytest.mark.parametrize("N,H", [(2048, 1000), (10241, 600), (22529, 1000), (45057, 300)])
 def test_embedding_gradient_of_many_atoms_at_other_widths(N, H):
     test_embedding_at_other_widths(N, H, 20)
+
+
+# the vector form: one chunk (whose sums are the result) and several, species of no, one and most atoms of a chunk, and a result
+# at an address that takes no 16-byte stores
+@pytest.mark.parametrize("N,H,elements", [(1, 64, 1), (2047, 128, 2), (2048, 256, 94), (2049, 64, 3), (6001, 256, 1), (9000, 128, 40)])
+def test_embedding_gradient_at_vector_widths(N, H, elements):
+    import torch
+    from paper_2506_21788_amd import binding as B
+    test_embedding_at_other_widths(N, H, elements)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Z = torch.randint(1, elements + 1, (N,), dtype=torch.int32, device="cuda", generator=gen)
+    g = torch.randn((N, H), device="cuda", generator=gen)
+    ws = torch.empty(B.embed_bwd_workspace_bytes(N, H), dtype=torch.uint8, device="cuda")
+    n, out = (B.ZMAX + 1) * H, []
+    for off in (0, 1):
+        buf = torch.full((n + 2,), float("nan"), device="cuda")
+        B.embed_bwd(N, H, Z, g, buf[off:off + n], ws)
+        assert bool(buf[:off].isnan().all()) and bool(buf[off + n:].isnan().all())
+        out.append(buf[off:off + n])
+    assert torch.equal(*out)
