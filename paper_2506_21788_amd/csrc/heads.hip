@@ -72,15 +72,14 @@ k_embed_bwd_part(int N, int H, const int32_t* __restrict__ Z, const float* __res
     float4 v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (zz[u] == z) v[u] = *reinterpret_cast<const float4*>(g_h + (size_t)(i0 + u * nph) * H + q * 4);
+      const int k = k0 + u * nph;
+      v[u] = *reinterpret_cast<const float4*>(g_h + (size_t)list[k < total ? k : total - 1] * H + q * 4);
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (zz[u] == z) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
-    }
+    for (int u = 0; u < 8; ++u)
+      if (k0 + u * nph < total) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
   }
-  sh[threadIdx.x] = acc;
+  sh[tid] = acc;
   __syncthreads();
   if (ph == 0) {
     for (int k = 1; k < nph; ++k) {
@@ -350,8 +349,15 @@ k_pool_bwd_any(int N, int G, int H, RowRuns rr, int mode, const int32_t* __restr
 // lane scans, leaves its totals per source in LDS, and adds the totals of the wavefronts before it (643 graphs: 54 us
 // with one wavefront walking all graphs, 10 us with sixteen). More sources: one wavefront walks the graphs.
 constexpr int PLAN_FEW = 64;
+// place atom i, whose graph has been placed
+__device__ __forceinline__ void plan_atom(int i, int G, const int32_t* graph_off, const PlanView& v) {
+  const int g = find_graph_of_atom(graph_off, G, i);
+  v.atom_graph[i] = g;
+  v.atom_perm[v.graph_dst_off[g] + (i - graph_off[g])] = i;
+}
+// N > 0: the workgroup places the atoms as well (few sources only, see PLAN_ATOMS)
 __global__ void __launch_bounds__(1024)
-k_plan_graphs(int G, int S, const int32_t* __restrict__ graph_off, const int32_t* __restrict__ source_id, PlanView v,
+k_plan_graphs(int N, int G, int S, const int32_t* __restrict__ graph_off, const int32_t* __restrict__ source_id, PlanView v,
               HostMail* mail) {
   __shared__ int sh_a[1024];
   __shared__ int sh_b[1024];
@@ -482,6 +488,9 @@ k_plan_graphs(int G, int S, const int32_t* __restrict__ graph_off, const int32_t
       }
       __syncthreads();
     }
+    __threadfence_block();
+    __syncthreads();
+    for (int i = tid; i < N; i += 1024) plan_atom(i, G, graph_off, v);
     return;
   }
   // one wavefront, 64 graphs at a time: a lane ranks its graph among the earlier lanes of the same source (lane values
@@ -529,12 +538,13 @@ k_plan_graphs(int G, int S, const int32_t* __restrict__ graph_off, const int32_t
   }
 }
 
+// Up to here the workgroup that places the graphs places the atoms too: the call, two launches -> one, 384 atoms 33.9 -> 30.3 us,
+// 4,096 33.5 -> 29.5, 7,105 33.4 -> 31.5; past the line 9,680 33.3 -> 35.0, 16,384 33.4 -> 49.
+constexpr int PLAN_ATOMS = 6144;
 __global__ void k_plan_atoms(int N, int G, const int32_t* __restrict__ graph_off, PlanView v) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N || v.status[0]) return;    // bad source ids: nothing has been placed
-  const int g = find_graph_of_atom(graph_off, G, i);
-  v.atom_graph[i] = g;
-  v.atom_perm[v.graph_dst_off[g] + (i - graph_off[g])] = i;
+  plan_atom(i, G, graph_off, v);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -827,9 +837,10 @@ extern "C" int32_t hgnn_multihead_plan(void* stream, int32_t N, int32_t G, int32
   PlanView v = plan_view(plan, N, G, S);
   MailSlot mail;
   HGNN_TRY(mail.take(st));
-  k_plan_graphs<<<1, 1024, 0, st>>>(G, S, graph_off, source_id, v, mail.dev());
+  const bool one = S <= PLAN_FEW && N <= PLAN_ATOMS;
+  k_plan_graphs<<<1, 1024, 0, st>>>(one ? N : 0, G, S, graph_off, source_id, v, mail.dev());
   HGNN_LAUNCH_CHECK("k_plan_graphs");
-  if (N > 0) {
+  if (N > 0 && !one) {
     k_plan_atoms<<<nb64(N, 256), 256, 0, st>>>(N, G, graph_off, v);
     HGNN_LAUNCH_CHECK("k_plan_atoms");
   }

@@ -261,3 +261,22 @@ def test_work_items_of_thin_cells_next_to_molecules(atoms):
             want[k] = np.concatenate([want[k], np.full(rest, want["E"], np.int32)])
     assert many.N == atoms
     assert_graph_equal(gpu_graph(many, rc).to_numpy(), want)
+
+
+# atoms placed by the workgroup that places the graphs, or by a launch of their own
+@pytest.mark.parametrize("N", [6144, 6145])
+@pytest.mark.parametrize("G,S", [(1, 1), (1100, 64), (1100, 65), (7000, 5)])
+def test_routing_plan_atom_counts(N, G, S):
+    import torch
+    from paper_2506_21788_amd import binding as B
+    print("routing plan", N, G, S, flush=True)
+    rng = np.random.default_rng(N + G + S)
+    off = np.concatenate([[0], np.sort(rng.integers(0, N + 1, G - 1)), [N]]).astype(np.int32)   # some graphs are empty
+    src = rng.integers(0, S, G).astype(np.int32)
+    plan = torch.full((B.multihead_plan_ints(N, G, S),), -7, dtype=torch.int32, device="cuda")
+    B.multihead_plan(N, G, S, torch.as_tensor(off).cuda(), torch.as_tensor(src).cuda(), plan)
+    got = {k: v.cpu().numpy() for k, v in B.plan_fields(plan, N, G, S).items()}
+    order = np.argsort(src, kind="stable")
+    assert np.array_equal(got["graph_perm"], order)
+    assert np.array_equal(got["atom_perm"], np.concatenate([np.arange(off[g], off[g + 1]) for g in order]))
+    assert np.array_equal(got["atom_graph"], np.repeat(np.arange(G), np.diff(off)))
