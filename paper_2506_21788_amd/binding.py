@@ -1,7 +1,9 @@
-"""ctypes binding of libhgnn.so: one Python function per C entry point, same name without the
-`hgnn_` prefix. Arguments are torch tensors on the GPU (used as device memory only) or Python
-scalars; this module only marshals pointers and checks the status code. Every step of the path runs
-inside the library's kernels. There is no fallback: if the library is missing, importing fails."""
+"""Binding of libhgnn.so: one Python function per C entry point, same name without the `hgnn_`
+prefix. Arguments are torch tensors on the GPU (used as device memory only) or Python scalars; this
+module names them and checks the status code. The entry points that enqueue work are called through
+`_native` (csrc/native.cpp), which turns tensors into pointers, the rest through ctypes. Every step of
+the path runs inside the library's kernels. There is no fallback: if the library is missing, importing
+fails."""
 from __future__ import annotations
 
 import ctypes as C
@@ -51,6 +53,10 @@ def _load():
 
 
 _lib = _load()
+try:
+    from . import _native as _n
+except ImportError as e:
+    raise ImportError(f"{os.path.join(_HERE, '_native.so')}: {e} (build it: python -c 'import __graft_entry__ as g; g.build()')") from e
 
 vp, i32, i64, f32, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_size_t
 
@@ -63,42 +69,11 @@ def _sig(name, *argtypes):
 
 
 _rg_ws = _sig("hgnn_radius_graph_workspace_bytes", i32, i32, C.POINTER(sz))
-_rg_count = _sig("hgnn_radius_graph_count", vp, i32, i32, vp, vp, vp, vp, f32, vp, sz, vp, C.POINTER(i64))
-_rg_fill = _sig("hgnn_radius_graph_fill", vp, i32, i32, vp, vp, vp, vp, f32, vp, sz, vp, sz, vp, i64,
-                vp, vp, vp, vp, vp, vp, vp, vp)
-_embed_fwd = _sig("hgnn_embed_fwd", vp, i32, i32, vp, vp, vp)
-_embed_bwd = _sig("hgnn_embed_bwd", vp, i32, i32, vp, vp, vp, vp, sz)
-_embed_bwd_static = _sig("hgnn_embed_bwd_static", vp, i32, i32, vp, vp, vp)
 _embed_bwd_ws = _sig("hgnn_embed_bwd_workspace_bytes", i32, i32, C.POINTER(sz))
 _mp_ws = _sig("hgnn_mp_layer_workspace_bytes", i32, i64, i32, i32, C.POINTER(sz), C.POINTER(sz))
-_mp_fwd = _sig("hgnn_mp_layer_fwd", vp, i32, i64, i32, i32, f32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp,
-               vp, sz, vp, sz)
-_mp_bwd = _sig("hgnn_mp_layer_bwd", vp, i32, i64, i32, i32, f32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz,
-               vp, vp, vp, vp, vp, vp, sz)
-_rbf = _sig("hgnn_edge_rbf", vp, i64, vp, i32, f32, vp)
 _mpa_ws = _sig("hgnn_mp_layer_attr_workspace_bytes", i32, i64, i32, i32, i32, C.POINTER(sz), C.POINTER(sz))
-_mpa_fwd = _sig("hgnn_mp_layer_attr_fwd", vp, i32, i64, i32, i32, i32, f32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp,
-                vp, sz, vp, sz)
-_mpa_bwd = _sig("hgnn_mp_layer_attr_bwd", vp, i32, i64, i32, i32, i32, f32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz,
-                vp, vp, vp, vp, vp, vp, vp, vp, sz)
-_rbf_bwd = _sig("hgnn_edge_rbf_bwd", vp, i64, vp, i32, f32, vp, vp)
-_geom_fwd = _sig("hgnn_edge_geometry_fwd", vp, i32, i64, vp, vp, vp, vp, vp, vp)
-_geom_bwd = _sig("hgnn_edge_geometry_bwd", vp, i32, i64, vp, vp, vp, vp, vp, vp, vp, vp, vp)
-_adamw = _sig("hgnn_adamw_step", vp, i64, vp, vp, vp, vp, i32, C.c_double, C.c_double, C.c_double, C.c_double,
-              C.c_double)
-_pool_fwd = _sig("hgnn_pool_by_graph_fwd", vp, i32, i32, i32, i32, vp, vp, vp)
-_pool_bwd = _sig("hgnn_pool_by_graph_bwd", vp, i32, i32, i32, i32, vp, vp, vp, i32)
-_plan = _sig("hgnn_multihead_plan", vp, i32, i32, i32, vp, vp, vp)
 _dec_ws = _sig("hgnn_multihead_decode_workspace_bytes", i32, i32, i32, i32, i32, i32, C.POINTER(sz), C.POINTER(sz))
-_dec_fwd = _sig("hgnn_multihead_decode_fwd", vp, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp,
-                vp, sz, vp, sz)
-_dec_bwd = _sig("hgnn_multihead_decode_bwd", vp, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, sz,
-                vp, vp, vp, vp, vp, vp, vp, sz)
 _deep_ws = _sig("hgnn_multihead_deep_workspace_bytes", i32, i32, i32, i32, i32, i32, i32, C.POINTER(sz), C.POINTER(sz))
-_deep_fwd = _sig("hgnn_multihead_deep_fwd", vp, i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp,
-                 vp, sz, vp, sz)
-_deep_bwd = _sig("hgnn_multihead_deep_bwd", vp, i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, sz,
-                 vp, vp, vp, vp, vp, vp, vp, sz)
 
 
 def last_error_string() -> str:
@@ -121,20 +96,8 @@ def _check(code):
         raise HgnnError(code, last_error_string())
 
 
-def _p(t):
-    """Device pointer of a tensor (None -> NULL)."""
-    if t is None:
-        return None
-    assert t.is_cuda and t.is_contiguous(), "libhgnn takes contiguous device tensors"
-    return C.c_void_p(t.data_ptr())
-
-
 def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
-
-
-def _nbytes(t):
-    return 0 if t is None else t.numel() * t.element_size()
 
 
 # ------------------------------------------------------------------------------------------------
@@ -145,21 +108,20 @@ def radius_graph_workspace_bytes(N, G):
 
 
 def radius_graph_count(N, G, pos, graph_off, cell, pbc, rc, ws, row_ptr):
-    E = i64(0)
-    _check(_rg_count(_stream(), N, G, _p(pos), _p(graph_off), _p(cell), _p(pbc), rc, _p(ws), _nbytes(ws),
-                     _p(row_ptr), C.byref(E)))
-    return E.value
+    E = _n.radius_graph_count(N, G, pos, graph_off, cell, pbc, rc, ws, row_ptr)
+    if E < 0:
+        _check(E)
+    return E
 
 
 def radius_graph_fill(N, G, pos, graph_off, cell, pbc, rc, ws, tmp, row_ptr, E, dst, col, shift, d2, rvec,
                       edge_graph_ptr, colT_ptr, permT):
-    _check(_rg_fill(_stream(), N, G, _p(pos), _p(graph_off), _p(cell), _p(pbc), rc, _p(ws), _nbytes(ws),
-                    _p(tmp), _nbytes(tmp), _p(row_ptr), E, _p(dst), _p(col), _p(shift), _p(d2), _p(rvec),
-                    _p(edge_graph_ptr), _p(colT_ptr), _p(permT)))
+    _check(_n.radius_graph_fill(N, G, pos, graph_off, cell, pbc, rc, ws, tmp, row_ptr, E, dst, col, shift, d2, rvec,
+                                edge_graph_ptr, colT_ptr, permT))
 
 
 def embed_fwd(N, H, Z, emb, h):
-    _check(_embed_fwd(_stream(), N, H, _p(Z), _p(emb), _p(h)))
+    _check(_n.embed_fwd(N, H, Z, emb, h))
 
 
 def embed_bwd_workspace_bytes(N, H):
@@ -169,14 +131,14 @@ def embed_bwd_workspace_bytes(N, H):
 
 
 def embed_bwd(N, H, Z, g_h, g_emb, ws):
-    _check(_embed_bwd(_stream(), N, H, _p(Z), _p(g_h), _p(g_emb), _p(ws), _nbytes(ws)))
+    _check(_n.embed_bwd(N, H, Z, g_h, g_emb, ws))
 
 
 EMBED_BWD_STATIC_MAX_BYTES = 8 << 20
 
 
 def embed_bwd_static(N, H, Z, g_h, g_emb):
-    _check(_embed_bwd_static(_stream(), N, H, _p(Z), _p(g_h), _p(g_emb)))
+    _check(_n.embed_bwd_static(N, H, Z, g_h, g_emb))
 
 
 def mp_layer_workspace_bytes(N, E, H, dtype):
@@ -186,7 +148,7 @@ def mp_layer_workspace_bytes(N, E, H, dtype):
 
 
 def edge_rbf(E, d2, k, rc, attr):
-    _check(_rbf(_stream(), E, _p(d2), k, rc, _p(attr)))
+    _check(_n.edge_rbf(E, d2, k, rc, attr))
 
 
 def mp_layer_attr_workspace_bytes(N, E, H, k, dtype):
@@ -196,48 +158,45 @@ def mp_layer_attr_workspace_bytes(N, E, H, k, dtype):
 
 
 def mp_layer_attr_fwd(N, E, H, k, dtype, alpha, row_ptr, dst, col, attr, rvec, h_in, v_in, W, h_out, v_out, saved, ws):
-    _check(_mpa_fwd(_stream(), N, E, H, k, dtype, alpha, _p(row_ptr), _p(dst), _p(col), _p(attr), _p(rvec),
-                    _p(h_in), _p(v_in), _p(W), _p(h_out), _p(v_out), _p(saved), _nbytes(saved), _p(ws), _nbytes(ws)))
+    _check(_n.mp_layer_attr_fwd(N, E, H, k, dtype, alpha, row_ptr, dst, col, attr, rvec, h_in, v_in, W, h_out, v_out,
+                                saved, ws))
 
 
 def mp_layer_attr_bwd(N, E, H, k, dtype, alpha, row_ptr, dst, col, attr, rvec, colT_ptr, permT, h_in, W, saved,
                       g_h_out, g_v_out, g_h_in, g_v_in, gW, ws, g_attr=None, g_rvec=None):
-    _check(_mpa_bwd(_stream(), N, E, H, k, dtype, alpha, _p(row_ptr), _p(dst), _p(col), _p(attr), _p(rvec),
-                    _p(colT_ptr), _p(permT), _p(h_in), _p(W), _p(saved), _nbytes(saved), _p(g_h_out), _p(g_v_out),
-                    _p(g_h_in), _p(g_v_in), _p(gW), _p(g_attr), _p(g_rvec), _p(ws), _nbytes(ws)))
+    _check(_n.mp_layer_attr_bwd(N, E, H, k, dtype, alpha, row_ptr, dst, col, attr, rvec, colT_ptr, permT, h_in, W,
+                                saved, g_h_out, g_v_out, g_h_in, g_v_in, gW, g_attr, g_rvec, ws))
 
 
 def edge_rbf_bwd(E, d2, k, rc, g_attr, g_d2):
-    _check(_rbf_bwd(_stream(), E, _p(d2), k, rc, _p(g_attr), _p(g_d2)))
+    _check(_n.edge_rbf_bwd(E, d2, k, rc, g_attr, g_d2))
 
 
 def edge_geometry_fwd(N, E, rvec0, v, dst, col, rvec, d2):
-    _check(_geom_fwd(_stream(), N, E, _p(rvec0), _p(v), _p(dst), _p(col), _p(rvec), _p(d2)))
+    _check(_n.edge_geometry_fwd(N, E, rvec0, v, dst, col, rvec, d2))
 
 
 def edge_geometry_bwd(N, E, row_ptr, colT_ptr, permT, rvec, g_rvec, g_d2, g_r, g_r_sum, g_v):
-    _check(_geom_bwd(_stream(), N, E, _p(row_ptr), _p(colT_ptr), _p(permT), _p(rvec), _p(g_rvec), _p(g_d2), _p(g_r),
-                     _p(g_r_sum), _p(g_v)))
+    _check(_n.edge_geometry_bwd(N, E, row_ptr, colT_ptr, permT, rvec, g_rvec, g_d2, g_r, g_r_sum, g_v))
 
 
 def mp_layer_fwd(N, E, H, dtype, alpha, row_ptr, dst, col, d2, rvec, h_in, v_in, W, h_out, v_out, saved, ws):
-    _check(_mp_fwd(_stream(), N, E, H, dtype, alpha, _p(row_ptr), _p(dst), _p(col), _p(d2), _p(rvec),
-                   _p(h_in), _p(v_in), _p(W), _p(h_out), _p(v_out), _p(saved), _nbytes(saved), _p(ws), _nbytes(ws)))
+    _check(_n.mp_layer_fwd(N, E, H, dtype, alpha, row_ptr, dst, col, d2, rvec, h_in, v_in, W, h_out, v_out, saved,
+                           ws))
 
 
 def mp_layer_bwd(N, E, H, dtype, alpha, row_ptr, dst, col, d2, rvec, colT_ptr, permT, h_in, W, saved,
                  g_h_out, g_v_out, g_h_in, g_v_in, gW, ws):
-    _check(_mp_bwd(_stream(), N, E, H, dtype, alpha, _p(row_ptr), _p(dst), _p(col), _p(d2), _p(rvec),
-                   _p(colT_ptr), _p(permT), _p(h_in), _p(W), _p(saved), _nbytes(saved), _p(g_h_out), _p(g_v_out),
-                   _p(g_h_in), _p(g_v_in), _p(gW), _p(ws), _nbytes(ws)))
+    _check(_n.mp_layer_bwd(N, E, H, dtype, alpha, row_ptr, dst, col, d2, rvec, colT_ptr, permT, h_in, W, saved,
+                           g_h_out, g_v_out, g_h_in, g_v_in, gW, ws))
 
 
 def pool_by_graph_fwd(N, G, H, mode, graph_off, h, p):
-    _check(_pool_fwd(_stream(), N, G, H, mode, _p(graph_off), _p(h), _p(p)))
+    _check(_n.pool_by_graph_fwd(N, G, H, mode, graph_off, h, p))
 
 
 def pool_by_graph_bwd(N, G, H, mode, graph_off, g_p, g_h, accumulate):
-    _check(_pool_bwd(_stream(), N, G, H, mode, _p(graph_off), _p(g_p), _p(g_h), int(accumulate)))
+    _check(_n.pool_by_graph_bwd(N, G, H, mode, graph_off, g_p, g_h, int(accumulate)))
 
 
 def multihead_plan_ints(N, G, S):
@@ -245,7 +204,7 @@ def multihead_plan_ints(N, G, S):
 
 
 def multihead_plan(N, G, S, graph_off, source_id, plan):
-    _check(_plan(_stream(), N, G, S, _p(graph_off), _p(source_id), _p(plan)))
+    _check(_n.multihead_plan(N, G, S, graph_off, source_id, plan))
 
 
 def plan_fields(plan, N, G, S):
@@ -265,15 +224,13 @@ def multihead_decode_workspace_bytes(N, G, H, Hh, S, dtype):
 
 
 def multihead_decode_fwd(N, G, H, Hh, S, dtype, plan, p, h, v, Whead, energy, force, saved, ws):
-    _check(_dec_fwd(_stream(), N, G, H, Hh, S, dtype, _p(plan), _p(p), _p(h), _p(v), _p(Whead), _p(energy),
-                    _p(force), _p(saved), _nbytes(saved), _p(ws), _nbytes(ws)))
+    _check(_n.multihead_decode_fwd(N, G, H, Hh, S, dtype, plan, p, h, v, Whead, energy, force, saved, ws))
 
 
 def multihead_decode_bwd(N, G, H, Hh, S, dtype, plan, p, h, v, Whead, saved, g_energy, g_force, g_p, g_h, g_v,
                          gWhead, ws):
-    _check(_dec_bwd(_stream(), N, G, H, Hh, S, dtype, _p(plan), _p(p), _p(h), _p(v), _p(Whead), _p(saved),
-                    _nbytes(saved), _p(g_energy), _p(g_force), _p(g_p), _p(g_h), _p(g_v), _p(gWhead), _p(ws),
-                    _nbytes(ws)))
+    _check(_n.multihead_decode_bwd(N, G, H, Hh, S, dtype, plan, p, h, v, Whead, saved, g_energy, g_force, g_p, g_h,
+                                   g_v, gWhead, ws))
 
 
 def multihead_deep_workspace_bytes(N, G, H, Hh, D, S, dtype):
@@ -283,15 +240,13 @@ def multihead_deep_workspace_bytes(N, G, H, Hh, D, S, dtype):
 
 
 def multihead_deep_fwd(N, G, H, Hh, D, S, dtype, plan, p, h, v, Whead, energy, force, saved, ws):
-    _check(_deep_fwd(_stream(), N, G, H, Hh, D, S, dtype, _p(plan), _p(p), _p(h), _p(v), _p(Whead), _p(energy),
-                     _p(force), _p(saved), _nbytes(saved), _p(ws), _nbytes(ws)))
+    _check(_n.multihead_deep_fwd(N, G, H, Hh, D, S, dtype, plan, p, h, v, Whead, energy, force, saved, ws))
 
 
 def multihead_deep_bwd(N, G, H, Hh, D, S, dtype, plan, p, h, v, Whead, saved, g_energy, g_force, g_p, g_h, g_v,
                        gWhead, ws):
-    _check(_deep_bwd(_stream(), N, G, H, Hh, D, S, dtype, _p(plan), _p(p), _p(h), _p(v), _p(Whead), _p(saved),
-                     _nbytes(saved), _p(g_energy), _p(g_force), _p(g_p), _p(g_h), _p(g_v), _p(gWhead), _p(ws),
-                     _nbytes(ws)))
+    _check(_n.multihead_deep_bwd(N, G, H, Hh, D, S, dtype, plan, p, h, v, Whead, saved, g_energy, g_force, g_p, g_h,
+                                 g_v, gWhead, ws))
 
 
 # ------------------------------------------------------------------------------------------------
@@ -313,7 +268,7 @@ def profile_tag_name(tag):
 
 def adamw_step(w, g, m, v, step, lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01):
     """In-place AdamW update of the flat float32 device tensor w (moments m, v; gradient g); step counts from 1."""
-    _check(_adamw(_stream(), w.numel(), _p(w), _p(g), _p(m), _p(v), step, lr, beta1, beta2, eps, weight_decay))
+    _check(_n.adamw_step(w.numel(), w, g, m, v, step, lr, beta1, beta2, eps, weight_decay))
 
 def profile_begin(tag_mask):
     _check(_prof_begin(tag_mask))

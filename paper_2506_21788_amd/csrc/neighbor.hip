@@ -1154,7 +1154,7 @@ extern "C" int32_t hgnn_radius_graph_count(void* stream, int32_t N, int32_t G, c
     k_fill_i32<<<1, 64, 0, st>>>(row_ptr, 1, 0);
     k_fill_i32<<<1, 64, 0, st>>>(w.colT_ptr, 1, 0);
     HGNN_LAUNCH_CHECK("k_fill_i32");
-    HGNN_HIP(wait_stream(st));
+    HGNN_HIP(hipStreamSynchronize(st));
     return HGNN_OK;
   }
   MailSlot mail;

@@ -132,3 +132,28 @@ def test_geometry_entry_points_check_their_arguments_on_the_host():
     assert bwd(None, i32(5), i64(10), None, None, None, fake(4), fake(1), fake(2), fake(3), fake(3), None) == -2     # g_r_sum aliases g_r
     assert b"alias" in lib.hgnn_last_error_string()
     assert bwd(None, i32(5), i64(2 ** 31), None, None, None, fake(4), fake(1), fake(2), fake(3), None, None) == -7   # 3 E overflows
+
+
+def test_native_entry_points_refuse_what_is_no_device_tensor():
+    """Tensors on the host, arguments that are no tensors, missing and surplus ones: refused before anything is called."""
+    import pytest
+    import torch
+    from paper_2506_21788_amd import _native, binding as B
+    host = torch.zeros(4)
+    with pytest.raises(AssertionError, match="contiguous device tensors"):
+        B.embed_fwd(1, 4, host, host, host)
+    with pytest.raises(TypeError, match="argument 3: expected a tensor or None, got numpy.ndarray"):
+        B.embed_fwd(1, 4, host.numpy(), None, None)
+    with pytest.raises(TypeError):
+        B.embed_fwd(1.0, 4, None, None, None)
+    with pytest.raises(TypeError):
+        B.edge_rbf(0, None, 4, "5", None)
+    with pytest.raises(TypeError, match="too few"):
+        _native.embed_fwd(1, 4, None)
+    with pytest.raises(TypeError, match="too many"):
+        _native.embed_fwd(1, 4, None, None, None, None)
+    # every function that enqueues work has its native entry point (the others are called through ctypes)
+    by_ctypes = {"hgnn_last_error_string", "hgnn_version", "hgnn_set_side_stream", "hgnn_multihead_plan_ints"}
+    for name in declared_symbols():
+        if name not in by_ctypes and not name.startswith("hgnn_profile_") and not name.endswith("_workspace_bytes"):
+            assert hasattr(_native, name[len("hgnn_"):]), name
