@@ -14,7 +14,9 @@ enum { EPI_T = 0, EPI_ROW = 1, EPI_PART = 2 };
 inline int64_t frag_group_rows(int64_t M, int S) { return (M + 255) / 256 * 256 + 256 * (int64_t)S; }
 
 struct FGemmArgs {
-  const char* A = nullptr;   // fragment (i, kb) at A + (i * a_si + kb * a_sk) KiB
+  // row products: fragment (i, kb) at A + (i * a_si + kb * a_sk) KiB; split partials (EPI_PART): R fragments of the rows to
+  // contract over, 16-column block c of row block rb at A + (rb * a_sk + c) KiB, likewise B
+  const char* A = nullptr;
   long a_si = 0, a_sk = 0;
   const char* B = nullptr;   // fragment (j, kb) at B + group * b_grp_stride + (j * b_sj + kb * b_sk) KiB
   long b_sj = 0, b_sk = 0;
@@ -73,11 +75,11 @@ int32_t launch_fgemm_rows(hipStream_t st, const FGemmArgs& a);     // EPI_ROW, 2
 int32_t launch_fgemm_rows_T(hipStream_t st, const FGemmArgs& a);   // EPI_T, 256 x 128 tiles
 
 // dest[group * dest_grp_stride + pa * strideA + pb * strideB + r1 * HB + r2] = (A^T B)[pa * HpA + r1][pb * HpB + r2]
-// for r1 < HA, r2 < HB, summed over the rows (of each group) in a fixed order. A, B: T fragments.
+// for r1 < HA, r2 < HB, summed over the rows (of each group) in a fixed order. A, B: R fragments.
 struct FWgradArgs {
-  const char* A_T = nullptr;
-  int a_ncb = 0, a_cb0 = 0, nI = 0;   // column blocks per row group, first block used, blocks used (multiple of 4)
-  const char* B_T = nullptr;
+  const char* A_R = nullptr;
+  int a_ncb = 0, a_cb0 = 0, nI = 0;   // 32-column blocks per row block, first block used, blocks used (multiple of 4)
+  const char* B_R = nullptr;
   int b_ncb = 0, b_cb0 = 0, nJ = 0;
   int64_t rows = 0;                    // padded rows (ungrouped), or the largest possible group's padded rows
   const int32_t* grp_ptr = nullptr;
@@ -126,8 +128,6 @@ struct ToFragArgs {
   const int32_t* row_idx = nullptr;   // grouped: position -> source row; null: the source is indexed by padded row
   char* R = nullptr;  // R fragments: r_nkb contraction blocks per row block, this tensor starts at block r_kb0
   int r_nkb = 0, r_kb0 = 0;
-  char* T = nullptr;  // T fragments: t_ncb column blocks per row group, this tensor starts at block t_cb0
-  int t_ncb = 0, t_cb0 = 0;
   // optional: the column sums of every 32 rows of the padded row order (before the rounding), [padded rows / 32][ncol],
   // colsum_rows_partial_floats(rows, ncol, S); launch_frag_colsum() adds them up
   float* cs_partial = nullptr;

@@ -150,7 +150,7 @@ static DeepSaved carve_deep_saved(void* p, const DeepDims& d) {
 
 struct DeepWs {
   unsigned short* packed;   // [S][Pmax x Pmax] bf16, one layer at a time
-  char *R0, *R1, *T0, *T1;  // fragment operands [Pb, Pmax]
+  char *R0, *R1;            // fragment operands [Pb, Pmax]
   float* ga;                // [Pb, Hhp] gradient of a hidden activation, padded row order
   float* gzD[2];            // gradient of the last hidden pre-activation, caller's row order
   float* gq;                // [N]
@@ -168,8 +168,6 @@ static DeepWs carve_deep_ws(void* p, const DeepDims& d) {
   const size_t fb = (size_t)Pb * d.Pmax * 2;
   w.R0 = c.take<char>(fb);
   w.R1 = c.take<char>(fb);
-  w.T0 = c.take<char>(fb);
-  w.T1 = c.take<char>(fb);
   w.ga = c.take<float>((size_t)Pb * d.Hhp);
   w.gzD[0] = c.take<float>((size_t)d.G * d.Hhp + 4);
   w.gzD[1] = c.take<float>((size_t)d.N * d.Hhp + 4);
@@ -340,24 +338,23 @@ extern "C" int32_t hgnn_multihead_deep_bwd(void* stream, int32_t N, int32_t G, i
       t.X = w.gzD[hd]; t.ldx = d.Hhp; t.ncol = Hh; t.Cp = d.Hhp; t.Mp = d.Mp[hd];
       t.grp_ptr = gptr; t.S = S; t.row_idx = ridx;
       t.R = w.R0; t.r_nkb = d.Hhp / 16;
-      t.T = w.T0; t.t_ncb = d.Hhp / 32;
       HGNN_TRY(launch_to_frag(st, t));
     }
     for (int l = D; l >= 1; --l) {
       const int K = l == 1 ? H : Hh, Kp = l == 1 ? d.Hp : d.Hhp;
       HGNN_TRY(launch_frag_colsum(st, tz, gWhead + o.b[hd][l], o.per));
-      {  // the layer's input as T fragments: the gathered rows, or silu of the previous pre-activation
+      {  // the layer's input: the gathered rows, or silu of the previous pre-activation
         ToFragArgs t;
         t.Mp = d.Mp[hd]; t.grp_ptr = gptr; t.S = S;
-        t.T = w.T1; t.t_ncb = Kp / 32;
+        t.R = w.R1; t.r_nkb = Kp / 16;
         if (l == 1) { t.X = X; t.ldx = H; t.ncol = H; t.Cp = d.Hp; t.row_idx = ridx; }
         else { t.X = s.z[hd][l - 1]; t.ldx = d.Hhp; t.mode = 1; t.ncol = Hh; t.Cp = d.Hhp; }
         HGNN_TRY(launch_to_frag(st, t));
       }
       {  // g_W_l = input^T g_z_l per source
         FWgradArgs a;
-        a.A_T = w.T1; a.a_ncb = Kp / 32; a.nI = Kp / 32;
-        a.B_T = w.T0; a.b_ncb = d.Hhp / 32; a.nJ = d.Hhp / 32;
+        a.A_R = w.R1; a.a_ncb = Kp / 32; a.nI = Kp / 32;
+        a.B_R = w.R0; a.b_ncb = d.Hhp / 32; a.nJ = d.Hhp / 32;
         a.rows = d.Mp[hd]; a.grp_ptr = gptr; a.S = S;
         a.HpA = Kp; a.HA = K; a.HpB = d.Hhp; a.HB = Hh;
         a.partial = w.partial; a.partial_floats = w.partial_floats;
@@ -385,7 +382,6 @@ extern "C" int32_t hgnn_multihead_deep_bwd(void* stream, int32_t N, int32_t G, i
         t.X = w.ga; t.ldx = d.Hhp; t.Z = s.z[hd][l - 1]; t.ldz = d.Hhp; t.mode = 2; t.ncol = Hh; t.Cp = d.Hhp;
         t.Mp = d.Mp[hd]; t.grp_ptr = gptr; t.S = S;
         t.R = w.R0; t.r_nkb = d.Hhp / 16;
-        t.T = w.T0; t.t_ncb = d.Hhp / 32;
         HGNN_TRY(launch_to_frag(st, t));
       }
     }

@@ -7,9 +7,9 @@
 // v_mfma_f32_32x32x16_bf16 (64 lanes x 8 bf16), so that staging and operand loads are straight copies:
 //   R(X) [rb32][kb16][lane][8]  lane (g, r)  holds X[32 rb32 + r, 16 kb16 + 8 g + (0..7)]     (rows x contraction)
 //   T(X) [rb16][cb32][lane][8]  lane (g, c)  holds X[16 rb16 + 8 (u >> 2) + 4 g + (u & 3), 32 cb32 + c], u = 0..7
-// R feeds products that contract over columns (X W). T feeds products that contract over rows (X^T Y; the row
-// order inside a group of 16 is the same for both operands and cancels) and is also exactly what the accumulator
-// registers of a product hold, so a product's result is stored as T without any shuffle.
+// R feeds products that contract over columns (X W) and, through transposing LDS reads, products that contract over rows
+// (X^T Y). T is exactly what the accumulator registers of a product hold, so the result of a per-edge product, which only
+// element-wise kernels read, is stored as T without any shuffle.
 // Widths are padded to a multiple of 128 (Hp) and row counts to a multiple of 256, padding filled with zeros.
 #pragma once
 

@@ -5,9 +5,9 @@
 //                  also forms M_i = alpha sum silu(z2) per destination atom and x_e = wx . m_e in its epilogue
 //   k_seg_fwd_fix  the atoms whose edges span several 64-row strips of that epilogue, v'_i = v_i + alpha sum x_e rvec_e
 //   k_pack_frag    fp32 weight slices -> B fragments (zero padded)
-//   k_to_frag      row-major fp32 atom tensor -> R and / or T fragments (optionally silu(x) or x * silu'(z))
-//   k_edge_elem    the three element-wise edge kernels on 32 x 128 tiles: a1 = silu(P[dst] + Q[col] + d2 w1d) -> R, T;
-//                  g_z2 = (alpha g_M[dst] + c_e wx) silu'(z2) -> R, T (+ column sums for g_b2, g_wx);
+//   k_to_frag      row-major fp32 atom tensor -> R fragments (optionally silu(x) or x * silu'(z))
+//   k_edge_elem    the three element-wise edge kernels on 32 x 128 tiles: a1 = silu(P[dst] + Q[col] + d2 w1d) -> R;
+//                  g_z2 = (alpha g_M[dst] + c_e wx) silu'(z2) -> R (+ column sums for g_b2, g_wx);
 //                  g_z1 = g_a1 silu'(z1) -> row-major (+ column sums for g_b1, g_w1d)
 //   k_segsum_rows  per-atom sums of g_z1 over the destination-sorted rows and over the source-sorted edge list
 // The layer follows the same algebra as the narrow path: the first edge layer is split by linearity into per-atom
@@ -50,6 +50,21 @@ struct FCfg {
   static constexpr int LDS_BYTES = 2 * NF * 1024;   // two steps: one being multiplied, one being written
   static_assert(NF % NW == 0, "fragments per step must divide among the wavefronts");
 };
+
+// Split partials contract over rows, of operands that are R fragments like every other: the two fragments of 16 columns that a
+// 32-column block of 32 rows is are staged as they are, and an operand (eight rows of one column per lane) is two transposing
+// LDS reads. A transposing read takes four rows of 16 columns per 16 lanes, 64 bytes of either half of a fragment; the rows of a
+// fragment are placed (xor) so that the halves and the fragments of a pair lie in different banks. Before, a second copy of
+// every such operand was written in the order of the accumulators ("T"): 0.45 GB per edge tensor at 254,000 edges of 866
+// columns. Steps: 128 mixed structures at H = 866 10.96 -> 10.27 ms, at H = 320 4.21 -> 3.83, 60 crystals at H = 1000 3.63 -> 3.44
+// (at 866 the two element-wise kernels 217 -> 132 and 263 -> 146 us per layer, conversions 13.8 -> 11.2 us; the W2 gradient pays 387 -> 421:
+// a transposing read takes the LDS as long as an ordinary one of twice the bytes, 83 % busy).
+typedef short s16x4_frag_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8_t frag_read_tr(const char* lo, const char* hi) {
+  const s16x4_frag_t l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_frag_t*)(lo));
+  const s16x4_frag_t h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_frag_t*)(hi));
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 // RB: rows per batch of the row epilogue
 template <int WI, int WJ, int EPI, int RB = 8, int NW = 4, int KC = 2>
@@ -103,17 +118,24 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
   const int kend = kbeg + kper < kbase + knum ? kbeg + kper : kbase + knum;
   const char* Bg = p.B + (long)grp * p.b_grp_stride;
 
-  // pass s copies fragment f = 4 s + wave of the step: first the KC x TI fragments of A, then the KC x TJ of B
+  // pass s copies fragment f = NW s + wave of the step: first the KC x TI fragments of A, then the KC x TJ of B
+  // (split partials: a step is the 32 rows of one row block, its fragments the 16-column blocks of the tile)
+  static_assert(EPI != EPI_PART || (KC == 2 && NW % 2 == 0), "a row block per step, the parity of a fragment that of its wavefront");
   const char* src[C::PASSES];
   long kst[C::PASSES];
 #pragma unroll
   for (int s = 0; s < C::PASSES; ++s) {
     const int f = NW * s + wave;
-    if (f < C::KC * C::TI) {
+    if (EPI == EPI_PART) {
+      const bool isa = f < C::KC * C::TI;
+      const int cc = isa ? f : f - C::KC * C::TI;     // 16-column block
+      const int b0 = (isa ? i0 : j0) + (cc >> 1), nb = isa ? p.nI : p.nJ;
+      const int b = b0 < nb ? b0 : nb - 1;            // (blocks past the last one repeat it and are never stored)
+      src[s] = (isa ? p.A : Bg) + (long)(2 * b + (cc & 1)) * 1024 + lane * 16;
+      kst[s] = (isa ? p.a_sk : p.b_sk) * 512;         // per 16 rows: a_sk fragments per row block
+    } else if (f < C::KC * C::TI) {
       const int kk = f / C::TI, ii = f % C::TI;
-      // (split partials: row blocks past nI repeat the last one and are never stored)
-      const int ib = (EPI == EPI_PART && i0 + ii >= p.nI) ? p.nI - 1 : i0 + ii;
-      src[s] = p.A + ((long)ib * p.a_si + (long)kk * p.a_sk) * 1024 + lane * 16;
+      src[s] = p.A + ((long)(i0 + ii) * p.a_si + (long)kk * p.a_sk) * 1024 + lane * 16;
       kst[s] = p.a_sk * 1024;
     } else {
       const int f2 = f - C::KC * C::TI;
@@ -140,6 +162,15 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
   u32x4_t preX[C::PASSES], preY[C::PASSES];
   auto kclamp = [&](int ch) { return kbeg + (ch < nch ? ch : (nch > 0 ? nch - 1 : 0)) * C::KC; };
   constexpr int STAGE = C::NF * 64;   // 16-byte units per half
+  // where a lane's 16 bytes (half lane >> 5, row lane & 31) of a fragment go, and its transposing reads start
+  const int put = EPI == EPI_PART ? (lane ^ ((lane >> 5) << 2) ^ ((wave & 1) << 3)) : lane;
+  [[maybe_unused]] unsigned tr_lo = 0, tr_hi = 0;
+  if constexpr (EPI == EPI_PART) {
+    const int gc = (lane & 3) >> 1, odd = (lane >> 4) & 1;
+    const int r = ((lane >> 2) & 3) | (((lane >> 5) ^ gc) << 2);
+    tr_lo = odd * 1024 + (gc * 32 + (r | (odd << 3))) * 16 + (lane & 1) * 8;
+    tr_hi = odd * 1024 + (gc * 32 + (r | ((odd ^ 1) << 3))) * 16 + (lane & 1) * 8;
+  }
   if (nch > 0) {
     {
       const long k0 = kclamp(0), k1 = kclamp(1), k2 = kclamp(2);
@@ -148,7 +179,7 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
 #pragma unroll
       for (int s = 0; s < C::PASSES; ++s) preY[s] = *reinterpret_cast<const u32x4_t*>(src[s] + k1 * kst[s]);
 #pragma unroll
-      for (int s = 0; s < C::PASSES; ++s) lds[(NW * s + wave) * 64 + lane] = preX[s];
+      for (int s = 0; s < C::PASSES; ++s) lds[(NW * s + wave) * 64 + put] = preX[s];
 #pragma unroll
       for (int s = 0; s < C::PASSES; ++s) preX[s] = *reinterpret_cast<const u32x4_t*>(src[s] + k2 * kst[s]);
     }
@@ -166,11 +197,20 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
 #pragma unroll
           for (int kk = 0; kk < C::KC; ++kk) {
             bf16x8_t a[WI], b[WJ];
+            if constexpr (EPI == EPI_PART) {
+              const char* pa = reinterpret_cast<const char*>(cur) + (wi * WI) * 2048 + kk * 256;
+              const char* pb = reinterpret_cast<const char*>(cur) + (C::TI + wj * WJ) * 2048 + kk * 256;
 #pragma unroll
-            for (int i = 0; i < WI; ++i) a[i] = __builtin_bit_cast(bf16x8_t, cur[(kk * C::TI + wi * WI + i) * 64 + lane]);
+              for (int i = 0; i < WI; ++i) a[i] = frag_read_tr(pa + tr_lo + i * 2048, pa + tr_hi + i * 2048);
 #pragma unroll
-            for (int j = 0; j < WJ; ++j)
-              b[j] = __builtin_bit_cast(bf16x8_t, cur[(C::KC * C::TI + kk * C::TJ + wj * WJ + j) * 64 + lane]);
+              for (int j = 0; j < WJ; ++j) b[j] = frag_read_tr(pb + tr_lo + j * 2048, pb + tr_hi + j * 2048);
+            } else {
+#pragma unroll
+              for (int i = 0; i < WI; ++i) a[i] = __builtin_bit_cast(bf16x8_t, cur[(kk * C::TI + wi * WI + i) * 64 + lane]);
+#pragma unroll
+              for (int j = 0; j < WJ; ++j)
+                b[j] = __builtin_bit_cast(bf16x8_t, cur[(C::KC * C::TI + kk * C::TJ + wj * WJ + j) * 64 + lane]);
+            }
 #pragma unroll
             for (int i = 0; i < WI; ++i)
 #pragma unroll
@@ -181,12 +221,12 @@ __global__ void __launch_bounds__(64 * NW, (WI * WJ <= 8 ? 2 : 1)) k_fgemm(FGemm
           const long kn = kclamp(cc + 3);
           if (par == 0) {
 #pragma unroll
-            for (int s = 0; s < C::PASSES; ++s) lds[nslot * STAGE + (NW * s + wave) * 64 + lane] = preY[s];
+            for (int s = 0; s < C::PASSES; ++s) lds[nslot * STAGE + (NW * s + wave) * 64 + put] = preY[s];
 #pragma unroll
             for (int s = 0; s < C::PASSES; ++s) preY[s] = *reinterpret_cast<const u32x4_t*>(src[s] + kn * kst[s]);
           } else {
 #pragma unroll
-            for (int s = 0; s < C::PASSES; ++s) lds[nslot * STAGE + (NW * s + wave) * 64 + lane] = preX[s];
+            for (int s = 0; s < C::PASSES; ++s) lds[nslot * STAGE + (NW * s + wave) * 64 + put] = preX[s];
 #pragma unroll
             for (int s = 0; s < C::PASSES; ++s) preX[s] = *reinterpret_cast<const u32x4_t*>(src[s] + kn * kst[s]);
           }
@@ -651,9 +691,8 @@ int32_t launch_pack_frag(hipStream_t st, const PackFragArgs& a) {
 // row-major fp32 -> fragments.  mode 0: x, 1: silu(x), 2: x * silu'(z)
 // ---------------------------------------------------------------------------------------------
 // One workgroup per tile of 32 rows x 128 columns, in the two mappings of the element-wise edge kernels below:
-// compute mapping thread (q, x) = the 8 rows of one row set x the column pair 128 slab + 2 x, + 1 (T fragments leave
-// in this mapping, 32 bytes per lane), R fragments through an LDS copy of the tile (one whole fragment per store
-// instruction). VEC2: the column pair is read with one 8-byte load (the launcher checks the alignment).
+// compute mapping thread (q, x) = the 8 rows of one row set x the column pair 128 slab + 2 x, + 1; the fragments leave
+// through an LDS copy of the tile (one whole fragment per store instruction). VEC2: the column pair is read with one 8-byte load (the launcher checks the alignment).
 template <bool VEC2>
 __global__ void __launch_bounds__(256) k_to_frag(ToFragArgs a) {
   __shared__ __align__(16) unsigned short tile[32 * 136];
@@ -716,39 +755,26 @@ __global__ void __launch_bounds__(256) k_to_frag(ToFragArgs a) {
       if (c + 1 < a.ncol) o[c + 1] = cs1;
     }
   }
-  if (a.T) {   // destination rows are the padded ones
-    const long rb16 = pad0 / 16 + 2 * rb + hh;
-    const long tfrag = ((rb16 * a.t_ncb + a.t_cb0 + (c >> 5)) * 64 + g * 32 + (c & 31)) * 16;
-    u32x4_t t0, t1;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      t0[k] = (packed[2 * k] & 0xffffu) | (packed[2 * k + 1] << 16);
-      t1[k] = (packed[2 * k] >> 16) | (packed[2 * k + 1] & 0xffff0000u);
-    }
-    *reinterpret_cast<u32x4_t*>(a.T + tfrag) = t0;
-    *reinterpret_cast<u32x4_t*>(a.T + tfrag + 16) = t1;
+  for (int u = 0; u < 8; ++u) {
+    const int lr = 16 * hh + 8 * (u >> 2) + 4 * g + (u & 3);
+    *reinterpret_cast<unsigned*>(&tile[lr * 136 + 2 * x]) = packed[u];
   }
-  if (a.R) {
+  __syncthreads();
+  const int lr = x & 31, g2 = x >> 5;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int lr = 16 * hh + 8 * (u >> 2) + 4 * g + (u & 3);
-      *reinterpret_cast<unsigned*>(&tile[lr * 136 + 2 * x]) = packed[u];
-    }
-    __syncthreads();
-    const int lr = x & 31, g2 = x >> 5;
-#pragma unroll
-    for (int kb2 = 0; kb2 < 2; ++kb2) {
-      const int kbl = 2 * q + kb2;   // contraction block inside the tile
-      const u32x4_t w = *reinterpret_cast<const u32x4_t*>(&tile[lr * 136 + kbl * 16 + g2 * 8]);
-      const long frag = (long)(pad0 / 32 + rb) * a.r_nkb + a.r_kb0 + 8 * slab + kbl;
-      *reinterpret_cast<u32x4_t*>(a.R + (frag * 64 + x) * 16) = w;
-    }
+  for (int kb2 = 0; kb2 < 2; ++kb2) {   // destination rows are the padded ones
+    const int kbl = 2 * q + kb2;        // contraction block inside the tile
+    const u32x4_t w = *reinterpret_cast<const u32x4_t*>(&tile[lr * 136 + kbl * 16 + g2 * 8]);
+    const long frag = (long)(pad0 / 32 + rb) * a.r_nkb + a.r_kb0 + 8 * slab + kbl;
+    *reinterpret_cast<u32x4_t*>(a.R + (frag * 64 + x) * 16) = w;
   }
 }
 
 int32_t launch_to_frag(hipStream_t st, const ToFragArgs& a) {
   HGNN_REQUIRE(a.Mp % 256 == 0 && a.Cp % 128 == 0, HGNN_ERR_BAD_SHAPE, "to_frag: padded extents do not tile");
   if (a.Mp == 0 || a.Cp == 0) return HGNN_OK;
+  HGNN_REQUIRE(a.R != nullptr, HGNN_ERR_NULLPTR, "to_frag: null destination");
   HGNN_REQUIRE(a.Mp / 32 <= 65535, HGNN_ERR_OVERFLOW, "to_frag: too many rows");
   ProfScope ps(PT_TO_FRAG, st);
   const dim3 grid(a.Cp / 128, a.Mp / 32, a.grp_ptr ? a.S : 1);
@@ -884,7 +910,7 @@ __global__ void __launch_bounds__(256) k_reduce_wgrad(const float* __restrict__ 
 // ---------------------------------------------------------------------------------------------
 // element-wise edge kernels. A workgroup walks tiles of 32 edges (one row block) x 128 columns:
 //   compute mapping, thread (q, x) = (tid >> 6, tid & 63): the 8 edges of row set (row group 2 rb32 + (q >> 1), lane
-//     half q & 1) in the column pair 128 slab + 2 x, + 1. T fragments are loaded and stored in this mapping (32 bytes
+//     half q & 1) in the column pair 128 slab + 2 x, + 1. T fragments are loaded in this mapping (32 bytes
 //     per lane, a wavefront moves four contiguous half fragments); a gather fetches both columns with one 4-byte load
 //     (the vector memory pipe takes one address per lane whatever the width: 2-byte gathers made these kernels
 //     address-bound).
@@ -903,7 +929,6 @@ struct EdgeElemArgs {
   const unsigned short* PQ = nullptr;   // [N, 2 Hp] bf16 row-major: P | Q
   const float* w1d = nullptr;           // [k, H]: the rows of W1 that act on the attributes
   char* a1_R = nullptr;
-  char* a1_T = nullptr;
   // reverse
   const char* z2_T = nullptr;
   const unsigned short* gM = nullptr;   // bf16 row-major g_M, row pitch ldgM elements
@@ -912,7 +937,6 @@ struct EdgeElemArgs {
   const float* wx = nullptr;            // [H]
   float alpha = 1.f;
   char* gz2_R = nullptr;
-  char* gz2_T = nullptr;
   const char* ga1_T = nullptr;          // g_a1
   unsigned short* gz1_rm = nullptr;     // g_z1, bf16 row-major [rows, Hp]: what the two per-atom sums read
   float* colpart = nullptr;             // [gridDim.y][2 (g_z2) or 1 + k (g_z1)][Hp] column-sum partials
@@ -932,8 +956,8 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
 enum { EE_A1 = 0, EE_GZ2 = 1, EE_GZ1 = 2 };
 constexpr int EE_PITCH = 136;   // LDS tile row pitch in bf16 elements (128 + 8: 16-byte reads of a column of rows spread over the banks)
 
-// EE_A1:  a1 = silu(z1), z1 = P[dst] + Q[col] + sum_j attr_j w1d_j               -> R and T
-// EE_GZ2: g_z2 = (alpha g_M[dst] + c_e wx) silu'(z2)                            -> R and T; sums: g_b2 = sum g_z2, g_wx = sum c_e silu(z2)
+// EE_A1:  a1 = silu(z1), z1 = P[dst] + Q[col] + sum_j attr_j w1d_j               -> R
+// EE_GZ2: g_z2 = (alpha g_M[dst] + c_e wx) silu'(z2)                            -> R; sums: g_b2 = sum g_z2, g_wx = sum c_e silu(z2)
 // EE_GZ1: g_z1 = g_a1 silu'(z1), z1 recomputed from the gathers                 -> row-major; sums: g_b1 = sum g_z1, g_w1d_j = sum attr_j g_z1
 // KMAX: most edge attributes the instance handles (1: the squared distance alone; 16: p.k of them, p.k <= 16)
 template <int MODE, int KMAX>
@@ -960,7 +984,6 @@ __global__ void __launch_bounds__(256) k_edge_elem(EdgeElemArgs p) {
     w1[j] = on && c + 1 < p.H ? wv[c + 1] : 0.f;
   }
   const long lastrow = p.E > 0 ? p.E - 1 : 0;
-  char* Tdst = MODE == EE_A1 ? p.a1_T : p.gz2_T;
   float s00 = 0.f, s01 = 0.f;          // column sums of the result
   float s10[KMAX], s11[KMAX];          // weighted column sums
 #pragma unroll
@@ -1055,16 +1078,6 @@ __global__ void __launch_bounds__(256) k_edge_elem(EdgeElemArgs p) {
       // (several attributes: keep the rows apart, or the scheduler fetches the attributes of all eight rows first
       // and the kernel runs out of registers)
       if (KMAX > 1) __builtin_amdgcn_sched_barrier(0);
-    }
-    if (MODE != EE_GZ1) {   // g_z1 is only read row by row: it goes out row-major below
-      u32x4_t t0, t1;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        t0[k] = pack_bf16x2(o0[2 * k], o0[2 * k + 1]);
-        t1[k] = pack_bf16x2(o1[2 * k], o1[2 * k + 1]);
-      }
-      *reinterpret_cast<u32x4_t*>(Tdst + tfrag) = t0;
-      *reinterpret_cast<u32x4_t*>(Tdst + tfrag + 16) = t1;
     }
     // the tile in row-major order for the second mapping (rows of this row set: 16 hh + 8 (u >> 2) + 4 g + (u & 3))
     __syncthreads();   // the previous tile has been read
@@ -1251,12 +1264,11 @@ struct LayerOffW {
 struct WideSaved {
   unsigned short* PQ;   // [Np, 2 Hp] bf16 row-major
   char* a1_R;           // [Ep, Hp]
-  char* a1_T;
   char* z2_T;
   float* M;             // [Np, Hp] fp32 row-major
   float* z3;            // [Np, Hp]
-  char* hM_T;           // [Np, 2 Hp] T fragments of [h ; M]     (operands of the reverse pass's weight gradients)
-  char* a3_T;           // [Np, Hp] T fragments of silu(z3)
+  char* hM_R;           // [Np, 2 Hp] R fragments of [h ; M]     (operands of the reverse pass's weight gradients, too)
+  char* a3_R;           // [Np, Hp] R fragments of silu(z3)
   float* xe;            // [Ep] x_e = wx . m_e
   size_t bytes;
 };
@@ -1265,12 +1277,11 @@ static WideSaved carve_saved_w(void* p, const WideDims& d) {
   WideSaved s;
   s.PQ = c.take<unsigned short>((size_t)d.Np * 2 * d.Hp);
   s.a1_R = c.take<char>(d.edge_bytes());
-  s.a1_T = c.take<char>(d.edge_bytes());
   s.z2_T = c.take<char>(d.edge_bytes());
   s.M = c.take<float>((size_t)d.Np * d.Hp);
   s.z3 = c.take<float>((size_t)d.Np * d.Hp);
-  s.hM_T = c.take<char>(d.node_frag_bytes(2));
-  s.a3_T = c.take<char>(d.node_frag_bytes(1));
+  s.hM_R = c.take<char>(d.node_frag_bytes(2));
+  s.a3_R = c.take<char>(d.node_frag_bytes(1));
   s.xe = c.take<float>((size_t)d.Ep + 4);
   s.bytes = c.used();
   return s;
@@ -1278,17 +1289,14 @@ static WideSaved carve_saved_w(void* p, const WideDims& d) {
 
 struct WideWs {
   unsigned short* packed;   // 6 Hp^2 bf16 (the forward or the transposed set)
-  char* hM_R;               // [Np, 2 Hp] R fragments of [h ; M]
-  char* x_R;                // [Np, 2 Hp] scratch R operand (a3, g_h', g_z3, g_PQ)
-  char* gh_T;               // [Np, Hp] T operands of the weight gradients (read on the side stream: each its own)
-  char* gz3_T;              // [Np, Hp]
-  char* gPQ_T;              // [Np, 2 Hp]
+  char* gh_R;               // [Np, Hp] R fragments of g_h' (read on the side stream as well, as the next two: each its own)
+  char* gz3_R;              // [Np, Hp]
+  char* gPQ_R;              // [Np, 2 Hp]
   float* nodeA;             // [Np, Hp] fp32 g_a3
   float* nodeB;             // [Np, 2 Hp] fp32 g_hM
   unsigned short* gM_b;     // [Np, 2 Hp] bf16 row-major copy of g_hM
   float* g_PQ;              // [Np, 2 Hp] fp32
   char* gz2_R;              // [Ep, Hp]
-  char* gz2_T;
   char* ga1_T;
   float* seg_first;         // [Ep / 64, Hp] forward: sums of m over the part of a 64-row strip that belongs to an atom
   float* seg_last;          //   that began before the strip / reaches past its end
@@ -1307,17 +1315,14 @@ static WideWs carve_ws_w(void* p, const WideDims& d) {
   Carver c(p);
   WideWs w;
   w.packed = c.take<unsigned short>((size_t)6 * d.Hp * d.Hp);
-  w.hM_R = c.take<char>(d.node_frag_bytes(2));
-  w.x_R = c.take<char>(d.node_frag_bytes(2));
-  w.gh_T = c.take<char>(d.node_frag_bytes(1));
-  w.gz3_T = c.take<char>(d.node_frag_bytes(1));
-  w.gPQ_T = c.take<char>(d.node_frag_bytes(2));
+  w.gh_R = c.take<char>(d.node_frag_bytes(1));
+  w.gz3_R = c.take<char>(d.node_frag_bytes(1));
+  w.gPQ_R = c.take<char>(d.node_frag_bytes(2));
   w.nodeA = c.take<float>((size_t)d.Np * d.Hp);
   w.nodeB = c.take<float>((size_t)d.Np * 2 * d.Hp);
   w.gM_b = c.take<unsigned short>((size_t)d.Np * 2 * d.Hp);
   w.g_PQ = c.take<float>((size_t)d.Np * 2 * d.Hp);
   w.gz2_R = c.take<char>(d.edge_bytes());
-  w.gz2_T = c.take<char>(d.edge_bytes());
   w.ga1_T = c.take<char>(d.edge_bytes());
   w.cvec = c.take<float>((size_t)d.E + 4);
   w.colpart = c.take<float>((size_t)ELEM_MAX_BLOCKS * 2 * d.Hp);
@@ -1354,8 +1359,8 @@ static FGemmArgs nn_args(const char* A_R, int a_nkb, int nI, const unsigned shor
 constexpr int WIDE_MAX_SPLITS = 256;   // (the partial buffers hold 24 splits of the widest outputs, more of narrow ones)
 int32_t launch_fwgrad(hipStream_t st, const FWgradArgs& a) {
   FGemmArgs g;
-  g.A = a.A_T + (long)a.a_cb0 * 1024; g.a_si = 1; g.a_sk = a.a_ncb;
-  g.B = a.B_T + (long)a.b_cb0 * 1024; g.b_sj = 1; g.b_sk = a.b_ncb;
+  g.A = a.A_R + (long)a.a_cb0 * 2048; g.a_sk = 2 * a.a_ncb;   // (two fragments per column block)
+  g.B = a.B_R + (long)a.b_cb0 * 2048; g.b_sk = 2 * a.b_ncb;
   g.nI = a.nI; g.nJ = a.nJ;
   g.nkb = (int)(a.rows / 16);
   g.grp_ptr = a.grp_ptr; g.S = a.S;
@@ -1432,12 +1437,12 @@ int32_t launch_fgemm_rows(hipStream_t st, const FGemmArgs& a0) {
 int32_t launch_fgemm_rows_T(hipStream_t st, const FGemmArgs& a) { return launch_fgemm_ad(st, a); }
 
 // layer-level shorthand: square Hp blocks, no groups
-static int32_t wgrad_w(hipStream_t st, const WideDims& d, const char* A_T, int a_ncb, int a_cb0, int nI, const char* B_T,
+static int32_t wgrad_w(hipStream_t st, const WideDims& d, const char* A_R, int a_ncb, int a_cb0, int nI, const char* B_R,
                        int b_ncb, int b_cb0, int nJ, int64_t rows, float* partial, size_t partial_floats, float* dest,
                        long strideA, long strideB, int tag) {
   FWgradArgs a;
-  a.A_T = A_T; a.a_ncb = a_ncb; a.a_cb0 = a_cb0; a.nI = nI;
-  a.B_T = B_T; a.b_ncb = b_ncb; a.b_cb0 = b_cb0; a.nJ = nJ;
+  a.A_R = A_R; a.a_ncb = a_ncb; a.a_cb0 = a_cb0; a.nI = nI;
+  a.B_R = B_R; a.b_ncb = b_ncb; a.b_cb0 = b_cb0; a.nJ = nJ;
   a.rows = rows;
   a.HpA = d.Hp; a.HA = d.H; a.HpB = d.Hp; a.HB = d.H;
   a.partial = partial; a.partial_floats = partial_floats;
@@ -1471,12 +1476,11 @@ int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
   {  // h -> first half of the [h ; M] operand
     ToFragArgs t;
     t.X = a.h_in; t.ldx = H; t.M = d.N; t.Mp = d.Np; t.ncol = H; t.Cp = Hp;
-    t.R = w.hM_R; t.r_nkb = 2 * d.nkb; t.r_kb0 = 0;
-    t.T = s.hM_T; t.t_ncb = 2 * d.ncb; t.t_cb0 = 0;
+    t.R = s.hM_R; t.r_nkb = 2 * d.nkb; t.r_kb0 = 0;
     HGNN_TRY(launch_to_frag(st, t));
   }
   {  // P | Q = h [W1a | W1b] + [b1 | 0], bf16 row-major for the edge gathers
-    FGemmArgs g = nn_args(w.hM_R, 2 * d.nkb, d.Np / 32, w.packed, 2 * d.ncb, PT_GEMM_NODE);
+    FGemmArgs g = nn_args(s.hM_R, 2 * d.nkb, d.Np / 32, w.packed, 2 * d.ncb, PT_GEMM_NODE);
     g.nkb = d.nkb; g.kper = d.nkb;            // only the h half of the operand rows
     g.b_sj = d.nkb;
     g.M = d.N; g.Cb = s.PQ; g.ldcb = 2 * Hp;
@@ -1486,7 +1490,7 @@ int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
   EdgeElemArgs e;
   e.E = d.E; e.nrb = (int)(d.Ep / 32); e.H = H; e.Hp = Hp;
   e.dst = a.dst; e.col = a.col; e.attr = a.attr ? a.attr : a.d2; e.k = k; e.PQ = s.PQ; e.w1d = W + o.W1 + 2 * HH;
-  e.a1_R = s.a1_R; e.a1_T = s.a1_T;
+  e.a1_R = s.a1_R;
   if (d.Ep > 0) {
     {
       ProfScope ps(PT_EDGE_ELEM, st);
@@ -1513,12 +1517,11 @@ int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
   {  // M -> second half of the [h ; M] operand
     ToFragArgs t;
     t.X = s.M; t.ldx = Hp; t.M = d.N; t.Mp = d.Np; t.ncol = Hp; t.Cp = Hp;
-    t.R = w.hM_R; t.r_nkb = 2 * d.nkb; t.r_kb0 = d.nkb;
-    t.T = s.hM_T; t.t_ncb = 2 * d.ncb; t.t_cb0 = d.ncb;
+    t.R = s.hM_R; t.r_nkb = 2 * d.nkb; t.r_kb0 = d.nkb;
     HGNN_TRY(launch_to_frag(st, t));
   }
   {  // z3 = [h ; M] W3 + b3
-    FGemmArgs g = nn_args(w.hM_R, 2 * d.nkb, d.Np / 32, w.packed + 3 * PP, d.ncb, PT_GEMM_NODE);
+    FGemmArgs g = nn_args(s.hM_R, 2 * d.nkb, d.Np / 32, w.packed + 3 * PP, d.ncb, PT_GEMM_NODE);
     g.M = d.N; g.Cf = s.z3; g.ldc = Hp; g.ncol_f = Hp;
     g.bias = W + o.b3; g.nbias = H;
     HGNN_TRY(launch_fgemm_rows(st, g));
@@ -1526,12 +1529,11 @@ int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
   {  // a3 = silu(z3)
     ToFragArgs t;
     t.X = s.z3; t.ldx = Hp; t.mode = 1; t.M = d.N; t.Mp = d.Np; t.ncol = H; t.Cp = Hp;
-    t.R = w.x_R; t.r_nkb = d.nkb; t.r_kb0 = 0;
-    t.T = s.a3_T; t.t_ncb = d.ncb; t.t_cb0 = 0;
+    t.R = s.a3_R; t.r_nkb = d.nkb; t.r_kb0 = 0;
     HGNN_TRY(launch_to_frag(st, t));
   }
   {  // h' = h + a3 W4 + b4
-    FGemmArgs g = nn_args(w.x_R, d.nkb, d.Np / 32, w.packed + 5 * PP, d.ncb, PT_GEMM_NODE);
+    FGemmArgs g = nn_args(s.a3_R, d.nkb, d.Np / 32, w.packed + 5 * PP, d.ncb, PT_GEMM_NODE);
     g.M = d.N; g.Cf = a.h_out; g.ldc = H; g.ncol_f = H;
     g.r1 = a.h_in; g.ld1 = H;
     g.bias = W + o.b4; g.nbias = H;
@@ -1572,37 +1574,35 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   hipStream_t sx = side_stream_enabled(true) ? ss.s : st;
   // the column sums of both (g_b4, g_b3) are formed on the way
   ToFragArgs u, t;
-  {  // g_h' as R and T ([h ; M] and silu(z3) were left as T fragments by the forward pass)
+  {  // g_h' as R ([h ; M] and silu(z3) were left by the forward pass)
     u.cs_partial = w.cs_partial[0];
     u.X = a.g_h_out; u.ldx = H; u.M = d.N; u.Mp = d.Np; u.ncol = H; u.Cp = Hp;
-    u.R = w.x_R; u.r_nkb = d.nkb; u.r_kb0 = 0;
-    u.T = w.gh_T; u.t_ncb = d.ncb; u.t_cb0 = 0;
+    u.R = w.gh_R; u.r_nkb = d.nkb; u.r_kb0 = 0;
     HGNN_TRY(launch_to_frag(st, u));
   }
   HGNN_TRY(stream_after(sx, st, ss.ev[0]));
   // side: g_W4 = a3^T g_h', g_b4 = column sums of g_h'
-  HGNN_TRY(wgrad_w(sx, d, s.a3_T, d.ncb, 0, d.ncb, w.gh_T, d.ncb, 0, d.ncb, d.Np, w.partial, w.partial_floats, gW + o.W4,
+  HGNN_TRY(wgrad_w(sx, d, s.a3_R, d.ncb, 0, d.ncb, w.gh_R, d.ncb, 0, d.ncb, d.Np, w.partial, w.partial_floats, gW + o.W4,
                    0, 0, PT_WGRAD_NODE));
   HGNN_TRY(launch_frag_colsum(sx, u, gW + o.b4, 0));
   {  // g_a3 = g_h' W4^T
-    FGemmArgs g = nn_args(w.x_R, d.nkb, d.Np / 32, w.packed, d.ncb, PT_GEMM_NODE);
+    FGemmArgs g = nn_args(w.gh_R, d.nkb, d.Np / 32, w.packed, d.ncb, PT_GEMM_NODE);
     g.M = d.N; g.Cf = w.nodeA; g.ldc = Hp; g.ncol_f = Hp;
     HGNN_TRY(launch_fgemm_rows(st, g));
   }
-  {  // g_z3 = g_a3 silu'(z3) as R and T
+  {  // g_z3 = g_a3 silu'(z3) as R
     t.cs_partial = w.cs_partial[1];
     t.X = w.nodeA; t.ldx = Hp; t.Z = s.z3; t.ldz = Hp; t.mode = 2; t.M = d.N; t.Mp = d.Np; t.ncol = H; t.Cp = Hp;
-    t.R = w.x_R; t.r_nkb = d.nkb; t.r_kb0 = 0;
-    t.T = w.gz3_T; t.t_ncb = d.ncb; t.t_cb0 = 0;
+    t.R = w.gz3_R; t.r_nkb = d.nkb; t.r_kb0 = 0;
     HGNN_TRY(launch_to_frag(st, t));
   }
   HGNN_TRY(stream_after(sx, st, ss.ev[1]));
   // side: g_b3 = column sums of g_z3, g_W3 = [h ; M]^T g_z3
   HGNN_TRY(launch_frag_colsum(sx, t, gW + o.b3, 0));
-  HGNN_TRY(wgrad_w(sx, d, s.hM_T, 2 * d.ncb, 0, 2 * d.ncb, w.gz3_T, d.ncb, 0, d.ncb, d.Np, w.partial, w.partial_floats,
+  HGNN_TRY(wgrad_w(sx, d, s.hM_R, 2 * d.ncb, 0, 2 * d.ncb, w.gz3_R, d.ncb, 0, d.ncb, d.Np, w.partial, w.partial_floats,
                    gW + o.W3, HH, 0, PT_WGRAD_NODE));
   {  // [g_h(a) | g_M] = g_z3 [W3a^T | W3b^T]: fp32 for the residual, bf16 for the edge gathers
-    FGemmArgs g = nn_args(w.x_R, d.nkb, d.Np / 32, w.packed + PP, 2 * d.ncb, PT_GEMM_NODE);
+    FGemmArgs g = nn_args(w.gz3_R, d.nkb, d.Np / 32, w.packed + PP, 2 * d.ncb, PT_GEMM_NODE);
     g.M = d.N; g.Cf = w.nodeB; g.ldc = 2 * Hp; g.ncol_f = 2 * Hp;
     g.Cb = w.gM_b; g.ldcb = 2 * Hp;
     HGNN_TRY(launch_fgemm_rows(st, g));
@@ -1612,8 +1612,8 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   e.E = d.E; e.nrb = (int)(d.Ep / 32); e.H = H; e.Hp = Hp;
   e.dst = a.dst; e.col = a.col; e.attr = a.attr ? a.attr : a.d2; e.k = k; e.PQ = s.PQ; e.w1d = W + o.W1 + 2 * HH;
   e.z2_T = s.z2_T; e.gM = w.gM_b + Hp; e.ldgM = 2 * Hp; e.cvec = w.cvec; e.wx = W + o.wx; e.alpha = a.alpha;
-  e.gz2_R = w.gz2_R; e.gz2_T = w.gz2_T; e.ga1_T = w.ga1_T; e.colpart = w.colpart;
-  e.gz1_rm = reinterpret_cast<unsigned short*>(w.gz2_R);   // free again once g_a1 has been formed
+  e.gz2_R = w.gz2_R; e.ga1_T = w.ga1_T; e.colpart = w.colpart;
+  e.gz1_rm = reinterpret_cast<unsigned short*>(w.gz2_R);   // free again once g_W2 and g_a1 have been formed
   const dim3 egrid = elem_grid(e.nrb, Hp);
   const int eg = (int)egrid.y;   // column-sum partials
   HGNN_TRY(launch_edge_cvec(st, d.E, a.dst, a.rvec, a.g_v_out, a.alpha, w.cvec));
@@ -1628,7 +1628,7 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
     HGNN_TRY(launch_reduce_cols(sx, w.colpart, eg, 2 * Hp, H, gW + o.b2, 2, Hp, o.wx - o.b2));
   }
   // g_W2 = a1^T g_z2 fills the chip by itself: it stays on the caller's stream, with a partial buffer of its own
-  HGNN_TRY(wgrad_w(st, d, s.a1_T, d.ncb, 0, d.ncb, w.gz2_T, d.ncb, 0, d.ncb, d.Ep, w.partial_e, w.partial_e_floats,
+  HGNN_TRY(wgrad_w(st, d, s.a1_R, d.ncb, 0, d.ncb, w.gz2_R, d.ncb, 0, d.ncb, d.Ep, w.partial_e, w.partial_e_floats,
                    gW + o.W2, 0, 0, PT_FRAG_WGRAD_EDGE));
   if (d.Ep > 0) {  // g_a1 = g_z2 W2^T (T fragments)
     FGemmArgs g = nn_args(w.gz2_R, d.nkb, (int)(d.Ep / 32), w.packed + 3 * PP, d.ncb, PT_FRAG_GEMM_EDGE);
@@ -1660,11 +1660,10 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
     k_segsum_rows<<<(unsigned)((d.N + 3) / 4), 256, 0, st>>>(d.N, Hp, a.colT_ptr, a.permT, e.gz1_rm, w.g_PQ + Hp, 2 * Hp);
     HGNN_LAUNCH_CHECK("k_segsum_rows");
   }
-  {  // [g_P | g_Q] as R (contraction 2 Hp) and T
+  {  // [g_P | g_Q] as R (contraction 2 Hp)
     ToFragArgs t;
     t.X = w.g_PQ; t.ldx = 2 * Hp; t.M = d.N; t.Mp = d.Np; t.ncol = 2 * Hp; t.Cp = 2 * Hp;
-    t.R = w.x_R; t.r_nkb = 2 * d.nkb; t.r_kb0 = 0;
-    t.T = w.gPQ_T; t.t_ncb = 2 * d.ncb; t.t_cb0 = 0;
+    t.R = w.gPQ_R; t.r_nkb = 2 * d.nkb; t.r_kb0 = 0;
     HGNN_TRY(launch_to_frag(st, t));
   }
   HGNN_TRY(stream_after(sx, st, ss.ev[3]));
@@ -1674,10 +1673,10 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
     // the k rows of W1 that act on the edge attributes: one group per row
     HGNN_TRY(launch_reduce_cols(sx, w.colpart2 + Hp, eg, (long)(1 + k) * Hp, H, gW + o.W1 + 2 * HH, k, Hp, H));
   }
-  HGNN_TRY(wgrad_w(sx, d, s.hM_T, 2 * d.ncb, 0, d.ncb, w.gPQ_T, 2 * d.ncb, 0, 2 * d.ncb, d.Np, w.partial, w.partial_floats,
+  HGNN_TRY(wgrad_w(sx, d, s.hM_R, 2 * d.ncb, 0, d.ncb, w.gPQ_R, 2 * d.ncb, 0, 2 * d.ncb, d.Np, w.partial, w.partial_floats,
                    gW + o.W1, 0, HH, PT_WGRAD_NODE));
   {  // g_h = g_h' + g_h(a) + [g_P | g_Q] [W1a^T ; W1b^T]
-    FGemmArgs g = nn_args(w.x_R, 2 * d.nkb, d.Np / 32, w.packed + 4 * PP, d.ncb, PT_GEMM_NODE);
+    FGemmArgs g = nn_args(w.gPQ_R, 2 * d.nkb, d.Np / 32, w.packed + 4 * PP, d.ncb, PT_GEMM_NODE);
     g.M = d.N; g.Cf = a.g_h_in; g.ldc = H; g.ncol_f = H;
     g.r1 = a.g_h_out; g.ld1 = H;
     g.r2 = w.nodeB; g.ld2 = 2 * Hp;

@@ -262,6 +262,13 @@ def test_layer_wide_widths(H, N, E):
     _run_layer(N=N, E=E, H=H, dtype="bf16", seed=H + E)
 
 
+# The weight gradient of W2 in 256 x 128 tiles whose last row tile sticks out (12 and 4 column blocks of 32 past the last whole
+# tile), with ragged row blocks at the end of the edges
+@pytest.mark.parametrize("H,N,E", [(300, 700, 65281), (641, 500, 65536 + 33)])
+def test_layer_wide_weight_gradient_of_many_edges(H, N, E):
+    _run_layer(N=N, E=E, H=H, dtype="bf16", seed=E)
+
+
 # ------------------------------------------------------------------------------------------------
 # k edge attributes (radial basis of the edge length) in place of d2
 # ------------------------------------------------------------------------------------------------
