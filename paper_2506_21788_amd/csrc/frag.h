@@ -58,9 +58,8 @@ struct FGemmArgs {
   //   atoms that reach past the strip's end / begin before it:  seg_last / seg_first [strip][col] = sum (unscaled)
   // and x_e = wx . m_e per edge and column tile:  seg_xe[tile * seg_xe_stride + edge]
   const int32_t* seg_dst = nullptr;
-  const int32_t* seg_row_ptr = nullptr;
   const float* seg_wx = nullptr;
-  int seg_H = 0;            // valid columns of wx
+  int seg_H = 0;            // valid columns of wx (z1_w1d)
   long seg_E = 0;           // valid rows
   float seg_alpha = 0.f;
   float* seg_M = nullptr;
@@ -70,6 +69,16 @@ struct FGemmArgs {
   long seg_ldp = 0;         // pitch of seg_first / seg_last
   float* seg_xe = nullptr;
   long seg_xe_stride = 0;
+  // launch_fgemm_rows_T only, optional (z1_out != null): rows as above, and the product is g_a1. Formed from it and not stored as T:
+  //   z1_out [rows][nJ * 32] = g_z1 = g_a1 silu'(z1), bf16 row-major, z1 = P[dst] + Q[col] + attr w1d from z1_PQ [atoms][P | Q]
+  //   seg_M / seg_last / seg_first: sums of g_z1 per destination atom as above (seg_alpha = 1)
+  //   z1_colpart [row tile of 256][2][nJ * 32]: column sums of g_z1 and of attr g_z1
+  unsigned short* z1_out = nullptr;
+  const int32_t* z1_col = nullptr;
+  const float* z1_attr = nullptr;
+  const unsigned short* z1_PQ = nullptr;
+  const float* z1_w1d = nullptr;
+  float* z1_colpart = nullptr;
 };
 int32_t launch_fgemm_rows(hipStream_t st, const FGemmArgs& a);     // EPI_ROW, 256 x 128 tiles (128 x 128 for few rows)
 int32_t launch_fgemm_rows_T(hipStream_t st, const FGemmArgs& a);   // EPI_T, 256 x 128 tiles

@@ -392,12 +392,21 @@ static int32_t launch_fgemm_t(hipStream_t st, const FGemmArgs& a) {
 // (Measured against this: the same kernel with eight wavefronts on a 256 x 256 tile, which loads a third fewer
 // operand bytes per flop, runs 12 - 20 % slower: one workgroup per compute unit leaves nothing to run while its
 // wavefronts meet at the barrier; with 128 x 128 tiles and three workgroups per compute unit it runs 20 % slower.)
-// SEG: the rows are destination-sorted edges and the product is z2: the epilogue also forms m = silu(z2), its sums per
+// AD_SEG: the rows are destination-sorted edges and the product is z2: the epilogue also forms m = silu(z2), its sums per
 // destination atom over the wavefront's 64 rows and x_e = wx . m_e per edge (see FGemmArgs::seg_*), so that no other
 // kernel has to read z2 in the forward pass. The vector units are idle during the products: the other resident
 // workgroup keeps the matrix cores busy meanwhile.
-template <bool SEG>
+// AD_GZ1: the product is g_a1, and the epilogue forms g_z1 = g_a1 silu'(z1) from it, z1 recomputed from the gathers: row-major g_z1, its
+// column sums (g_b1, g_w1d) and its sums per destination atom (g_P). A wavefront puts its strip through the LDS, 32 rows at a time, so
+// that a lane holds two neighbouring columns (a gather of both is one 4-byte load) and walks the rows in order: a destination's
+// edges are a run, whose sum goes to g_P or, where the row leaves the strip, to the strip's partial rows. As kernels of their own
+// (element-wise pass and sum over the destination-sorted list) this wrote g_a1 and read it and g_z1 again: 254,000 edges of 866
+// columns, per layer: 340 us (product) + 174 + 102 -> 487, and 15 in the source sum for the rows over several strips. What bounds it is
+// the epilogue's issue slots: the products alone are 190 us at the rate of a large matrix product.
+enum { AD_T = 0, AD_SEG = 1, AD_GZ1 = 2 };
+template <int MODE>
 __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
+  constexpr bool SEG = MODE == AD_SEG;
   constexpr int NW = 4, WI = 2, WJ = 4, KC = 2, TI = 8, TJ = 4;
   constexpr int STAGE = KC * TJ * 64;   // 16-byte units of B per step
   __shared__ __align__(16) u32x4_t lds[2 * STAGE];
@@ -411,6 +420,25 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
   const int i0 = ti * TI, j0 = tj * TJ;
   const int nch = p.nkb / KC;
   auto kclamp = [&](int ch) { return (long)(ch < nch ? ch : nch - 1) * KC; };
+  // The tile's edges for the epilogues: the destinations (edst[1 + r]: row r of the tile, with a neighbour on either side; -1 past the
+  // edges), which say where an atom's run begins and ends, and what AD_GZ1 gathers by. Read where they are used, from memory, they
+  // put two memory latencies in a row into every batch of rows and two more into every run (254,000 edges of 866 columns: AD_GZ1
+  // 658 -> 487 us, AD_SEG 418 -> 408).
+  __shared__ int edst[MODE == AD_T ? 1 : 258];
+  __shared__ int ecol[MODE == AD_GZ1 ? 256 : 1];
+  __shared__ float eattr[MODE == AD_GZ1 ? 256 : 1];
+  if constexpr (MODE != AD_T) {
+    const long row = (long)ti * 256 + tid;
+    edst[1 + tid] = row < p.seg_E ? p.seg_dst[row] : -1;
+    if (tid < 2) {
+      const long r2 = (long)ti * 256 + (tid ? 256 : -1);
+      edst[tid ? 257 : 0] = r2 >= 0 && r2 < p.seg_E ? p.seg_dst[r2] : -1;
+    }
+    if constexpr (MODE == AD_GZ1) {
+      ecol[tid] = row < p.seg_E ? p.z1_col[row] : 0;
+      eattr[tid] = row < p.seg_E ? p.z1_attr[row] : 0.f;
+    }
+  }
 
   const char* asrc[WI];
 #pragma unroll
@@ -498,6 +526,98 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
   }
   const int x = lane & 31, g = lane >> 5;
   const long R0 = (long)(i0 + wi * WI) * 32;   // first row of this wavefront's strip of 64 rows
+  if constexpr (MODE == AD_GZ1) {
+    constexpr int PITCH = 136, NB = 8;                    // rows per batch
+    __shared__ __align__(16) unsigned short ztile[NW][32 * PITCH];
+    __shared__ float2 csum[NW][2][64];
+    unsigned short* zt = ztile[wave];
+    const int c = j0 * 32 + 2 * lane, Hp = p.nJ * 32;     // this lane's columns: c, c + 1
+    const float w0 = c < p.seg_H ? p.z1_w1d[c] : 0.f, w1 = c + 1 < p.seg_H ? p.z1_w1d[c + 1] : 0.f;
+    float s00 = 0.f, s01 = 0.f, s10 = 0.f, s11 = 0.f;     // column sums
+    float a0 = 0.f, a1 = 0.f;                             // the run at hand
+    int cur = -1;                                         // its atom
+    unsigned ga[2][NB], gb[2][NB];
+    float sc[2][NB];
+    int di[2][NB];
+    auto issue = [&](int b, unsigned (&go)[NB], unsigned (&qo)[NB], float (&so)[NB], int (&dio)[NB]) {
+      const int r0 = wave * 64 + b * NB;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {   // (rows past the last edge gather row 0)
+        dio[u] = __builtin_amdgcn_readfirstlane(edst[1 + r0 + u]);
+        const long ci = __builtin_amdgcn_readfirstlane(ecol[r0 + u]);
+        so[u] = eattr[r0 + u];
+        go[u] = *reinterpret_cast<const unsigned*>(p.z1_PQ + (long)(dio[u] < 0 ? 0 : dio[u]) * 2 * Hp + c);
+        qo[u] = *reinterpret_cast<const unsigned*>(p.z1_PQ + ci * 2 * Hp + Hp + c);
+      }
+    };
+    // does the strip's first row belong to an atom that began before it, and its last one to an atom that goes on behind it
+    const int s0 = wave * 64;
+    const bool before = __builtin_amdgcn_readfirstlane(edst[s0]) == __builtin_amdgcn_readfirstlane(edst[s0 + 1]);
+    const int tail = __builtin_amdgcn_readfirstlane(edst[s0 + 64]);   // -1: the strip ends with the edges
+    const bool behind = tail >= 0 && tail == __builtin_amdgcn_readfirstlane(edst[s0 + 65]);
+    bool first = true;   // the run at hand is the strip's first one
+    auto flush = [&](bool last) {
+      float* dest = first && before ? p.seg_first + (R0 >> 6) * p.seg_ldp : last && behind ? p.seg_last + (R0 >> 6) * p.seg_ldp : p.seg_M + (long)cur * p.seg_ldm;
+      *reinterpret_cast<float2*>(dest + c) = make_float2(a0, a1);
+      first = false;
+    };
+    issue(0, ga[0], gb[0], sc[0], di[0]);
+#pragma unroll
+    for (int b = 0; b < 64 / NB; ++b) {
+      if (b % (32 / NB) == 0) {   // the next 32 rows, rounded as g_a1 was when it was stored
+        const int i = b / (32 / NB);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < WJ; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; v += 2) {
+            const unsigned w = pack_bf16x2(acc[i][j][v], acc[i][j][v + 1]);
+            const int r = 8 * (v >> 2) + 4 * g + (v & 3);
+            zt[r * PITCH + j * 32 + x] = (unsigned short)(w & 0xffffu);
+            zt[(r + 1) * PITCH + j * 32 + x] = (unsigned short)(w >> 16);
+          }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (b + 1 < 64 / NB) issue(b + 1, ga[(b + 1) & 1], gb[(b + 1) & 1], sc[(b + 1) & 1], di[(b + 1) & 1]);
+      const int sl = b & 1;
+      unsigned pw[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const unsigned xw = *reinterpret_cast<const unsigned*>(&zt[((b * NB + u) & 31) * PITCH + 2 * lane]);
+        const bool ok = di[sl][u] >= 0;   // uniform
+        const float z0 = fmaf(sc[sl][u], w0, bf_lo(ga[sl][u]) + bf_lo(gb[sl][u])), z1 = fmaf(sc[sl][u], w1, bf_hi(ga[sl][u]) + bf_hi(gb[sl][u]));
+        const float g0 = ok ? bf_lo(xw) * dsilu_f(z0) : 0.f, g1 = ok ? bf_hi(xw) * dsilu_f(z1) : 0.f;
+        s00 += g0; s01 += g1;
+        s10 = fmaf(sc[sl][u], g0, s10); s11 = fmaf(sc[sl][u], g1, s11);
+        pw[u] = pack_bf16x2(g0, g1);
+        *reinterpret_cast<unsigned*>(p.z1_out + (R0 + b * NB + u) * Hp + c) = pw[u];
+      }
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        if (di[sl][u] >= 0) {
+          if (di[sl][u] != cur) {
+            if (cur >= 0) flush(false);
+            cur = di[sl][u];
+            a0 = a1 = 0.f;
+          }
+          a0 += bf_lo(pw[u]); a1 += bf_hi(pw[u]);
+        }
+      }
+    }
+    if (cur >= 0) flush(true);
+    csum[wave][0][lane] = make_float2(s00, s01);
+    csum[wave][1][lane] = make_float2(s10, s11);
+    __syncthreads();
+    if (tid < 128) {   // the four strips in order; a partial per row tile
+      const int which = tid >> 6;
+      float2 t = csum[0][which][lane];
+#pragma unroll
+      for (int k = 1; k < NW; ++k) { t.x += csum[k][which][lane].x; t.y += csum[k][which][lane].y; }
+      *reinterpret_cast<float2*>(p.z1_colpart + ((long)ti * 2 + which) * Hp + c) = t;
+    }
+    return;
+  }
   float xe[SEG ? 32 : 1];                      // SEG: wx . m of the rows (i, v) of this lane, index 16 i + v
   if constexpr (SEG) {
 #pragma unroll
@@ -557,18 +677,21 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
       const long row = R0 + 32 * i + 8 * (v >> 2) + 4 * g + (v & 3);
       if (row < p.seg_E) p.seg_xe[(long)tj * p.seg_xe_stride + row] = tot;
     }
-    // sums per destination atom over the strip: the atoms of the strip one after the other (rows are sorted by
-    // destination; an atom without edges has an empty range)
+    // sums per destination atom over the strip: the runs of the strip one after the other (rows are sorted by destination)
     if (R0 < p.seg_E) {
-      const long Rend = R0 + 64 < p.seg_E ? R0 + 64 : p.seg_E;
-      const int a_first = __builtin_amdgcn_readfirstlane(p.seg_dst[R0]);
-      const int a_last = __builtin_amdgcn_readfirstlane(p.seg_dst[Rend - 1]);
+      const int s0 = wave * 64;
+      const int mine = edst[1 + s0 + lane];
+      const bool before = __builtin_amdgcn_readfirstlane(edst[s0] == mine);                    // (lane 0: the strip's first row)
+      const bool behind = __builtin_amdgcn_readfirstlane(edst[s0 + 65]) == __builtin_amdgcn_readlane(mine, 63);
+      const int nrow = p.seg_E - R0 < 64 ? (int)(p.seg_E - R0) : 64;
       const long strip = R0 >> 6;
-      for (int a = a_first; a <= a_last; ++a) {
-        const long e0 = __builtin_amdgcn_readfirstlane(p.seg_row_ptr[a]);
-        const long e1 = __builtin_amdgcn_readfirstlane(p.seg_row_ptr[a + 1]);
-        const int lo = (int)((e0 > R0 ? e0 : R0) - R0), hi = (int)((e1 < R0 + 64 ? e1 : R0 + 64) - R0);
-        if (lo >= hi) continue;
+      unsigned long long starts = __ballot(lane == 0 || mine != edst[s0 + lane]);   // bit r: row r of the strip begins a run
+      if (nrow < 64) starts &= (1ull << nrow) - 1ull;
+      while (starts) {
+        const int lo = __ffsll((long long)starts) - 1;
+        starts &= starts - 1ull;
+        const int hi = starts ? __ffsll((long long)starts) - 1 : nrow;
+        const int a = __builtin_amdgcn_readlane(mine, lo);
         float t[WJ];
 #pragma unroll
         for (int j = 0; j < WJ; ++j) t[j] = 0.f;
@@ -585,8 +708,8 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
         for (int j = 0; j < WJ; ++j) t[j] += __shfl_xor(t[j], 32);
         float* dest;
         float scale = 1.f;
-        if (e0 < R0) dest = p.seg_first + strip * p.seg_ldp;
-        else if (e1 > R0 + 64) dest = p.seg_last + strip * p.seg_ldp;
+        if (lo == 0 && before) dest = p.seg_first + strip * p.seg_ldp;
+        else if (hi == 64 && behind) dest = p.seg_last + strip * p.seg_ldp;
         else { dest = p.seg_M + (long)a * p.seg_ldm; scale = p.seg_alpha; }
         if (g == 0) {
 #pragma unroll
@@ -647,12 +770,17 @@ static int32_t launch_fgemm_ad(hipStream_t st, const FGemmArgs& a) {
   const long gx = (a.nI / 8 + 7) / 8 * 8 * (long)(a.nJ / 4);
   HGNN_REQUIRE(gx <= 2147483647L, HGNN_ERR_OVERFLOW, "fragment GEMM: grid too large");
   ProfScope ps(a.tag, st);
-  if (a.seg_dst) {
-    HGNN_REQUIRE(a.seg_row_ptr && a.seg_wx && a.seg_M && a.seg_first && a.seg_last && a.seg_xe && a.seg_E <= (long)a.nI * 32,
+  if (a.z1_out) {
+    HGNN_REQUIRE(a.seg_dst && a.seg_M && a.seg_first && a.seg_last && a.z1_col && a.z1_attr && a.z1_PQ && a.z1_w1d &&
+                     a.z1_colpart && a.seg_E > 0 && a.seg_E <= (long)a.nI * 32 && a.seg_ldm % 2 == 0 && a.seg_ldp % 2 == 0,
+                 HGNN_ERR_NULLPTR, "fragment GEMM: incomplete arguments of the g_z1 epilogue");
+    k_fgemm_ad<AD_GZ1><<<dim3((unsigned)gx), 256, 0, st>>>(a);
+  } else if (a.seg_dst) {
+    HGNN_REQUIRE(a.seg_wx && a.seg_M && a.seg_first && a.seg_last && a.seg_xe && a.seg_E <= (long)a.nI * 32,
                  HGNN_ERR_NULLPTR, "fragment GEMM: incomplete per-atom sum arguments");
-    k_fgemm_ad<true><<<dim3((unsigned)gx), 256, 0, st>>>(a);
+    k_fgemm_ad<AD_SEG><<<dim3((unsigned)gx), 256, 0, st>>>(a);
   } else {
-    k_fgemm_ad<false><<<dim3((unsigned)gx), 256, 0, st>>>(a);
+    k_fgemm_ad<AD_T><<<dim3((unsigned)gx), 256, 0, st>>>(a);
   }
   HGNN_LAUNCH_CHECK("k_fgemm_ad");
   return HGNN_OK;
@@ -1127,14 +1255,36 @@ static dim3 elem_grid(int nrb, int Hp) {
   return dim3(Hp / 128, nrb < 1 ? 1 : (nrb < ELEM_MAX_BLOCKS ? nrb : ELEM_MAX_BLOCKS));
 }
 
+// Destination sums formed in the epilogue of the g_a1 product: what is left of them, rows without edges and rows that reach over
+// several 64-row strips (as in k_seg_fwd_fix)
+struct StripFix {
+  const int32_t* row_ptr;   // null: nothing to fix
+  const float *first, *last;
+  float* out;
+  long ldo;
+};
+
 // out[i][c] = sum over k in ptr[i] .. ptr[i+1] of X[perm[k]][c] (perm == null: X[k][c]), X bf16 row-major with pitch
 // Hp (one wavefront per atom, 16-byte pieces of a row per lane, two rows in flight)
 __global__ void __launch_bounds__(256) k_segsum_rows(int N, int Hp, const int32_t* __restrict__ ptr,
                                                      const int32_t* __restrict__ perm, const unsigned short* __restrict__ X,
-                                                     float* __restrict__ out, long ldo) {
+                                                     float* __restrict__ out, long ldo, StripFix fx) {
   const int lane = threadIdx.x & 63;
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= N) return;
+  if (fx.row_ptr) {
+    const int r0 = fx.row_ptr[i], r1 = fx.row_ptr[i + 1], s0 = r0 >> 6, s1 = (r1 - 1) >> 6;
+    if (r0 == r1 || s0 != s1) {
+      for (int c = lane; c < Hp; c += 64) {
+        float t = 0.f;
+        if (r0 != r1) {
+          t = fx.last[(long)s0 * Hp + c];
+          for (int s = s0 + 1; s <= s1; ++s) t += fx.first[(long)s * Hp + c];
+        }
+        fx.out[(long)i * fx.ldo + c] = t;
+      }
+    }
+  }
   const int e0 = ptr[i], e1 = ptr[i + 1];
   const int nch = Hp >> 3;                 // 16-byte pieces per row (at most 128)
   const bool two = lane + 64 < nch;
@@ -1326,7 +1476,8 @@ static WideWs carve_ws_w(void* p, const WideDims& d) {
   w.ga1_T = c.take<char>(d.edge_bytes());
   w.cvec = c.take<float>((size_t)d.E + 4);
   w.colpart = c.take<float>((size_t)ELEM_MAX_BLOCKS * 2 * d.Hp);
-  w.colpart2 = c.take<float>((size_t)ELEM_MAX_BLOCKS * (1 + d.k) * d.Hp);
+  const size_t row_tiles = (size_t)(d.Ep / 256);   // (a partial each from the g_a1 product)
+  w.colpart2 = c.take<float>((row_tiles > ELEM_MAX_BLOCKS ? row_tiles : ELEM_MAX_BLOCKS) * (1 + d.k) * d.Hp);
   w.cs_partial[0] = c.take<float>(colsum_rows_partial_floats(d.N, d.Hp, 1));
   w.cs_partial[1] = c.take<float>(colsum_rows_partial_floats(d.N, d.Hp, 1));
   w.partial_floats = (size_t)24 * 2 * d.Hp * d.Hp;
@@ -1503,7 +1654,7 @@ int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
     g.T = s.z2_T; g.t_ncb = d.ncb;
     g.bias = W + o.b2; g.nbias = H;
     // with the per-atom sums of m = silu(z2) and x_e = wx . m_e formed in the epilogue
-    g.seg_dst = a.dst; g.seg_row_ptr = a.row_ptr; g.seg_wx = W + o.wx; g.seg_H = H; g.seg_E = d.E; g.seg_alpha = a.alpha;
+    g.seg_dst = a.dst; g.seg_wx = W + o.wx; g.seg_H = H; g.seg_E = d.E; g.seg_alpha = a.alpha;
     g.seg_M = s.M; g.seg_ldm = Hp; g.seg_first = w.seg_first; g.seg_last = w.seg_last; g.seg_ldp = Hp;
     g.seg_xe = w.xe_part; g.seg_xe_stride = d.Ep;
     HGNN_TRY(launch_fgemm_rows_T(st, g));
@@ -1608,12 +1759,15 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
     HGNN_TRY(launch_fgemm_rows(st, g));
   }
   // edge part
+  const bool fused = k == 1 && d.Ep > 0;   // g_z1, its column sums and g_P leave the g_a1 product (several attributes: their weights and
+                                           // sums would take 64 registers more than its epilogue has)
   EdgeElemArgs e;
   e.E = d.E; e.nrb = (int)(d.Ep / 32); e.H = H; e.Hp = Hp;
   e.dst = a.dst; e.col = a.col; e.attr = a.attr ? a.attr : a.d2; e.k = k; e.PQ = s.PQ; e.w1d = W + o.W1 + 2 * HH;
   e.z2_T = s.z2_T; e.gM = w.gM_b + Hp; e.ldgM = 2 * Hp; e.cvec = w.cvec; e.wx = W + o.wx; e.alpha = a.alpha;
   e.gz2_R = w.gz2_R; e.ga1_T = w.ga1_T; e.colpart = w.colpart;
-  e.gz1_rm = reinterpret_cast<unsigned short*>(w.gz2_R);   // free again once g_W2 and g_a1 have been formed
+  // (g_z2 is free again once g_W2 and g_a1 have been formed; fused, g_z1 is written while g_z2 is read)
+  e.gz1_rm = reinterpret_cast<unsigned short*>(fused ? w.ga1_T : w.gz2_R);
   const dim3 egrid = elem_grid(e.nrb, Hp);
   const int eg = (int)egrid.y;   // column-sum partials
   HGNN_TRY(launch_edge_cvec(st, d.E, a.dst, a.rvec, a.g_v_out, a.alpha, w.cvec));
@@ -1632,14 +1786,20 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
                    gW + o.W2, 0, 0, PT_FRAG_WGRAD_EDGE));
   if (d.Ep > 0) {  // g_a1 = g_z2 W2^T (T fragments)
     FGemmArgs g = nn_args(w.gz2_R, d.nkb, (int)(d.Ep / 32), w.packed + 3 * PP, d.ncb, PT_FRAG_GEMM_EDGE);
-    g.T = w.ga1_T; g.t_ncb = d.ncb;
+    if (fused) {
+      g.seg_dst = a.dst; g.seg_H = H; g.seg_E = d.E;
+      g.seg_M = w.g_PQ; g.seg_ldm = 2 * Hp; g.seg_first = w.seg_first; g.seg_last = w.seg_last; g.seg_ldp = Hp;
+      g.z1_col = a.col; g.z1_attr = e.attr; g.z1_PQ = s.PQ; g.z1_w1d = e.w1d; g.z1_out = e.gz1_rm; g.z1_colpart = w.colpart2;
+    } else {
+      g.T = w.ga1_T; g.t_ncb = d.ncb;
+    }
     HGNN_TRY(launch_fgemm_rows_T(st, g));
   }
-  e.colpart = w.colpart2;
-  {
+  const int eg1 = fused ? (int)(d.Ep / 256) : eg;
+  if (!fused) {
     ProfScope ps(PT_EDGE_ELEM, st);
-    if (k == 1) k_edge_elem<EE_GZ1, 1><<<egrid, 256, 0, st>>>(e);
-    else k_edge_elem<EE_GZ1, 16><<<egrid, 256, 0, st>>>(e);
+    e.colpart = w.colpart2;
+    k_edge_elem<EE_GZ1, 16><<<egrid, 256, 0, st>>>(e);
     HGNN_LAUNCH_CHECK("k_edge_elem (g_z1)");
   }
   if (a.g_attr && d.E > 0) {  // gradient with respect to the edge attributes: g_z1 W1d^T
@@ -1650,14 +1810,15 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   }
   if (a.g_rvec) HGNN_TRY(launch_edge_grvec(st, d.E, a.dst, s.xe, a.g_v_out, a.alpha, a.g_rvec));
   // g_P, g_Q: per-atom sums of g_z1 over the destination-sorted and the source-sorted lists
-  if (d.N > 0) {
+  if (d.N > 0 && !fused) {
     ProfScope ps(PT_SEGSUM_DST, st);
-    k_segsum_rows<<<(unsigned)((d.N + 3) / 4), 256, 0, st>>>(d.N, Hp, a.row_ptr, nullptr, e.gz1_rm, w.g_PQ, 2 * Hp);
+    k_segsum_rows<<<(unsigned)((d.N + 3) / 4), 256, 0, st>>>(d.N, Hp, a.row_ptr, nullptr, e.gz1_rm, w.g_PQ, 2 * Hp, StripFix{});
     HGNN_LAUNCH_CHECK("k_segsum_rows");
   }
   if (d.N > 0) {
     ProfScope ps(PT_SEGSUM_SRC, st);
-    k_segsum_rows<<<(unsigned)((d.N + 3) / 4), 256, 0, st>>>(d.N, Hp, a.colT_ptr, a.permT, e.gz1_rm, w.g_PQ + Hp, 2 * Hp);
+    k_segsum_rows<<<(unsigned)((d.N + 3) / 4), 256, 0, st>>>(d.N, Hp, a.colT_ptr, a.permT, e.gz1_rm, w.g_PQ + Hp, 2 * Hp,
+                                                             fused ? StripFix{a.row_ptr, w.seg_first, w.seg_last, w.g_PQ, 2 * Hp} : StripFix{});
     HGNN_LAUNCH_CHECK("k_segsum_rows");
   }
   {  // [g_P | g_Q] as R (contraction 2 Hp)
@@ -1669,9 +1830,9 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   HGNN_TRY(stream_after(sx, st, ss.ev[3]));
   {  // side: g_b1, g_w1d from the g_z1 kernel's column sums; g_W1a = h^T g_P, g_W1b = h^T g_Q
     ProfScope ps(PT_COLSUM, sx);
-    HGNN_TRY(launch_reduce_cols(sx, w.colpart2, eg, (long)(1 + k) * Hp, H, gW + o.b1));
+    HGNN_TRY(launch_reduce_cols(sx, w.colpart2, eg1, (long)(1 + k) * Hp, H, gW + o.b1));
     // the k rows of W1 that act on the edge attributes: one group per row
-    HGNN_TRY(launch_reduce_cols(sx, w.colpart2 + Hp, eg, (long)(1 + k) * Hp, H, gW + o.W1 + 2 * HH, k, Hp, H));
+    HGNN_TRY(launch_reduce_cols(sx, w.colpart2 + Hp, eg1, (long)(1 + k) * Hp, H, gW + o.W1 + 2 * HH, k, Hp, H));
   }
   HGNN_TRY(wgrad_w(sx, d, s.hM_R, 2 * d.ncb, 0, d.ncb, w.gPQ_R, 2 * d.ncb, 0, 2 * d.ncb, d.Np, w.partial, w.partial_floats,
                    gW + o.W1, 0, HH, PT_WGRAD_NODE));

@@ -269,6 +269,15 @@ def test_layer_wide_weight_gradient_of_many_edges(H, N, E):
     _run_layer(N=N, E=E, H=H, dtype="bf16", seed=E)
 
 
+# The per-atom sums of the fragment path's epilogues work on strips of 64 rows in tiles of 256: atoms that end and begin at a strip's
+# and at a tile's edge, one atom of exactly a strip, atoms over two and over five strips, an atom of its own in a ragged last
+# strip, atoms without edges at either end and in between
+@pytest.mark.parametrize("H,lengths", [(300, [64, 64, 1, 63, 0, 64, 200, 56, 3]), (130, [0, 30, 300, 0, 0, 118, 5, 0]),
+                                       (866, [256, 0, 256, 1]), (40, [10, 20, 34, 40, 24, 7, 121, 0]), (257, [255, 2, 255, 64, 63])])
+def test_layer_wide_rows_at_strip_edges(H, lengths):
+    _run_layer(N=len(lengths), E=sum(lengths), H=H, dtype="bf16", seed=H, lengths=lengths)
+
+
 # ------------------------------------------------------------------------------------------------
 # k edge attributes (radial basis of the edge length) in place of d2
 # ------------------------------------------------------------------------------------------------
