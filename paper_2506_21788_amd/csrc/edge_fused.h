@@ -32,6 +32,14 @@ inline bool edge_pairs(int H, bool bf16) { return bf16 && H == 256; }
 // at H = 128 with k > 1 edge attributes, which need registers of their own, 72 registers spill.
 constexpr bool edge_bwd_forms_w2(int H, int k) { return H <= 64 || (H == 128 && k <= 1); }
 
+// Where the forward edge kernel also forms the sums over m = silu(z2) (M, v') from the z2 in its accumulators, instead of a kernel
+// that reads z2 back. Whole steps, kernel of its own -> in the edge kernel: four cells of 20,000 atoms, H = 128 fp32, 22.04 -> 21.24 ms
+// (per layer 2100 + 627 us -> 2210 + 66), a crystal's conservative forces 500 -> 470 us, 19,000 atoms with 8 radial attributes at H = 128
+// 1.38 -> 1.28 ms, at H = 256 with moving atoms 2.88 -> 2.81, forward alone (z2 is not even stored then) H = 64 fp32 357 -> 320 us,
+// H = 128 fp32 600 -> 549. With bf16 operands and one attribute at H = 256 the kernel's vector units and its 256 registers are
+// full, and reading z2 back at 5.3 TB/s is the shorter: 643 mixed graphs 9.16 ms, in the edge kernel 9.43 (233 + 117 us -> 384 + 20).
+constexpr bool edge_fwd_sums(int H, bool bf16, bool attr) { return !(H == 256 && bf16 && !attr); }
+
 struct EdgeFwdArgs {
   int64_t E;
   const int32_t *dst, *col;
@@ -41,7 +49,16 @@ struct EdgeFwdArgs {
   const void* W2p;     // packed W2 block
   const float* b2;     // [H]
   void* a1_pk;         // out: silu(z1), operand-packed (bf16 or fp32); null: not stored
-  void* z2_vm;         // out: z2, v-major (bf16 or fp32)
+  void* z2_vm;         // out: z2, v-major (bf16 or fp32); null: not stored (where edge_fwd_sums())
+  // Where edge_fwd_sums(): M[i,:] = alpha sum over the edges of destination row i, where the row lies inside one wavefront's strip of a
+  // tile; the others leave one partial per strip in mpart ([strips][2][H]: slot 1 = the strip in which the row starts, slot 0 = every
+  // later one). And x_e = wx . m_e in parts, one per column wavefront. launch_seg_fwd_rows() finishes both.
+  const float* wx;     // [H]
+  float alpha;
+  float* M;            // out [N,H]
+  float* mpart;        // scratch: edge_fwd_mpart_floats(E, H)
+  float* xe_part;      // scratch: up to 4 x xe_stride
+  int64_t xe_stride;   // >= E
   // k > 1 edge attributes in place of d2 (bf16 operands only): z1 = P[dst] + Q[col] + attr_e . W1a, the last term
   // formed on the matrix cores from a bf16 copy of the tile's attributes; null: the d2 term above
   const float* attr = nullptr;   // [E,k]
@@ -50,11 +67,17 @@ struct EdgeFwdArgs {
 };
 int32_t launch_edge_fwd(hipStream_t st, int H, bool bf16, const EdgeFwdArgs& a);
 
-// M[i,:] = alpha * sum_{e in row i} silu(z2[e,:]);  v_out = v_in + alpha * sum (wx . silu(z2[e,:])) rvec[e,:]
+// Where the edge kernel does not: M[i,:] = alpha * sum_{e in row i} silu(z2[e,:]);  v_out = v_in + alpha * sum (wx . silu(z2[e,:])) rvec[e,:]
 // xe (optional): [E] out, x_e = wx . m_e of every edge
-int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, int64_t E, const int32_t* row_ptr, const void* z2_vm,
+int32_t launch_seg_fwd_vm(hipStream_t st, int N, int64_t E, const int32_t* row_ptr, const void* z2_vm,
                           const float* rvec, const float* wx, float alpha, const float* v_in, float* M,
                           float* v_out, float* xe = nullptr);
+
+// (strips of 64 rows, of 32 at H = 64)
+inline size_t edge_fwd_mpart_floats(int64_t E, int H) { return (size_t)((E + 31) / 32) * 2 * H; }
+// The rest of M, and v_out = v_in + alpha sum_e x_e rvec[e,:]; xe_out (optional): [E] out, x_e = wx . m_e of every edge
+int32_t launch_seg_fwd_rows(hipStream_t st, int H, bool bf16, int N, const int32_t* row_ptr, const EdgeFwdArgs& a,
+                            const float* rvec, const float* v_in, float* v_out, float* xe_out);
 
 // what finishes the rows of g_P that the reverse edge kernel left as per-unit partials (see EdgeBwdArgs::gP)
 struct DsumFix {

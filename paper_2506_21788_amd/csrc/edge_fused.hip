@@ -1,7 +1,9 @@
 // Fused per-edge kernels (see edge_fused.h for the fragment-order layouts).
 //
-//   k_edge_fwd    gather P[dst]+Q[col]+d2*w1d -> SiLU -> (A tile in LDS) x W2 on the matrix cores -> z2
-//   k_seg_fwd_vm  destination-sorted segmented reduction of SiLU(z2) into M and the vector channel
+//   k_edge_fwd    gather P[dst]+Q[col]+d2*w1d -> SiLU -> (A tile in LDS) x W2 on the matrix cores -> z2, and the sums of
+//                 SiLU(z2) per destination inside a strip of rows
+//   k_seg_fwd_rows  the destinations over several strips, and the vector channel
+//   k_seg_fwd_vm  where the edge kernel does not sum: segmented reduction of SiLU(z2) into M and the vector channel
 //   k_edge_bwd    g_z2 from z2 / g_M / g_v -> x W2^T -> recompute z1 -> g_z1, plus the three per-column
 //                 sums that are bias / vector gradients
 //   k_wgrad_frag  g_W2 = a1^T g_z2 streamed straight from memory into matrix-core operands
@@ -54,6 +56,12 @@ __device__ __forceinline__ float bf_bits_to_f(unsigned short b) { return __uint_
 
 // Streaming accesses are written as (uniform 64-bit base) + (32-bit per-lane byte offset): the base lives in scalar
 // registers, the lane part is one register shared by every access, and constant strides fold into the instruction.
+typedef unsigned u32x2_t_ __attribute__((ext_vector_type(2)));
+// the value of another lane of the same row of 16 (data-parallel pattern CTRL)
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
 template <typename T>
 __device__ __forceinline__ T ldg_nt(const void* ubase, unsigned off) {
   return __builtin_nontemporal_load(reinterpret_cast<const T*>(reinterpret_cast<const char*>(ubase) + off));
@@ -527,18 +535,29 @@ __device__ __forceinline__ void fwd_issue_group(const void* PQ, const int* s, in
 // tile; on return they hold those of the next tile's first group.
 // ATTR: k > 1 edge attributes take the place of the d2 term (at: this tile's attributes in LDS, at_next / nxa: where and
 // what to store for the next tile, bW1a: this lane's attribute weights as matrix-core operands).
-template <int H, bool BF16, bool BRES, bool FULL, bool ATTR>
+// MODE: FWD_Z2 stores z2 alone, FWD_BOTH also forms the sums of m = silu(z2) (see edge_fwd_sums()), FWD_SUMS does not store z2.
+// The sums are taken in the accumulator mapping, without LDS or a barrier: a lane half adds its own rows of a run, the halves are added
+// where a run ends.
+enum { FWD_Z2 = 0, FWD_BOTH = 1, FWD_SUMS = 2 };
+template <int H, bool BF16, bool BRES, bool FULL, bool ATTR, int MODE>
 __device__ __forceinline__ void edge_fwd_tile(
     const EdgeFwdArgs& p, unsigned char* smem, const int* s, int* s_next, int nxt, int tile, int E, int tid, int wr,
     int wc, int lane, const float (&w1d)[ECfg<H, BF16>::CB], const float (&b2)[ECfg<H, BF16>::CB],
     const typename BFrag<H, BF16>::type (&breg)[BRES ? BFrag<H, BF16>::NKB : 1][ECfg<H, BF16>::CB],
     unsigned (&wp0)[8], unsigned (&wq0)[8], float (&dd0)[8], const unsigned short* at, unsigned short* at_next,
-    uint2 nxa, const bf16x8_t (&bW1a)[ECfg<H, BF16>::CB]) {
+    uint2 nxa, const bf16x8_t (&bW1a)[ECfg<H, BF16>::CB], const float (&wx)[ECfg<H, BF16>::CB]) {
   using C = ECfg<H, BF16>;
   constexpr bool PAIRS = BF16 && C::CB == 2;
   const int g = lane >> 5, x = lane & 31;
   // byte offset of this lane's first column inside a row: word wc*32 + x of bf16 pairs, else column wc*CB*32 + x
   const unsigned colb = (unsigned)((PAIRS ? wc * 32 : wc * C::CB * 32) + x) * 4u;
+  // the destinations next to the wavefront's strip of rows decide whether its first and last run are whole atoms
+  int dprev = -1, dnext = -1;
+  if constexpr (MODE != FWD_Z2) {
+    const int R0 = tile * C::TM + wr * C::RB * 32;
+    if (R0 > 0 && (FULL || R0 < E)) dprev = p.dst[R0 - 1];
+    if (R0 + C::RB * 32 < E) dnext = p.dst[R0 + C::RB * 32];
+  }
   // attribute term of z1 for all of this wavefront's blocks (the accumulator registers are free in this phase)
   f32x16_t zat[ATTR ? C::RB : 1][C::CB];
   if constexpr (ATTR) {
@@ -626,33 +645,169 @@ __device__ __forceinline__ void edge_fwd_tile(
   if constexpr (ATTR) store_attr4(at_next, tid, nxa);
   __syncthreads();
   // ---- z2 = acc + b2, stored v-major (as bf16 pairs of this lane's two column blocks when PAIRS)
+  if constexpr (MODE == FWD_Z2) {
+#pragma unroll
+    for (int i = 0; i < C::RB; ++i) {
+      const int eb = tile * (C::TM / 32) + wr * C::RB + i;
+      if (!FULL && eb * 32 >= E) continue;
+      if constexpr (PAIRS) {
+        char* o = uoff(p.z2_vm, ((size_t)eb * (C::NCB / 2) + wc) * 16 * 256);
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          stg_nt<unsigned>(o, lane * 4u + v * 256u, pack_bf16x2(acc[i][0][v] + b2[0], acc[i][1][v] + b2[1]));
+      } else {
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j) {
+          const size_t blk = ((size_t)eb * C::NCB + (wc * C::CB + j)) * 16 * 64;   // first element of the block
+          if (BF16) {
+            char* o = uoff(p.z2_vm, blk * 2);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+              const unsigned pk = pack_bf16x2(acc[i][j][2 * t] + b2[j], acc[i][j][2 * t + 1] + b2[j]);
+              stg_nt<unsigned short>(o, lane * 2u + (2 * t) * 128u, (unsigned short)(pk & 0xffffu));
+              stg_nt<unsigned short>(o, lane * 2u + (2 * t + 1) * 128u, (unsigned short)(pk >> 16));
+            }
+          } else {
+            char* o = uoff(p.z2_vm, blk * 4);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) stg_nt<float>(o, lane * 4u + v * 256u, acc[i][j][v] + b2[j]);
+          }
+        }
+      }
+      // the next tile's scalars are in LDS now: its first gathers travel behind the first block's stores, whose
+      // accumulators are free by then (past the last tile the scalars are zeros and the gathers read row 0)
+      if constexpr (C::WORD && FULL) {
+        if (i == 0) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
+      }
+    }
+    if constexpr (C::WORD && !FULL) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
+    return;
+  }
+  // ---- and m = silu(z2) of the stored (rounded) value, summed per destination over the wavefront's strip of rows and, times wx, per
+  // edge over its columns
+  constexpr int S = C::RB * 32;                       // rows of a strip
+  const int sh = wr * S, R0 = tile * C::TM + sh;      // its first row in the tile, and of all
+  const int dl = s[lane], dq = s[lane ? lane - 1 : 0];
+  unsigned long long starts = __ballot(lane && dl != dq);   // bit r: row r of the tile begins a run
+  const int nrow = FULL ? S : (E - R0 < S ? (E - R0 > 0 ? E - R0 : 0) : S);
+  if constexpr (S < 64) starts = (starts >> sh) & ((1ull << S) - 1ull) & ~1ull;
+  if (!FULL && nrow < 64) starts &= (1ull << nrow) - 1ull;
+  const bool before = dprev == __builtin_amdgcn_readlane(dl, sh), behind = dnext == __builtin_amdgcn_readlane(dl, sh + S - 1);
+  float run[C::CB];   // the run at hand: lane half g adds its own rows
+  int k0 = 0;         // its first row in the strip
+#pragma unroll
+  for (int j = 0; j < C::CB; ++j) run[j] = 0.f;
+  auto flush = [&](int end, bool last) {
+    const bool sf = k0 != 0 || !before, ef = !last || !behind;   // the atom's edges begin and end in the strip
+    float* o = sf && ef ? p.M + (size_t)__builtin_amdgcn_readlane(dl, sh + k0) * H : p.mpart + ((size_t)(R0 / S) * 2 + (sf ? 1 : 0)) * H;
+    const u32x2_t_ w = __builtin_amdgcn_permlane32_swap(__float_as_uint(run[0]), __float_as_uint(run[C::CB - 1]), false, false);
+    const float t = (__uint_as_float(w[0]) + __uint_as_float(w[1])) * (sf && ef ? p.alpha : 1.f);
+    if constexpr (C::CB == 2) o[wc * 64 + lane] = t;
+    else if (g == 0) o[wc * 32 + x] = t;
+    k0 = end;
+#pragma unroll
+    for (int j = 0; j < C::CB; ++j) run[j] = 0.f;
+  };
 #pragma unroll
   for (int i = 0; i < C::RB; ++i) {
     const int eb = tile * (C::TM / 32) + wr * C::RB + i;
     if (!FULL && eb * 32 >= E) continue;
-    if constexpr (PAIRS) {
-      char* o = uoff(p.z2_vm, ((size_t)eb * (C::NCB / 2) + wc) * 16 * 256);
+    float y[8];   // x_e, see below
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        stg_nt<unsigned>(o, lane * 4u + v * 256u, pack_bf16x2(acc[i][0][v] + b2[0], acc[i][1][v] + b2[1]));
-    } else {
+    for (int q = 0; q < 4; ++q) {   // eight rows at a time, four of either lane half
+      float m[C::CB][4];
+      if constexpr (PAIRS) {
+        char* o = uoff(p.z2_vm, ((size_t)eb * (C::NCB / 2) + wc) * 16 * 256);
 #pragma unroll
-      for (int j = 0; j < C::CB; ++j) {
-        const size_t blk = ((size_t)eb * C::NCB + (wc * C::CB + j)) * 16 * 64;   // first element of the block
-        if (BF16) {
-          char* o = uoff(p.z2_vm, blk * 2);
+        for (int u = 0; u < 4; ++u) {
+          const int v = 4 * q + u;
+          const unsigned pk = pack_bf16x2(acc[i][0][v] + b2[0], acc[i][1][v] + b2[1]);
+          if constexpr (MODE != FWD_SUMS) stg_nt<unsigned>(o, lane * 4u + v * 256u, pk);
+          m[0][u] = __uint_as_float(pk << 16);
+          m[1][u] = __uint_as_float(pk & 0xffff0000u);
+        }
+      } else {
 #pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            const unsigned pk = pack_bf16x2(acc[i][j][2 * t] + b2[j], acc[i][j][2 * t + 1] + b2[j]);
-            stg_nt<unsigned short>(o, lane * 2u + (2 * t) * 128u, (unsigned short)(pk & 0xffffu));
-            stg_nt<unsigned short>(o, lane * 2u + (2 * t + 1) * 128u, (unsigned short)(pk >> 16));
+        for (int j = 0; j < C::CB; ++j) {
+          const size_t blk = ((size_t)eb * C::NCB + (wc * C::CB + j)) * 16 * 64;   // first element of the block
+          if constexpr (BF16) {
+            char* o = uoff(p.z2_vm, blk * 2);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              const int v = 4 * q + 2 * t;
+              const unsigned pk = pack_bf16x2(acc[i][j][v] + b2[j], acc[i][j][v + 1] + b2[j]);
+              if constexpr (MODE != FWD_SUMS) {
+                stg_nt<unsigned short>(o, lane * 2u + v * 128u, (unsigned short)(pk & 0xffffu));
+                stg_nt<unsigned short>(o, lane * 2u + (v + 1) * 128u, (unsigned short)(pk >> 16));
+              }
+              m[j][2 * t] = __uint_as_float(pk << 16);
+              m[j][2 * t + 1] = __uint_as_float(pk & 0xffff0000u);
+            }
+          } else {
+            char* o = uoff(p.z2_vm, blk * 4);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              m[j][u] = acc[i][j][4 * q + u] + b2[j];
+              if constexpr (MODE != FWD_SUMS) stg_nt<float>(o, lane * 4u + (4 * q + u) * 256u, m[j][u]);
+            }
           }
-        } else {
-          char* o = uoff(p.z2_vm, blk * 4);
-#pragma unroll
-          for (int v = 0; v < 16; ++v) stg_nt<float>(o, lane * 4u + v * 256u, acc[i][j][v] + b2[j]);
         }
       }
+      float xs[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j) {
+          m[j][u] = silu_f(m[j][u]);
+          if (!FULL && 32 * i + 8 * q + 4 * g + u >= nrow) m[j][u] = 0.f;
+          xs[u] = j == 0 ? wx[0] * m[0][u] : fmaf(wx[j], m[j][u], xs[u]);
+        }
+      }
+      // sums over the 32 lanes of a half of the 16 values of the block's rows share one butterfly, each exchange halving the values
+      // that a lane still carries; here over lane ^ 16, between the values v and v + 4
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (q % 2 == 0) {
+          y[2 * q + u] = xs[u];
+        } else {
+          const u32x2_t_ w = __builtin_amdgcn_permlane16_swap(__float_as_uint(y[2 * (q - 1) + u]), __float_as_uint(xs[u]), false, false);
+          y[2 * (q - 1) + u] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+        }
+      }
+      // where no atom begins among the rows, they are added as they are
+      unsigned bits = (unsigned)(starts >> (32 * i + 8 * q)) & 0xffu;
+      if (__builtin_expect(bits == 0, 1)) {
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) run[j] += m[j][u];
+      } else {
+        int lo = 0;
+        do {
+          const int hi = bits ? __builtin_ctz(bits) : 8;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const bool in = 4 * g + u >= lo && 4 * g + u < hi;
+#pragma unroll
+            for (int j = 0; j < C::CB; ++j) run[j] += in ? m[j][u] : 0.f;
+          }
+          if (hi < 8) flush(32 * i + 8 * q + hi, false);
+          lo = hi;
+          bits &= bits - 1u;
+        } while (lo < 8);
+      }
+      __builtin_amdgcn_sched_barrier(0);   // (the values of the next rows need the same registers)
+    }
+    {   // the other exchanges: lanes 2 k and 2 k + 1 of a half end up with one value
+      const bool b3 = x & 8, b2x = x & 4, b1 = x & 2;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = (b3 ? y[q + 4] : y[q]) + dpp_f<0x140>(b3 ? y[q] : y[q + 4]);     // lane ^ 15
+#pragma unroll
+      for (int q = 0; q < 2; ++q) y[q] = (b2x ? y[q + 2] : y[q]) + dpp_f<0x141>(b2x ? y[q] : y[q + 2]);   // lane ^ 7
+      y[0] = (b1 ? y[1] : y[0]) + dpp_f<0x1b>(b1 ? y[0] : y[1]);                                          // lane ^ 3
+      y[0] += dpp_f<0xb1>(y[0]);                                                                          // lane ^ 1
+      const int row = 32 * i + 16 * ((x >> 3) & 1) + 8 * (x >> 4) + 4 * g + ((x >> 1) & 3);   // v = 8 (bit 3) + 4 (bit 4) + bits 2, 1
+      if (!(x & 1) && (FULL || row < nrow)) p.xe_part[(size_t)wc * p.xe_stride + R0 + row] = y[0];
     }
     // the next tile's scalars are in LDS now: its first gathers travel behind the first block's stores, whose
     // accumulators are free by then (past the last tile the scalars are zeros and the gathers read row 0)
@@ -660,11 +815,12 @@ __device__ __forceinline__ void edge_fwd_tile(
       if (i == 0) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
     }
   }
+  if (FULL || nrow > 0) flush(S, true);
   if constexpr (C::WORD && !FULL) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
 }
 
-template <int H, bool BF16, bool BRES_REQ, bool ATTR>
-__global__ void __launch_bounds__(256, 2) k_edge_fwd(EdgeFwdArgs p, int ntiles) {
+template <int H, bool BF16, bool BRES_REQ, bool ATTR, int MODE>
+__global__ void __launch_bounds__(256, H <= 128 ? 3 : 2) k_edge_fwd(EdgeFwdArgs p, int ntiles) {
   using C = ECfg<H, BF16>;
   static_assert(!ATTR || (BF16 && C::TM == 64), "edge attributes: bf16 operands, 64-edge tiles");
   // keep this wavefront's slice of W2 in registers? (not with attributes: their accumulators need the room)
@@ -677,13 +833,14 @@ __global__ void __launch_bounds__(256, 2) k_edge_fwd(EdgeFwdArgs p, int ntiles) 
   const int wr = wave / C::WC, wc = wave % C::WC;
   const int x = lane & 31;
   const int E = (int)p.E;
-  float w1d[C::CB], b2[C::CB];
+  float w1d[C::CB], b2[C::CB], wx[C::CB];
   bf16x8_t bW1a[C::CB];
 #pragma unroll
   for (int j = 0; j < C::CB; ++j) {
     const int n = (wc * C::CB + j) * 32 + x;
     w1d[j] = ATTR ? 0.f : p.w1d[n];
     b2[j] = p.b2[n];
+    wx[j] = MODE == FWD_Z2 ? 0.f : p.wx[n];
     if constexpr (ATTR) bW1a[j] = attr_weight_operand(p.W1a, p.k, H, n, lane);
   }
   typename BFrag<H, BF16>::type breg[BRES ? BFrag<H, BF16>::NKB : 1][C::CB];
@@ -710,11 +867,11 @@ __global__ void __launch_bounds__(256, 2) k_edge_fwd(EdgeFwdArgs p, int ntiles) 
     const unsigned short* at = atb + buf * ATTR_TILE;
     unsigned short* at_next = atb + (buf ^ 1) * ATTR_TILE;
     if ((tile + 1) * C::TM <= E)
-      edge_fwd_tile<H, BF16, BRES, true, ATTR>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
-                                               dd0, at, at_next, nxa, bW1a);
+      edge_fwd_tile<H, BF16, BRES, true, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
+                                               dd0, at, at_next, nxa, bW1a, wx);
     else
-      edge_fwd_tile<H, BF16, BRES, false, ATTR>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
-                                                dd0, at, at_next, nxa, bW1a);
+      edge_fwd_tile<H, BF16, BRES, false, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
+                                                dd0, at, at_next, nxa, bW1a, wx);
   }
 }
 
@@ -730,24 +887,34 @@ static int resident_per_cu(const void* kernel, size_t dyn_lds, int fallback) {
   return n > 8 ? 8 : n;
 }
 
-template <int H, bool BF16, bool ATTR>
-static int32_t launch_edge_fwd_t(hipStream_t st, const EdgeFwdArgs& a) {
+template <int H, bool BF16, bool ATTR, int MODE>
+static int32_t launch_edge_fwd_m(hipStream_t st, const EdgeFwdArgs& a) {
   using C = ECfg<H, BF16>;
   const int64_t ntiles = (a.E + C::TM - 1) / C::TM;
   if (ntiles <= 0) return HGNN_OK;
   constexpr size_t lds = C::LDS_BYTES + 6 * C::TM * 4 + (ATTR ? 2 * ATTR_TILE * 2 : 0);
   static int per_cu = 0;
   if (!per_cu) {
-    HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_edge_fwd<H, BF16, true, ATTR>),
+    HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_edge_fwd<H, BF16, true, ATTR, MODE>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    per_cu = resident_per_cu(reinterpret_cast<const void*>(&k_edge_fwd<H, BF16, true, ATTR>), lds, 2);
+    per_cu = resident_per_cu(reinterpret_cast<const void*>(&k_edge_fwd<H, BF16, true, ATTR, MODE>), lds, 2);
   }
   int64_t grid = (int64_t)num_cus() * per_cu;
   if (grid > ntiles) grid = ntiles;
   ProfScope ps(PT_EDGE_FUSED_FWD, st);
-  k_edge_fwd<H, BF16, true, ATTR><<<dim3((unsigned)grid), 256, lds, st>>>(a, (int)ntiles);
+  k_edge_fwd<H, BF16, true, ATTR, MODE><<<dim3((unsigned)grid), 256, lds, st>>>(a, (int)ntiles);
   HGNN_LAUNCH_CHECK("k_edge_fwd");
   return HGNN_OK;
+}
+
+template <int H, bool BF16, bool ATTR>
+static int32_t launch_edge_fwd_t(hipStream_t st, const EdgeFwdArgs& a) {
+  if constexpr (!edge_fwd_sums(H, BF16, ATTR)) {
+    HGNN_REQUIRE(a.z2_vm || a.E == 0, HGNN_ERR_NULLPTR, "the forward edge kernel only stores z2 here");
+    return launch_edge_fwd_m<H, BF16, ATTR, FWD_Z2>(st, a);
+  } else {
+    return a.z2_vm ? launch_edge_fwd_m<H, BF16, ATTR, FWD_BOTH>(st, a) : launch_edge_fwd_m<H, BF16, ATTR, FWD_SUMS>(st, a);
+  }
 }
 
 int32_t launch_edge_fwd(hipStream_t st, int H, bool bf16, const EdgeFwdArgs& a) {
@@ -1059,12 +1226,12 @@ k_seg_fwd_vm(int N, const int32_t* __restrict__ row_ptr, const void* __restrict_
 }
 
 // Fewer rows than the chip holds wavefronts (32 per compute unit). Per launch, without and with the split: 187 rows of 57
-// edges, H = 128 fp32, forward with x_e 36 -> 12.5 us, source sum with the dots 28 -> 9.8 us; steps: a crystal's conservative
-// forces 845 -> 694 us, 16 crystals 1083 -> 999, 64 crystals (4,096 rows) 1886 -> 1849, 128 molecules (4,600 rows)
-// 999 -> 976. Past the line it changes nothing (12,900 and 18,600 rows: within 1 %).
+// edges, H = 128 fp32, source sum with the dots 28 -> 9.8 us; steps (when the forward sums of every width were such a launch too): a
+// crystal's conservative forces 845 -> 694 us, 16 crystals 1083 -> 999, 64 crystals (4,096 rows) 1886 -> 1849, 128 molecules
+// (4,600 rows) 999 -> 976. Past the line it changes nothing (12,900 and 18,600 rows: within 1 %).
 // And rows long enough for their number: the split saves time with every trip of a row, and costs it with every row
 // (wavefronts without a trip, and the sum over the four). The least mean row is N / (per_cu * compute units). Whole layers,
-// without -> with the split, H = 128 bf16, forward (per_cu = 2; 4 at H = 256, where a trip is twice as long): 8,000 rows of 2
+// without -> with the split, H = 128 bf16, forward sums as a launch (per_cu = 2; 4 at H = 256, which still has it: a trip is twice as long): 8,000 rows of 2
 // edges 32 -> 36 us, of 8 40 -> 41, of 30 69 -> 64, 2,000 rows of 4 23 -> 23, of 17 31 -> 27; reverse, one sum (per_cu = 8):
 // 8,000 rows of 1 edge 60 -> 62, of 4 77 -> 72, 2,000 rows of 1 51 -> 50, of 4 56 -> 51, with the dots of every edge
 // (per_cu = 16) 6,000 rows of 2 68 -> 65, 8,000 70 -> 71.
@@ -1072,28 +1239,20 @@ static bool seg_split(int N, int64_t E, int per_cu) {
   return N <= num_cus() * 32 && E * per_cu * num_cus() >= (int64_t)N * N;
 }
 
-int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, int64_t E, const int32_t* row_ptr, const void* z2_vm,
+int32_t launch_seg_fwd_vm(hipStream_t st, int N, int64_t E, const int32_t* row_ptr, const void* z2_vm,
                           const float* rvec, const float* wx, float alpha, const float* v_in, float* M,
                           float* v_out, float* xe) {
   if (N <= 0) return HGNN_OK;
-  const bool split = seg_split(N, E, H == 256 ? 4 : 2);
+  const bool split = seg_split(N, E, 4);
   const unsigned grid = split ? (unsigned)N : (unsigned)(((int64_t)N * 64 + 255) / 256);
   ProfScope ps(PT_SEG_FWD, st);
-#define HGNN_SEGF1(HH, BB, XX, SS) \
-  k_seg_fwd_vm<HH, BB, XX, SS><<<grid, 256, 0, st>>>(N, row_ptr, z2_vm, rvec, wx, alpha, v_in, M, v_out, xe)
-#define HGNN_SEGF(HH, BB)                              \
-  if (xe && split) HGNN_SEGF1(HH, BB, true, true);     \
-  else if (xe) HGNN_SEGF1(HH, BB, true, false);        \
-  else if (split) HGNN_SEGF1(HH, BB, false, true);     \
-  else HGNN_SEGF1(HH, BB, false, false)
-  switch (H) {
-    case 64: if (bf16) { HGNN_SEGF(64, true); } else { HGNN_SEGF(64, false); } break;
-    case 128: if (bf16) { HGNN_SEGF(128, true); } else { HGNN_SEGF(128, false); } break;
-    case 256: if (bf16) { HGNN_SEGF(256, true); } else { HGNN_SEGF(256, false); } break;
-    default: return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256");
-  }
+#define HGNN_SEGF(XX, SS) \
+  k_seg_fwd_vm<256, true, XX, SS><<<grid, 256, 0, st>>>(N, row_ptr, z2_vm, rvec, wx, alpha, v_in, M, v_out, xe)
+  if (xe && split) HGNN_SEGF(true, true);
+  else if (xe) HGNN_SEGF(true, false);
+  else if (split) HGNN_SEGF(false, true);
+  else HGNN_SEGF(false, false);
 #undef HGNN_SEGF
-#undef HGNN_SEGF1
   HGNN_LAUNCH_CHECK("k_seg_fwd_vm");
   return HGNN_OK;
 }
@@ -1102,7 +1261,7 @@ int32_t launch_seg_fwd_vm(hipStream_t st, int H, bool bf16, int N, int64_t E, co
 // which row i starts (slot 1) plus the partials of the later units (slot 0), in unit order; an empty row is set to
 // zero. One wavefront per atom, H/64 columns per lane. In two steps, so that the loads of the first four partials
 // travel while the wavefront does its other work.
-template <int H>
+template <int H, int UNIT = DSUM_UNIT>
 struct DsumFixRow {
   static_assert(H % 64 == 0, "whole columns per lane");
   typedef float vec_t __attribute__((ext_vector_type(H / 64)));
@@ -1112,8 +1271,8 @@ struct DsumFixRow {
   __device__ __forceinline__ void issue(int i, int lane, const DsumFix& f) {
     ra = f.row_ptr[i];
     rb = f.row_ptr[i + 1];
-    u0 = ra / DSUM_UNIT;
-    uk = rb > ra ? (rb - 1) / DSUM_UNIT : u0;
+    u0 = ra / UNIT;
+    uk = rb > ra ? (rb - 1) / UNIT : u0;
 #pragma unroll
     for (int q = 0; q < AHEAD; ++q) {
       p[q] = vec_t(0.f);
@@ -1121,7 +1280,7 @@ struct DsumFixRow {
         p[q] = reinterpret_cast<const vec_t*>(f.dpart + ((size_t)(u0 + q) * 2 + (q == 0 ? 1 : 0)) * H)[lane];
     }
   }
-  __device__ __forceinline__ void finish(int i, int lane, const DsumFix& f) const {
+  __device__ __forceinline__ void finish(int i, int lane, const DsumFix& f, float scale = 1.f) const {
     vec_t* o = reinterpret_cast<vec_t*>(f.gP + (size_t)i * f.ldgP) + lane;
     if (ra == rb) {
       *o = vec_t(0.f);
@@ -1132,9 +1291,60 @@ struct DsumFixRow {
 #pragma unroll
     for (int q = 1; q < AHEAD; ++q) a += p[q];   // units beyond the row's last one hold zeros here
     for (int u = u0 + AHEAD; u <= uk; ++u) a += reinterpret_cast<const vec_t*>(f.dpart + (size_t)u * 2 * H)[lane];
-    *o = a;
+    *o = a * scale;
   }
 };
+
+// What the forward edge kernel leaves to do per atom (one wavefront each): M of the atoms whose edges lie in several strips, zeros
+// for those without edges; v'_i = v_i + alpha sum_e x_e rvec_e with x_e the sum of its column parts (xe_out: also kept)
+template <int H, bool BF16>
+__global__ void __launch_bounds__(256)
+k_seg_fwd_rows(int N, DsumFix f, const float* __restrict__ xe_part, int64_t xe_stride, const float* __restrict__ rvec, float alpha,
+               const float* __restrict__ v_in, float* __restrict__ v_out, float* __restrict__ xe_out) {
+  using C = ECfg<H, BF16>;
+  const int lane = threadIdx.x & 63;
+  const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (i >= N) return;
+  DsumFixRow<H, C::RB * 32> row;
+  row.issue(i, lane, f);
+  float sx = 0.f, sy = 0.f, sz = 0.f;
+  for (int e = row.ra + lane; e < row.rb; e += 64) {
+    float t = xe_part[e];
+#pragma unroll
+    for (int c = 1; c < C::WC; ++c) t += xe_part[(size_t)c * xe_stride + e];
+    if (xe_out) xe_out[e] = t;
+    sx = fmaf(t, rvec[3 * (size_t)e], sx);
+    sy = fmaf(t, rvec[3 * (size_t)e + 1], sy);
+    sz = fmaf(t, rvec[3 * (size_t)e + 2], sz);
+  }
+  row.finish(i, lane, f, alpha);
+  sx = wave_sum64(sx);
+  sy = wave_sum64(sy);
+  sz = wave_sum64(sz);
+  if (lane == 0) {
+    v_out[3 * (size_t)i] = v_in[3 * (size_t)i] + alpha * sx;
+    v_out[3 * (size_t)i + 1] = v_in[3 * (size_t)i + 1] + alpha * sy;
+    v_out[3 * (size_t)i + 2] = v_in[3 * (size_t)i + 2] + alpha * sz;
+  }
+}
+
+int32_t launch_seg_fwd_rows(hipStream_t st, int H, bool bf16, int N, const int32_t* row_ptr, const EdgeFwdArgs& a,
+                            const float* rvec, const float* v_in, float* v_out, float* xe_out) {
+  if (N <= 0) return HGNN_OK;
+  const DsumFix f{row_ptr, a.mpart, a.M, H};
+  ProfScope ps(PT_SEG_FWD, st);
+#define HGNN_SEGR(HH, BB) \
+  k_seg_fwd_rows<HH, BB><<<(unsigned)(((int64_t)N + 3) / 4), 256, 0, st>>>(N, f, a.xe_part, a.xe_stride, rvec, a.alpha, v_in, v_out, xe_out)
+  switch (H) {
+    case 64: if (bf16) HGNN_SEGR(64, true); else HGNN_SEGR(64, false); break;
+    case 128: if (bf16) HGNN_SEGR(128, true); else HGNN_SEGR(128, false); break;
+    case 256: if (bf16) HGNN_SEGR(256, true); else HGNN_SEGR(256, false); break;
+    default: return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256");
+  }
+#undef HGNN_SEGR
+  HGNN_LAUNCH_CHECK("k_seg_fwd_rows");
+  return HGNN_OK;
+}
 
 // DOT: also dot[e] = sum_c wdot[c] X[e][c] for every edge of the list (the gradient with respect to d2 when X = g_z1
 // and wdot is the row of W1 that acts on d2)

@@ -195,13 +195,13 @@ static size_t unsaved_extra_bytes(int N, int64_t E, int H, bool bf16, int k) {
 
 // Everything of the forward pass that the reverse pass needs again (P|Q, z2 (a1), M, z3), written to `s`; also v_out.
 // Packs its own weight blocks into w.packed: 0 W1a, 1 W1b, 2 W2, 3 W3a, 4 W3b, 5 W4.
-// keep_xe: also keep x_e = wx . m_e per edge (fused kernels only; the fragment path always does)
+// keep_xe: also keep x_e = wx . m_e per edge (fused kernels only; the fragment path always does); keep_z2: z2 as well
 // k == 1: `attr` is the single per-edge attribute (the squared length); k > 1: [E,k] attributes, bf16 operands
 // h_out (optional): also h' = h + silu(z3) W4 + b4, formed by the kernel that forms z3 while its tile is on the chip
 static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, int32_t k, bool bf16, float alpha,
                               const int32_t* row_ptr, const int32_t* dst, const int32_t* col, const float* attr,
                               const float* rvec, const float* h_in, const float* v_in, const float* W, float* v_out,
-                              const LayerWs& w, const LayerSaved& s, bool keep_xe, float* h_out) {
+                              const LayerWs& w, const LayerSaved& s, bool keep_xe, bool keep_z2, float* h_out) {
   const LayerOff o(H, k);
   PackArgs pk;
   pk.src = W;
@@ -229,7 +229,8 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     }
     HGNN_TRY(launch_pack_gemm_chain(st, H, bf16, pk, nullptr, g, 0));   // h is staged once for both halves
   }
-  {  // per edge: a1 = silu(P[dst] + Q[col] + d2*w1d), z2 = a1 W2 + b2   (one fused kernel)
+  {  // per edge: a1 = silu(P[dst] + Q[col] + d2*w1d), z2 = a1 W2 + b2, and the sums of silu(z2)   (one fused kernel)
+    const bool sums = edge_fwd_sums(H, bf16, k > 1);
     EdgeFwdArgs e;
     e.E = E; e.dst = dst; e.col = col;
     if (k > 1) { e.d2 = nullptr; e.attr = attr; e.k = k; e.W1a = W + o.W1 + 2 * HH; }
@@ -238,11 +239,16 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     e.W2p = static_cast<const char*>(w.packed) + 2 * packed_block_bytes(H, bf16);
     if (!bf16) e.W2p = w.packed_x3;
     e.b2 = W + o.b2;
-    e.a1_pk = s.a1_pk; e.z2_vm = s.z2_vm;
+    e.a1_pk = s.a1_pk; e.z2_vm = keep_z2 || !sums ? s.z2_vm : nullptr;
+    e.wx = W + o.wx; e.alpha = alpha; e.M = s.M;
+    e.xe_stride = (E + 3) / 4 * 4;   // (scratch: the reverse pass's g_z1, at least 128 bytes per edge of whole 32-edge blocks)
+    e.xe_part = static_cast<float*>(w.gz1_vm);
+    e.mpart = e.xe_part + 4 * e.xe_stride;
     HGNN_TRY(launch_edge_fwd(st, H, bf16, e));
+    float* xe = keep_xe ? s.xe : nullptr;
+    if (sums) HGNN_TRY(launch_seg_fwd_rows(st, H, bf16, N, row_ptr, e, rvec, v_in, v_out, xe));
+    else HGNN_TRY(launch_seg_fwd_vm(st, N, E, row_ptr, s.z2_vm, rvec, e.wx, alpha, v_in, s.M, v_out, xe));
   }
-  HGNN_TRY(launch_seg_fwd_vm(st, H, bf16, N, E, row_ptr, s.z2_vm, rvec, W + o.wx, alpha, v_in, s.M, v_out,
-                             keep_xe ? s.xe : nullptr));
   {  // z3 = [h ; M] W3 + b3
     GemmArgs g;
     g.A[0] = h_in; g.lda[0] = H; g.A[1] = s.M; g.lda[1] = H; g.nkc = 2;
@@ -291,7 +297,8 @@ static int32_t mp_layer_fwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   }
   const bool bf16 = dtype == HGNN_BF16;
   LayerWs w = carve_ws(ws, N, E, H, bf16, k);
-  if (saved == nullptr) {
+  const bool keep = saved != nullptr;
+  if (!keep) {
     // nothing is kept for the reverse pass: the intermediates live behind the workspace proper for this call only
     const size_t need = w.bytes + unsaved_extra_bytes(N, E, H, bf16, k);
     HGNN_REQUIRE(ws_bytes >= need, HGNN_ERR_WORKSPACE_TOO_SMALL,
@@ -303,7 +310,7 @@ static int32_t mp_layer_fwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
   HGNN_REQUIRE(ws_bytes >= w.bytes, HGNN_ERR_WORKSPACE_TOO_SMALL, "mp_layer workspace: need %zu bytes, got %zu", w.bytes, ws_bytes);
   HGNN_REQUIRE(saved_bytes >= s.bytes, HGNN_ERR_WORKSPACE_TOO_SMALL, "mp_layer saved buffer: need %zu bytes, got %zu", s.bytes, saved_bytes);
   const LayerOff o(H, k);
-  HGNN_TRY(layer_fwd_core(st, N, E, H, k, bf16, alpha, row_ptr, dst, col, d2, rvec, h_in, v_in, W, v_out, w, s, keep_xe, h_out));
+  HGNN_TRY(layer_fwd_core(st, N, E, H, k, bf16, alpha, row_ptr, dst, col, d2, rvec, h_in, v_in, W, v_out, w, s, keep_xe, keep, h_out));
   return HGNN_OK;
 }
 
@@ -368,7 +375,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
     // the forward pass of this layer once more, up to z3 (its v' goes to scratch; the input v does not matter for
     // anything the reverse pass reads, so any valid [N,3] array serves)
     float* v_scratch = reinterpret_cast<float*>(static_cast<char*>(const_cast<void*>(saved)) + s.bytes);
-    HGNN_TRY(layer_fwd_core(st, N, E, H, k, bf16, alpha, row_ptr, dst, col, d2, rvec, h_in, g_v_out, W, v_scratch, w, s, false, nullptr));
+    HGNN_TRY(layer_fwd_core(st, N, E, H, k, bf16, alpha, row_ptr, dst, col, d2, rvec, h_in, g_v_out, W, v_scratch, w, s, false, true, nullptr));
   }
 
   // transposed blocks: 0 W4^T, 1 W3a^T, 2 W3b^T, 3 W2^T, 4 W1a^T, 5 W1b^T

@@ -64,6 +64,30 @@ def _run_layer(N, E, H, dtype, seed, lengths=None):
         assert e <= (tol["fwd"] if k in ("h", "v") else tol["grad"]), (k, e)
 
 
+def _run_layer_unsaved(N, H, dtype, lengths):
+    """Forward alone, without a saved buffer, against the oracle."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+    rng = np.random.default_rng(N)
+    E = sum(lengths)
+    _, _, col, d2, rvec = _edges(rng, N, E)
+    dst = np.repeat(np.arange(N, dtype=np.int32), lengths)
+    row_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    W = init_layer_weights(rng, H).astype(np.float32)
+    h = rng.standard_normal((N, H)).astype(np.float32)
+    v = (rng.standard_normal((N, 3)) * 0.3).astype(np.float32)
+    dt = {"f32": B.F32, "bf16": B.BF16}[dtype]
+    ws = torch.empty(sum(B.mp_layer_workspace_bytes(N, E, H, dt)) + (1 << 20), dtype=torch.uint8, device="cuda")
+    dev = lambda a: torch.as_tensor(a).cuda()
+    h_out, v_out = torch.empty((N, H), device="cuda"), torch.empty((N, 3), device="cuda")
+    B.mp_layer_fwd(N, E, H, dt, 0.25, dev(row_ptr), dev(dst), dev(col), dev(d2), dev(rvec), dev(h), dev(v), dev(W), h_out, v_out,
+                   None, ws)
+    torch.cuda.synchronize()
+    ho, vo, _ = oracle.mp_layer_fwd(h, v, dst, col, d2, rvec, W.astype(np.float64), 0.25)
+    assert relerr(h_out.cpu().numpy(), ho) <= TOL[dtype]["fwd"]
+    assert relerr(v_out.cpu().numpy(), vo) <= TOL[dtype]["fwd"]
+
+
 @pytest.mark.parametrize("H,dtype,N,E", [(256, "bf16", 700, 40001), (128, "f32", 300, 8191), (64, "bf16", 90, 1000),
                                          (256, "f32", 50, 0)])
 def test_layer_without_saved_buffer_recomputes(H, dtype, N, E):
@@ -267,6 +291,16 @@ def test_layer_wide_widths(H, N, E):
 @pytest.mark.parametrize("H,N,E", [(300, 700, 65281), (641, 500, 65536 + 33)])
 def test_layer_wide_weight_gradient_of_many_edges(H, N, E):
     _run_layer(N=N, E=E, H=H, dtype="bf16", seed=E)
+
+
+# The forward edge kernel sums the messages of a strip of 64 rows (32 at H = 64) in its accumulators, eight rows at a time: atoms that end
+# and begin at a strip's edge, inside its groups of eight, one after the other in one group, over two and many strips, a ragged last
+# strip of one row, no edges at either end and in between. Without a saved buffer z2 is not stored.
+@pytest.mark.parametrize("H,dtype", [(64, "f32"), (64, "bf16"), (128, "f32"), (128, "bf16"), (256, "f32")])
+@pytest.mark.parametrize("lengths", [[0, 32, 32, 64, 1, 31, 0, 16, 8, 8, 40, 200, 0], [1, 1, 2, 3, 1, 5, 0, 19, 33, 63], [7, 57, 129]])
+def test_layer_rows_at_strip_edges(H, dtype, lengths):
+    _run_layer(N=len(lengths), E=sum(lengths), H=H, dtype=dtype, seed=H + len(lengths), lengths=lengths)
+    _run_layer_unsaved(len(lengths), H, dtype, lengths)
 
 
 # The per-atom sums of the fragment path's epilogues work on strips of 64 rows in tiles of 256: atoms that end and begin at a strip's
