@@ -9,6 +9,12 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
+// the value of another lane of the same row of 16 (data-parallel pattern CTRL: 0x140 lane ^ 15, 0x141 ^ 7, 0x1b ^ 3, 0xb1 ^ 1)
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+
 // silu(t) = t / (1 + exp(-t)); exp through the hardware 2^x, reciprocal through v_rcp_f32
 __device__ __forceinline__ float silu_f(float t) {
   const float e = __expf(-t);

@@ -52,7 +52,7 @@ struct EdgeFwdArgs {
   void* z2_vm;         // out: z2, v-major (bf16 or fp32); null: not stored (where edge_fwd_sums())
   // Where edge_fwd_sums(): M[i,:] = alpha sum over the edges of destination row i, where the row lies inside one wavefront's strip of a
   // tile; the others leave one partial per strip in mpart ([strips][2][H]: slot 1 = the strip in which the row starts, slot 0 = every
-  // later one). And x_e = wx . m_e in parts, one per column wavefront. launch_seg_fwd_rows() finishes both.
+  // later one). And x_e = wx . m_e in parts, one per column wavefront. SegRows (gemm.h) is what is left to do.
   const float* wx;     // [H]
   float alpha;
   float* M;            // out [N,H]
@@ -75,9 +75,9 @@ int32_t launch_seg_fwd_vm(hipStream_t st, int N, int64_t E, const int32_t* row_p
 
 // (strips of 64 rows, of 32 at H = 64)
 inline size_t edge_fwd_mpart_floats(int64_t E, int H) { return (size_t)((E + 31) / 32) * 2 * H; }
-// The rest of M, and v_out = v_in + alpha sum_e x_e rvec[e,:]; xe_out (optional): [E] out, x_e = wx . m_e of every edge
-int32_t launch_seg_fwd_rows(hipStream_t st, int H, bool bf16, int N, const int32_t* row_ptr, const EdgeFwdArgs& a,
-                            const float* rvec, const float* v_in, float* v_out, float* xe_out);
+// The rest of M and v' (the chain of products that reads M does it itself for small batches)
+struct SegRows;
+int32_t launch_seg_fwd_rows(hipStream_t st, int H, int N, const SegRows& rows);
 
 // what finishes the rows of g_P that the reverse edge kernel left as per-unit partials (see EdgeBwdArgs::gP)
 struct DsumFix {

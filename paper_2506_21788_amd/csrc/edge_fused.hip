@@ -57,11 +57,6 @@ __device__ __forceinline__ float bf_bits_to_f(unsigned short b) { return __uint_
 // Streaming accesses are written as (uniform 64-bit base) + (32-bit per-lane byte offset): the base lives in scalar
 // registers, the lane part is one register shared by every access, and constant strides fold into the instruction.
 typedef unsigned u32x2_t_ __attribute__((ext_vector_type(2)));
-// the value of another lane of the same row of 16 (data-parallel pattern CTRL)
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, false));
-}
 template <typename T>
 __device__ __forceinline__ T ldg_nt(const void* ubase, unsigned off) {
   return __builtin_nontemporal_load(reinterpret_cast<const T*>(reinterpret_cast<const char*>(ubase) + off));
@@ -1295,53 +1290,49 @@ struct DsumFixRow {
   }
 };
 
-// What the forward edge kernel leaves to do per atom (one wavefront each): M of the atoms whose edges lie in several strips, zeros
-// for those without edges; v'_i = v_i + alpha sum_e x_e rvec_e with x_e the sum of its column parts (xe_out: also kept)
-template <int H, bool BF16>
-__global__ void __launch_bounds__(256)
-k_seg_fwd_rows(int N, DsumFix f, const float* __restrict__ xe_part, int64_t xe_stride, const float* __restrict__ rvec, float alpha,
-               const float* __restrict__ v_in, float* __restrict__ v_out, float* __restrict__ xe_out) {
-  using C = ECfg<H, BF16>;
+// SegRows as a kernel of its own, one wavefront per atom
+template <int H>
+__global__ void __launch_bounds__(256) k_seg_fwd_rows(int N, SegRows s) {
+  static_assert(SegRows::unit(H) == ECfg<H, true>::RB * 32 && SegRows::unit(H) == ECfg<H, false>::RB * 32 &&
+                    SegRows::parts(H) == ECfg<H, true>::WC && SegRows::parts(H) == ECfg<H, false>::WC,
+                "strips and column parts of the forward edge kernel");
   const int lane = threadIdx.x & 63;
   const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
   if (i >= N) return;
-  DsumFixRow<H, C::RB * 32> row;
+  const DsumFix f{s.row_ptr, s.mpart, s.M, H};
+  DsumFixRow<H, SegRows::unit(H)> row;
   row.issue(i, lane, f);
   float sx = 0.f, sy = 0.f, sz = 0.f;
   for (int e = row.ra + lane; e < row.rb; e += 64) {
-    float t = xe_part[e];
+    float t = s.xe_part[e];
 #pragma unroll
-    for (int c = 1; c < C::WC; ++c) t += xe_part[(size_t)c * xe_stride + e];
-    if (xe_out) xe_out[e] = t;
-    sx = fmaf(t, rvec[3 * (size_t)e], sx);
-    sy = fmaf(t, rvec[3 * (size_t)e + 1], sy);
-    sz = fmaf(t, rvec[3 * (size_t)e + 2], sz);
+    for (int c = 1; c < SegRows::parts(H); ++c) t += s.xe_part[(size_t)c * s.xe_stride + e];
+    if (s.xe_out) s.xe_out[e] = t;
+    sx = fmaf(t, s.rvec[3 * (size_t)e], sx);
+    sy = fmaf(t, s.rvec[3 * (size_t)e + 1], sy);
+    sz = fmaf(t, s.rvec[3 * (size_t)e + 2], sz);
   }
-  row.finish(i, lane, f, alpha);
+  row.finish(i, lane, f, s.alpha);
   sx = wave_sum64(sx);
   sy = wave_sum64(sy);
   sz = wave_sum64(sz);
   if (lane == 0) {
-    v_out[3 * (size_t)i] = v_in[3 * (size_t)i] + alpha * sx;
-    v_out[3 * (size_t)i + 1] = v_in[3 * (size_t)i + 1] + alpha * sy;
-    v_out[3 * (size_t)i + 2] = v_in[3 * (size_t)i + 2] + alpha * sz;
+    s.v_out[3 * (size_t)i] = s.v_in[3 * (size_t)i] + s.alpha * sx;
+    s.v_out[3 * (size_t)i + 1] = s.v_in[3 * (size_t)i + 1] + s.alpha * sy;
+    s.v_out[3 * (size_t)i + 2] = s.v_in[3 * (size_t)i + 2] + s.alpha * sz;
   }
 }
 
-int32_t launch_seg_fwd_rows(hipStream_t st, int H, bool bf16, int N, const int32_t* row_ptr, const EdgeFwdArgs& a,
-                            const float* rvec, const float* v_in, float* v_out, float* xe_out) {
+int32_t launch_seg_fwd_rows(hipStream_t st, int H, int N, const SegRows& rows) {
   if (N <= 0) return HGNN_OK;
-  const DsumFix f{row_ptr, a.mpart, a.M, H};
+  const unsigned grid = (unsigned)(((int64_t)N + 3) / 4);
   ProfScope ps(PT_SEG_FWD, st);
-#define HGNN_SEGR(HH, BB) \
-  k_seg_fwd_rows<HH, BB><<<(unsigned)(((int64_t)N + 3) / 4), 256, 0, st>>>(N, f, a.xe_part, a.xe_stride, rvec, a.alpha, v_in, v_out, xe_out)
   switch (H) {
-    case 64: if (bf16) HGNN_SEGR(64, true); else HGNN_SEGR(64, false); break;
-    case 128: if (bf16) HGNN_SEGR(128, true); else HGNN_SEGR(128, false); break;
-    case 256: if (bf16) HGNN_SEGR(256, true); else HGNN_SEGR(256, false); break;
+    case 64: k_seg_fwd_rows<64><<<grid, 256, 0, st>>>(N, rows); break;
+    case 128: k_seg_fwd_rows<128><<<grid, 256, 0, st>>>(N, rows); break;
+    case 256: k_seg_fwd_rows<256><<<grid, 256, 0, st>>>(N, rows); break;
     default: return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256");
   }
-#undef HGNN_SEGR
   HGNN_LAUNCH_CHECK("k_seg_fwd_rows");
   return HGNN_OK;
 }

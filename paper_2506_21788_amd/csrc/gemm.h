@@ -42,6 +42,24 @@ inline size_t packed_x3_bytes(int H) { return (size_t)H * H * 6; }
 
 // ---- row-tile GEMM --------------------------------------------------------------------------
 // C[rows, cb*H + (0..H)] = epilogue( sum_kc  f(A[kc][rows, 0..H]) x B[blk[kc][cb]] )
+// What is left to do per atom of the sums that the forward edge kernel took over its messages (see EdgeFwdArgs::M): M of the atoms
+// whose edges lie in several strips (zeros for those without edges) and v_out = v_in + alpha sum_e x_e rvec_e with x_e the sum of
+// its column parts (xe_out: also kept)
+struct SegRows {
+  static constexpr int unit(int H) { return H == 64 ? 32 : 64; }   // rows of a strip
+  static constexpr int parts(int H) { return H == 64 ? 2 : 4; }    // column parts of x_e
+  const int32_t* row_ptr;
+  const float* mpart;
+  float* M;
+  const float* xe_part;
+  int64_t xe_stride;
+  const float* rvec;
+  float alpha;
+  const float* v_in;
+  float* v_out;
+  float* xe_out;
+};
+
 struct GemmArgs {
   const float* A[2] = {nullptr, nullptr};
   int lda[2] = {0, 0};
@@ -83,7 +101,10 @@ int32_t launch_gemm_pair(hipStream_t st, int H, bool bf16, const GemmArgs& a, co
 // Two products in a row per row tile, the second one reading the first one's finished tile (through silu when
 // keep_silu is set) from LDS instead of its own A; with first == nullptr the second one alone, its A tile (one k
 // chunk) staged once for all of its column blocks. One launch; no groups, no row indirection.
-int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu);
+// rows (optional, where gemm_chain_takes_rows()): A[1] of the first product is rows->M, finished here on the way
+int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu,
+                          const SegRows* rows = nullptr);
+bool gemm_chain_takes_rows(int H, bool bf16, int M);
 // launch_pack() and a launch_gemm_chain() whose weights are among the packed blocks; one launch for small batches
 int32_t launch_pack_gemm_chain(hipStream_t st, int H, bool bf16, const PackArgs& pk, const GemmArgs* first,
                                const GemmArgs& second, int keep_silu);

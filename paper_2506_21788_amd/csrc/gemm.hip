@@ -561,8 +561,10 @@ struct SmallAux {   // operands of an epilogue, in the accumulator mapping: row 
 struct GemmJobs {
   GemmArgs job[2];
 };
-template <int H, bool BF16, bool CHAIN, bool RAW>
-__device__ __forceinline__ void gemm_small(const GemmJobs& m, int keep_silu, const PackArgs& pk, int tiles, unsigned char* smem) {
+// SEG: the second chunk of A is rows.M, whose last steps (and v') are taken here, see SegRows
+template <int H, bool BF16, bool CHAIN, bool RAW, bool SEG = false>
+__device__ __forceinline__ void gemm_small(const GemmJobs& m, int keep_silu, const PackArgs& pk, int tiles, unsigned char* smem,
+                                           const SegRows& rows) {
   using C = SmallCfg<H, BF16>;
   const GemmArgs& p1 = m.job[0];
   const GemmArgs& p2 = m.job[CHAIN ? 1 : RAW ? 0 : blockIdx.z];
@@ -664,11 +666,78 @@ __device__ __forceinline__ void gemm_small(const GemmJobs& m, int keep_silu, con
   }
 #pragma unroll
   for (int kc = 0; kc < NKC; ++kc)
-    if (kc < pa.nkc) {
+    if (kc < pa.nkc && !(SEG && kc == 1)) {
 #pragma unroll
       for (int u = 0; u < NA; ++u)
         av[kc][u] = *reinterpret_cast<const float4*>(pa.A[kc] + arow[u] * pa.lda[kc] + ((tid + u * C::THREADS) % CH) * 4);
     }
+  if constexpr (SEG) {
+    constexpr int UNIT = SegRows::unit(H);
+    int ra[NA], rb[NA];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      ra[u] = rows.row_ptr[arow[u]];
+      rb[u] = rows.row_ptr[arow[u] + 1];
+    }
+    float4 p[NA][2];   // M, or the partials of the first two strips
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      const int q = ((tid + u * C::THREADS) % CH) * 4, s0 = ra[u] / UNIT;
+      const bool over = rb[u] > ra[u] && (rb[u] - 1) / UNIT != s0;
+      p[u][0] = p[u][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (rb[u] > ra[u]) p[u][0] = *reinterpret_cast<const float4*>(over ? rows.mpart + ((size_t)s0 * 2 + 1) * H + q : rows.M + arow[u] * H + q);
+      if (over) p[u][1] = *reinterpret_cast<const float4*>(rows.mpart + (size_t)(s0 + 1) * 2 * H + q);
+    }
+    // v': sixteen lanes per row
+    if (tid < 16 * C::TM) {
+      const int pos = rbeg + (tid >> 4);
+      const long i = pos < rend ? pos : rend - 1;
+      const int e1 = rows.row_ptr[i + 1];
+      float sv[3] = {0.f, 0.f, 0.f};
+      for (int e0 = rows.row_ptr[i] + (tid & 15); e0 < e1; e0 += 32) {   // two edges per trip
+        float t[2], r[2][3];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int e = e0 + 16 * h < e1 ? e0 + 16 * h : e0;
+          t[h] = rows.xe_part[e];
+#pragma unroll
+          for (int k = 1; k < SegRows::parts(H); ++k) t[h] += rows.xe_part[k * rows.xe_stride + e];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) r[h][k] = rows.rvec[3 * (size_t)e + k];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (e0 + 16 * h < e1) {
+            if (rows.xe_out && pos < rend) rows.xe_out[e0 + 16 * h] = t[h];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) sv[k] = fmaf(t[h], r[h][k], sv[k]);
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        sv[k] += dpp_f<0x140>(sv[k]);
+        sv[k] += dpp_f<0x141>(sv[k]);
+        sv[k] += dpp_f<0x1b>(sv[k]);
+        sv[k] += dpp_f<0xb1>(sv[k]);
+      }
+      const int k = tid & 15;
+      if (k < 3 && pos < rend) rows.v_out[3 * i + k] = rows.v_in[3 * i + k] + rows.alpha * (k == 0 ? sv[0] : k == 1 ? sv[1] : sv[2]);
+    }
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      const int q = ((tid + u * C::THREADS) % CH) * 4, s0 = ra[u] / UNIT, s1 = (rb[u] - 1) / UNIT;
+      float4 w = p[u][0];
+      if (rb[u] == ra[u] || s1 != s0) {
+        auto add = [&](const float4& t) { w.x += t.x; w.y += t.y; w.z += t.z; w.w += t.w; };
+        add(p[u][1]);
+        if (rb[u] > ra[u])
+          for (int s = s0 + 2; s <= s1; ++s) add(*reinterpret_cast<const float4*>(rows.mpart + (size_t)s * 2 * H + q));
+        w.x *= rows.alpha; w.y *= rows.alpha; w.z *= rows.alpha; w.w *= rows.alpha;
+        if (rbeg + (tid + u * C::THREADS) / CH < rend) *reinterpret_cast<float4*>(rows.M + arow[u] * H + q) = w;
+      }
+      av[NKC - 1][u] = w;
+    }
+  }
   // ---- rows of this lane's accumulators and the epilogues' operands
   long gr[4];
   bool ok[4];
@@ -793,16 +862,22 @@ __device__ __forceinline__ void gemm_small(const GemmJobs& m, int keep_silu, con
 template <int H, bool BF16, bool CHAIN, bool RAW>
 __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small(GemmJobs m, int keep_silu, PackArgs pk, int tiles) {
   extern __shared__ __align__(16) unsigned char smem[];
-  gemm_small<H, BF16, CHAIN, RAW>(m, keep_silu, pk, tiles, smem);
+  gemm_small<H, BF16, CHAIN, RAW>(m, keep_silu, pk, tiles, smem, SegRows{});
+}
+template <int H, bool BF16>
+__global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small_rows(GemmJobs m, int keep_silu, SegRows rows) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  gemm_small<H, BF16, true, false, true>(m, keep_silu, PackArgs{}, 0, smem, rows);
 }
 
 // (rule: see small_gemm())
 template <int H, bool BF16>
-static int32_t launch_gemm_small_t(hipStream_t st, const GemmArgs* first, const GemmArgs& a, int keep_silu) {
+static int32_t launch_gemm_small_t(hipStream_t st, const GemmArgs* first, const GemmArgs& a, int keep_silu, const SegRows* rows = nullptr) {
   using C = SmallCfg<H, BF16>;
   const int tiles = (a.M + C::TM - 1) / C::TM + (a.grp_ptr ? a.S : 0);
   ProfScope ps(a.tag, st);
-  if (first) k_gemm_small<H, BF16, true, false><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, PackArgs{}, tiles);
+  if (rows) k_gemm_small_rows<H, BF16><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, *rows);
+  else if (first) k_gemm_small<H, BF16, true, false><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, PackArgs{}, tiles);
   else k_gemm_small<H, BF16, false, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{a, a}}, 0, PackArgs{}, tiles);
   HGNN_LAUNCH_CHECK("k_gemm_small");
   return HGNN_OK;
@@ -876,14 +951,14 @@ static int32_t launch_gemm_t(hipStream_t st, const GemmArgs& a) {
 }
 
 template <int H, bool BF16>
-static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const GemmArgs& second, int keep_silu) {
+static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const GemmArgs& second, int keep_silu, const SegRows* rows) {
   constexpr int TM = GemmCfg<H, BF16>::WR == 1 ? 32 : 64;
   using C = GemmCfg<H, BF16, TM>;
   if (second.M <= 0) return HGNN_OK;
   // (chains at H = 256 only while every compute unit has one 16-row tile at most, 512 threads that hold two blocks of both
   // weights each: layer forward, 64- / 32-row tiles -> 16-row tiles, 4,000 atoms 44 -> 37 us, 5,000 44 -> 47, 8,000 49 -> 53)
   if constexpr (BF16 || H < 256) {
-    if (small_gemm(second, H == 256 ? 16 : TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu);
+    if (small_gemm(second, H == 256 ? 16 : TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu, rows);
   }
   constexpr size_t LDS = C::LDS_BYTES + C::A_BYTES;
   static bool raised = false;   // the kernel's LDS limit is raised once per variant
@@ -919,12 +994,24 @@ static int32_t check_gemm_chain(int H, const GemmArgs* first, const GemmArgs& se
   }
   return HGNN_OK;
 }
-int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu) {
+// Chains of 16-row tiles finish the forward sums of their rows themselves (the same rule as in launch_gemm_chain_t): a launch
+// fewer per layer, whose loads travel with the chain's own. Steps, launch of its own -> in the chain: one molecule, forward 131 -> 126 us,
+// 203 molecules, forward 272 -> 265, 32 small molecules 259 -> 254, 128 molecules 766 -> 762, one crystal of 60 atoms, forward 197 -> 191;
+// a crystal's conservative forces (12 tiles, rows of 57 edges) 473 -> 472.
+bool gemm_chain_takes_rows(int H, bool bf16, int M) {
+  GemmArgs a;
+  a.M = M;
+  return M > 0 && (bf16 || H < 256) && small_gemm(a, H == 256 ? 16 : H == 128 ? 32 : 64);
+}
+int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu,
+                          const SegRows* rows) {
   HGNN_TRY(check_gemm_chain(H, first, second));
+  HGNN_REQUIRE(!rows || (gemm_chain_takes_rows(H, bf16, second.M) && first && first->nkc == 2 && first->A[1] == rows->M && first->lda[1] == H),
+               HGNN_ERR_BAD_SHAPE, "gemm chain: the forward sums are finished by 16-row tiles that read them");
   switch (H) {
-    case 64: return bf16 ? launch_gemm_chain_t<64, true>(st, first, second, keep_silu) : launch_gemm_chain_t<64, false>(st, first, second, keep_silu);
-    case 128: return bf16 ? launch_gemm_chain_t<128, true>(st, first, second, keep_silu) : launch_gemm_chain_t<128, false>(st, first, second, keep_silu);
-    case 256: return bf16 ? launch_gemm_chain_t<256, true>(st, first, second, keep_silu) : launch_gemm_chain_t<256, false>(st, first, second, keep_silu);
+    case 64: return bf16 ? launch_gemm_chain_t<64, true>(st, first, second, keep_silu, rows) : launch_gemm_chain_t<64, false>(st, first, second, keep_silu, rows);
+    case 128: return bf16 ? launch_gemm_chain_t<128, true>(st, first, second, keep_silu, rows) : launch_gemm_chain_t<128, false>(st, first, second, keep_silu, rows);
+    case 256: return bf16 ? launch_gemm_chain_t<256, true>(st, first, second, keep_silu, rows) : launch_gemm_chain_t<256, false>(st, first, second, keep_silu, rows);
   }
   return set_error(HGNN_ERR_BAD_SHAPE, "H must be 64, 128 or 256 (got %d)", H);
 }
@@ -1145,7 +1232,7 @@ __global__ void __launch_bounds__((SmallCfg<H, BF16>::THREADS)) k_gemm_small_red
   extern __shared__ __align__(16) unsigned char smem[];
   static_assert(SmallCfg<H, BF16>::LDS_BYTES >= SmallCfg<H, BF16>::THREADS * sizeof(float), "a float per thread");
   if ((int)blockIdx.x < tiles) {
-    gemm_small<H, BF16, false, false>(m, 0, PackArgs{}, tiles, smem);
+    gemm_small<H, BF16, false, false>(m, 0, PackArgs{}, tiles, smem, SegRows{});
   } else {
     const long wg = (long)((int)blockIdx.x - tiles) * gridDim.z + blockIdx.z;
     if (wg < q.off[q.njobs]) reduce_queue<SmallCfg<H, BF16>::THREADS>(q, wg, reinterpret_cast<float*>(smem));

@@ -229,6 +229,8 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     }
     HGNN_TRY(launch_pack_gemm_chain(st, H, bf16, pk, nullptr, g, 0));   // h is staged once for both halves
   }
+  SegRows rows{};
+  bool rows_in_chain = false;   // the sums' last steps are taken by the chain of products below
   {  // per edge: a1 = silu(P[dst] + Q[col] + d2*w1d), z2 = a1 W2 + b2, and the sums of silu(z2)   (one fused kernel)
     const bool sums = edge_fwd_sums(H, bf16, k > 1);
     EdgeFwdArgs e;
@@ -246,7 +248,10 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     e.mpart = e.xe_part + 4 * e.xe_stride;
     HGNN_TRY(launch_edge_fwd(st, H, bf16, e));
     float* xe = keep_xe ? s.xe : nullptr;
-    if (sums) HGNN_TRY(launch_seg_fwd_rows(st, H, bf16, N, row_ptr, e, rvec, v_in, v_out, xe));
+    rows = SegRows{row_ptr, e.mpart, s.M, e.xe_part, e.xe_stride, rvec, alpha, v_in, v_out, xe};
+    rows_in_chain = sums && h_out && gemm_chain_takes_rows(H, bf16, N);
+    if (rows_in_chain) {
+    } else if (sums) HGNN_TRY(launch_seg_fwd_rows(st, H, N, rows));
     else HGNN_TRY(launch_seg_fwd_vm(st, N, E, row_ptr, s.z2_vm, rvec, e.wx, alpha, v_in, s.M, v_out, xe));
   }
   {  // z3 = [h ; M] W3 + b3
@@ -263,7 +268,7 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
       g2.bias = W + o.b4; g2.bias_cb_mask = 1;
       g2.add1 = h_in; g2.ldadd1 = H;
       g2.C = h_out; g2.ldc = H;
-      HGNN_TRY(launch_gemm_chain(st, H, bf16, &g, g2, 1));
+      HGNN_TRY(launch_gemm_chain(st, H, bf16, &g, g2, 1, rows_in_chain ? &rows : nullptr));
     } else {
       HGNN_TRY(launch_gemm(st, H, bf16, g));
     }

@@ -303,6 +303,14 @@ def test_layer_rows_at_strip_edges(H, dtype, lengths):
     _run_layer_unsaved(len(lengths), H, dtype, lengths)
 
 
+# The last steps of those sums are taken by the chain of products up to one 32-row tile per compute unit (256), by a kernel of their own
+# beyond: on both sides of the line, rows of every length up to three strips, a last 16-row tile of one row
+@pytest.mark.parametrize("N", [8177, 8193])
+def test_layer_rows_either_side_of_the_short_chains(N):
+    lengths = np.random.default_rng(N).choice([0, 1, 3, 7, 70, 130], size=N, p=[.3, .3, .2, .18, .01, .01])
+    _run_layer(N=N, E=int(lengths.sum()), H=128, dtype="bf16", seed=N, lengths=lengths.tolist())
+
+
 # The per-atom sums of the fragment path's epilogues work on strips of 64 rows in tiles of 256: atoms that end and begin at a strip's
 # and at a tile's edge, one atom of exactly a strip, atoms over two and over five strips, an atom of its own in a ragged last
 # strip, atoms without edges at either end and in between
