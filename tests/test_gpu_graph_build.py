@@ -263,6 +263,23 @@ def test_work_items_of_thin_cells_next_to_molecules(atoms):
     assert_graph_equal(gpu_graph(many, rc).to_numpy(), want)
 
 
+# The workgroup that bins a single graph also clears the counters, up to 16,384 of them (2,303 atoms); the allocations are made of dirty
+# memory
+@pytest.mark.parametrize("N", [1, 187, 2303, 2304])
+def test_one_graph_clears_its_own_counters(N):
+    import torch
+    rng = np.random.default_rng(N)
+    side = max(4.0, (N * 9.0) ** (1.0 / 3.0))
+    a = np.array([[side, 0, 0], [0.3, side, 0], [0, -0.4, side]])
+    one = concat_graphs([((rng.random((N, 3)) @ a).astype(np.float32), rng.integers(1, 90, N).astype(np.int32), a.astype(np.float32))])
+    dirt = torch.full((64 << 20,), 0x5a, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    del dirt
+    want = oracle.radius_graph(one.pos, one.graph_off, one.cell, one.pbc, 4.5)
+    for _ in range(2):
+        assert_graph_equal(gpu_graph(one, 4.5).to_numpy(), want)
+
+
 # atoms placed by the workgroup that places the graphs, or by a launch of their own
 @pytest.mark.parametrize("N", [6144, 6145])
 @pytest.mark.parametrize("G,S", [(1, 1), (1100, 64), (1100, 65), (7000, 5)])
