@@ -659,63 +659,82 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
     }
   }
   if constexpr (SEG) {
-    // x_e: the 32 row sums over the 32 lanes of a half share one butterfly, each exchange halving the values a lane
-    // still carries (31 exchanges instead of 160); lane x ends up with the sum of value x = 16 i + v
-    {
-      float a16[16], a8[8], a4[4], a2[2];
-      const bool b4 = x & 16, b3 = x & 8, b2 = x & 4, b1 = x & 2, b0 = x & 1;
+    // x_e: the sums over the 32 lanes of a half of a block's 16 values share one butterfly, each exchange halving the values that
+    // a lane still carries (over lane ^ 16 between the values v and v + 8, then lane ^ 15, ^ 7, ^ 3, ^ 1, without the LDS); lanes
+    // 2 v and 2 v + 1 end up with value v
 #pragma unroll
-      for (int q = 0; q < 16; ++q) a16[q] = (b4 ? xe[16 + q] : xe[q]) + __shfl_xor(b4 ? xe[q] : xe[16 + q], 16);
+    for (int i = 0; i < WI; ++i) {
+      float y[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) a8[q] = (b3 ? a16[8 + q] : a16[q]) + __shfl_xor(b3 ? a16[q] : a16[8 + q], 8);
+      for (int q = 0; q < 8; ++q) {
+        const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(xe[16 * i + q]), __float_as_uint(xe[16 * i + q + 8]), false, false);
+        y[q] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+      }
+      const bool b3 = x & 8, b2 = x & 4, b1 = x & 2;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) a4[q] = (b2 ? a8[4 + q] : a8[q]) + __shfl_xor(b2 ? a8[q] : a8[4 + q], 4);
+      for (int q = 0; q < 4; ++q) y[q] = (b3 ? y[q + 4] : y[q]) + dpp_f<0x140>(b3 ? y[q] : y[q + 4]);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) a2[q] = (b1 ? a4[2 + q] : a4[q]) + __shfl_xor(b1 ? a4[q] : a4[2 + q], 2);
-      const float tot = (b0 ? a2[1] : a2[0]) + __shfl_xor(b0 ? a2[0] : a2[1], 1);
-      const int i = x >> 4, v = x & 15;
+      for (int q = 0; q < 2; ++q) y[q] = (b2 ? y[q + 2] : y[q]) + dpp_f<0x141>(b2 ? y[q] : y[q + 2]);
+      y[0] = (b1 ? y[1] : y[0]) + dpp_f<0x1b>(b1 ? y[0] : y[1]);
+      y[0] += dpp_f<0xb1>(y[0]);
+      const int v = x >> 1;
       const long row = R0 + 32 * i + 8 * (v >> 2) + 4 * g + (v & 3);
-      if (row < p.seg_E) p.seg_xe[(long)tj * p.seg_xe_stride + row] = tot;
+      if (!(x & 1) && row < p.seg_E) p.seg_xe[(long)tj * p.seg_xe_stride + row] = y[0];
     }
-    // sums per destination atom over the strip: the runs of the strip one after the other (rows are sorted by destination)
+    // sums per destination atom over the strip (rows are sorted by destination): eight rows at a time, four of either lane half,
+    // which are added as they are where no atom begins among them (every run over all 64 rows, under a mask: AD_SEG 408 us per launch,
+    // 392 now; steps at H = 320 3.715 -> 3.683 ms, at 500 1.462 -> 1.446)
     if (R0 < p.seg_E) {
       const int s0 = wave * 64;
       const int mine = edst[1 + s0 + lane];
-      const bool before = __builtin_amdgcn_readfirstlane(edst[s0] == mine);                    // (lane 0: the strip's first row)
-      const bool behind = __builtin_amdgcn_readfirstlane(edst[s0 + 65]) == __builtin_amdgcn_readlane(mine, 63);
       const int nrow = p.seg_E - R0 < 64 ? (int)(p.seg_E - R0) : 64;
-      const long strip = R0 >> 6;
-      unsigned long long starts = __ballot(lane == 0 || mine != edst[s0 + lane]);   // bit r: row r of the strip begins a run
+      const bool before = __builtin_amdgcn_readfirstlane(edst[s0] == mine);                    // (lane 0: the strip's first row)
+      const bool behind = nrow == 64 && __builtin_amdgcn_readfirstlane(edst[s0 + 65]) == __builtin_amdgcn_readlane(mine, 63);
+      unsigned long long starts = __ballot(lane != 0 && mine != edst[s0 + lane]);   // bit r: row r of the strip begins a run
       if (nrow < 64) starts &= (1ull << nrow) - 1ull;
-      while (starts) {
-        const int lo = __ffsll((long long)starts) - 1;
-        starts &= starts - 1ull;
-        const int hi = starts ? __ffsll((long long)starts) - 1 : nrow;
-        const int a = __builtin_amdgcn_readlane(mine, lo);
-        float t[WJ];
+      float t[WJ];
+      int k0 = 0;   // first row of the run at hand
 #pragma unroll
-        for (int j = 0; j < WJ; ++j) t[j] = 0.f;
+      for (int j = 0; j < WJ; ++j) t[j] = 0.f;
+      auto flush = [&](int end, bool last) {
+        const bool sf = k0 != 0 || !before, ef = !last || !behind;   // the atom's edges begin and end in the strip
+        float* dest = sf && ef ? p.seg_M + (long)__builtin_amdgcn_readlane(mine, k0) * p.seg_ldm : (sf ? p.seg_last : p.seg_first) + (R0 >> 6) * p.seg_ldp;
+        const float scale = sf && ef ? p.seg_alpha : 1.f;
 #pragma unroll
-        for (int i = 0; i < WI; ++i)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int rr = 32 * i + 8 * (v >> 2) + (v & 3) + 4 * g;
-            const bool in = (unsigned)(rr - lo) < (unsigned)(hi - lo);
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) t[j] += in ? acc[i][j][v] : 0.f;
-          }
-#pragma unroll
-        for (int j = 0; j < WJ; ++j) t[j] += __shfl_xor(t[j], 32);
-        float* dest;
-        float scale = 1.f;
-        if (lo == 0 && before) dest = p.seg_first + strip * p.seg_ldp;
-        else if (hi == 64 && behind) dest = p.seg_last + strip * p.seg_ldp;
-        else { dest = p.seg_M + (long)a * p.seg_ldm; scale = p.seg_alpha; }
-        if (g == 0) {
-#pragma unroll
-          for (int j = 0; j < WJ; ++j) dest[(j0 + wj * WJ + j) * 32 + x] = scale * t[j];
+        for (int j = 0; j < WJ; j += 2) {   // the halves added; 64 columns in a row
+          const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[j]), __float_as_uint(t[j + 1]), false, false);
+          dest[(j0 + wj * WJ + j) * 32 + lane] = scale * (__uint_as_float(w[0]) + __uint_as_float(w[1]));
+          t[j] = t[j + 1] = 0.f;
         }
-      }
+        k0 = end;
+      };
+#pragma unroll
+      for (int i = 0; i < WI; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          unsigned bits = (unsigned)(starts >> (32 * i + 8 * q)) & 0xffu;
+          if (__builtin_expect(bits == 0, 1)) {
+#pragma unroll
+            for (int j = 0; j < WJ; ++j)
+#pragma unroll
+              for (int u = 0; u < 4; ++u) t[j] += acc[i][j][4 * q + u];
+          } else {
+            int lo = 0;
+            do {
+              const int hi = bits ? __builtin_ctz(bits) : 8;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const bool in = 4 * g + u >= lo && 4 * g + u < hi;
+#pragma unroll
+                for (int j = 0; j < WJ; ++j) t[j] += in ? acc[i][j][4 * q + u] : 0.f;
+              }
+              if (hi < 8) flush(32 * i + 8 * q + hi, false);
+              lo = hi;
+              bits &= bits - 1u;
+            } while (lo < 8);
+          }
+        }
+      flush(64, true);
     }
   }
 }
