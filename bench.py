@@ -33,7 +33,9 @@ def kernel_work(tag, N, E, H, dtype, dsum_in_edge_kernel=False, w2_in_edge_kerne
     # where that forms the W2 gradient itself
     pairs = dtype == "bf16" and H == 256
     if tag == "edge_fused_fwd":      # out: z2 (and a1 unless recomputed); in: dst, col, d2; gathers P|Q
-        return 2.0 * EH * H, (1 if pairs or w2_in_edge_kernel else 2) * EH * b + 12.0 * E + 2 * NH * b
+        # except for the bf16 pairs also the sums of silu(z2) per atom and x_e (four parts per edge)
+        return 2.0 * EH * H, ((1 if pairs or w2_in_edge_kernel else 2) * EH * b + 12.0 * E + 2 * NH * b
+                              + (0.0 if pairs else NH * 4 + 16.0 * E))
     if tag == "edge_fused_bwd":      # in: z2, dst, col, d2, c; out: g_z1, and g_z2 or the W2 gradient; gathers P|Q, g_M
         # where the kernel also sums g_z1 per destination (no separate pass over g_z1 for that): out g_P as well
         w2 = w2_in_edge_kernel
@@ -43,8 +45,12 @@ def kernel_work(tag, N, E, H, dtype, dsum_in_edge_kernel=False, w2_in_edge_kerne
         if pairs:
             return 2.0 * EH * H, EH * b + 12.0 * E + 2 * NH * b + 4.0 * H * H
         return 2.0 * EH * H, 2 * EH * b + 4.0 * H * H
-    if tag == "seg_fwd":             # in: z2, rvec, row_ptr; out: M, v
-        return 0.0, EH * b + 12.0 * E + 4.0 * (N + 1) + (NH + 6.0 * N) * 4
+    if tag == "seg_fwd":             # bf16 pairs: in z2, rvec, row_ptr; out M, v
+        if pairs:
+            return 0.0, EH * b + 12.0 * E + 4.0 * (N + 1) + (NH + 6.0 * N) * 4
+        # else what the edge kernel leaves: in the parts of x_e, rvec, row_ptr; out v (the rows of M over several
+        # strips are not algorithmic bytes)
+        return 0.0, 28.0 * E + 4.0 * (N + 1) + 24.0 * N
     if tag in ("segsum_dst", "segsum_src"):
         # (where the edge kernel forms the destination sums, the source-sorted launch also adds the per-unit partials
         # of the rows that cross units: not algorithmic bytes)
@@ -56,14 +62,14 @@ def kernel_work(tag, N, E, H, dtype, dsum_in_edge_kernel=False, w2_in_edge_kerne
     if tag == "colsum":
         return 0.0, NH * 4
     # widths other than 64 / 128 / 256 (fragment-GEMM path, bf16): per-edge products run as plain GEMMs over materialised tensors
-    if tag == "frag_gemm_edge":      # in: a1 (or g_z2) + W2; out: z2 (or g_a1)
+    if tag == "frag_gemm_edge":      # in: a1 (or g_z2) + W2; out: z2 (or g_z1)
         return 2.0 * EH * H, 2 * EH * b + 2.0 * H * H
     if tag == "frag_wgrad_edge":     # in: a1, g_z2; out: H x H. The class has two launches per product (the split
         # product and the ordered sum of its partials): the product's work is spread over both
         return EH * H, (2 * EH * b + 4.0 * H * H) / 2.0
-    if tag == "edge_elementwise":    # three kernels per layer: a1 (out 2 copies), g_z2 (in z2, out 2 copies), g_z1 (in g_a1,
-        # out 1 copy) = 7 edge tensors, 36 B of per-edge scalars and 5 gathered atom tensors over 3 launches
-        return 0.0, (7 * EH * b + 36.0 * E + 5 * NH * b) / 3.0
+    if tag == "edge_elementwise":    # two kernels per layer: a1 (out), g_z2 (in z2, out) = 3 edge tensors, 24 B of per-edge
+        # scalars and 3 gathered atom tensors over 2 launches
+        return 0.0, (3 * EH * b + 24.0 * E + 3 * NH * b) / 2.0
     if tag.startswith("neigh"):      # whole graph build: in pos; out col, shift, d2, rvec, dst, permT, offsets
         return 0.0, 12.0 * N + 31.0 * E + 12.0 * N
     return 0.0, 0.0
