@@ -157,10 +157,12 @@ int32_t hgnn_embed_bwd_static(void* stream, int32_t N, int32_t H, const int32_t*
  * atom-level launches leave compute units idle, not used by the fused kernels, which fill the chip by themselves).
  * The environment variable HGNN_SIDE_STREAM = 0 / 1, read before the first call, sets the same. Returns the previous
  * setting (-1 / 0 / 1). The results do not depend on it bit for bit.
- * _bwd needs dst sorted ascending and consistent with row_ptr (a destination-sorted CSR, as hgnn_radius_graph_fill
- * writes it): at H = 64, 128 and 256 (there with bf16 operands) the reverse edge kernel sums the
- * gradients of an atom's incoming edges as runs of consecutive edges with equal dst. The environment variable
- * HGNN_DSUM_IN_KERNEL = 0, read at every call, makes those sums a pass of its own over the edge tensor again (for
+ * _fwd and _bwd take a destination-sorted CSR, as hgnn_radius_graph_fill writes it: dst[e] = i for row_ptr[i] <= e <
+ * row_ptr[i+1], because the edge kernels form sums per atom over runs of consecutive edges with equal dst. The edge arrays may
+ * be longer than the rows (row_ptr[0] > 0, row_ptr[N] < E): _fwd leaves the edges of no row out of every sum, whatever
+ * atoms 0 <= dst, col < N they name. _bwd needs every edge in a row (E = row_ptr[N], row_ptr[0] = 0): its weight gradients
+ * take all E edges. The environment variable HGNN_DSUM_IN_KERNEL = 0, read at every call, makes the sums of the gradients
+ * of an atom's incoming edges a pass of its own over the edge tensor again (H = 64, 128 and, with bf16 operands, 256; for
  * comparing the two forms; the results then differ in the last places, both orders of addition are fixed).
  * The library keeps per-process state without locks: call it from one host thread at a time.
  * ------------------------------------------------------------------------------------------- */

@@ -50,9 +50,11 @@ struct EdgeFwdArgs {
   const float* b2;     // [H]
   void* a1_pk;         // out: silu(z1), operand-packed (bf16 or fp32); null: not stored
   void* z2_vm;         // out: z2, v-major (bf16 or fp32); null: not stored (where edge_fwd_sums())
-  // Where edge_fwd_sums(): M[i,:] = alpha sum over the edges of destination row i, where the row lies inside one wavefront's strip of a
-  // tile; the others leave one partial per strip in mpart ([strips][2][H]: slot 1 = the strip in which the row starts, slot 0 = every
+  // Where edge_fwd_sums(): M[i,:] = alpha sum over the edges of destination row i (edges outside row_ptr[0] .. row_ptr[N] belong to no
+  // row and to no sum, whatever dst they carry), where the row lies inside one wavefront's strip of a tile; the others leave one partial per strip in mpart ([strips][2][H]: slot 1 = the strip in which the row starts, slot 0 = every
   // later one). And x_e = wx . m_e in parts, one per column wavefront. SegRows (gemm.h) is what is left to do.
+  const int32_t* row_ptr;   // [N+1]
+  int N;
   const float* wx;     // [H]
   float alpha;
   float* M;            // out [N,H]

@@ -532,11 +532,11 @@ __device__ __forceinline__ void fwd_issue_group(const void* PQ, const int* s, in
 // what to store for the next tile, bW1a: this lane's attribute weights as matrix-core operands).
 // MODE: FWD_Z2 stores z2 alone, FWD_BOTH also forms the sums of m = silu(z2) (see edge_fwd_sums()), FWD_SUMS does not store z2.
 // The sums are taken in the accumulator mapping, without LDS or a barrier: a lane half adds its own rows of a run, the halves are added
-// where a run ends.
+// where a run ends. E0 .. E1: the edges of the rows; the others count as runs of atom -1, which no sum is written for.
 enum { FWD_Z2 = 0, FWD_BOTH = 1, FWD_SUMS = 2 };
 template <int H, bool BF16, bool BRES, bool FULL, bool ATTR, int MODE>
 __device__ __forceinline__ void edge_fwd_tile(
-    const EdgeFwdArgs& p, unsigned char* smem, const int* s, int* s_next, int nxt, int tile, int E, int tid, int wr,
+    const EdgeFwdArgs& p, unsigned char* smem, const int* s, int* s_next, int nxt, int tile, int E, int E0, int E1, int tid, int wr,
     int wc, int lane, const float (&w1d)[ECfg<H, BF16>::CB], const float (&b2)[ECfg<H, BF16>::CB],
     const typename BFrag<H, BF16>::type (&breg)[BRES ? BFrag<H, BF16>::NKB : 1][ECfg<H, BF16>::CB],
     unsigned (&wp0)[8], unsigned (&wq0)[8], float (&dd0)[8], const unsigned short* at, unsigned short* at_next,
@@ -550,8 +550,9 @@ __device__ __forceinline__ void edge_fwd_tile(
   int dprev = -1, dnext = -1;
   if constexpr (MODE != FWD_Z2) {
     const int R0 = tile * C::TM + wr * C::RB * 32;
-    if (R0 > 0 && (FULL || R0 < E)) dprev = p.dst[R0 - 1];
-    if (R0 + C::RB * 32 < E) dnext = p.dst[R0 + C::RB * 32];
+    const int R1 = R0 + C::RB * 32;
+    if (R0 > E0 && R0 <= E1) dprev = p.dst[R0 - 1];
+    if (R1 >= E0 && R1 < E1) dnext = p.dst[R1];
   }
   // attribute term of z1 for all of this wavefront's blocks (the accumulator registers are free in this phase)
   f32x16_t zat[ATTR ? C::RB : 1][C::CB];
@@ -682,23 +683,27 @@ __device__ __forceinline__ void edge_fwd_tile(
   // edge over its columns
   constexpr int S = C::RB * 32;                       // rows of a strip
   const int sh = wr * S, R0 = tile * C::TM + sh;      // its first row in the tile, and of all
-  const int dl = s[lane], dq = s[lane ? lane - 1 : 0];
+  const int rl = tile * C::TM + lane;                 // this lane's row, the atom of its edge and of the edge before it
+  const int dl = rl >= E0 && rl < E1 ? s[lane] : -1, dq = rl > E0 && rl <= E1 ? s[lane ? lane - 1 : 0] : -1;
   unsigned long long starts = __ballot(lane && dl != dq);   // bit r: row r of the tile begins a run
-  const int nrow = FULL ? S : (E - R0 < S ? (E - R0 > 0 ? E - R0 : 0) : S);
   if constexpr (S < 64) starts = (starts >> sh) & ((1ull << S) - 1ull) & ~1ull;
-  if (!FULL && nrow < 64) starts &= (1ull << nrow) - 1ull;
-  const bool before = dprev == __builtin_amdgcn_readlane(dl, sh), behind = dnext == __builtin_amdgcn_readlane(dl, sh + S - 1);
+  const bool before = dprev == __builtin_amdgcn_readlane(dl, sh);
+  // (a last block without edges is skipped below: the run at hand at the end is then one before it)
+  const bool behind = dnext >= 0 && dnext == __builtin_amdgcn_readlane(dl, sh + S - 1);
   float run[C::CB];   // the run at hand: lane half g adds its own rows
   int k0 = 0;         // its first row in the strip
 #pragma unroll
   for (int j = 0; j < C::CB; ++j) run[j] = 0.f;
   auto flush = [&](int end, bool last) {
     const bool sf = k0 != 0 || !before, ef = !last || !behind;   // the atom's edges begin and end in the strip
-    float* o = sf && ef ? p.M + (size_t)__builtin_amdgcn_readlane(dl, sh + k0) * H : p.mpart + ((size_t)(R0 / S) * 2 + (sf ? 1 : 0)) * H;
-    const u32x2_t_ w = __builtin_amdgcn_permlane32_swap(__float_as_uint(run[0]), __float_as_uint(run[C::CB - 1]), false, false);
-    const float t = (__uint_as_float(w[0]) + __uint_as_float(w[1])) * (sf && ef ? p.alpha : 1.f);
-    if constexpr (C::CB == 2) o[wc * 64 + lane] = t;
-    else if (g == 0) o[wc * 32 + x] = t;
+    const int atom = __builtin_amdgcn_readlane(dl, sh + k0);
+    if (atom >= 0) {
+      float* o = sf && ef ? p.M + (size_t)atom * H : p.mpart + ((size_t)(R0 / S) * 2 + (sf ? 1 : 0)) * H;
+      const u32x2_t_ w = __builtin_amdgcn_permlane32_swap(__float_as_uint(run[0]), __float_as_uint(run[C::CB - 1]), false, false);
+      const float t = (__uint_as_float(w[0]) + __uint_as_float(w[1])) * (sf && ef ? p.alpha : 1.f);
+      if constexpr (C::CB == 2) o[wc * 64 + lane] = t;
+      else if (g == 0) o[wc * 32 + x] = t;
+    }
     k0 = end;
 #pragma unroll
     for (int j = 0; j < C::CB; ++j) run[j] = 0.f;
@@ -754,7 +759,6 @@ __device__ __forceinline__ void edge_fwd_tile(
 #pragma unroll
         for (int j = 0; j < C::CB; ++j) {
           m[j][u] = silu_f(m[j][u]);
-          if (!FULL && 32 * i + 8 * q + 4 * g + u >= nrow) m[j][u] = 0.f;
           xs[u] = j == 0 ? wx[0] * m[0][u] : fmaf(wx[j], m[j][u], xs[u]);
         }
       }
@@ -802,7 +806,7 @@ __device__ __forceinline__ void edge_fwd_tile(
       y[0] = (b1 ? y[1] : y[0]) + dpp_f<0x1b>(b1 ? y[0] : y[1]);                                          // lane ^ 3
       y[0] += dpp_f<0xb1>(y[0]);                                                                          // lane ^ 1
       const int row = 32 * i + 16 * ((x >> 3) & 1) + 8 * (x >> 4) + 4 * g + ((x >> 1) & 3);   // v = 8 (bit 3) + 4 (bit 4) + bits 2, 1
-      if (!(x & 1) && (FULL || row < nrow)) p.xe_part[(size_t)wc * p.xe_stride + R0 + row] = y[0];
+      if (!(x & 1) && (FULL || R0 + row < E)) p.xe_part[(size_t)wc * p.xe_stride + R0 + row] = y[0];
     }
     // the next tile's scalars are in LDS now: its first gathers travel behind the first block's stores, whose
     // accumulators are free by then (past the last tile the scalars are zeros and the gathers read row 0)
@@ -810,7 +814,7 @@ __device__ __forceinline__ void edge_fwd_tile(
       if (i == 0) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
     }
   }
-  if (FULL || nrow > 0) flush(S, true);
+  flush(S, true);
   if constexpr (C::WORD && !FULL) fwd_issue_group<H, BF16>(p.PQ, s_next, wr, 0, g, colb, wp0, wq0, dd0);
 }
 
@@ -828,6 +832,12 @@ __global__ void __launch_bounds__(256, H <= 128 ? 3 : 2) k_edge_fwd(EdgeFwdArgs 
   const int wr = wave / C::WC, wc = wave % C::WC;
   const int x = lane & 31;
   const int E = (int)p.E;
+  int E0 = 0, E1 = E;
+  if constexpr (MODE != FWD_Z2) {
+    E0 = __builtin_amdgcn_readfirstlane(p.row_ptr[0]);
+    E1 = __builtin_amdgcn_readfirstlane(p.row_ptr[p.N]);
+    E1 = E1 < E ? E1 : E;
+  }
   float w1d[C::CB], b2[C::CB], wx[C::CB];
   bf16x8_t bW1a[C::CB];
 #pragma unroll
@@ -862,10 +872,10 @@ __global__ void __launch_bounds__(256, H <= 128 ? 3 : 2) k_edge_fwd(EdgeFwdArgs 
     const unsigned short* at = atb + buf * ATTR_TILE;
     unsigned short* at_next = atb + (buf ^ 1) * ATTR_TILE;
     if ((tile + 1) * C::TM <= E)
-      edge_fwd_tile<H, BF16, BRES, true, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
+      edge_fwd_tile<H, BF16, BRES, true, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, E0, E1, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
                                                dd0, at, at_next, nxa, bW1a, wx);
     else
-      edge_fwd_tile<H, BF16, BRES, false, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
+      edge_fwd_tile<H, BF16, BRES, false, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, E0, E1, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
                                                 dd0, at, at_next, nxa, bW1a, wx);
   }
 }

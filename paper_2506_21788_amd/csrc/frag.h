@@ -57,7 +57,10 @@ struct FGemmArgs {
   //   atoms that lie inside one strip:  seg_M[atom][col] = seg_alpha * sum
   //   atoms that reach past the strip's end / begin before it:  seg_last / seg_first [strip][col] = sum (unscaled)
   // and x_e = wx . m_e per edge and column tile:  seg_xe[tile * seg_xe_stride + edge]
+  // (edges outside seg_row_ptr[0] .. seg_row_ptr[seg_N] belong to no atom and to no sum per atom, whatever dst they carry)
   const int32_t* seg_dst = nullptr;
+  const int32_t* seg_row_ptr = nullptr;
+  int seg_N = 0;            // atoms
   const float* seg_wx = nullptr;
   int seg_H = 0;            // valid columns of wx (z1_w1d)
   long seg_E = 0;           // valid rows

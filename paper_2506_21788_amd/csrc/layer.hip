@@ -242,7 +242,7 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     if (!bf16) e.W2p = w.packed_x3;
     e.b2 = W + o.b2;
     e.a1_pk = s.a1_pk; e.z2_vm = keep_z2 || !sums ? s.z2_vm : nullptr;
-    e.wx = W + o.wx; e.alpha = alpha; e.M = s.M;
+    e.row_ptr = row_ptr; e.N = N; e.wx = W + o.wx; e.alpha = alpha; e.M = s.M;
     e.xe_stride = (E + 3) / 4 * 4;   // (scratch: the reverse pass's g_z1, at least 128 bytes per edge of whole 32-edge blocks)
     e.xe_part = static_cast<float*>(w.gz1_vm);
     e.mpart = e.xe_part + 4 * e.xe_stride;

@@ -420,20 +420,21 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
   const int i0 = ti * TI, j0 = tj * TJ;
   const int nch = p.nkb / KC;
   auto kclamp = [&](int ch) { return (long)(ch < nch ? ch : nch - 1) * KC; };
-  // The tile's edges for the epilogues: the destinations (edst[1 + r]: row r of the tile, with a neighbour on either side; -1 past the
-  // edges), which say where an atom's run begins and ends, and what AD_GZ1 gathers by. Read where they are used, from memory, they
+  // The tile's edges for the epilogues: the destinations (edst[1 + r]: row r of the tile, with a neighbour on either side; negative
+  // where the edge belongs to no atom: -1 - dst, and -1 past the edges), which say where an atom's run begins and ends, and what AD_GZ1 gathers by. Read where they are used, from memory, they
   // put two memory latencies in a row into every batch of rows and two more into every run (254,000 edges of 866 columns: AD_GZ1
   // 658 -> 487 us, AD_SEG 418 -> 408).
   __shared__ int edst[MODE == AD_T ? 1 : 258];
   __shared__ int ecol[MODE == AD_GZ1 ? 256 : 1];
   __shared__ float eattr[MODE == AD_GZ1 ? 256 : 1];
   if constexpr (MODE != AD_T) {
-    const long row = (long)ti * 256 + tid;
-    edst[1 + tid] = row < p.seg_E ? p.seg_dst[row] : -1;
-    if (tid < 2) {
-      const long r2 = (long)ti * 256 + (tid ? 256 : -1);
-      edst[tid ? 257 : 0] = r2 >= 0 && r2 < p.seg_E ? p.seg_dst[r2] : -1;
-    }
+    const long row = (long)ti * 256 + tid, e0 = p.seg_row_ptr[0], e1 = p.seg_row_ptr[p.seg_N];
+    auto atom_of = [&](long r) {
+      const int d = r >= 0 && r < p.seg_E ? p.seg_dst[r] : 0;
+      return r >= e0 && r < e1 && r < p.seg_E ? d : -1 - d;
+    };
+    edst[1 + tid] = atom_of(row);
+    if (tid < 2) edst[tid ? 257 : 0] = atom_of((long)ti * 256 + (tid ? 256 : -1));
     if constexpr (MODE == AD_GZ1) {
       ecol[tid] = row < p.seg_E ? p.z1_col[row] : 0;
       eattr[tid] = row < p.seg_E ? p.z1_attr[row] : 0.f;
@@ -542,18 +543,20 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
     auto issue = [&](int b, unsigned (&go)[NB], unsigned (&qo)[NB], float (&so)[NB], int (&dio)[NB]) {
       const int r0 = wave * 64 + b * NB;
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {   // (rows past the last edge gather row 0)
+      for (int u = 0; u < NB; ++u) {   // (rows past the last edge gather row 0; edges of no atom still have a g_z1)
         dio[u] = __builtin_amdgcn_readfirstlane(edst[1 + r0 + u]);
         const long ci = __builtin_amdgcn_readfirstlane(ecol[r0 + u]);
         so[u] = eattr[r0 + u];
-        go[u] = *reinterpret_cast<const unsigned*>(p.z1_PQ + (long)(dio[u] < 0 ? 0 : dio[u]) * 2 * Hp + c);
+        go[u] = *reinterpret_cast<const unsigned*>(p.z1_PQ + (long)(dio[u] < 0 ? -1 - dio[u] : dio[u]) * 2 * Hp + c);
         qo[u] = *reinterpret_cast<const unsigned*>(p.z1_PQ + ci * 2 * Hp + Hp + c);
       }
     };
     // does the strip's first row belong to an atom that began before it, and its last one to an atom that goes on behind it
     const int s0 = wave * 64;
-    const bool before = __builtin_amdgcn_readfirstlane(edst[s0]) == __builtin_amdgcn_readfirstlane(edst[s0 + 1]);
-    const int tail = __builtin_amdgcn_readfirstlane(edst[s0 + 64]);   // -1: the strip ends with the edges
+    const int nrow = p.seg_E - R0 < 64 ? (int)(p.seg_E - R0) : 64;   // (may be negative)
+    const int head = __builtin_amdgcn_readfirstlane(edst[s0 + 1]);
+    const bool before = head >= 0 && head == __builtin_amdgcn_readfirstlane(edst[s0]);
+    const int tail = __builtin_amdgcn_readfirstlane(edst[s0 + 64]);   // negative: the strip ends with edges of no atom, or with the edges
     const bool behind = tail >= 0 && tail == __builtin_amdgcn_readfirstlane(edst[s0 + 65]);
     bool first = true;   // the run at hand is the strip's first one
     auto flush = [&](bool last) {
@@ -585,7 +588,7 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         const unsigned xw = *reinterpret_cast<const unsigned*>(&zt[((b * NB + u) & 31) * PITCH + 2 * lane]);
-        const bool ok = di[sl][u] >= 0;   // uniform
+        const bool ok = b * NB + u < nrow;   // uniform
         const float z0 = fmaf(sc[sl][u], w0, bf_lo(ga[sl][u]) + bf_lo(gb[sl][u])), z1 = fmaf(sc[sl][u], w1, bf_hi(ga[sl][u]) + bf_hi(gb[sl][u]));
         const float g0 = ok ? bf_lo(xw) * dsilu_f(z0) : 0.f, g1 = ok ? bf_hi(xw) * dsilu_f(z1) : 0.f;
         s00 += g0; s01 += g1;
@@ -687,25 +690,27 @@ __global__ void __launch_bounds__(256, 2) k_fgemm_ad(FGemmArgs p) {
     if (R0 < p.seg_E) {
       const int s0 = wave * 64;
       const int mine = edst[1 + s0 + lane];
-      const int nrow = p.seg_E - R0 < 64 ? (int)(p.seg_E - R0) : 64;
       const bool before = __builtin_amdgcn_readfirstlane(edst[s0] == mine);                    // (lane 0: the strip's first row)
-      const bool behind = nrow == 64 && __builtin_amdgcn_readfirstlane(edst[s0 + 65]) == __builtin_amdgcn_readlane(mine, 63);
+      const bool behind = __builtin_amdgcn_readfirstlane(edst[s0 + 65]) == __builtin_amdgcn_readlane(mine, 63);
       unsigned long long starts = __ballot(lane != 0 && mine != edst[s0 + lane]);   // bit r: row r of the strip begins a run
-      if (nrow < 64) starts &= (1ull << nrow) - 1ull;
       float t[WJ];
       int k0 = 0;   // first row of the run at hand
 #pragma unroll
       for (int j = 0; j < WJ; ++j) t[j] = 0.f;
       auto flush = [&](int end, bool last) {
         const bool sf = k0 != 0 || !before, ef = !last || !behind;   // the atom's edges begin and end in the strip
-        float* dest = sf && ef ? p.seg_M + (long)__builtin_amdgcn_readlane(mine, k0) * p.seg_ldm : (sf ? p.seg_last : p.seg_first) + (R0 >> 6) * p.seg_ldp;
-        const float scale = sf && ef ? p.seg_alpha : 1.f;
+        const int atom = __builtin_amdgcn_readlane(mine, k0);
+        if (atom >= 0) {
+          float* dest = sf && ef ? p.seg_M + (long)atom * p.seg_ldm : (sf ? p.seg_last : p.seg_first) + (R0 >> 6) * p.seg_ldp;
+          const float scale = sf && ef ? p.seg_alpha : 1.f;
 #pragma unroll
-        for (int j = 0; j < WJ; j += 2) {   // the halves added; 64 columns in a row
-          const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[j]), __float_as_uint(t[j + 1]), false, false);
-          dest[(j0 + wj * WJ + j) * 32 + lane] = scale * (__uint_as_float(w[0]) + __uint_as_float(w[1]));
-          t[j] = t[j + 1] = 0.f;
+          for (int j = 0; j < WJ; j += 2) {   // the halves added; 64 columns in a row
+            const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[j]), __float_as_uint(t[j + 1]), false, false);
+            dest[(j0 + wj * WJ + j) * 32 + lane] = scale * (__uint_as_float(w[0]) + __uint_as_float(w[1]));
+          }
         }
+#pragma unroll
+        for (int j = 0; j < WJ; ++j) t[j] = 0.f;
         k0 = end;
       };
 #pragma unroll
@@ -790,12 +795,12 @@ static int32_t launch_fgemm_ad(hipStream_t st, const FGemmArgs& a) {
   HGNN_REQUIRE(gx <= 2147483647L, HGNN_ERR_OVERFLOW, "fragment GEMM: grid too large");
   ProfScope ps(a.tag, st);
   if (a.z1_out) {
-    HGNN_REQUIRE(a.seg_dst && a.seg_M && a.seg_first && a.seg_last && a.z1_col && a.z1_attr && a.z1_PQ && a.z1_w1d &&
+    HGNN_REQUIRE(a.seg_dst && a.seg_row_ptr && a.seg_M && a.seg_first && a.seg_last && a.z1_col && a.z1_attr && a.z1_PQ && a.z1_w1d &&
                      a.z1_colpart && a.seg_E > 0 && a.seg_E <= (long)a.nI * 32 && a.seg_ldm % 2 == 0 && a.seg_ldp % 2 == 0,
                  HGNN_ERR_NULLPTR, "fragment GEMM: incomplete arguments of the g_z1 epilogue");
     k_fgemm_ad<AD_GZ1><<<dim3((unsigned)gx), 256, 0, st>>>(a);
   } else if (a.seg_dst) {
-    HGNN_REQUIRE(a.seg_wx && a.seg_M && a.seg_first && a.seg_last && a.seg_xe && a.seg_E <= (long)a.nI * 32,
+    HGNN_REQUIRE(a.seg_row_ptr && a.seg_wx && a.seg_M && a.seg_first && a.seg_last && a.seg_xe && a.seg_E <= (long)a.nI * 32,
                  HGNN_ERR_NULLPTR, "fragment GEMM: incomplete per-atom sum arguments");
     k_fgemm_ad<AD_SEG><<<dim3((unsigned)gx), 256, 0, st>>>(a);
   } else {
@@ -1673,7 +1678,7 @@ int32_t wide_layer_fwd(hipStream_t st, const WideLayerArgs& a) {
     g.T = s.z2_T; g.t_ncb = d.ncb;
     g.bias = W + o.b2; g.nbias = H;
     // with the per-atom sums of m = silu(z2) and x_e = wx . m_e formed in the epilogue
-    g.seg_dst = a.dst; g.seg_wx = W + o.wx; g.seg_H = H; g.seg_E = d.E; g.seg_alpha = a.alpha;
+    g.seg_dst = a.dst; g.seg_row_ptr = a.row_ptr; g.seg_N = d.N; g.seg_wx = W + o.wx; g.seg_H = H; g.seg_E = d.E; g.seg_alpha = a.alpha;
     g.seg_M = s.M; g.seg_ldm = Hp; g.seg_first = w.seg_first; g.seg_last = w.seg_last; g.seg_ldp = Hp;
     g.seg_xe = w.xe_part; g.seg_xe_stride = d.Ep;
     HGNN_TRY(launch_fgemm_rows_T(st, g));
@@ -1806,7 +1811,7 @@ int32_t wide_layer_bwd(hipStream_t st, const WideLayerArgs& a) {
   if (d.Ep > 0) {  // g_a1 = g_z2 W2^T (T fragments)
     FGemmArgs g = nn_args(w.gz2_R, d.nkb, (int)(d.Ep / 32), w.packed + 3 * PP, d.ncb, PT_FRAG_GEMM_EDGE);
     if (fused) {
-      g.seg_dst = a.dst; g.seg_H = H; g.seg_E = d.E;
+      g.seg_dst = a.dst; g.seg_row_ptr = a.row_ptr; g.seg_N = d.N; g.seg_H = H; g.seg_E = d.E;
       g.seg_M = w.g_PQ; g.seg_ldm = 2 * Hp; g.seg_first = w.seg_first; g.seg_last = w.seg_last; g.seg_ldp = Hp;
       g.z1_col = a.col; g.z1_attr = e.attr; g.z1_PQ = s.PQ; g.z1_w1d = e.w1d; g.z1_out = e.gz1_rm; g.z1_colpart = w.colpart2;
     } else {

@@ -394,3 +394,73 @@ def _run_layer_attr(N, E, H, k, seed, rc=5.0):
                                      (300, 8193, 128, 13), (90, 1000, 64, 16), (40, 63, 128, 7), (500, 20000, 256, 3)])
 def test_layer_with_edge_attributes(N, E, H, k):
     _run_layer_attr(N=N, E=E, H=H, k=k, seed=H + E + k)
+
+
+# ------------------------------------------------------------------------------------------------
+# rows inside longer edge arrays
+# ------------------------------------------------------------------------------------------------
+def _rows_problem(seed, H, k, lengths, lead=0, tail=0, pad_dst=0):
+    """Atoms of the given row lengths; `lead` and `tail` edges in front of row_ptr[0] and behind row_ptr[N], which belong to no row.
+    Device arrays (dict) and the oracle's arguments for the edges of the rows."""
+    import torch
+    rng = np.random.default_rng(seed)
+    N, E = len(lengths), sum(lengths)
+    row_ptr, dst, col, d2, rvec = _edges(rng, N, lead + E + tail)
+    dst = np.concatenate([np.full(lead, pad_dst), np.repeat(np.arange(N), lengths), np.full(tail, pad_dst)]).astype(np.int32)
+    row_ptr = (lead + np.concatenate([[0], np.cumsum(lengths)])).astype(np.int32)
+    d2 = np.minimum(d2, np.float32(25.0))
+    attr = oracle.edge_rbf(d2, k, 5.0).astype(np.float32) if k > 1 else d2[:, None].copy()
+    colT_ptr, permT = oracle.transpose_plan(col[lead:lead + E], N)
+    a = dict(row_ptr=row_ptr, dst=dst, col=col, attr=attr, rvec=rvec, colT=colT_ptr.astype(np.int32), permT=(permT + lead).astype(np.int32),
+             h=rng.standard_normal((N, H)).astype(np.float32), v=(rng.standard_normal((N, 3)) * 0.3).astype(np.float32),
+             W=init_layer_weights(rng, H, k=k).astype(np.float32), gh=rng.standard_normal((N, H)).astype(np.float32),
+             gv=rng.standard_normal((N, 3)).astype(np.float32))
+    return {n: torch.as_tensor(np.ascontiguousarray(x)).cuda() for n, x in a.items()}, a, slice(lead, lead + E)
+
+
+def _rows_call(t, H, k, dtype, keep=True, backward=False, alpha=0.25):
+    """h', v' (g_h, g_v) of the attribute entry points, or of the plain ones (k = 0); outputs and scratch start as NaN."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+    N, E, dt = t["h"].shape[0], t["dst"].numel(), {"f32": B.F32, "bf16": B.BF16}[dtype]
+    bytes_ = B.mp_layer_attr_workspace_bytes(N, E, H, k, dt) if k else B.mp_layer_workspace_bytes(N, E, H, dt)
+    ws, saved = (torch.full((n,), 0xff, dtype=torch.uint8, device="cuda") for n in (bytes_[0] + (0 if keep else bytes_[1] + 512 + 24 * N), bytes_[1]))
+    attr = t["attr"] if k else t["attr"][:, 0].contiguous()
+    out = [torch.full_like(t[n], float("nan")) for n in ("h", "v", "h", "v")]
+    graph = (t["row_ptr"], t["dst"], t["col"], attr, t["rvec"])
+    args = (N, E, H, k, dt, alpha) if k else (N, E, H, dt, alpha)
+    (B.mp_layer_attr_fwd if k else B.mp_layer_fwd)(*args, *graph, t["h"], t["v"], t["W"], out[0], out[1], saved if keep else None, ws)
+    if backward:
+        (B.mp_layer_attr_bwd if k else B.mp_layer_bwd)(*args, *graph, t["colT"], t["permT"], t["h"], t["W"], saved, t["gh"], t["gv"],
+                                                       out[2], out[3], torch.empty_like(t["W"]), ws)
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in (out if backward else out[:2])]
+
+
+# Edge arrays longer than the rows (so that one recorded graph serves several batches, or a slice of a batch): the forward pass
+# leaves out the edges in front of row_ptr[0] and behind row_ptr[N], whatever atom they name. Last rows that end inside a group of
+# eight, at a strip's and at a tile's edge; no edge of any row.
+@pytest.mark.parametrize("H,dtype,k", [(64, "f32", 0), (64, "bf16", 0), (128, "f32", 0), (128, "bf16", 0), (256, "f32", 0), (256, "bf16", 0),
+                                       (64, "bf16", 3), (128, "bf16", 16), (256, "bf16", 4), (300, "bf16", 0), (130, "bf16", 2)])
+@pytest.mark.parametrize("lengths", [[5, 0, 40, 16], [30, 34, 0, 64, 128], [0, 0, 0]])
+def test_layer_forward_leaves_out_edges_of_no_row(H, dtype, k, lengths):
+    for lead, tail, pad_dst in [(0, 3, 0), (0, 200, 0), (0, 200, len(lengths) - 1), (9, 70, 1), (64, 0, 0)]:
+        t, a, rows = _rows_problem(H + tail, H, max(k, 1), lengths, lead, tail, pad_dst)
+        ho, vo, _ = oracle.mp_layer_fwd(a["h"], a["v"], a["dst"][rows], a["col"][rows], a["attr"][rows, 0], a["rvec"][rows],
+                                        a["W"].astype(np.float64), 0.25, attr=a["attr"][rows])
+        for keep in (True, False) if H in (64, 128, 256) else (True,):
+            got = _rows_call(t, H, k, dtype, keep=keep)
+            for x, want in zip(got, (ho, vo)):
+                assert relerr(x, want) <= TOL[dtype]["fwd"], (lead, tail, pad_dst, keep)
+
+
+# At other widths the reverse pass's sums per atom go by the rows as well (the weight gradients take every edge)
+@pytest.mark.parametrize("H", [300, 130])
+@pytest.mark.parametrize("lead,tail,pad_dst", [(0, 3, 0), (0, 200, 4), (9, 70, 1), (64, 0, 0)])
+def test_layer_wide_reverse_sums_go_by_the_rows(H, lead, tail, pad_dst):
+    t, a, rows = _rows_problem(H + tail, H, 1, [30, 34, 0, 64, 130], lead, tail, pad_dst)
+    _, _, cache = oracle.mp_layer_fwd(a["h"], a["v"], a["dst"][rows], a["col"][rows], a["attr"][rows, 0], a["rvec"][rows],
+                                      a["W"].astype(np.float64), 0.25)
+    g_h, g_v, _ = oracle.mp_layer_bwd(cache, a["gh"], a["gv"])
+    got = _rows_call(t, H, 0, "bf16", backward=True)
+    assert relerr(got[2], g_h) <= TOL["bf16"]["grad"] and relerr(got[3], g_v) <= TOL["bf16"]["grad"]
