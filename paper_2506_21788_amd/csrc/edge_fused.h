@@ -58,9 +58,9 @@ struct EdgeFwdArgs {
   const float* wx;     // [H]
   float alpha;
   float* M;            // out [N,H]
-  float* mpart;        // scratch: edge_fwd_mpart_floats(E, H)
-  float* xe_part;      // scratch: up to 4 x xe_stride
-  int64_t xe_stride;   // >= E
+  float* xe_part;      // scratch: EDGE_FWD_XE_PARTS x xe_stride (both: edge_fwd_scratch_floats(E, H))
+  int64_t xe_stride;   // edge_fwd_xe_stride(E)
+  float* mpart;        // scratch
   // k > 1 edge attributes in place of d2 (bf16 operands only): z1 = P[dst] + Q[col] + attr_e . W1a, the last term
   // formed on the matrix cores from a bf16 copy of the tile's attributes; null: the d2 term above
   const float* attr = nullptr;   // [E,k]
@@ -75,8 +75,12 @@ int32_t launch_seg_fwd_vm(hipStream_t st, int N, int64_t E, const int32_t* row_p
                           const float* rvec, const float* wx, float alpha, const float* v_in, float* M,
                           float* v_out, float* xe = nullptr);
 
-// (strips of 64 rows, of 32 at H = 64)
-inline size_t edge_fwd_mpart_floats(int64_t E, int H) { return (size_t)((E + 31) / 32) * 2 * H; }
+// Scratch of those sums: the column parts of x_e, then two partial rows per strip (of 64 edges, of 32 at H = 64)
+constexpr int EDGE_FWD_XE_PARTS = 4;
+inline int64_t edge_fwd_xe_stride(int64_t E) { return (E + 3) / 4 * 4; }
+inline size_t edge_fwd_scratch_floats(int64_t E, int H) {
+  return (size_t)EDGE_FWD_XE_PARTS * edge_fwd_xe_stride(E) + (size_t)((E + 31) / 32) * 2 * H;
+}
 // The rest of M and v' (the chain of products that reads M does it itself for small batches)
 struct SegRows;
 int32_t launch_seg_fwd_rows(hipStream_t st, int H, int N, const SegRows& rows);

@@ -1304,7 +1304,8 @@ struct DsumFixRow {
 template <int H>
 __global__ void __launch_bounds__(256) k_seg_fwd_rows(int N, SegRows s) {
   static_assert(SegRows::unit(H) == ECfg<H, true>::RB * 32 && SegRows::unit(H) == ECfg<H, false>::RB * 32 &&
-                    SegRows::parts(H) == ECfg<H, true>::WC && SegRows::parts(H) == ECfg<H, false>::WC,
+                    SegRows::parts(H) == ECfg<H, true>::WC && SegRows::parts(H) == ECfg<H, false>::WC &&
+                    SegRows::unit(H) >= 32 && SegRows::parts(H) <= EDGE_FWD_XE_PARTS,
                 "strips and column parts of the forward edge kernel");
   const int lane = threadIdx.x & 63;
   const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));

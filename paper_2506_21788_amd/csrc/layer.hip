@@ -87,7 +87,9 @@ static LayerWs carve_ws(void* p, int N, int64_t E, int H, bool bf16, int k = 1) 
   w.packed = c.take<char>(6 * packed_block_bytes(H, bf16));
   w.packed_x3 = bf16 ? nullptr : c.take<char>(packed_x3_bytes(H));
   w.gz2_pk = edge_bwd_forms_w2(H, k) ? nullptr : c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
-  w.gz1_vm = c.take<char>(frag_rows(E) * H * (bf16 ? 2 : 4));
+  // (the forward pass keeps the scratch of its sums here)
+  const size_t gz1 = frag_rows(E) * H * (bf16 ? 2 : 4), fwd = edge_fwd_scratch_floats(E, H) * sizeof(float);
+  w.gz1_vm = c.take<char>(gz1 > fwd ? gz1 : fwd);
   w.cvec = c.take<float>((size_t)E + 4);
   w.g_z3 = c.take<float>((size_t)N * H);
   w.g_hM = c.take<float>((size_t)N * 2 * H);
@@ -243,9 +245,9 @@ static int32_t layer_fwd_core(hipStream_t st, int32_t N, int64_t E, int32_t H, i
     e.b2 = W + o.b2;
     e.a1_pk = s.a1_pk; e.z2_vm = keep_z2 || !sums ? s.z2_vm : nullptr;
     e.row_ptr = row_ptr; e.N = N; e.wx = W + o.wx; e.alpha = alpha; e.M = s.M;
-    e.xe_stride = (E + 3) / 4 * 4;   // (scratch: the reverse pass's g_z1, at least 128 bytes per edge of whole 32-edge blocks)
-    e.xe_part = static_cast<float*>(w.gz1_vm);
-    e.mpart = e.xe_part + 4 * e.xe_stride;
+    e.xe_stride = edge_fwd_xe_stride(E);
+    e.xe_part = static_cast<float*>(w.gz1_vm);   // sized for both in carve_ws()
+    e.mpart = e.xe_part + EDGE_FWD_XE_PARTS * e.xe_stride;
     HGNN_TRY(launch_edge_fwd(st, H, bf16, e));
     float* xe = keep_xe ? s.xe : nullptr;
     rows = SegRows{row_ptr, e.mpart, s.M, e.xe_part, e.xe_stride, rvec, alpha, v_in, v_out, xe};
