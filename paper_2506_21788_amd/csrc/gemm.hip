@@ -905,9 +905,14 @@ static int32_t launch_pack_gemm_small_t(hipStream_t st, const PackArgs& pk, cons
 // Groups count as a tile each: rows are rarely whole tiles of a group, every workgroup walks the groups to find its own, and
 // the shorter the tiles, the more workgroups walk. Heads, forward, taller tiles -> 16-row tiles: 400 rows, 200 groups,
 // H = 128, 70 -> 61 us; 4,600 rows, 64 groups 38 -> 37; past the line 8,000 rows, 64 groups 40 -> 44, 500 groups 169 -> 357.
-static bool small_gemm(const GemmArgs& a, int tile_rows) {
-  return (a.M + tile_rows - 1) / tile_rows + (a.grp_ptr ? a.S : 0) <= num_cus();
+constexpr int tall_rows(int H) { return H >= 128 ? 32 : 64; }   // rows of the taller tiles
+static bool small_gemm(int H, bool bf16, const GemmArgs& a, int tile_rows) {
+  return (bf16 || H < 256) && a.M > 0 && (a.M + tile_rows - 1) / tile_rows + (a.grp_ptr ? a.S : 0) <= num_cus();
 }
+static bool small_gemm(int H, bool bf16, const GemmArgs& a) { return small_gemm(H, bf16, a, tall_rows(H)); }
+// Chains at H = 256 only while every compute unit has one 16-row tile at most: 512 threads hold two blocks of both weights each
+// (layer forward, 64- / 32-row tiles -> 16-row tiles, 4,000 atoms 44 -> 37 us, 5,000 44 -> 47, 8,000 49 -> 53).
+static bool small_chain(int H, bool bf16, const GemmArgs& a) { return small_gemm(H, bf16, a, H == 256 ? 16 : tall_rows(H)); }
 
 // workgroups of this variant that one CU holds at a time (asked once; also raises the LDS limit of the kernel)
 template <int H, bool BF16, int TM>
@@ -944,22 +949,20 @@ template <int H, bool BF16>
 static int32_t launch_gemm_t(hipStream_t st, const GemmArgs& a) {
   if (a.M <= 0) return HGNN_OK;
   if constexpr (BF16 || H < 256) {
-    if (small_gemm(a, GemmCfg<H, BF16>::WR == 1 ? 32 : 64)) return launch_gemm_small_t<H, BF16>(st, nullptr, a, 0);
+    if (small_gemm(H, BF16, a)) return launch_gemm_small_t<H, BF16>(st, nullptr, a, 0);
   }
-  if constexpr (GemmCfg<H, BF16>::WR == 1) return launch_gemm_tm<H, BF16, 32>(st, a);
-  else return launch_gemm_tm<H, BF16, 64>(st, a);
+  return launch_gemm_tm<H, BF16, tall_rows(H)>(st, a);
 }
 
 template <int H, bool BF16>
 static int32_t launch_gemm_chain_t(hipStream_t st, const GemmArgs* first, const GemmArgs& second, int keep_silu, const SegRows* rows) {
-  constexpr int TM = GemmCfg<H, BF16>::WR == 1 ? 32 : 64;
+  constexpr int TM = tall_rows(H);
   using C = GemmCfg<H, BF16, TM>;
   if (second.M <= 0) return HGNN_OK;
-  // (chains at H = 256 only while every compute unit has one 16-row tile at most, 512 threads that hold two blocks of both
-  // weights each: layer forward, 64- / 32-row tiles -> 16-row tiles, 4,000 atoms 44 -> 37 us, 5,000 44 -> 47, 8,000 49 -> 53)
   if constexpr (BF16 || H < 256) {
-    if (small_gemm(second, H == 256 ? 16 : TM)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu, rows);
+    if (small_chain(H, BF16, second)) return launch_gemm_small_t<H, BF16>(st, first, second, keep_silu, rows);
   }
+  HGNN_REQUIRE(!rows, HGNN_ERR_BAD_SHAPE, "gemm chain: the forward sums are finished by 16-row tiles only");
   constexpr size_t LDS = C::LDS_BYTES + C::A_BYTES;
   static bool raised = false;   // the kernel's LDS limit is raised once per variant
   if (!raised) {
@@ -994,20 +997,19 @@ static int32_t check_gemm_chain(int H, const GemmArgs* first, const GemmArgs& se
   }
   return HGNN_OK;
 }
-// Chains of 16-row tiles finish the forward sums of their rows themselves (the same rule as in launch_gemm_chain_t): a launch
-// fewer per layer, whose loads travel with the chain's own. Steps, launch of its own -> in the chain: one molecule, forward 131 -> 126 us,
-// 203 molecules, forward 272 -> 265, 32 small molecules 259 -> 254, 128 molecules 766 -> 762, one crystal of 60 atoms, forward 197 -> 191;
+// Chains of 16-row tiles finish the forward sums of their rows themselves: a launch fewer per layer, whose loads travel with the
+// chain's own. Steps, launch of its own -> in the chain: one molecule, forward 131 -> 126 us, 203 molecules, forward 272 -> 265, 32 small molecules 259 -> 254, 128 molecules 766 -> 762, one crystal of 60 atoms, forward 197 -> 191;
 // a crystal's conservative forces (12 tiles, rows of 57 edges) 473 -> 472.
 bool gemm_chain_takes_rows(int H, bool bf16, int M) {
   GemmArgs a;
   a.M = M;
-  return M > 0 && (bf16 || H < 256) && small_gemm(a, H == 256 ? 16 : H == 128 ? 32 : 64);
+  return small_chain(H, bf16, a);
 }
 int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* first, const GemmArgs& second, int keep_silu,
                           const SegRows* rows) {
   HGNN_TRY(check_gemm_chain(H, first, second));
-  HGNN_REQUIRE(!rows || (gemm_chain_takes_rows(H, bf16, second.M) && first && first->nkc == 2 && first->A[1] == rows->M && first->lda[1] == H),
-               HGNN_ERR_BAD_SHAPE, "gemm chain: the forward sums are finished by 16-row tiles that read them");
+  HGNN_REQUIRE(!rows || (first && first->nkc == 2 && first->A[1] == rows->M && first->lda[1] == H), HGNN_ERR_BAD_SHAPE,
+               "gemm chain: the forward sums are finished by the product that reads them");
   switch (H) {
     case 64: return bf16 ? launch_gemm_chain_t<64, true>(st, first, second, keep_silu, rows) : launch_gemm_chain_t<64, false>(st, first, second, keep_silu, rows);
     case 128: return bf16 ? launch_gemm_chain_t<128, true>(st, first, second, keep_silu, rows) : launch_gemm_chain_t<128, false>(st, first, second, keep_silu, rows);
@@ -1020,8 +1022,8 @@ int32_t launch_gemm_chain(hipStream_t st, int H, bool bf16, const GemmArgs* firs
 // bytes of packed ones with bf16 operands). Per step, two launches against one: one molecule, forward 215 -> 208 us, 32 small
 // molecules 395 -> 377, a crystal's conservative forces 605 -> 598, 16 molecules at H = 128 497 -> 482; past the line nothing changes.
 constexpr long RAW_BYTES = 16l << 20;
-static bool pack_along(int H, const PackArgs& pk, const GemmArgs* first, const GemmArgs& second) {
-  if (H > 128 || second.M <= 0 || !small_gemm(second, H >= 128 ? 32 : 64)) return false;
+static bool pack_along(int H, bool bf16, const PackArgs& pk, const GemmArgs* first, const GemmArgs& second) {
+  if (H > 128 || !small_gemm(H, bf16, second)) return false;
   if (first && first->nkc != 1) return false;
   const int nblk = (first ? 1 : 0) + second.ncb;
   if (((second.M + 15) / 16) * (long)nblk * H * H * 4 > RAW_BYTES) return false;
@@ -1039,7 +1041,7 @@ static bool pack_along(int H, const PackArgs& pk, const GemmArgs* first, const G
 }
 int32_t launch_pack_gemm_chain(hipStream_t st, int H, bool bf16, const PackArgs& pk, const GemmArgs* first,
                                const GemmArgs& second, int keep_silu) {
-  if (!pack_along(H, pk, first, second)) {
+  if (!pack_along(H, bf16, pk, first, second)) {
     HGNN_TRY(launch_pack(st, H, bf16, pk));
     return launch_gemm_chain(st, H, bf16, first, second, keep_silu);
   }
@@ -1077,8 +1079,7 @@ static int32_t launch_gemm_small_pair_t(hipStream_t st, const GemmArgs& a, const
   return HGNN_OK;
 }
 int32_t launch_gemm_pair(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs& b) {
-  const int rows = H >= 128 ? 32 : 64;
-  const bool one = (bf16 || H < 256) && a.M > 0 && b.M > 0 && a.ncb == b.ncb && small_gemm(a, rows) && small_gemm(b, rows);
+  const bool one = a.ncb == b.ncb && small_gemm(H, bf16, a) && small_gemm(H, bf16, b);
   if (!one) {
     HGNN_TRY(launch_gemm(st, H, bf16, a));
     return launch_gemm(st, H, bf16, b);
@@ -1289,9 +1290,8 @@ static int32_t launch_gemm_small_reduce_t(hipStream_t st, const GemmArgs& a, con
   return HGNN_OK;
 }
 int32_t ReduceQueueScope::flush_with(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs* b) {
-  const int rows = H >= 128 ? 32 : 64;
-  const bool one = active_ && tl_reduce_queue->q.njobs > 0 && tl_reduce_queue->st == st && (bf16 || H < 256) && a.M > 0 && a.ncb == 1 &&
-                   small_gemm(a, rows) && (!b || (b->M > 0 && b->ncb == 1 && small_gemm(*b, rows))) &&
+  const bool one = active_ && tl_reduce_queue->q.njobs > 0 && tl_reduce_queue->st == st && a.ncb == 1 && small_gemm(H, bf16, a) &&
+                   (!b || (b->ncb == 1 && small_gemm(H, bf16, *b))) &&
                    tl_reduce_queue->q.off[tl_reduce_queue->q.njobs] <= REDUCE_WITH_WGS && tl_reduce_queue->q.bytes() <= REDUCE_WITH_BYTES;
   if (!one) {
     if (b) HGNN_TRY(launch_gemm_pair(st, H, bf16, a, *b));
