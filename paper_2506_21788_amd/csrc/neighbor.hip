@@ -474,16 +474,17 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
   const int off = first_bin(lo, g);
   if (wave == 0) {
     graph_meta(lo, hi, periodic, p.cell + 9 * (size_t)g, mn, mx, p.rc, &m, p.status);
-    if (lane == 0) {
-      m.bin_off = off;
-      const float block = (float)(2 * m.R[0] + 1) * (float)(2 * m.R[1] + 1) * (float)(2 * m.R[2] + 1);   // bins around one
-      const bool few = (float)(hi - lo) * block <= HOME_FEW * (float)(m.nb[0] * m.nb[1] * m.nb[2]);
-      m.home = few || hi - lo > HOME_LARGE ? SR_HOME : p.home;
-    }
+    if (lane == 0) m.bin_off = off;
   }
-  __syncthreads();
-  if (tid == 0) p.meta[g] = m;
+  __syncthreads();   // (graph_meta() leaves a lattice direction to a lane each)
   const int nbins = m.nb[0] * m.nb[1] * m.nb[2];
+  const float block = (float)(2 * m.R[0] + 1) * (float)(2 * m.R[1] + 1) * (float)(2 * m.R[2] + 1);   // bins around one
+  const bool few = (float)(hi - lo) * block <= HOME_FEW * (float)nbins;
+  const int home = few || hi - lo > HOME_LARGE ? SR_HOME : p.home;
+  if (tid == 0) {
+    p.meta[g] = m;
+    p.meta[g].home = home;
+  }
   const bool in_lds = nbins <= BG_BINS;
   int* cnt = p.bin_cnt + off;                        // cleared by the launch before
   if (in_lds)
@@ -507,7 +508,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       const int b = b0 + tid * 4 + u;
       c[u] = b < nbins ? (in_lds ? hist[b] : __hip_atomic_load(&cnt[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
       own += c[u];
-      items += (c[u] + m.home - 1) / m.home;
+      items += (c[u] + home - 1) / home;
     }
     int ia = own, ii = items;
 #pragma unroll
@@ -533,7 +534,7 @@ __global__ void __launch_bounds__(256) k_bin_graphs(BinArgs p) {
       if (b < nbins) {
         p.bin_start[off + b] = ex;
         if (in_lds) hist[b] = ex; else cnt[b] = ex;   // from here on: the bin's next free record
-        for (int k = 0; k < c[u]; k += m.home, ++at) p.list[at] = make_int2(off + b, k);
+        for (int k = 0; k < c[u]; k += home, ++at) p.list[at] = make_int2(off + b, k);
       }
       ex += c[u];
     }
