@@ -263,21 +263,31 @@ def test_work_items_of_thin_cells_next_to_molecules(atoms):
     assert_graph_equal(gpu_graph(many, rc).to_numpy(), want)
 
 
-# The workgroup that bins a single graph also clears the counters, up to 16,384 of them (2,303 atoms); the allocations are made of dirty
-# memory
+# The workgroup that bins a single graph also clears the counters, up to 16,384 of them (2,303 atoms): every byte of the workspace is
+# dirty before each count, and what lies behind it stays as it is
 @pytest.mark.parametrize("N", [1, 187, 2303, 2304])
 def test_one_graph_clears_its_own_counters(N):
     import torch
+    from paper_2506_21788_amd import binding as B
+    print("one graph", N, flush=True)
     rng = np.random.default_rng(N)
     side = max(4.0, (N * 9.0) ** (1.0 / 3.0))
     a = np.array([[side, 0, 0], [0.3, side, 0], [0, -0.4, side]])
     one = concat_graphs([((rng.random((N, 3)) @ a).astype(np.float32), rng.integers(1, 90, N).astype(np.int32), a.astype(np.float32))])
-    dirt = torch.full((64 << 20,), 0x5a, dtype=torch.uint8, device="cuda")
-    torch.cuda.synchronize()
-    del dirt
     want = oracle.radius_graph(one.pos, one.graph_off, one.cell, one.pbc, 4.5)
-    for _ in range(2):
-        assert_graph_equal(gpu_graph(one, 4.5).to_numpy(), want)
+    inputs = (N, 1, *(torch.as_tensor(x).cuda() for x in (one.pos, one.graph_off, one.cell, one.pbc)), 4.5)
+    need, guard, E = B.radius_graph_workspace_bytes(N, 1), 1 << 16, want["E"]
+    ws = torch.empty(need + guard, dtype=torch.uint8, device="cuda")
+    tmp = torch.empty(8 * E + 16, dtype=torch.uint8, device="cuda")
+    for dirt in (0x5A, 0xFF, 0x01):
+        ws.fill_(dirt)
+        out = {k: torch.full(want[k].shape, 77, dtype={"float32": torch.float32, "int8": torch.int8}.get(str(want[k].dtype), torch.int32),
+                             device="cuda") for k in ("dst", "col", "shift", "d2", "rvec", "edge_graph_ptr", "colT_ptr", "permT")}
+        row_ptr = torch.full((N + 1,), -7, dtype=torch.int32, device="cuda")
+        assert B.radius_graph_count(*inputs, ws, row_ptr) == E
+        B.radius_graph_fill(*inputs, ws, tmp, row_ptr, E, *out.values())
+        assert_graph_equal(dict({k: v.cpu().numpy() for k, v in out.items()}, row_ptr=row_ptr.cpu().numpy(), E=E), want)
+        assert bool((ws[need:] == dirt).all())
 
 
 # atoms placed by the workgroup that places the graphs, or by a launch of their own

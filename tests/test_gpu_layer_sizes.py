@@ -343,11 +343,15 @@ def test_edge_rbf_matches_the_oracle(E, k, rc):
     assert relerr(got, want) <= TOL["f32"]["fwd"]      # float32 arithmetic against the float64 definition
 
 
-def _run_layer_attr(N, E, H, k, seed, rc=5.0):
+def _run_layer_attr(N, E, H, k, seed, rc=5.0, lengths=None):
     import torch
     from paper_2506_21788_amd import binding as B
     rng = np.random.default_rng(seed)
     row_ptr, dst, col, d2, rvec = _edges(rng, N, E)
+    if lengths is not None:   # chosen row lengths instead of random destinations
+        assert len(lengths) == N and sum(lengths) == E
+        dst = np.repeat(np.arange(N, dtype=np.int32), lengths)
+        row_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
     d2 = np.minimum(d2, np.float32(rc * rc))
     attr = oracle.edge_rbf(d2, k, rc).astype(np.float32) if k > 1 else d2[:, None].copy()
     colT_ptr, permT = oracle.transpose_plan(col, N)
@@ -397,17 +401,20 @@ def test_layer_with_edge_attributes(N, E, H, k):
 
 
 # ------------------------------------------------------------------------------------------------
-# rows inside longer edge arrays
+# rows inside longer edge arrays, and values that are no numbers
 # ------------------------------------------------------------------------------------------------
-def _rows_problem(seed, H, k, lengths, lead=0, tail=0, pad_dst=0):
+def _rows_problem(seed, H, k, lengths, lead=0, tail=0, pad_dst=0, two_sets=False):
     """Atoms of the given row lengths; `lead` and `tail` edges in front of row_ptr[0] and behind row_ptr[N], which belong to no row.
-    Device arrays (dict) and the oracle's arguments for the edges of the rows."""
+    two_sets: edges join atoms of even or of odd number only. Device arrays (dict) and the oracle's arguments for the edges of the rows."""
     import torch
     rng = np.random.default_rng(seed)
     N, E = len(lengths), sum(lengths)
     row_ptr, dst, col, d2, rvec = _edges(rng, N, lead + E + tail)
     dst = np.concatenate([np.full(lead, pad_dst), np.repeat(np.arange(N), lengths), np.full(tail, pad_dst)]).astype(np.int32)
     row_ptr = (lead + np.concatenate([[0], np.cumsum(lengths)])).astype(np.int32)
+    if two_sets:
+        assert N % 2 == 0
+        col = col // 2 * 2 + dst % 2
     d2 = np.minimum(d2, np.float32(25.0))
     attr = oracle.edge_rbf(d2, k, 5.0).astype(np.float32) if k > 1 else d2[:, None].copy()
     colT_ptr, permT = oracle.transpose_plan(col[lead:lead + E], N)
@@ -464,3 +471,36 @@ def test_layer_wide_reverse_sums_go_by_the_rows(H, lead, tail, pad_dst):
     g_h, g_v, _ = oracle.mp_layer_bwd(cache, a["gh"], a["gv"])
     got = _rows_call(t, H, 0, "bf16", backward=True)
     assert relerr(got[2], g_h) <= TOL["bf16"]["grad"] and relerr(got[3], g_v) <= TOL["bf16"]["grad"]
+
+
+# The sums of the forward edge kernel with edge attributes, an instance of its own, at the edges of its strips; at H = 256 their last
+# steps are taken by the chain of products up to 4,096 atoms, by a kernel of their own beyond
+@pytest.mark.parametrize("H,k", [(64, 4), (128, 5), (256, 16)])
+@pytest.mark.parametrize("lengths", [[0, 32, 32, 64, 1, 31, 0, 16, 8, 8, 40, 200, 0], [1, 1, 2, 3, 1, 5, 0, 19, 33, 63], [7, 57, 129]])
+def test_layer_attribute_rows_at_strip_edges(H, k, lengths):
+    _run_layer_attr(N=len(lengths), E=sum(lengths), H=H, k=k, seed=H + len(lengths), lengths=lengths)
+
+
+@pytest.mark.parametrize("N", [4081, 4097])
+def test_layer_attribute_rows_either_side_of_the_short_chains(N):
+    lengths = np.random.default_rng(N).choice([0, 1, 3, 7, 70, 130], size=N, p=[.3, .3, .2, .18, .01, .01])
+    _run_layer_attr(N=N, E=int(lengths.sum()), H=256, k=4, seed=N, lengths=lengths.tolist())
+
+
+# A value that is no number spoils the atoms that it reaches through edges and no other: every second atom has edges with every
+# second atom only, so sums over runs next to one another in one strip, one group of eight rows and one wavefront stay apart
+@pytest.mark.parametrize("H,dtype,k", [(64, "f32", 0), (64, "bf16", 0), (128, "f32", 0), (128, "bf16", 0), (256, "f32", 0), (256, "bf16", 0),
+                                       (128, "bf16", 3), (256, "bf16", 4), (300, "bf16", 0), (300, "bf16", 3)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_layer_sums_of_other_atoms_stay_apart(H, dtype, k, value):
+    lengths = [3, 2, 1, 5, 0, 4, 21, 28, 64, 1, 7, 80, 40, 2] * 3
+    t, _, _ = _rows_problem(H, H, max(k, 1), lengths, two_sets=True)
+    plain = _rows_call(t, H, k, dtype, backward=True)
+    assert all(np.isfinite(x).all() for x in plain)
+    for atom in (1, 6, 8, 25):
+        other = np.arange(len(lengths)) % 2 != atom % 2
+        bad = dict(t, h=t["h"].clone())
+        bad["h"][atom, H // 2] = value
+        for got, want in zip(_rows_call(bad, H, k, dtype, backward=True), plain):
+            assert np.array_equal(got[other].view(np.uint32), want[other].view(np.uint32)), atom
+        assert not np.isfinite(_rows_call(bad, H, k, dtype)[0][atom]).all()
