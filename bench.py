@@ -57,6 +57,12 @@ def kernel_work(tag, N, E, H, dtype, dsum_in_edge_kernel=False, w2_in_edge_kerne
         return 0.0, EH * b + 4.0 * (N + 1) + NH * 4 + (4.0 * E if tag == "segsum_src" else 0.0)
     if tag == "gemm_node":           # one H x H block product per atom row, fp32 in / out
         return 2.0 * NH * H, 2 * NH * 4
+    if tag == "gemm_node_rows":      # small batches: [h ; M] W3 and silu(z3) W4 in one launch (in: h, M; out: z3, h'), which also
+        # does what "seg_fwd" does below where that is a launch of its own
+        return 6.0 * NH * H, 4 * NH * 4 + 28.0 * E + 4.0 * (N + 1) + 24.0 * N
+    if tag == "gemm_node_reduce":    # small batches: g_P W1a^T + g_Q W1b^T (in: g_P, g_Q, g_h; out: g_h) and the reductions of a
+        # layer's weight gradients, of which only the results are algorithmic bytes (up to 80 MB of split partials are not)
+        return 4.0 * NH * H, 4 * NH * 4 + 24.0 * H * H
     if tag == "wgrad_node":
         return 2.0 * NH * H, 2 * NH * 4
     if tag == "colsum":

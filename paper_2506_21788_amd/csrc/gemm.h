@@ -179,8 +179,8 @@ struct ReduceQueueScope {
   ~ReduceQueueScope();
   int32_t flush();
   // flush() and one product, or two independent ones, that read none of the results and whose result no reduction reads;
-  // one launch for small batches
-  int32_t flush_with(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs* b = nullptr);
+  // one launch for small batches (a class of its own to the profile; else tag: that of the reductions)
+  int32_t flush_with(hipStream_t st, int H, bool bf16, int tag, const GemmArgs& a, const GemmArgs* b = nullptr);
   ReduceQueueScope(const ReduceQueueScope&) = delete;
   ReduceQueueScope& operator=(const ReduceQueueScope&) = delete;
  private:

@@ -875,7 +875,7 @@ template <int H, bool BF16>
 static int32_t launch_gemm_small_t(hipStream_t st, const GemmArgs* first, const GemmArgs& a, int keep_silu, const SegRows* rows = nullptr) {
   using C = SmallCfg<H, BF16>;
   const int tiles = (a.M + C::TM - 1) / C::TM + (a.grp_ptr ? a.S : 0);
-  ProfScope ps(a.tag, st);
+  ProfScope ps(rows ? (int)PT_GEMM_ROWS : a.tag, st);
   if (rows) k_gemm_small_rows<H, BF16><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, *rows);
   else if (first) k_gemm_small<H, BF16, true, false><<<dim3(tiles), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{*first, a}}, keep_silu, PackArgs{}, tiles);
   else k_gemm_small<H, BF16, false, false><<<dim3(tiles, a.ncb), C::THREADS, C::LDS_BYTES, st>>>(GemmJobs{{a, a}}, 0, PackArgs{}, tiles);
@@ -1283,20 +1283,20 @@ static int32_t launch_gemm_small_reduce_t(hipStream_t st, const GemmArgs& a, con
   }
   const auto tiles_of = [](const GemmArgs& g) { return (g.M + C::TM - 1) / C::TM + (g.grp_ptr ? g.S : 0); };
   const int ta = tiles_of(a), tb = b ? tiles_of(*b) : 0, tiles = ta > tb ? ta : tb, gz = b ? 2 : 1;
-  ProfScope ps(a.tag, st);
+  ProfScope ps(PT_GEMM_REDUCE, st);
   k_gemm_small_reduce<H, BF16><<<dim3((unsigned)(tiles + (q.off[q.njobs] + gz - 1) / gz), 1, gz), C::THREADS, C::LDS_BYTES, st>>>(
       GemmJobs{{a, b ? *b : a}}, q, tiles);
   HGNN_LAUNCH_CHECK("k_gemm_small_reduce");
   return HGNN_OK;
 }
-int32_t ReduceQueueScope::flush_with(hipStream_t st, int H, bool bf16, const GemmArgs& a, const GemmArgs* b) {
+int32_t ReduceQueueScope::flush_with(hipStream_t st, int H, bool bf16, int tag, const GemmArgs& a, const GemmArgs* b) {
   const bool one = active_ && tl_reduce_queue->q.njobs > 0 && tl_reduce_queue->st == st && a.ncb == 1 && small_gemm(H, bf16, a) &&
                    (!b || (b->ncb == 1 && small_gemm(H, bf16, *b))) &&
                    tl_reduce_queue->q.off[tl_reduce_queue->q.njobs] <= REDUCE_WITH_WGS && tl_reduce_queue->q.bytes() <= REDUCE_WITH_BYTES;
   if (!one) {
     if (b) HGNN_TRY(launch_gemm_pair(st, H, bf16, a, *b));
     else HGNN_TRY(launch_gemm(st, H, bf16, a));
-    ProfScope ps(PT_MISC, st);
+    ProfScope ps(tag, st);
     return flush();
   }
   HGNN_TRY(check_gemm(H, a));

@@ -1004,5 +1004,5 @@ extern "C" int32_t hgnn_multihead_decode_bwd(void* stream, int32_t N, int32_t G,
   }
   HGNN_TRY(launch_colsum_multi(st, Hh, cs, 2 * nb));
   HGNN_TRY(launch_wgrad_own_rows(st, H, bf16, wg, nb));
-  return reductions.flush_with(st, H, bf16, gx[0], nb == 2 ? &gx[1] : nullptr);
+  return reductions.flush_with(st, H, bf16, PT_COLSUM, gx[0], nb == 2 ? &gx[1] : nullptr);
 }

@@ -520,7 +520,7 @@ static int32_t mp_layer_bwd_impl(void* stream, int32_t N, int64_t E, int32_t H, 
     g.M = N;
     g.add1 = w.g_hM; g.ldadd1 = 2 * H;
     g.C = g_h_in; g.ldc = H;
-    HGNN_TRY(reductions.flush_with(st, H, bf16, g));
+    HGNN_TRY(reductions.flush_with(st, H, bf16, PT_MISC, g));
   }
   HGNN_TRY(stream_after(st, sx, ss.ev[4]));   // join: the caller's stream now also orders after every gradient
   return HGNN_OK;

@@ -33,6 +33,8 @@ enum ProfTag : int {
   PT_FRAG_WGRAD_EDGE,   // fragment path (widths other than 64 / 128 / 256): g_W2 = a1^T g_z2 (+ its partial reduction)
   PT_EDGE_ELEM,         // fragment path (widths other than 64 / 128 / 256): element-wise edge kernels (a1, g_z2, g_z1)
   PT_TO_FRAG,           // fragment path (widths other than 64 / 128 / 256): row-major -> fragment conversions of atom tensors
+  PT_GEMM_ROWS,         // small batches: the chain of products that also finishes the forward sums
+  PT_GEMM_REDUCE,       // small batches: the last product of a reverse pass and its reductions of split partials
   PT_COUNT
 };
 

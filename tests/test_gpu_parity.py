@@ -502,3 +502,28 @@ def test_step_many_sources(H, dtype, S):
     b = small_mixed_batch(21, n_mol=6, n_cry=5, S=S, mol_atoms=(3, 30), cry_atoms=(2, 20))
     P = problem_from_batch(b, 4.5, H, 1, S, dtype, seed=S)
     compare_step(P, f"many sources H={H} {dtype} S={S}")
+
+
+def test_kernel_classes_of_merged_launches():
+    """The launches of small batches that do another class's work as well are classes of their own to the profile; where they are
+    apart, the reductions of the heads count as column sums."""
+    import torch
+    from paper_2506_21788_amd import binding as B
+
+    def launches(P):
+        hot = gpu_hotpath(P)
+        gE, gF = (torch.as_tensor(P[k]).cuda() for k in ("gE", "gF"))
+        hot.step(gE, gF)
+        side = B.set_side_stream(False)
+        B.profile_begin((1 << B.profile_num_tags()) - 1)
+        hot.step(gE, gF, with_graph=False)
+        B.profile_end()
+        B.set_side_stream(side)
+        return {B.profile_tag_name(t): B.profile_read(t)[0] for t in range(B.profile_num_tags())}
+
+    n = launches(problem_from_config("cfg1"))
+    assert n["gemm_node_rows"] == 3 and n["gemm_node_reduce"] == 3 + 1 and n["seg_fwd"] == 0 and n["colsum"] == 1, n
+    rng = np.random.default_rng(3)
+    big = concat_graphs([(rng.uniform(0, 60.0, (9000, 3)).astype(np.float32), np.ones(9000, np.int32))])
+    n = launches(problem_from_batch(big, 4.0, 128, 2, 1, "bf16"))
+    assert n["gemm_node_rows"] == n["gemm_node_reduce"] == 0 and n["seg_fwd"] == 2 and n["colsum"] == 2, n
