@@ -35,8 +35,9 @@ constexpr bool edge_bwd_forms_w2(int H, int k) { return H <= 64 || (H == 128 && 
 // Where the forward edge kernel also forms the sums over m = silu(z2) (M, v') from the z2 in its accumulators, instead of a kernel
 // that reads z2 back. Whole steps, kernel of its own -> in the edge kernel: four cells of 20,000 atoms, H = 128 fp32, 22.04 -> 21.24 ms
 // (per layer 2100 + 627 us -> 2210 + 66), a crystal's conservative forces 500 -> 470 us, 19,000 atoms with 8 radial attributes at H = 128
-// 1.38 -> 1.28 ms, at H = 256 with moving atoms 2.88 -> 2.81, forward alone (z2 is not even stored then) H = 64 fp32 357 -> 320 us,
-// H = 128 fp32 600 -> 549. With bf16 operands and one attribute at H = 256 the kernel's vector units and its 256 registers are
+// 1.38 -> 1.28 ms, at H = 256 with moving atoms 2.88 -> 2.81. One layer, forward, 40,000 atoms of 30 edges, with a saved buffer / without
+// one (z2 is not even stored then): H = 64 fp32 206 -> 186 / 197 -> 161 us, H = 128 fp32 462 -> 425 / 461 -> 380, bf16 250 -> 224 / 239 -> 207,
+// H = 256 fp32 1499 -> 1431 / 1499 -> 1272. The smallest batches pay a little at H = 256 fp32 (13 atoms of 12 edges 76 -> 79 us). With bf16 operands and one attribute at H = 256 the kernel's vector units and its 256 registers are
 // full, and reading z2 back at 5.3 TB/s is the shorter: 643 mixed graphs 9.16 ms, in the edge kernel 9.43 (233 + 117 us -> 384 + 20).
 constexpr bool edge_fwd_sums(int H, bool bf16, bool attr) { return !(H == 256 && bf16 && !attr); }
 
