@@ -525,18 +525,31 @@ __device__ __forceinline__ void fwd_issue_group(const void* PQ, const int* s, in
   }
 }
 
-// One tile of the forward kernel. FULL: all TM edges of the tile exist (no masking anywhere).
+// Where the forward kernel keeps the first edge of the rows and the first one behind them: in the padding of the A tile's first row
+template <int H, bool BF16>
+__device__ __forceinline__ int2* row_bounds(unsigned char* smem) {
+  using C = ECfg<H, BF16>;
+  constexpr int ESZ = BF16 || C::PLANES ? 2 : 4;
+  static_assert((C::STRIDE - H) * ESZ >= (int)sizeof(int2) && H * ESZ % sizeof(int2) == 0, "padding behind a row");
+  return reinterpret_cast<int2*>(smem + H * ESZ);
+}
+
+// One tile of the forward kernel. FULL: all TM edges of the tile exist, and they and those next to the tile belong to rows (no masking
+// anywhere).
 // wp0 / wq0 / dd0 (one word per lane and edge only, see ECfg::WORD): the gathers of this tile's first group, asked for at the end of the previous
 // tile; on return they hold those of the next tile's first group.
 // ATTR: k > 1 edge attributes take the place of the d2 term (at: this tile's attributes in LDS, at_next / nxa: where and
 // what to store for the next tile, bW1a: this lane's attribute weights as matrix-core operands).
 // MODE: FWD_Z2 stores z2 alone, FWD_BOTH also forms the sums of m = silu(z2) (see edge_fwd_sums()), FWD_SUMS does not store z2.
 // The sums are taken in the accumulator mapping, without LDS or a barrier: a lane half adds its own rows of a run, the halves are added
-// where a run ends. E0 .. E1: the edges of the rows; the others count as runs of atom -1, which no sum is written for.
+// where a run ends. Edges of no row count as runs of atom -1, which no sum is written for; the test is only made in tiles that are not FULL.
+// The bounds of the rows' edges (row_bounds()) lie in the LDS because scalar registers are short here. No test at all -> bounds in scalar
+// registers and every tile tested -> this: 1.2 M edges with 16 attributes at H = 256 479 -> 484 -> 462 us, 3.6 M edges at H = 128 fp32
+// 972 -> 977 -> 983; forms with neither (a loop of its own for such edges, the bounds in vector registers) spill: 990-1000.
 enum { FWD_Z2 = 0, FWD_BOTH = 1, FWD_SUMS = 2 };
 template <int H, bool BF16, bool BRES, bool FULL, bool ATTR, int MODE>
 __device__ __forceinline__ void edge_fwd_tile(
-    const EdgeFwdArgs& p, unsigned char* smem, const int* s, int* s_next, int nxt, int tile, int E, int E0, int E1, int tid, int wr,
+    const EdgeFwdArgs& p, unsigned char* smem, const int* s, int* s_next, int nxt, int tile, int E, int tid, int wr,
     int wc, int lane, const float (&w1d)[ECfg<H, BF16>::CB], const float (&b2)[ECfg<H, BF16>::CB],
     const typename BFrag<H, BF16>::type (&breg)[BRES ? BFrag<H, BF16>::NKB : 1][ECfg<H, BF16>::CB],
     unsigned (&wp0)[8], unsigned (&wq0)[8], float (&dd0)[8], const unsigned short* at, unsigned short* at_next,
@@ -550,9 +563,8 @@ __device__ __forceinline__ void edge_fwd_tile(
   int dprev = -1, dnext = -1;
   if constexpr (MODE != FWD_Z2) {
     const int R0 = tile * C::TM + wr * C::RB * 32;
-    const int R1 = R0 + C::RB * 32;
-    if (R0 > E0 && R0 <= E1) dprev = p.dst[R0 - 1];
-    if (R1 >= E0 && R1 < E1) dnext = p.dst[R1];
+    if (R0 > 0 && (FULL || R0 < E)) dprev = p.dst[R0 - 1];
+    if (R0 + C::RB * 32 < E) dnext = p.dst[R0 + C::RB * 32];
   }
   // attribute term of z1 for all of this wavefront's blocks (the accumulator registers are free in this phase)
   f32x16_t zat[ATTR ? C::RB : 1][C::CB];
@@ -683,13 +695,21 @@ __device__ __forceinline__ void edge_fwd_tile(
   // edge over its columns
   constexpr int S = C::RB * 32;                       // rows of a strip
   const int sh = wr * S, R0 = tile * C::TM + sh;      // its first row in the tile, and of all
-  const int rl = tile * C::TM + lane;                 // this lane's row, the atom of its edge and of the edge before it
-  const int dl = rl >= E0 && rl < E1 ? s[lane] : -1, dq = rl > E0 && rl <= E1 ? s[lane ? lane - 1 : 0] : -1;
+  int dl = s[lane], dq = s[lane ? lane - 1 : 0];      // the atom of this lane's edge and of the edge before it
+  if constexpr (!FULL) {
+    const int2 rows = *row_bounds<H, BF16>(smem);
+    const auto of_row = [&](int e) { return e >= rows.x && e < rows.y; };
+    const int rl = tile * C::TM + lane;
+    if (!of_row(rl)) dl = -1;
+    if (!of_row(rl - 1)) dq = -1;
+    dprev = __builtin_amdgcn_readfirstlane(of_row(R0 - 1) ? dprev : -1);
+    dnext = __builtin_amdgcn_readfirstlane(of_row(R0 + S) ? dnext : -1);
+  }
   unsigned long long starts = __ballot(lane && dl != dq);   // bit r: row r of the tile begins a run
   if constexpr (S < 64) starts = (starts >> sh) & ((1ull << S) - 1ull) & ~1ull;
   const bool before = dprev == __builtin_amdgcn_readlane(dl, sh);
   // (a last block without edges is skipped below: the run at hand at the end is then one before it)
-  const bool behind = dnext >= 0 && dnext == __builtin_amdgcn_readlane(dl, sh + S - 1);
+  const bool behind = (FULL || dnext >= 0) && dnext == __builtin_amdgcn_readlane(dl, sh + S - 1);
   float run[C::CB];   // the run at hand: lane half g adds its own rows
   int k0 = 0;         // its first row in the strip
 #pragma unroll
@@ -697,7 +717,7 @@ __device__ __forceinline__ void edge_fwd_tile(
   auto flush = [&](int end, bool last) {
     const bool sf = k0 != 0 || !before, ef = !last || !behind;   // the atom's edges begin and end in the strip
     const int atom = __builtin_amdgcn_readlane(dl, sh + k0);
-    if (atom >= 0) {
+    if (FULL || atom >= 0) {
       float* o = sf && ef ? p.M + (size_t)atom * H : p.mpart + ((size_t)(R0 / S) * 2 + (sf ? 1 : 0)) * H;
       const u32x2_t_ w = __builtin_amdgcn_permlane32_swap(__float_as_uint(run[0]), __float_as_uint(run[C::CB - 1]), false, false);
       const float t = (__uint_as_float(w[0]) + __uint_as_float(w[1])) * (sf && ef ? p.alpha : 1.f);
@@ -832,11 +852,11 @@ __global__ void __launch_bounds__(256, H <= 128 ? 3 : 2) k_edge_fwd(EdgeFwdArgs 
   const int wr = wave / C::WC, wc = wave % C::WC;
   const int x = lane & 31;
   const int E = (int)p.E;
-  int E0 = 0, E1 = E;
   if constexpr (MODE != FWD_Z2) {
-    E0 = __builtin_amdgcn_readfirstlane(p.row_ptr[0]);
-    E1 = __builtin_amdgcn_readfirstlane(p.row_ptr[p.N]);
-    E1 = E1 < E ? E1 : E;
+    if (tid == 0) {
+      const int e1 = p.row_ptr[p.N];
+      *row_bounds<H, BF16>(smem) = make_int2(p.row_ptr[0], e1 < E ? e1 : E);
+    }
   }
   float w1d[C::CB], b2[C::CB], wx[C::CB];
   bf16x8_t bW1a[C::CB];
@@ -871,11 +891,16 @@ __global__ void __launch_bounds__(256, H <= 128 ? 3 : 2) k_edge_fwd(EdgeFwdArgs 
     int* s_next = sc + (buf ^ 1) * 3 * C::TM;
     const unsigned short* at = atb + buf * ATTR_TILE;
     unsigned short* at_next = atb + (buf ^ 1) * ATTR_TILE;
-    if ((tile + 1) * C::TM <= E)
-      edge_fwd_tile<H, BF16, BRES, true, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, E0, E1, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
+    bool full = (tile + 1) * C::TM <= E;
+    if constexpr (MODE != FWD_Z2) {
+      const int2 rows = *row_bounds<H, BF16>(smem);
+      full = full && __builtin_amdgcn_readfirstlane((rows.x <= 0 || tile * C::TM > rows.x) && (rows.y >= E || (tile + 1) * C::TM < rows.y));
+    }
+    if (full)
+      edge_fwd_tile<H, BF16, BRES, true, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
                                                dd0, at, at_next, nxa, bW1a, wx);
     else
-      edge_fwd_tile<H, BF16, BRES, false, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, E0, E1, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
+      edge_fwd_tile<H, BF16, BRES, false, ATTR, MODE>(p, smem, s, s_next, nxt, tile, E, tid, wr, wc, lane, w1d, b2, breg, wp0, wq0,
                                                 dd0, at, at_next, nxa, bW1a, wx);
   }
 }
