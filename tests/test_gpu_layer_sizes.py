@@ -461,6 +461,17 @@ def test_layer_forward_leaves_out_edges_of_no_row(H, dtype, k, lengths):
                 assert relerr(x, want) <= TOL[dtype]["fwd"], (lead, tail, pad_dst, keep)
 
 
+# More tiles than workgroups in flight: one walks whole tiles and tiles with edges of no row in turn, the next tile's gathers under way
+@pytest.mark.parametrize("H,dtype,k", [(64, "f32", 0), (128, "f32", 0), (128, "bf16", 0), (128, "bf16", 16), (256, "bf16", 4), (300, "bf16", 0)])
+def test_layer_forward_of_many_edges_leaves_out_edges_of_no_row(H, dtype, k):
+    lengths = np.random.default_rng(H).choice([0, 1, 17, 64, 200], size=2400).tolist()
+    t, a, rows = _rows_problem(H, H, max(k, 1), lengths, 9, 30001, 5)
+    ho, vo, _ = oracle.mp_layer_fwd(a["h"], a["v"], a["dst"][rows], a["col"][rows], a["attr"][rows, 0], a["rvec"][rows],
+                                    a["W"].astype(np.float64), 0.02, attr=a["attr"][rows])
+    got = _rows_call(t, H, k, dtype, alpha=0.02)
+    assert relerr(got[0], ho) <= TOL[dtype]["fwd"] and relerr(got[1], vo) <= TOL[dtype]["fwd"]
+
+
 # At other widths the reverse pass's sums per atom go by the rows as well (the weight gradients take every edge)
 @pytest.mark.parametrize("H", [300, 130])
 @pytest.mark.parametrize("lead,tail,pad_dst", [(0, 3, 0), (0, 200, 4), (9, 70, 1), (64, 0, 0)])
